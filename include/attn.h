@@ -84,8 +84,8 @@ int attn_fwd(const void *Q, const void *K, const void *V, void *O, float *LSE,
 /*
  * Bytes of device workspace attn_bwd asks for: two fp32 values per query row ([B*H][2][S]:
  * -rowsum(dO*O), and LSE rescaled to base 2), rounded up to 256 bytes, plus -- for problems
- * with so few query tiles that the dQ kernel is split over the keys, see
- * attn_bwd_rect_workspace_bytes -- the fp32 partial results of that split.
+ * with so few tiles that a kernel is split, see attn_bwd_rect_workspace_bytes -- the fp32
+ * partial results of that split.
  * Pure host function; returns 0 for an invalid problem.
  */
 size_t attn_bwd_workspace_bytes(const attn_params_t *p);
@@ -189,10 +189,13 @@ int attn_bwd_gqa_stages(const void *Q, const void *K, const void *V, const void 
  * statistics (two fp32 per query row, rounded up to 256 bytes) and, when B*Hq*ceil(Sq/256)
  * work-groups of the dQ kernel would leave most of the chip idle (Sq >= 256, at least 1024
  * keys), the fp32 partial dQ of a split of that kernel over the keys ([splits][B*Hq*Sq][64 or
- * 128]); a third small kernel adds them.  attn_bwd_rect_workspace_bytes(p) is the sum.  A
- * workspace that holds the statistics but not the partial results is accepted too: the dQ
- * kernel then runs unsplit.  Either way the plan depends only on the shape and the workspace
- * size, so results are deterministic.
+ * 128]); a third small kernel adds them.  The dK/dV kernel is split over the query rows in the
+ * same way when the key blocks of the K/V heads (128 keys; 64 above D = 128) leave most of the
+ * chip idle and a block has at least 48 x 32 query rows to walk; its partial results (at most
+ * 64 MiB) take the place of the partial dQ.  attn_bwd_rect_workspace_bytes(p) covers the
+ * statistics and the larger of the two.  A workspace that holds the statistics but not the
+ * partial results of a kernel is accepted too: that kernel then runs unsplit.  Either way the
+ * plan depends only on the shape and the workspace size, so results are deterministic.
  */
 typedef struct {
     int32_t B, Hq, Hkv, Sq, Sk, D;

@@ -2,6 +2,7 @@
 #include "../../include/attn.h"
 #include "attn_launch.hpp"
 
+#include <algorithm>
 #include <cmath>
 #include <limits>
 #include <mutex>
@@ -141,6 +142,22 @@ static size_t bwd_stats_bytes(const attn_rect_params_t *p)
     return round_ws(2 * (size_t)p->B * p->Hq * p->Sq * sizeof(float));
 }
 
+// The fp32 partial results of the dQ kernel's split over the keys and of the dK/dV kernel's split
+// over the query slots (0: not split).  The two kernels run one after the other, each with its
+// merge, so their partial results share one region behind the statistics.
+static size_t dq_part_bytes(const attn_rect_params_t *p)
+{
+    const int nsplit = attn::dq_split_plan(p->B * p->Hq, p->Sq, p->Sk, kernel_d(p->D), p->causal != 0, nullptr);
+    return nsplit > 1 ? round_ws((size_t)nsplit * p->B * p->Hq * p->Sq * kernel_d(p->D) * sizeof(float)) : 0;
+}
+static size_t dkdv_part_bytes(const attn_rect_params_t *p, bool causal)
+{
+    const int D = kernel_d(p->D);
+    int chunk = 0;
+    const int items = attn::dkdv_split_plan(p->B * p->Hkv, p->Hq / p->Hkv, p->Sq, p->Sk, D, causal, &chunk);
+    return chunk ? round_ws((size_t)p->B * p->Hkv * items * 2 * attn::dkdv_split_keys(D) * D * sizeof(float)) : 0;
+}
+
 // Rotary embedding fused into the call (both tables NULL: none).
 struct Rope {
     const float *cos_table = nullptr, *sin_table = nullptr;
@@ -216,8 +233,8 @@ static int bwd_impl(const void *Q, const void *K, const void *V, const void *O, 
         !aligned(dO, 16) || !aligned(dQ, 16) || !aligned(dK, 16) || !aligned(dV, 16) ||
         !aligned(LSE, 4))
         return ATTN_ERR_ALIGN;
-    // The row statistics always; the partial dQ of a key split only if they fit as well (a
-    // smaller workspace runs the dQ kernel unsplit).  No split with rotary tables: the merge
+    // The row statistics always; the partial results of a split only if they fit as well (a
+    // smaller workspace runs that kernel unsplit).  No split of dQ with rotary tables: the merge
     // does not rotate back.
     const size_t stats_bytes = bwd_stats_bytes(p);
     if (!workspace || !aligned(workspace, kWsAlign) || workspace_bytes < stats_bytes)
@@ -225,7 +242,11 @@ static int bwd_impl(const void *Q, const void *K, const void *V, const void *O, 
     if (stages == 0 || (stages & ~7u)) return ATTN_ERR_SHAPE;
     int dq_kps = 0;
     int dq_nsplit = attn::dq_split_plan(p->B * p->Hq, p->Sq, p->Sk, kernel_d(p->D), p->causal != 0, &dq_kps);
-    if (rope || workspace_bytes < attn_bwd_rect_workspace_bytes(p)) dq_nsplit = 1;
+    if (rope || workspace_bytes < stats_bytes + dq_part_bytes(p)) dq_nsplit = 1;
+    int dkdv_chunk = 0;
+    const int dkdv_items = attn::dkdv_split_plan(p->B * p->Hkv, p->Hq / p->Hkv, p->Sq, p->Sk, kernel_d(p->D),
+                                                 p->causal != 0, &dkdv_chunk);
+    if (workspace_bytes < stats_bytes + dkdv_part_bytes(p, p->causal != 0)) dkdv_chunk = 0;
     attn::BwdArgsT<E> a;
     a.Q = static_cast<const E *>(Q);
     a.K = static_cast<const E *>(K);
@@ -236,6 +257,8 @@ static int bwd_impl(const void *Q, const void *K, const void *V, const void *O, 
     a.delta = static_cast<float *>(workspace);
     a.dq_nsplit = dq_nsplit; a.dq_kps = dq_kps;
     a.dQpart = reinterpret_cast<float *>(static_cast<char *>(workspace) + stats_bytes);
+    a.dkdv_chunk = dkdv_chunk; a.dkdv_items = dkdv_items;
+    a.dKVpart = a.dQpart;
     a.dQ = static_cast<E *>(dQ);
     a.dK = static_cast<E *>(dK);
     a.dV = static_cast<E *>(dV);
@@ -353,10 +376,9 @@ int attn_fwd(const void *Q, const void *K, const void *V, void *O, float *LSE,
 size_t attn_bwd_rect_workspace_bytes(const attn_rect_params_t *p)
 {
     if (check_params(p) != ATTN_OK) return 0;
-    const size_t rows = (size_t)p->B * p->Hq * p->Sq;
-    const int nsplit = attn::dq_split_plan(p->B * p->Hq, p->Sq, p->Sk, kernel_d(p->D), p->causal != 0, nullptr);
-    const size_t part = nsplit > 1 ? round_ws((size_t)nsplit * rows * kernel_d(p->D) * sizeof(float)) : 0;
-    return bwd_stats_bytes(p) + part;
+    // (the larger of the masked and the unmasked plan: a workspace asked for with one serves the other)
+    const size_t dq = dq_part_bytes(p), kv = std::max(dkdv_part_bytes(p, false), p->causal ? dkdv_part_bytes(p, true) : 0);
+    return bwd_stats_bytes(p) + std::max(dq, kv);
 }
 
 size_t attn_bwd_gqa_workspace_bytes(const attn_gqa_params_t *p)

@@ -103,7 +103,38 @@ struct DkdvCfg {
     static_assert(kOffXchg % 16 == 0 && kLdsBytes <= 160 * 1024, "LDS layout");
 };
 
-template <int D, int P, bool CAUSAL>
+// Chunk `item` of a K/V head's chunks (see dkdv_split_plan), ordered by key block: its key block and
+// its place among that block's chunks.  Every wave finds it for itself, 64 key blocks at a time: a
+// prefix sum of the blocks' chunk counts over the lanes.
+__device__ __forceinline__ int dkdv_chunks(const BwdArgs &a, int kt, int keys, bool causal)
+{
+    return max(1, (dkdv_slots(kt, keys, a.group, a.S, a.Sk, causal) + a.dkdv_chunk - 1) / a.dkdv_chunk);
+}
+__device__ __forceinline__ void dkdv_find_item(const BwdArgs &a, int item, int keys, int n_block, bool causal,
+                                               int &kt, int &z)
+{
+    const int l = threadIdx.x & 63;
+    for (int k0 = 0;; k0 += 64) {
+        const int c = k0 + l < n_block ? dkdv_chunks(a, k0 + l, keys, causal) : 0;
+        int upto = c;
+#pragma unroll
+        for (int s = 1; s < 64; s <<= 1) {
+            const int o = __shfl_up(upto, s);
+            if (l >= s) upto += o;
+        }
+        const int total = __builtin_amdgcn_readlane(upto, 63);
+        if (item < total || k0 + 64 >= n_block) {
+            const int at = __builtin_ctzll(__builtin_amdgcn_ballot_w64(upto > item) | (1ull << 63));
+            kt = k0 + at;
+            z = item - (__builtin_amdgcn_readlane(upto, at) - __builtin_amdgcn_readlane(c, at));
+            return;
+        }
+        item -= total;
+    }
+}
+
+// SPLIT: the work-group takes one chunk of its key block's slots (see dkdv_split_plan).
+template <int D, int P, bool CAUSAL, bool SPLIT>
 __global__ void __launch_bounds__(P * 128) __attribute__((amdgpu_waves_per_eu(P >= 4 ? P / 2 : 1)))
 attn_bwd_dkdv_kernel(const BwdArgs a)
 {
@@ -121,6 +152,11 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
     const int Hkv = a.H / a.group;
     int bkv, kt;  // causal: key block 0 is the heaviest
     xcd_tile_order<CAUSAL>(blockIdx.x, a.ntile, a.BH / a.group, bkv, kt);
+    int item = 0, z = 0;  // SPLIT: chunk of the head, and of the key block
+    if (SPLIT) {
+        item = __builtin_amdgcn_readfirstlane(kt);
+        dkdv_find_item(a, item, C::kBlk, (a.Sk + C::kBlk - 1) / C::kBlk, CAUSAL, kt, z);
+    }
     const int64_t base_kv = (int64_t)(bkv / Hkv) * a.kv_stride_b + (int64_t)(bkv % Hkv) * a.kv_stride_h;
     const int bh0 = (bkv / Hkv) * a.H + (bkv % Hkv) * a.group;  // first query head of the group
 
@@ -131,7 +167,15 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
     const int n_slot = (S + C::kRows - 1) / C::kRows;
     // first slot with a row that sees a key of this block (row >= key - coff)
     const int t0 = CAUSAL ? max(0, kt * C::kBlk - coff) / C::kRows : 0;
-    const int n_seq = n_slot > t0 ? a.group * (n_slot - t0) : 0;  // slots of all heads of the group
+    const int n_all = n_slot > t0 ? a.group * (n_slot - t0) : 0;  // slots of all heads of the group
+    // the slots this work-group walks: n_seq of them from t_first of query head g_first of the group on
+    int n_seq = n_all, t_first = t0, g_first = 0;
+    if (SPLIT && n_all > 0) {
+        const int begin = z * a.dkdv_chunk;
+        n_seq = min(a.dkdv_chunk, n_all - begin);
+        g_first = begin / (n_slot - t0);
+        t_first = t0 + begin % (n_slot - t0);
+    }
 
     // chunk position swizzle: rows 0..15 get 16 distinct values (row reads of 16 lanes hit 16
     // different 16-byte bank groups) and 4 consecutive rows differ in the upper two bits (the
@@ -210,7 +254,7 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
     // the consumers for the rows): the slots of the group's query heads form ONE sequence (head
     // after head, slots t0 .. n_slot-1 of each), so that the ring stays full across the change of
     // head; past the last head the rows lie beyond S and read as zero
-    int tf = t0, gqf = 0;
+    int tf = t_first, gqf = g_first;
     auto advance_fetch = [&]() __attribute__((always_inline)) {
         ++tf;
         if (tf == n_slot && gqf + 1 < a.group) {
@@ -229,7 +273,7 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
     if (producer) {
         // The statistics of the first kAhead slots are requested before anything else (the
         // consumers request the rows meanwhile).
-        set_head(bh0);
+        set_head(bh0 + g_first);
 #pragma unroll
         for (int i = 0; i < C::kAhead; ++i) {
             dma_stat(tf, i);
@@ -277,7 +321,7 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
         const int lane_off = r * RB + ((h ^ swz(r)) << 4);  // chunk 2ks+h of row r: ^ (ks*32)
 
         int rs = 0;  // ring position of the current slot
-        int t = t0;  // its rows: slot t of the current head
+        int t = t_first;  // its rows: slot t of the current head
         for (int g = 0; g < n_seq; ++g) {
             slot_barrier();
             int rd = rs + C::kAhead;
@@ -400,14 +444,14 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
         };
 
         // the rows of the first kAhead slots
-        set_head(bh0);
+        set_head(bh0 + g_first);
 #pragma unroll
         for (int i = 0; i < C::kAhead; ++i) {
             dma_pieces(tf, i);
             advance_fetch();
         }
         int rs = 0;  // ring position of the producers' slot; the consumers' is one behind
-        int t = t0, tp = t0;  // rows of the producers' slot and of the one before it
+        int t = t_first, tp = t_first;  // rows of the producers' slot and of the one before it
         for (int g = 0; g < n_seq; ++g) {
             slot_barrier();
             // slot g + kAhead goes into the ring position that slot g - 2 has left
@@ -438,6 +482,37 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
             slot += slot >= last ? 1 : 0;
             char *stg = smem + slot * C::kSlotBytes + (cw & 1) * C::kTensorBytes;
             const int lr = l / CPR, lc = l % CPR;
+            if (SPLIT && n_all > a.dkdv_chunk) {
+                // unscaled fp32 partial of this chunk; an fp32 row is twice as long as the
+                // staging area's, so it goes in two halves
+                float *const part = a.dKVpart + ((int64_t)(bkv * a.dkdv_items + item) * 2 + kind) * (C::kBlk * D);
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int hp = 0; hp < 2; ++hp) {
+#pragma unroll
+                        for (int db = hp * (DB / 2); db < (hp + 1) * (DB / 2); ++db)
+#pragma unroll
+                            for (int g = 0; g < 4; ++g) {
+                                f32x4 v;
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) v[e] = acc[kb][db][4 * g + e];
+                                const int chunk = (db % (DB / 2)) * 8 + 2 * g + h;
+                                *(f32x4 *)(stg + r * RB + ((chunk ^ swz(r)) << 4)) = v;
+                            }
+                        asm volatile("" ::: "memory");  // a wave's LDS accesses execute in order
+#pragma unroll
+                        for (int j = 0; j < 32 / RPI; ++j) {
+                            const int row = RPI * j + lr;
+                            const f32x4 v = *(const f32x4 *)(stg + row * RB + ((lc ^ swz(row)) << 4));
+                            const int okey = half * 64 + 32 * kb + row;
+                            if (kt * C::kBlk + okey < Sk)
+                                *(f32x4 *)(part + okey * D + hp * (D / 2) + lc * 4) = v;
+                        }
+                        asm volatile("" ::: "memory");
+                    }
+                return;
+            }
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb) {
 #pragma unroll
@@ -460,6 +535,46 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
             }
         }
     }
+}
+
+// Sum of the partial dK and dV of the key blocks that were cut into several chunks, in the order of
+// the chunks, dK times scale, rounded.  A work-group owns 1024 / D keys of one block and tensor,
+// a thread 4 consecutive columns of one key; HBM-bound and small.
+template <int D, bool CAUSAL>
+__global__ void __launch_bounds__(256) attn_bwd_dkdv_merge_kernel(const BwdArgs a)
+{
+    constexpr int keys = dkdv_split_keys(D), kRows = 1024 / D, kSub = keys / kRows;
+    const int n_block = (a.Sk + keys - 1) / keys;
+    const int sub = blockIdx.x % kSub, kind = blockIdx.y;
+    const int kt = (blockIdx.x / kSub) % n_block, bkv = blockIdx.x / (kSub * n_block);
+    const int n = dkdv_chunks(a, kt, keys, CAUSAL);
+    if (n < 2) return;  // (written by its one work-group)
+    int first = 0;  // the block's first chunk: the chunks of the blocks before it, summed over the lanes
+    for (int k = threadIdx.x & 63; k < kt; k += 64) first += dkdv_chunks(a, k, keys, CAUSAL);
+#pragma unroll
+    for (int s = 32; s >= 1; s >>= 1) first += __shfl_xor(first, s);
+    const int row = sub * kRows + threadIdx.x / (D / 4), d0 = (threadIdx.x % (D / 4)) * 4;
+    const int key = kt * keys + row;
+    if (key >= a.Sk || d0 >= a.Dr) return;
+    const float *part = a.dKVpart + ((int64_t)(bkv * a.dkdv_items + first) * 2 + kind) * (keys * D) + row * D + d0;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int z0 = 0; z0 < n; z0 += 4) {  // four chunks' loads in flight together
+        f32x4 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            v[k] = *(const f32x4 *)(part + (int64_t)(z0 + k < n ? z0 + k : z0) * (2 * keys * D));
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (z0 + k < n) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[e] += v[k][e];
+            }
+    }
+    const int Hkv = a.H / a.group;
+    const float sc = kind ? a.scale : 1.f;
+    elem *out = (kind ? a.dK : a.dV) + (int64_t)(bkv / Hkv) * a.kv_stride_b + (int64_t)(bkv % Hkv) * a.kv_stride_h +
+                (int64_t)key * a.kv_stride_s + d0;
+    *(elem4 *)out = pack4(acc[0] * sc, acc[1] * sc, acc[2] * sc, acc[3] * sc);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -933,9 +1048,28 @@ static int launch_dkdv_p(BwdArgs a, hipStream_t st)
 {
     using C = DkdvCfg<D, P>;
     a.ntile = (a.Sk + C::kBlk - 1) / C::kBlk;
-    if (!allow_lds(attn_bwd_dkdv_kernel<D, P, CAUSAL>, C::kLdsBytes)) return -1;
-    hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, P, CAUSAL>), dim3(a.ntile * (a.BH / a.group)),
+    if (!allow_lds(attn_bwd_dkdv_kernel<D, P, CAUSAL, false>, C::kLdsBytes)) return -1;
+    hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, P, CAUSAL, false>), dim3(a.ntile * (a.BH / a.group)),
                        dim3(C::kThreads), C::kLdsBytes, st, a);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+// Split over the query slots: one work-group per chunk, then the merge.
+template <int D, bool CAUSAL>
+static int launch_dkdv_split(BwdArgs a, hipStream_t st)
+{
+    constexpr int P = D > 128 ? 2 : 4, keys = dkdv_split_keys(D);
+    using C = DkdvCfg<D, P>;
+    static_assert(C::kBlk == keys, "keys per work-group");
+    const int BHkv = a.BH / a.group;
+    a.ntile = a.dkdv_items;
+    if (!allow_lds(attn_bwd_dkdv_kernel<D, P, CAUSAL, true>, C::kLdsBytes)) return -1;
+    hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, P, CAUSAL, true>), dim3(a.ntile * BHkv), dim3(C::kThreads),
+                       C::kLdsBytes, st, a);
+    if (hipGetLastError() != hipSuccess) return -1;
+    const int n_block = (a.Sk + keys - 1) / keys;
+    hipLaunchKernelGGL((attn_bwd_dkdv_merge_kernel<D, CAUSAL>), dim3(BHkv * n_block * (keys * D / 1024), 2),
+                       dim3(256), 0, st, a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -947,6 +1081,7 @@ static int launch_dkdv_p(BwdArgs a, hipStream_t st)
 template <int D, bool CAUSAL>
 static int launch_dkdv(const BwdArgs &a, hipStream_t st)
 {
+    if (a.dkdv_chunk) return launch_dkdv_split<D, CAUSAL>(a, st);
     // D = 256: two pairs, one wave per SIMD (a consumer's two 32 x 256 accumulators alone are
     // 256 registers), 64 keys per work-group
     if constexpr (D > 128) return launch_dkdv_p<D, 2, CAUSAL>(a, st);
@@ -1060,6 +1195,43 @@ int dq_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps)
     nsplit = (tiles + tiles_per - 1) / tiles_per;  // no empty split
     if (kps) *kps = tiles_per * 64;
     return nsplit;
+}
+
+// Split the dK/dV kernel over the query slots when its work-groups (one per key block of a K/V head)
+// leave compute units idle: few K/V heads, e.g. grouped-query heads, whose one work-group per block
+// walks the slots of every query head of the group.  The slots of a key block are cut into chunks of
+// equal length, the shortest for which all chunks of the launch are resident at once (256 compute
+// units; two work-groups fit one at D = 64), at least 16 slots each; blocks of one chunk write their
+// result directly.  Whole backward, unsplit -> split, us: B=2 Hq=16 Hkv=4 S=1537 D=96 causal (104
+// blocks, the first with 196 slots) 208 -> 129, without mask 226 -> 176; B=1 H=8 S=2048 D=128 causal
+// 89 -> 74; B=1 H=4 S=8192 D=64 causal 235 -> 192; B=1 H=8 S=2048 D=64 71 -> 67.  Not below 48 slots in
+// the longest block, where the merge (about 5 us) takes most of what is gained and dK and dV keep
+// the one order of their sums that does not depend on the workspace; nor unless a chunk is at most
+// three quarters of the longest block.
+int dkdv_split_plan(int BHkv, int group, int S, int Sk, int D, bool causal, int *chunk)
+{
+    const int keys = dkdv_split_keys(D), n_block = (Sk + keys - 1) / keys;
+    const int64_t resident = D == 64 ? 512 : 256;
+    *chunk = 0;
+    if ((int64_t)BHkv * n_block >= resident) return n_block;
+    const int longest = dkdv_slots(0, keys, group, S, Sk, causal);
+    if (longest < 48) return n_block;
+    int64_t slots = 0;
+    for (int kt = 0; kt < n_block; ++kt) slots += dkdv_slots(kt, keys, group, S, Sk, causal);
+    int64_t L = (slots * BHkv + resident - 1) / resident;
+    if (L < 16) L = 16;
+    for (; 4 * L <= 3 * (int64_t)longest; L += (L + 31) / 32) {
+        int64_t items = 0;
+        for (int kt = 0; kt < n_block; ++kt) {
+            const int64_t n = dkdv_slots(kt, keys, group, S, Sk, causal);
+            items += n ? (n + L - 1) / L : 1;
+        }
+        if (items * BHkv <= resident) {
+            *chunk = (int)L;
+            return (int)items;
+        }
+    }
+    return n_block;
 }
 #endif
 

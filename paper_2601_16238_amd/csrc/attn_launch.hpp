@@ -83,6 +83,12 @@ struct BwdArgsT {
     // dq_nsplit == 1: dQ is written directly.
     int dq_nsplit, dq_kps;   // dq_kps is a multiple of the 64-key tile
     float *dQpart;           // [dq_nsplit][B*H][S][D]
+    // dK/dV kernel split over the query slots (see dkdv_split_plan): a key block's slots are cut
+    // into chunks of dkdv_chunk, dkdv_items chunks per K/V head in all; a block of several chunks
+    // writes unscaled fp32 partial results, item by item, which attn_bwd_dkdv_merge_kernel adds.
+    // dkdv_chunk == 0: not split.
+    int dkdv_chunk, dkdv_items;
+    float *dKVpart;          // [B*Hkv][dkdv_items][dV, dK][keys of a block][D]
     // Rotary embedding: Q holds ROTATED rows; dQ is rotated back (by the transpose of the
     // rotation) before it is stored, so that it is the gradient of the unrotated rows.  NULL
     // tables: none.
@@ -109,6 +115,19 @@ int fwd_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps);
 // Number of key splits the dQ kernel would use for this problem (1: none) and the keys per
 // split; a pure host function of the shape.
 int dq_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps);
+// Split of the dK/dV kernel over the query slots: returns the chunks (work-groups) per K/V head and
+// the slots per chunk (0: not split, one work-group per key block); a pure host function of the shape.
+int dkdv_split_plan(int BHkv, int group, int S, int Sk, int D, bool causal, int *chunk);
+// Keys per work-group of the split dK/dV kernel, and the 32-row query slots (over all query heads of
+// the group) that key block kt has to walk: all of them, or under a causal mask those from the
+// block's diagonal on.
+__host__ __device__ inline constexpr int dkdv_split_keys(int D) { return D > 128 ? 64 : 128; }
+__host__ __device__ inline int dkdv_slots(int kt, int keys, int group, int S, int Sk, bool causal)
+{
+    const int n_slot = (S + 31) / 32, first = kt * keys - (Sk - S);
+    const int t0 = causal && first > 0 ? first / 32 : 0;
+    return n_slot > t0 ? group * (n_slot - t0) : 0;
+}
 // The whole backward in one launch for heads of at most bwd_small_max_rows(D) query rows and keys
 // (attn_bwd_small.hip; called by launch_bwd when all three stages are asked for).
 int bwd_small_max_rows(int D);
