@@ -192,7 +192,7 @@ int attn_bwd_gqa_stages(const void *Q, const void *K, const void *V, const void 
  * 128]); a third small kernel adds them.  The dK/dV kernel is split over the query rows in the
  * same way when the key blocks of the K/V heads (128 keys; 64 above D = 128) leave most of the
  * chip idle and a block has at least 48 x 32 query rows to walk; its partial results (at most
- * 64 MiB) take the place of the partial dQ.  attn_bwd_rect_workspace_bytes(p) covers the
+ * 32 MiB) take the place of the partial dQ.  attn_bwd_rect_workspace_bytes(p) covers the
  * statistics and the larger of the two.  A workspace that holds the statistics but not the
  * partial results of a kernel is accepted too: that kernel then runs unsplit.  Either way the
  * plan depends only on the shape and the workspace size, so results are deterministic.

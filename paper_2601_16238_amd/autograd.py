@@ -11,28 +11,11 @@ import torch
 from . import binding
 
 
-def _like(ref, t):
-    """t with the shape, strides and type of ref (copied only if it differs)."""
-    if t.dtype == ref.dtype and t.stride() == ref.stride():
-        return t
-    out = torch.empty_strided(ref.shape, ref.stride(), dtype=ref.dtype, device=ref.device)
-    out.copy_(t)
-    return out
-
-
-def _dense(t):
-    """Layouts the library takes: unit stride along D, other strides multiples of 8 elements,
-    16-byte aligned base.  Anything else is copied to a contiguous tensor."""
-    ok = t.stride(3) == 1 and all(s % 8 == 0 for s in t.stride()[:3]) and t.data_ptr() % 16 == 0
-    return t if ok else t.contiguous()
-
-
 class _FusedAttention(torch.autograd.Function):
     @staticmethod
     def forward(ctx, q, k, v, scale, causal):
-        q, k = _dense(q), _dense(k)
-        v = _like(k, _dense(v))
-        O, LSE = binding.attn_fwd_rect(q, k, v, scale, causal)
+        # (layouts the library does not take are copied to ones it does; what is saved is what ran)
+        q, k, v, O, LSE = binding.marshal().fused_forward(q, k, v, scale, causal)
         ctx.save_for_backward(q, k, v, O, LSE)
         ctx.scale, ctx.causal = scale, causal
         return O
@@ -40,7 +23,7 @@ class _FusedAttention(torch.autograd.Function):
     @staticmethod
     def backward(ctx, dO):
         q, k, v, O, LSE = ctx.saved_tensors
-        dQ, dK, dV = binding.attn_bwd_rect(q, k, v, O, _like(O, dO), LSE, ctx.scale, ctx.causal)
+        dQ, dK, dV = binding.marshal().fused_backward(q, k, v, O, LSE, dO, ctx.scale, ctx.causal)
         return dQ, dK, dV, None, None
 
 

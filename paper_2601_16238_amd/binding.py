@@ -1,9 +1,10 @@
-"""ctypes binding of libmi355attn.so -- argument marshalling only.
+"""Binding of libmi355attn.so -- argument marshalling only.
 
 Every step of the attention path runs inside the HIP library; this file passes device
 pointers of torch tensors (PyTorch is used for device memory and streams only) through the
-C ABI declared in include/attn.h.  There is no CPU or PyTorch fallback: if the library has
-not been built, loading fails with an error.
+C ABI declared in include/attn.h: the calls on tensors through the native module _marshal
+(csrc/marshal.cpp: checks, allocation, call), everything else through ctypes.  There is no CPU or
+PyTorch fallback: if the library has not been built, loading fails with an error.
 """
 import ctypes
 import os
@@ -150,6 +151,25 @@ def lib():
     return _lib
 
 
+_marshal = None
+
+
+def marshal():
+    """The native marshalling module (built in-tree by build.py); raise if it is missing."""
+    global _marshal
+    if _marshal is None:
+        lib()
+        try:
+            from . import _marshal as m
+        except ImportError as e:
+            raise RuntimeError("the marshalling module is not built or does not load (%s): run "
+                               "`python -c 'import __graft_entry__ as g; g.build()'`; there is no "
+                               "fallback path" % e) from e
+        m.set_error_class(AttnError)
+        _marshal = m
+    return _marshal
+
+
 def status_string(status):
     return lib().attn_status_string(int(status)).decode()
 
@@ -227,13 +247,6 @@ def _strides3(t):
     return sb, sh, ss
 
 
-def _params_for(t, scale, causal):
-    if t.dim() != 4 or t.stride(3) != 1:
-        raise ValueError("expected a [B,H,S,D] tensor with a contiguous D axis")
-    B, H, S, D = t.shape
-    return make_params(B, H, S, D, scale, causal, _strides3(t))
-
-
 def _same_layout(ref, *ts):
     # (the stride of an axis of length 1 is never used and may be anything)
     def strides(t):
@@ -249,101 +262,25 @@ def _stream_ptr(torch, stream):
     return ctypes.c_void_p(s.cuda_stream)
 
 
-def _on_stream(torch, stream):
-    """Context in which tensors this binding allocates itself belong to the stream the kernels
-    are enqueued on: torch's caching allocator ties a block to the stream that was current when
-    it was allocated, and would otherwise hand a dropped workspace to other work of the
-    current stream while kernels on `stream` still use it."""
-    import contextlib
-    return contextlib.nullcontext() if stream is None else torch.cuda.stream(stream)
-
-
-
-def _elem_types(torch):
-    return (torch.bfloat16, torch.float16)
-
-
 def _check_lse(torch, LSE, shape):
     if LSE.dtype != torch.float32 or not LSE.is_contiguous() or tuple(LSE.shape) != tuple(shape):
         raise ValueError("LSE must be a contiguous fp32 [B,Hq,Sq] tensor")
 
 
-def _forward(where, entry, params, ws_bytes_fn, Q, K, V, O, LSE, workspace, split, stream,
-             dtypes):
-    """Shared marshalling of the three forward entry points: checks, output allocation and the
-    call `entry(Q, K, V, O, LSE, [workspace, bytes,] params, stream)`."""
+def _call(entry, stream, *args):
+    """entry(*args, raw stream): tensors that the call allocates belong to the stream its kernels
+    are enqueued on."""
+    if stream is None:
+        return entry(*args, None)
     import torch
-    if Q.dtype not in dtypes or not Q.is_cuda:
-        raise ValueError("Q,K,V must be %s tensors on the GPU" % " or ".join(str(d) for d in dtypes))
-    _same_layout(K, V)
-    if K.dtype != Q.dtype or K.device != Q.device:
-        raise ValueError("all tensors must share dtype and device")
-    B, H, S, D = Q.shape
-    with _on_stream(torch, stream):
-        if O is None:
-            O = torch.empty_strided(Q.shape, Q.stride(), dtype=Q.dtype, device=Q.device)
-        else:
-            _same_layout(Q, O)
-        if LSE is None:
-            LSE = torch.empty((B, H, S), dtype=torch.float32, device=Q.device)
-        else:
-            _check_lse(torch, LSE, (B, H, S))
-        args = [Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), LSE.data_ptr()]
-        if ws_bytes_fn is not None:  # the rectangular form takes an optional workspace
-            ws_ptr, ws_bytes = None, 0
-            if split:
-                need = int(ws_bytes_fn(ctypes.byref(params)))
-                if workspace is None and need:
-                    workspace = torch.empty(need, dtype=torch.uint8, device=Q.device)
-                if workspace is not None:
-                    ws_ptr, ws_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
-            args += [ws_ptr, ws_bytes]
-    rc = entry(*args, ctypes.byref(params), _stream_ptr(torch, stream))
-    if rc != ATTN_OK:
-        raise AttnError(rc, where)
-    return O, LSE
-
-
-def _backward(where, entry, params, ws_bytes_fn, Q, K, V, O, dO, LSE, dQ, dK, dV, workspace,
-              stream, dtypes, extra=()):
-    """Shared marshalling of the backward entry points."""
-    import torch
-    if Q.dtype not in dtypes or not Q.is_cuda:
-        raise ValueError("tensors must be %s on the GPU" % " or ".join(str(d) for d in dtypes))
-    _same_layout(Q, O, dO)
-    _same_layout(K, V)
-    if K.dtype != Q.dtype or K.device != Q.device:
-        raise ValueError("all tensors must share dtype and device")
-    B, H, S, D = Q.shape
-    _check_lse(torch, LSE, (B, H, S))
-    with _on_stream(torch, stream):
-        outs = []
-        for t, like in ((dQ, Q), (dK, K), (dV, K)):
-            if t is None:
-                t = torch.empty_strided(like.shape, like.stride(), dtype=like.dtype, device=like.device)
-            else:
-                _same_layout(like, t)
-            outs.append(t)
-        dQ, dK, dV = outs
-        if workspace is None:
-            workspace = torch.empty(int(ws_bytes_fn(ctypes.byref(params))), dtype=torch.uint8,
-                                    device=Q.device)
-    rc = entry(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), dO.data_ptr(),
-               LSE.data_ptr(), dQ.data_ptr(), dK.data_ptr(), dV.data_ptr(), workspace.data_ptr(),
-               workspace.numel() * workspace.element_size(), ctypes.byref(params),
-               _stream_ptr(torch, stream), *extra)
-    if rc != ATTN_OK:
-        raise AttnError(rc, where)
-    return dQ, dK, dV
+    with torch.cuda.stream(stream):
+        return entry(*args, stream.cuda_stream)
 
 
 def attn_fwd(Q, K, V, scale, causal, O=None, LSE=None, stream=None):
     """O, LSE = attention forward.  Q,K,V: bf16 device tensors [B,H,S,D] with equal strides.
     Enqueues on `stream` (default: torch's current stream); does not synchronise."""
-    import torch
-    _same_layout(Q, K, V)
-    return _forward("attn_fwd", lib().attn_fwd, _params_for(Q, scale, causal), None, Q, K, V, O,
-                    LSE, None, False, stream, (torch.bfloat16,))
+    return _call(marshal().attn_fwd, stream, Q, K, V, float(scale), bool(causal), O, LSE)
 
 
 def attn_bwd_workspace_bytes(B, H, S, D):
@@ -356,12 +293,8 @@ def attn_bwd(Q, K, V, O, dO, LSE, scale, causal, dQ=None, dK=None, dV=None, work
     """dQ, dK, dV = attention backward for upstream gradient dO (all bf16, same strides).
     `stages` (profiling aid) restricts the call to a subset of its kernels through
     attn_bwd_stages; None calls attn_bwd."""
-    import torch
-    _same_layout(Q, K, V)
-    entry, extra = (lib().attn_bwd, ()) if stages is None else (lib().attn_bwd_stages, (int(stages),))
-    return _backward("attn_bwd", entry, _params_for(Q, scale, causal),
-                     lib().attn_bwd_workspace_bytes, Q, K, V, O, dO, LSE, dQ, dK, dV, workspace,
-                     stream, (torch.bfloat16,), extra)
+    return _call(marshal().attn_bwd, stream, None if stages is None else int(stages), Q, K, V, O, dO, LSE,
+                 float(scale), bool(causal), dQ, dK, dV, workspace)
 
 
 # ---- grouped-query heads: Q, O, dO, dQ are [B,Hq,S,D]; K, V, dK, dV are [B,Hkv,S,D] ----------
@@ -378,21 +311,9 @@ def make_gqa_params(B, Hq, Hkv, S, D, scale, causal, q_strides=None, kv_strides=
     return p
 
 
-def _gqa_params_for(q, k, scale, causal):
-    for t in (q, k):
-        if t.dim() != 4 or t.stride(3) != 1:
-            raise ValueError("expected [B,H,S,D] tensors with a contiguous D axis")
-    B, Hq, S, D = q.shape
-    if k.shape[0] != B or k.shape[2] != S or k.shape[3] != D:
-        raise ValueError("K/V must be [B,Hkv,S,D] matching Q in B, S and D")
-    return make_gqa_params(B, Hq, k.shape[1], S, D, scale, causal, _strides3(q), _strides3(k))
-
-
 def attn_fwd_gqa(Q, K, V, scale, causal, O=None, LSE=None, stream=None):
     """O [B,Hq,S,D], LSE [B,Hq,S] = grouped-query attention forward; K, V: [B,Hkv,S,D]."""
-    import torch
-    return _forward("attn_fwd_gqa", lib().attn_fwd_gqa, _gqa_params_for(Q, K, scale, causal), None,
-                    Q, K, V, O, LSE, None, False, stream, (torch.bfloat16,))
+    return _call(marshal().attn_fwd_gqa, stream, Q, K, V, float(scale), bool(causal), O, LSE)
 
 
 def attn_bwd_gqa_workspace_bytes(B, Hq, Hkv, S, D):
@@ -403,12 +324,8 @@ def attn_bwd_gqa_workspace_bytes(B, Hq, Hkv, S, D):
 def attn_bwd_gqa(Q, K, V, O, dO, LSE, scale, causal, dQ=None, dK=None, dV=None, workspace=None,
                  stream=None, stages=None):
     """dQ [B,Hq,S,D], dK, dV [B,Hkv,S,D] = grouped-query attention backward."""
-    import torch
-    entry, extra = ((lib().attn_bwd_gqa, ()) if stages is None
-                    else (lib().attn_bwd_gqa_stages, (int(stages),)))
-    return _backward("attn_bwd_gqa", entry, _gqa_params_for(Q, K, scale, causal),
-                     lib().attn_bwd_gqa_workspace_bytes, Q, K, V, O, dO, LSE, dQ, dK, dV,
-                     workspace, stream, (torch.bfloat16,), extra)
+    return _call(marshal().attn_bwd_gqa, stream, None if stages is None else int(stages), Q, K, V, O, dO, LSE,
+                 float(scale), bool(causal), dQ, dK, dV, workspace)
 
 
 # ---- rectangular: Q, O, dO, dQ are [B,Hq,Sq,D]; K, V, dK, dV are [B,Hkv,Sk,D]; a causal mask
@@ -449,11 +366,8 @@ def attn_fwd_rect(Q, K, V, scale, causal, O=None, LSE=None, workspace=None, spli
     """O [B,Hq,Sq,D], LSE [B,Hq,Sq]; K, V: [B,Hkv,Sk,D].  `split=False` passes no workspace,
     which keeps the forward in one kernel; otherwise a workspace is allocated when the
     library's plan asks for one.  bf16 or fp16 tensors (all of one type)."""
-    import torch
-    entry = lib().attn_fwd_rect_f16 if Q.dtype == torch.float16 else lib().attn_fwd_rect
-    return _forward("attn_fwd_rect", entry, _rect_params_for(Q, K, scale, causal),
-                    lib().attn_fwd_rect_workspace_bytes, Q, K, V, O, LSE, workspace, split, stream,
-                    _elem_types(torch))
+    return _call(marshal().attn_fwd_rect, stream, Q, K, V, float(scale), bool(causal), O, LSE, workspace,
+                 bool(split))
 
 
 def attn_bwd_rect_workspace_bytes(B, Hq, Hkv, Sq, Sk, D):
@@ -464,11 +378,8 @@ def attn_bwd_rect_workspace_bytes(B, Hq, Hkv, Sq, Sk, D):
 def attn_bwd_rect(Q, K, V, O, dO, LSE, scale, causal, dQ=None, dK=None, dV=None, workspace=None,
                   stream=None):
     """dQ [B,Hq,Sq,D], dK, dV [B,Hkv,Sk,D] = rectangular attention backward (bf16 or fp16)."""
-    import torch
-    entry = lib().attn_bwd_rect_f16 if Q.dtype == torch.float16 else lib().attn_bwd_rect
-    return _backward("attn_bwd_rect", entry, _rect_params_for(Q, K, scale, causal),
-                     lib().attn_bwd_rect_workspace_bytes, Q, K, V, O, dO, LSE, dQ, dK, dV,
-                     workspace, stream, _elem_types(torch))
+    return _call(marshal().attn_bwd_rect, stream, Q, K, V, O, dO, LSE, float(scale), bool(causal), dQ, dK, dV,
+                 workspace)
 
 
 def attn_bwd_rect_noalloc(Q, K, V, O, dO, LSE, scale, causal, dQ, dK, dV, stream=None):
@@ -492,62 +403,17 @@ def attn_bwd_rect_noalloc(Q, K, V, O, dO, LSE, scale, causal, dQ, dK, dV, stream
 
 # ---- rotary embedding fused into the calls: Q unrotated in, K rotated in (see include/attn.h) ---
 
-def _check_tables(torch, cos, sin, Sk, D):
-    for t in (cos, sin):
-        if t.dtype != torch.float32 or not t.is_cuda or not t.is_contiguous() \
-                or tuple(t.shape) != (Sk, D // 2):
-            raise ValueError("cos/sin tables must be contiguous fp32 [Sk, D/2] tensors on the GPU")
-
-
 def attn_fwd_rope(Q, K_rot, V, cos, sin, scale, causal, O=None, LSE=None, Q_rot=None,
                   want_q_rot=True, split=True, stream=None):
     """O, LSE, Q_rot = attention forward with the rotary embedding of the query rows fused into
     their load.  Q: unrotated [B,Hq,Sq,D]; K_rot: rotated [B,Hkv,Sk,D]; cos, sin: fp32 [Sk,D/2].
     Q_rot (the rotated query rows the backward needs) is returned unless want_q_rot=False."""
-    import torch
-    if Q.dtype != torch.bfloat16 or not Q.is_cuda:
-        raise ValueError("Q,K,V must be bf16 tensors on the GPU")
-    _same_layout(K_rot, V)
-    B, H, S, D = Q.shape
-    _check_tables(torch, cos, sin, K_rot.shape[2], D)
-    p = _rect_params_for(Q, K_rot, scale, causal)
-    with _on_stream(torch, stream):
-        if O is None:
-            O = torch.empty_strided(Q.shape, Q.stride(), dtype=Q.dtype, device=Q.device)
-        else:
-            _same_layout(Q, O)
-        if LSE is None:
-            LSE = torch.empty((B, H, S), dtype=torch.float32, device=Q.device)
-        else:
-            _check_lse(torch, LSE, (B, H, S))
-        if Q_rot is None and want_q_rot:
-            Q_rot = torch.empty_strided(Q.shape, Q.stride(), dtype=Q.dtype, device=Q.device)
-        elif Q_rot is not None:
-            _same_layout(Q, Q_rot)
-        ws = None
-        if split:
-            need = int(lib().attn_fwd_rope_workspace_bytes(ctypes.byref(p)))
-            if need:
-                ws = torch.empty(need, dtype=torch.uint8, device=Q.device)
-    rc = lib().attn_fwd_rope(Q.data_ptr(), K_rot.data_ptr(), V.data_ptr(), cos.data_ptr(),
-                             sin.data_ptr(), O.data_ptr(), LSE.data_ptr(),
-                             Q_rot.data_ptr() if Q_rot is not None else None,
-                             ws.data_ptr() if ws is not None else None,
-                             ws.numel() if ws is not None else 0, ctypes.byref(p),
-                             _stream_ptr(torch, stream))
-    if rc != ATTN_OK:
-        raise AttnError(rc, "attn_fwd_rope")
-    return O, LSE, Q_rot
+    return _call(marshal().attn_fwd_rope, stream, Q, K_rot, V, cos, sin, float(scale), bool(causal), O, LSE, Q_rot,
+                 bool(want_q_rot), bool(split))
 
 
 def attn_bwd_rope(Q_rot, K_rot, V, O, dO, LSE, cos, sin, scale, causal, dQ=None, dK_rot=None,
                   dV=None, workspace=None, stream=None):
     """dQ (gradient of the UNROTATED query rows), dK_rot (gradient of the rotated K), dV."""
-    import torch
-    _check_tables(torch, cos, sin, K_rot.shape[2], Q_rot.shape[3])
-    p = _rect_params_for(Q_rot, K_rot, scale, causal)
-
-    def entry(*args):  # the tables sit between LSE and dQ in the C signature
-        return lib().attn_bwd_rope(*args[:6], cos.data_ptr(), sin.data_ptr(), *args[6:])
-    return _backward("attn_bwd_rope", entry, p, lib().attn_bwd_rect_workspace_bytes, Q_rot, K_rot,
-                     V, O, dO, LSE, dQ, dK_rot, dV, workspace, stream, (torch.bfloat16,))
+    return _call(marshal().attn_bwd_rope, stream, Q_rot, K_rot, V, O, dO, LSE, cos, sin, float(scale),
+                 bool(causal), dQ, dK_rot, dV, workspace)

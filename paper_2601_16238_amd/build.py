@@ -1,7 +1,9 @@
-"""Build libmi355attn.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree."""
+"""Build libmi355attn.so (HIP kernels + C ABI) for gfx950 with hipcc, and the torch marshalling
+module _marshal on top of it with the host compiler, in-tree."""
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -26,12 +28,37 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=f
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-command-line-argument"]
 
+MARSHAL = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
+
 
 def _hipcc():
     for c in (os.environ.get("HIPCC"), "/opt/rocm/bin/hipcc", "hipcc"):
         if c and (os.path.sep not in c or os.path.exists(c)):
             return c
     raise RuntimeError("hipcc not found")
+
+
+def build_marshal():
+    """Compile csrc/marshal.cpp (host code only) against torch; returns the function that links the
+    module with the library next to it."""
+    import torch
+    t = os.path.dirname(torch.__file__)
+    obj = os.path.join(OBJ, "marshal.o")
+    os.makedirs(OBJ, exist_ok=True)
+    includes = [os.path.join(t, "include"), os.path.join(t, "include", "torch", "csrc", "api", "include"),
+                "/opt/rocm/include", sysconfig.get_paths()["include"]]
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-w", "-D__HIP_PLATFORM_AMD__=1",
+                           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI]
+                          + ["-I" + d for d in includes]
+                          + ["-c", os.path.join(CSRC, "marshal.cpp"), "-o", obj])
+
+    def link():
+        tmp = MARSHAL + ".tmp%d" % os.getpid()
+        subprocess.check_call(["g++", "-shared", "-o", tmp, obj, "-L" + os.path.join(t, "lib"), "-lc10", "-lc10_hip",
+                               "-ltorch", "-ltorch_cpu", "-ltorch_python", "-L" + HERE, "-l:" + os.path.basename(LIB),
+                               "-Wl,-rpath,$ORIGIN"])
+        os.replace(tmp, MARSHAL)
+    return link
 
 
 def build(verbose=False, resource_usage=False, extra_flags=(), lib_path=LIB):
@@ -56,11 +83,14 @@ def build(verbose=False, resource_usage=False, extra_flags=(), lib_path=LIB):
             print(out)
         return obj
 
-    with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
+    with ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as ex:
+        link_marshal = ex.submit(build_marshal) if lib_path == LIB else None
         objs = list(ex.map(one, SOURCES))
     tmp = lib_path + ".tmp%d" % os.getpid()
     subprocess.check_call([cc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs)
     os.replace(tmp, lib_path)
+    if link_marshal is not None:
+        link_marshal.result()()
     return lib_path
 
 

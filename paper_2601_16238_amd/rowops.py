@@ -1,9 +1,9 @@
-"""Thin ctypes binding of the row-wise entry points of include/rowops.h (RMSNorm forward,
-LayerNorm forward and backward, rotary forward): argument marshalling only, every step runs
-in the HIP kernels of libmi355attn.so."""
+"""Thin binding of the row-wise entry points of include/rowops.h (RMSNorm forward, LayerNorm
+forward and backward, rotary forward): argument marshalling only (csrc/marshal.cpp), every step
+runs in the HIP kernels of libmi355attn.so."""
 import ctypes
 
-from .binding import ATTN_OK, AttnError, _stream_ptr, lib
+from .binding import lib, marshal
 
 EXPORTS = ("rowops_rmsnorm_fwd", "rowops_layernorm_fwd", "rowops_layernorm_bwd_workspace_bytes",
            "rowops_layernorm_bwd", "rowops_rotary_fwd")
@@ -28,47 +28,16 @@ def _lib():
     return L
 
 
-def _rows(t, name):
-    import torch
-    if t.dtype != torch.bfloat16 or not t.is_cuda or t.dim() != 2 or t.stride(1) != 1:
-        raise ValueError("%s must be a bf16 [rows, cols] GPU tensor with contiguous rows" % name)
-    return t
-
-
-def _f32(t, shape, name):
-    import torch
-    if t.dtype != torch.float32 or not t.is_cuda or not t.is_contiguous() or tuple(t.shape) != shape:
-        raise ValueError("%s must be a contiguous fp32 GPU tensor of shape %r" % (name, shape))
-    return t
-
-
-def _check(rc, where):
-    if rc != ATTN_OK:
-        raise AttnError(rc, where)
+def _stream(stream):
+    return None if stream is None else stream.cuda_stream
 
 
 def rmsnorm_fwd(x, w, eps, y=None, stream=None):
-    import torch
-    _rows(x, "x"); rows, cols = x.shape; _f32(w, (cols,), "w")
-    y = torch.empty_like(x) if y is None else _rows(y, "y")
-    _check(_lib().rowops_rmsnorm_fwd(x.data_ptr(), w.data_ptr(), y.data_ptr(), rows, cols,
-                                     x.stride(0), y.stride(0), float(eps),
-                                     _stream_ptr(torch, stream)), "rowops_rmsnorm_fwd")
-    return y
+    return marshal().rmsnorm_fwd(x, w, eps, y, _stream(stream))
 
 
 def layernorm_fwd(x, w, b, eps, y=None, mean=None, rstd=None, stream=None):
-    import torch
-    _rows(x, "x"); rows, cols = x.shape; _f32(w, (cols,), "w"); _f32(b, (cols,), "b")
-    y = torch.empty_like(x) if y is None else _rows(y, "y")
-    mean = torch.empty(rows, dtype=torch.float32, device=x.device) if mean is None else mean
-    rstd = torch.empty(rows, dtype=torch.float32, device=x.device) if rstd is None else rstd
-    _f32(mean, (rows,), "mean"); _f32(rstd, (rows,), "rstd")
-    _check(_lib().rowops_layernorm_fwd(x.data_ptr(), w.data_ptr(), b.data_ptr(), y.data_ptr(),
-                                       mean.data_ptr(), rstd.data_ptr(), rows, cols, x.stride(0),
-                                       y.stride(0), float(eps), _stream_ptr(torch, stream)),
-           "rowops_layernorm_fwd")
-    return y, mean, rstd
+    return marshal().layernorm_fwd(x, w, b, eps, y, mean, rstd, _stream(stream))
 
 
 def layernorm_bwd_workspace_bytes(rows, cols):
@@ -76,38 +45,8 @@ def layernorm_bwd_workspace_bytes(rows, cols):
 
 
 def layernorm_bwd(dy, x, w, mean, rstd, dx=None, dw=None, db=None, workspace=None, stream=None):
-    import torch
-    _rows(x, "x"); _rows(dy, "dy"); rows, cols = x.shape
-    if dy.shape != x.shape:
-        raise ValueError("dy and x must have one shape")
-    _f32(w, (cols,), "w"); _f32(mean, (rows,), "mean"); _f32(rstd, (rows,), "rstd")
-    dx = torch.empty_like(x) if dx is None else _rows(dx, "dx")
-    dw = torch.empty(cols, dtype=torch.float32, device=x.device) if dw is None else dw
-    db = torch.empty(cols, dtype=torch.float32, device=x.device) if db is None else db
-    _f32(dw, (cols,), "dw"); _f32(db, (cols,), "db")
-    need = layernorm_bwd_workspace_bytes(rows, cols)
-    if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
-    _check(_lib().rowops_layernorm_bwd(dy.data_ptr(), x.data_ptr(), w.data_ptr(), mean.data_ptr(),
-                                       rstd.data_ptr(), dx.data_ptr(), dw.data_ptr(), db.data_ptr(),
-                                       workspace.data_ptr(),
-                                       workspace.numel() * workspace.element_size(), rows, cols,
-                                       dy.stride(0), x.stride(0), dx.stride(0),
-                                       _stream_ptr(torch, stream)), "rowops_layernorm_bwd")
-    return dx, dw, db
+    return marshal().layernorm_bwd(dy, x, w, mean, rstd, dx, dw, db, workspace, _stream(stream))
 
 
 def rotary_fwd(x, cos, sin, y=None, stream=None):
-    import torch
-    if x.dtype != torch.bfloat16 or not x.is_cuda or x.dim() != 4 or x.stride(3) != 1:
-        raise ValueError("x must be a bf16 [B,H,S,D] GPU tensor with a contiguous D axis")
-    B, H, S, D = x.shape
-    _f32(cos, (S, D // 2), "cos"); _f32(sin, (S, D // 2), "sin")
-    if y is None:
-        y = torch.empty_strided(x.shape, x.stride(), dtype=x.dtype, device=x.device)
-    elif y.shape != x.shape or y.dtype != x.dtype or y.stride(3) != 1:
-        raise ValueError("y must match x in shape and type")
-    _check(_lib().rowops_rotary_fwd(x.data_ptr(), cos.data_ptr(), sin.data_ptr(), y.data_ptr(),
-                                    B, H, S, D, *x.stride()[:3], *y.stride()[:3],
-                                    _stream_ptr(torch, stream)), "rowops_rotary_fwd")
-    return y
+    return marshal().rotary_fwd(x, cos, sin, y, _stream(stream))
