@@ -1,12 +1,14 @@
 // Row-wise neighbours of attention for gfx950: RMSNorm forward, LayerNorm forward and
 // backward, rotary forward.  All are bound by HBM traffic: every activation element is read
 // once and written once, a whole row lives in the registers of one work-group between the
-// reduction and the normalisation, 16-byte accesses throughout.
+// reduction and the normalisation -- of one wave, for rows of at most kWaveCols columns --, 16-byte
+// accesses throughout.
 #include "../../include/attn.h"
 #include "../../include/rowops.h"
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace rowops {
 
@@ -17,6 +19,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kThreads = 256;          // threads that share one row
 constexpr int kWaves = kThreads / 64;
 constexpr int kMaxCols = 16384;        // 8 vectors of 8 elements per thread
+// Rows of at most this many columns belong to one wave each (up to 4 vectors of 8 elements per lane).
+constexpr int kWaveCols = 2048;
+constexpr int kWaveTeams = 8;          // waves = row teams of a LayerNorm backward work-group
 constexpr int kBwdTeams = 512;         // rows above which the LayerNorm backward pairs its row teams
 
 __device__ __forceinline__ bf16x8 load8(const __bf16 *p)
@@ -36,15 +41,34 @@ __device__ __forceinline__ void load8f(const float *p, float (&v)[8])
     v[4] = b[0]; v[5] = b[1]; v[6] = b[2]; v[7] = b[3];
 }
 
-// Sum of N values per thread over the work-group; every thread gets the result.  `red` is
-// LDS scratch of kWaves * N floats; the trailing barrier makes it reusable at once.
-template <int N>
-__device__ __forceinline__ void block_sum(float (&v)[N], float *red)
+// Sum of a value over the wave, in registers (a butterfly of cross-lane moves: lane distances 1, 2, 4
+// and 8 inside a row of 16 lanes, then 16 and 32); every lane gets the result.
+__device__ __forceinline__ float wave_sum(float v)
+{
+    auto moved = [](float x, auto ctrl) __attribute__((always_inline)) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), decltype(ctrl)::value,
+                                                                   0xf, 0xf, true));
+    };
+    v += moved(v, std::integral_constant<int, 0xB1>());   // quad_perm [1,0,3,2]
+    v += moved(v, std::integral_constant<int, 0x4E>());   // quad_perm [2,3,0,1]
+    v += moved(v, std::integral_constant<int, 0x141>());  // row_half_mirror: the other quad of 8 lanes
+    v += moved(v, std::integral_constant<int, 0x140>());  // row_mirror: the other 8 of 16 lanes
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r.x) + __uint_as_float(r.y);
+    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r.x) + __uint_as_float(r.y);
+}
+
+// Sum of N values per thread over the threads that share a row (TEAM of them: a wave, or the whole
+// work-group of the forward kernels); every thread gets the result.  `red` is LDS scratch of
+// kWaves * N floats; the trailing barrier makes it reusable at once.
+template <int TEAM, int N>
+__device__ __forceinline__ void team_sum(float (&v)[N], float *red)
 {
 #pragma unroll
-    for (int n = 0; n < N; ++n)
-#pragma unroll
-        for (int s = 32; s >= 1; s >>= 1) v[n] += __shfl_xor(v[n], s);
+    for (int n = 0; n < N; ++n) v[n] = wave_sum(v[n]);
+    if constexpr (TEAM == 64) return;
     const int w = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0)
 #pragma unroll
@@ -60,24 +84,6 @@ __device__ __forceinline__ void block_sum(float (&v)[N], float *red)
     __syncthreads();
 }
 
-// Thread t owns vectors t, t + 256, ... (V of them) of 8 consecutive columns each.
-template <int V>
-__device__ __forceinline__ void load_row(const __bf16 *row, int cols, float (&x)[V][8])
-{
-#pragma unroll
-    for (int v = 0; v < V; ++v) {
-        const int c = (threadIdx.x + v * kThreads) * 8;
-        if (c < cols) {
-            const bf16x8 b = load8(row + c);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) x[v][e] = (float)b[e];
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) x[v][e] = 0.f;
-        }
-    }
-}
-
 // Raw 16-byte vectors of a row, fetched one row ahead by the kernels that walk several rows.
 // With four or more vectors per thread the loads are unconditional (vectors past the row's end
 // re-read its first one; unpack_row zeroes them) and the widened values are pinned by an empty
@@ -85,62 +91,69 @@ __device__ __forceinline__ void load_row(const __bf16 *row, int cols, float (&x)
 // compiler can count the loads it waits for: -1 % at 8192 columns, -6 % at 16384.  Narrower
 // rows, whose three or four resident work-groups per unit already cover the latency, are
 // 5-8 % faster in the plain form.
-template <int V>
+template <int V, int TEAM>
 __device__ __forceinline__ void fetch_row(const __bf16 *row, int cols, u32x4 (&raw)[V], int t)
 {
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-        const int c = (t + v * kThreads) * 8;
-        if constexpr (V >= 4) raw[v] = *(const u32x4 *)(row + (c < cols ? c : 0));
+        const int c = (t + v * TEAM) * 8;
+        if constexpr (V >= 4 && TEAM == kThreads) raw[v] = *(const u32x4 *)(row + (c < cols ? c : 0));
         else if (c < cols) raw[v] = *(const u32x4 *)(row + c);
     }
 }
-template <int V>
+template <int V, int TEAM>
 __device__ __forceinline__ void unpack_row(const u32x4 (&raw)[V], int cols, float (&x)[V][8], int t)
 {
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-        const int c = (t + v * kThreads) * 8;
+        const int c = (t + v * TEAM) * 8;
         const bf16x8 b = __builtin_bit_cast(bf16x8, raw[v]);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             x[v][e] = c < cols ? (float)b[e] : 0.f;
-            if constexpr (V >= 4) asm volatile("" : "+v"(x[v][e]));
+            if constexpr (V >= 4 && TEAM == kThreads) asm volatile("" : "+v"(x[v][e]));
         }
     }
 }
 
-// The forward kernels run a fixed number of work-groups (see fwd_groups);
-// each walks rows group, group + G, ... with its slice of the parameters in registers (loaded
-// once instead of once per row) and fetches its next row while it works on the current one.
-template <int V>
+// The forward kernels run a fixed number of work-groups (see fwd_groups) of kThreads / TEAM row
+// teams; each team walks rows team, team + teams, ... with its slice of the parameters in registers
+// (loaded once instead of once per row) and fetches its next row while it works on the current one.
+// Thread t of a team owns vectors t, t + TEAM, ... (V of them) of 8 consecutive columns each.
+// TEAM = 64, rows of up to kWaveCols columns: a row is a wave's alone and its sums stay in registers.
+// With the whole work-group on such a row three quarters and more of the threads idle and every row
+// pays two barriers per sum.
+template <int V, int TEAM>
 __global__ void __launch_bounds__(kThreads)
 rmsnorm_fwd_kernel(const __bf16 *x, const float *w, __bf16 *y, int64_t rows, int cols, int64_t xs,
                    int64_t ys, float eps)
 {
     __shared__ float red[kWaves];
+    const int t = threadIdx.x % TEAM;
+    const int64_t first = (int64_t)blockIdx.x * (kThreads / TEAM) + threadIdx.x / TEAM;
+    const int64_t step = (int64_t)gridDim.x * (kThreads / TEAM);
     float wv[V][8];
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-        const int c = (threadIdx.x + v * kThreads) * 8;
+        const int c = (t + v * TEAM) * 8;
         if (c < cols) load8f(w + c, wv[v]);
     }
     u32x4 nx[V] = {};
-    if ((int64_t)blockIdx.x < rows) fetch_row<V>(x + blockIdx.x * xs, cols, nx, threadIdx.x);
-    for (int64_t i = blockIdx.x; i < rows; i += gridDim.x) {
+    if (first < rows) fetch_row<V, TEAM>(x + first * xs, cols, nx, t);
+    for (int64_t i = first; i < rows; i += step) {
         float xv[V][8];
-        unpack_row<V>(nx, cols, xv, threadIdx.x);
-        if (i + gridDim.x < rows) fetch_row<V>(x + (i + gridDim.x) * xs, cols, nx, threadIdx.x);
+        unpack_row<V, TEAM>(nx, cols, xv, t);
+        if (i + step < rows) fetch_row<V, TEAM>(x + (i + step) * xs, cols, nx, t);
         float ss[1] = {0.f};
 #pragma unroll
         for (int v = 0; v < V; ++v)
 #pragma unroll
             for (int e = 0; e < 8; ++e) ss[0] += xv[v][e] * xv[v][e];
-        block_sum<1>(ss, red);
+        team_sum<TEAM>(ss, red);
         const float r = 1.0f / sqrtf(ss[0] / (float)cols + eps);
 #pragma unroll
         for (int v = 0; v < V; ++v) {
-            const int c = (threadIdx.x + v * kThreads) * 8;
+            const int c = (t + v * TEAM) * 8;
             if (c < cols) {
                 float o[8];
 #pragma unroll
@@ -151,39 +164,42 @@ rmsnorm_fwd_kernel(const __bf16 *x, const float *w, __bf16 *y, int64_t rows, int
     }
 }
 
-template <int V>
+template <int V, int TEAM>
 __global__ void __launch_bounds__(kThreads)
 layernorm_fwd_kernel(const __bf16 *x, const float *w, const float *b, __bf16 *y, float *mean,
                      float *rstd, int64_t rows, int cols, int64_t xs, int64_t ys, float eps)
 {
     __shared__ float red[kWaves];
+    const int t = threadIdx.x % TEAM;
+    const int64_t first = (int64_t)blockIdx.x * (kThreads / TEAM) + threadIdx.x / TEAM;
+    const int64_t step = (int64_t)gridDim.x * (kThreads / TEAM);
     float wv[V][8], bv[V][8];
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-        const int c = (threadIdx.x + v * kThreads) * 8;
+        const int c = (t + v * TEAM) * 8;
         if (c < cols) {
             load8f(w + c, wv[v]);
             load8f(b + c, bv[v]);
         }
     }
     u32x4 nx[V] = {};
-    if ((int64_t)blockIdx.x < rows) fetch_row<V>(x + blockIdx.x * xs, cols, nx, threadIdx.x);
-    for (int64_t i = blockIdx.x; i < rows; i += gridDim.x) {
+    if (first < rows) fetch_row<V, TEAM>(x + first * xs, cols, nx, t);
+    for (int64_t i = first; i < rows; i += step) {
         float xv[V][8];
-        unpack_row<V>(nx, cols, xv, threadIdx.x);
-        if (i + gridDim.x < rows) fetch_row<V>(x + (i + gridDim.x) * xs, cols, nx, threadIdx.x);
+        unpack_row<V, TEAM>(nx, cols, xv, t);
+        if (i + step < rows) fetch_row<V, TEAM>(x + (i + step) * xs, cols, nx, t);
         float s[1] = {0.f};
 #pragma unroll
         for (int v = 0; v < V; ++v)
 #pragma unroll
             for (int e = 0; e < 8; ++e) s[0] += xv[v][e];
-        block_sum<1>(s, red);
+        team_sum<TEAM>(s, red);
         const float mu = s[0] / (float)cols;
         // second pass over the registers: the variance of the centred values
         float q[1] = {0.f};
 #pragma unroll
         for (int v = 0; v < V; ++v) {
-            const int c = (threadIdx.x + v * kThreads) * 8;
+            const int c = (t + v * TEAM) * 8;
             if (c < cols)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
@@ -191,15 +207,15 @@ layernorm_fwd_kernel(const __bf16 *x, const float *w, const float *b, __bf16 *y,
                     q[0] += xv[v][e] * xv[v][e];
                 }
         }
-        block_sum<1>(q, red);
+        team_sum<TEAM>(q, red);
         const float r = 1.0f / sqrtf(q[0] / (float)cols + eps);
-        if (threadIdx.x == 0) {
+        if (t == 0) {
             mean[i] = mu;
             rstd[i] = r;
         }
 #pragma unroll
         for (int v = 0; v < V; ++v) {
-            const int c = (threadIdx.x + v * kThreads) * 8;
+            const int c = (t + v * TEAM) * 8;
             if (c < cols) {
                 float o[8];
 #pragma unroll
@@ -210,25 +226,27 @@ layernorm_fwd_kernel(const __bf16 *x, const float *w, const float *b, __bf16 *y,
     }
 }
 
-// Backward.  A work-group is T teams of kThreads threads; each team takes one row at a time
+// Backward.  A work-group is T teams of TEAM threads; each team takes one row at a time
 // (round j of the work-group covers rows (j * G + group) * T + team) and computes its dx.  The
 // column sums of dw and db stay in registers across a team's rows; at the end the teams add
 // theirs together through LDS, in team order, and the work-group writes one partial row:
 // part[g][0][cols] = dw, part[g][1][cols] = db.  More teams per work-group mean fewer partial
 // rows to write here and to read in the column kernel, at the same number of waves per unit.
-template <int V, int T>
-__global__ void __launch_bounds__(kThreads * T)
+// TEAM = 64 (rows of up to kWaveCols columns): as in the forward, no barrier inside the loop.
+template <int V, int TEAM, int T>
+__global__ void __launch_bounds__(TEAM * T)
 layernorm_bwd_rows_kernel(const __bf16 *dy, const __bf16 *x, const float *w, const float *mean,
                           const float *rstd, __bf16 *dx, float *part, int64_t rows, int cols,
                           int64_t dys, int64_t xs, int64_t dxs)
 {
-    __shared__ float red[T * kWaves * 2];
-    __shared__ float comb[T > 1 ? 16 * kThreads : 1];
-    const int t = threadIdx.x % kThreads, team = threadIdx.x / kThreads;
+    constexpr int kWpt = TEAM / 64;  // waves per team
+    __shared__ float red[T * kWpt * 2];
+    __shared__ float comb[T == 1 ? 1 : (TEAM == 64 ? T : 1) * 16 * TEAM];
+    const int t = threadIdx.x % TEAM, team = threadIdx.x / TEAM;
     float wv[V][8], dwp[V][8], dbp[V][8];
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-        const int c = (t + v * kThreads) * 8;
+        const int c = (t + v * TEAM) * 8;
         if (c < cols) load8f(w + c, wv[v]);
 #pragma unroll
         for (int e = 0; e < 8; ++e) { dwp[v][e] = 0.f; dbp[v][e] = 0.f; }
@@ -243,7 +261,7 @@ layernorm_bwd_rows_kernel(const __bf16 *dy, const __bf16 *x, const float *w, con
     auto fetch = [&](int64_t i) __attribute__((always_inline)) {
 #pragma unroll
         for (int v = 0; v < V; ++v) {
-            const int c = (t + v * kThreads) * 8;
+            const int c = (t + v * TEAM) * 8;
             nx[v] = *(const u32x4 *)(x + i * xs + (c < cols ? c : 0));
             ng[v] = *(const u32x4 *)(dy + i * dys + (c < cols ? c : 0));
         }
@@ -261,8 +279,8 @@ layernorm_bwd_rows_kernel(const __bf16 *dy, const __bf16 *x, const float *w, con
         float s[2] = {0.f, 0.f};  // sum g, sum g*xhat with g = dy*w
         // (the fetch stands outside the `live` branch so that its registers are not merged
         // with another path at the branch's end, which would make the wave wait for them there)
-        unpack_row<V>(nx, cols, xv, t);
-        unpack_row<V>(ng, cols, gv, t);
+        unpack_row<V, TEAM>(nx, cols, xv, t);
+        unpack_row<V, TEAM>(ng, cols, gv, t);
         const float mu = nmu, r = nr;
         // the row is unpacked here, before the raw registers are loaded again
 #pragma unroll
@@ -273,7 +291,7 @@ layernorm_bwd_rows_kernel(const __bf16 *dy, const __bf16 *x, const float *w, con
         if (live) {
 #pragma unroll
             for (int v = 0; v < V; ++v) {
-                const int c = (t + v * kThreads) * 8;
+                const int c = (t + v * TEAM) * 8;
                 if (c < cols)
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
@@ -287,27 +305,27 @@ layernorm_bwd_rows_kernel(const __bf16 *dy, const __bf16 *x, const float *w, con
             }
         }
         // sums over the team
+        s[0] = wave_sum(s[0]);
+        s[1] = wave_sum(s[1]);
+        if constexpr (TEAM > 64) {
+            if ((threadIdx.x & 63) == 0) {
+                red[(threadIdx.x >> 6) * 2 + 0] = s[0];
+                red[(threadIdx.x >> 6) * 2 + 1] = s[1];
+            }
+            __syncthreads();
+            s[0] = s[1] = 0.f;
 #pragma unroll
-        for (int n = 0; n < 2; ++n)
-#pragma unroll
-            for (int m = 32; m >= 1; m >>= 1) s[n] += __shfl_xor(s[n], m);
-        if ((threadIdx.x & 63) == 0) {
-            red[(threadIdx.x >> 6) * 2 + 0] = s[0];
-            red[(threadIdx.x >> 6) * 2 + 1] = s[1];
+            for (int k = 0; k < kWpt; ++k) {
+                s[0] += red[(team * kWpt + k) * 2 + 0];
+                s[1] += red[(team * kWpt + k) * 2 + 1];
+            }
+            __syncthreads();
         }
-        __syncthreads();
-        s[0] = s[1] = 0.f;
-#pragma unroll
-        for (int k = 0; k < kWaves; ++k) {
-            s[0] += red[(team * kWaves + k) * 2 + 0];
-            s[1] += red[(team * kWaves + k) * 2 + 1];
-        }
-        __syncthreads();
         if (live) {
             const float mg = s[0] / (float)cols, mgx = s[1] / (float)cols;
 #pragma unroll
             for (int v = 0; v < V; ++v) {
-                const int c = (t + v * kThreads) * 8;
+                const int c = (t + v * TEAM) * 8;
                 if (c < cols) {
                     float o[8];
 #pragma unroll
@@ -317,6 +335,33 @@ layernorm_bwd_rows_kernel(const __bf16 *dy, const __bf16 *x, const float *w, con
             }
         }
     }
+    float *pw = part + (int64_t)blockIdx.x * 2 * cols, *pb = pw + cols;
+    if constexpr (TEAM == 64) {
+        // every team's column sums of one vector slot side by side in LDS; then a thread adds the
+        // teams' values of a column, in team order
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            float *mine = comb + team * 1024 + t * 8;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                f32x4 a, b;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { a[e] = dwp[v][4 * h + e]; b[e] = dbp[v][4 * h + e]; }
+                *(f32x4 *)(mine + 4 * h) = a;
+                *(f32x4 *)(mine + 512 + 4 * h) = b;
+            }
+            __syncthreads();
+            for (int j = threadIdx.x; j < 1024; j += 64 * T) {
+                float sum = comb[j];
+#pragma unroll
+                for (int k = 1; k < T; ++k) sum += comb[k * 1024 + j];
+                const int c = v * 512 + (j & 511);
+                if (c < cols) (j < 512 ? pw : pb)[c] = sum;
+            }
+            __syncthreads();
+        }
+        return;
+    }
     // teams 1 .. T-1 hand their column sums to team 0, one vector slot at a time
     if (T > 1) {
 #pragma unroll
@@ -325,24 +370,23 @@ layernorm_bwd_rows_kernel(const __bf16 *dy, const __bf16 *x, const float *w, con
                 if (team == k)
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
-                        comb[e * kThreads + t] = dwp[v][e];
-                        comb[(8 + e) * kThreads + t] = dbp[v][e];
+                        comb[e * TEAM + t] = dwp[v][e];
+                        comb[(8 + e) * TEAM + t] = dbp[v][e];
                     }
                 __syncthreads();
                 if (team == 0)
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
-                        dwp[v][e] += comb[e * kThreads + t];
-                        dbp[v][e] += comb[(8 + e) * kThreads + t];
+                        dwp[v][e] += comb[e * TEAM + t];
+                        dbp[v][e] += comb[(8 + e) * TEAM + t];
                     }
                 __syncthreads();
             }
     }
     if (team != 0) return;
-    float *pw = part + (int64_t)blockIdx.x * 2 * cols, *pb = pw + cols;
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-        const int c = (t + v * kThreads) * 8;
+        const int c = (t + v * TEAM) * 8;
         if (c < cols)
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
@@ -364,20 +408,26 @@ __global__ void __launch_bounds__(256)
 layernorm_bwd_cols_kernel(const float *part, float *dw, float *db, int groups, int cols)
 {
     constexpr int kLanes = W / 4, kSlices = 256 / kLanes;
-    __shared__ f32x4 red[kSlices][kLanes];
+    __shared__ f32x4 red[4][kLanes];
     const int q = threadIdx.x % kLanes, slice = threadIdx.x / kLanes;
     const int c = blockIdx.x * W + q * 4;  // position within the 2 * cols floats of a group
     const bool in_range = c < 2 * cols;    // the last work-group may be ragged
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     if (in_range)
+#pragma unroll 4
         for (int g = slice; g < groups; g += kSlices)
             acc += *(const f32x4 *)(part + (int64_t)g * 2 * cols + c);
-    red[slice][q] = acc;
+    // the slices of a wave by cross-lane exchange, then the waves through LDS
+#pragma unroll
+    for (int m = kLanes; m < 64; m <<= 1)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], m);
+    if ((threadIdx.x & 63) < kLanes) red[threadIdx.x >> 6][q] = acc;
     __syncthreads();
-    if (slice == 0 && in_range) {
+    if (threadIdx.x < kLanes && in_range) {
         f32x4 t = red[0][q];
 #pragma unroll
-        for (int i = 1; i < kSlices; ++i) t += red[i][q];
+        for (int i = 1; i < 4; ++i) t += red[i][q];
         *(f32x4 *)((c < cols ? dw : db - cols) + c) = t;
     }
 }
@@ -450,12 +500,40 @@ int fwd_groups(int64_t rows, int V, bool layernorm)
     return (int)(rows < g ? rows : g);
 }
 
-// vectors per thread: 1, 2, 4 or 8
+// vectors per thread: 1, 2, 4 or 8 with the work-group on a row, 1 .. 4 with a wave on it
 int vectors_for(int cols)
 {
     const int v = (cols / 8 + kThreads - 1) / kThreads;
     return v <= 1 ? 1 : v <= 2 ? 2 : v <= 4 ? 4 : 8;
 }
+int wave_vectors_for(int cols) { return (cols / 8 + 63) / 64; }
+
+// Kernels with a wave per row (up to kWaveCols columns).  Against the whole work-group on a row, us:
+// RMSNorm (8320, 384) 7.0 -> 4.3, (65536, 256) 31.2 -> 14.3, (16384, 1024) 13.2 -> 11.2, (16384, 2048)
+// 21.6 -> 21.2; LayerNorm forward 10.8 -> 5.2, 56.5 -> 18.6, 19.3 -> 12.5, 24.3 -> 22.6; backward
+// 19.3 -> 10.3, 85.8 -> 25.9, 31.6 -> 20.5, 40.6 -> 38.8.  Above 1024 columns the backward needs rows
+// enough for its eight-wave work-groups: (134, 1816) 8.4 against 6.7 with a work-group per row,
+// (2000, 1536) 12.1 against 15.8.  Wider rows cost registers the wave does not have (16 waves of V = 4
+// spill: 204 us at (16384, 2048)).
+bool wave_bwd(int64_t rows, int cols) { return cols <= kWaveCols && (cols <= 1024 || rows >= 1024); }
+// Backward work-groups: one per compute unit; two for long narrow problems ((35955, 320) 20.9 -> 18.6 us;
+// (8320, 384) 10.3 -> 10.6), whose partial sums are then small against the rows.
+int64_t wave_bwd_cap(int64_t rows, int V) { return V == 1 && rows > 16384 ? 512 : 256; }
+// Work-groups of `teams` waves: at most `cap`, and no more than give every wave the same number of
+// rows (or one fewer).
+int wave_groups(int64_t rows, int teams, int64_t cap)
+{
+    const int64_t per = (rows + cap * teams - 1) / (cap * teams);  // rows per wave
+    return (int)((rows + per * teams - 1) / (per * teams));
+}
+
+#define ROWOPS_WAVE_DISPATCH(V, CALL)       \
+    switch (V) {                            \
+        case 1: { constexpr int kV = 1; CALL; } break; \
+        case 2: { constexpr int kV = 2; CALL; } break; \
+        case 3: { constexpr int kV = 3; CALL; } break; \
+        default: { constexpr int kV = 4; CALL; } break; \
+    }
 
 #define ROWOPS_DISPATCH(V, CALL)            \
     switch (V) {                            \
@@ -479,8 +557,14 @@ int rowops_rmsnorm_fwd(const void *x, const float *w, void *y, int64_t rows, int
     if (rc != ATTN_OK) return rc;
     if (!aligned(x, 16) || !aligned(w, 16) || !aligned(y, 16)) return ATTN_ERR_ALIGN;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    if (cols <= kWaveCols) {
+        ROWOPS_WAVE_DISPATCH(wave_vectors_for(cols),
+            hipLaunchKernelGGL((rmsnorm_fwd_kernel<kV, 64>), dim3(wave_groups(rows, kWaves, 4096)), dim3(kThreads), 0, st,
+                               static_cast<const __bf16 *>(x), w, static_cast<__bf16 *>(y), rows, cols,
+                               x_row_stride, y_row_stride, eps));
+    } else
     ROWOPS_DISPATCH(vectors_for(cols),
-        hipLaunchKernelGGL((rmsnorm_fwd_kernel<kV>), dim3(fwd_groups(rows, kV, false)), dim3(kThreads), 0, st,
+        hipLaunchKernelGGL((rmsnorm_fwd_kernel<kV, kThreads>), dim3(fwd_groups(rows, kV, false)), dim3(kThreads), 0, st,
                            static_cast<const __bf16 *>(x), w, static_cast<__bf16 *>(y), rows, cols,
                            x_row_stride, y_row_stride, eps));
     return hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_ERR_LAUNCH;
@@ -497,8 +581,14 @@ int rowops_layernorm_fwd(const void *x, const float *w, const float *b, void *y,
         !aligned(mean, 4) || !aligned(rstd, 4))
         return ATTN_ERR_ALIGN;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    if (cols <= kWaveCols) {
+        ROWOPS_WAVE_DISPATCH(wave_vectors_for(cols),
+            hipLaunchKernelGGL((layernorm_fwd_kernel<kV, 64>), dim3(wave_groups(rows, kWaves, 4096)), dim3(kThreads), 0, st,
+                               static_cast<const __bf16 *>(x), w, b, static_cast<__bf16 *>(y), mean,
+                               rstd, rows, cols, x_row_stride, y_row_stride, eps));
+    } else
     ROWOPS_DISPATCH(vectors_for(cols),
-        hipLaunchKernelGGL((layernorm_fwd_kernel<kV>), dim3(fwd_groups(rows, kV, true)), dim3(kThreads), 0, st,
+        hipLaunchKernelGGL((layernorm_fwd_kernel<kV, kThreads>), dim3(fwd_groups(rows, kV, true)), dim3(kThreads), 0, st,
                            static_cast<const __bf16 *>(x), w, b, static_cast<__bf16 *>(y), mean,
                            rstd, rows, cols, x_row_stride, y_row_stride, eps));
     return hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_ERR_LAUNCH;
@@ -527,21 +617,25 @@ int rowops_layernorm_bwd(const void *dy, const void *x, const float *w, const fl
         workspace_bytes < rowops_layernorm_bwd_workspace_bytes(rows, cols))
         return ATTN_ERR_WORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    const int V = vectors_for(cols), groups = bwd_groups(rows, V);
+    const bool wave_rows = wave_bwd(rows, cols);
+    const int V = wave_rows ? wave_vectors_for(cols) : vectors_for(cols);
+    const int groups = wave_rows ? wave_groups(rows, kWaveTeams, wave_bwd_cap(rows, V)) : bwd_groups(rows, V);
     float *part = static_cast<float *>(workspace);
-#define ROWOPS_LN_BWD(T)                                                                          \
-    hipLaunchKernelGGL((layernorm_bwd_rows_kernel<kV, T>), dim3(groups), dim3(kThreads * T), 0,   \
+#define ROWOPS_LN_BWD(TEAM, T)                                                                    \
+    hipLaunchKernelGGL((layernorm_bwd_rows_kernel<kV, TEAM, T>), dim3(groups), dim3(TEAM * T), 0, \
                        st, static_cast<const __bf16 *>(dy), static_cast<const __bf16 *>(x), w,    \
                        mean, rstd, static_cast<__bf16 *>(dx), part, rows, cols, dy_row_stride,    \
                        x_row_stride, dx_row_stride)
-    if (bwd_teams(rows, V) == 2) {
+    if (wave_rows) {
+        ROWOPS_WAVE_DISPATCH(V, ROWOPS_LN_BWD(64, kWaveTeams));
+    } else if (bwd_teams(rows, V) == 2) {
         switch (V) {
-            case 1: { constexpr int kV = 1; ROWOPS_LN_BWD(2); } break;
-            case 2: { constexpr int kV = 2; ROWOPS_LN_BWD(2); } break;
-            default: { constexpr int kV = 4; ROWOPS_LN_BWD(2); } break;
+            case 1: { constexpr int kV = 1; ROWOPS_LN_BWD(kThreads, 2); } break;
+            case 2: { constexpr int kV = 2; ROWOPS_LN_BWD(kThreads, 2); } break;
+            default: { constexpr int kV = 4; ROWOPS_LN_BWD(kThreads, 2); } break;
         }
     } else {
-        ROWOPS_DISPATCH(V, ROWOPS_LN_BWD(1));
+        ROWOPS_DISPATCH(V, ROWOPS_LN_BWD(kThreads, 1));
     }
 #undef ROWOPS_LN_BWD
     if (hipGetLastError() != hipSuccess) return ATTN_ERR_LAUNCH;
