@@ -151,7 +151,7 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
     // read it (grouped-query attention; group == 1 is multi-head attention).
     const int Hkv = a.H / a.group;
     int bkv, kt;  // causal: key block 0 is the heaviest
-    xcd_tile_order<CAUSAL>(blockIdx.x, a.ntile, a.BH / a.group, bkv, kt);
+    xcd_tile_order<CAUSAL, D == 64>(blockIdx.x, a.ntile, a.BH / a.group, bkv, kt);
     int item = 0, z = 0;  // SPLIT: chunk of the head, and of the key block
     if (SPLIT) {
         item = __builtin_amdgcn_readfirstlane(kt);
@@ -650,7 +650,7 @@ attn_bwd_dq_kernel(const BwdArgs a)
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int S = a.S;
     int bh, rank;
-    xcd_tile_order<CAUSAL>(blockIdx.x, a.ntile, a.BH, bh, rank);
+    xcd_tile_order<CAUSAL, D == 64 && NW == 4>(blockIdx.x, a.ntile, a.BH, bh, rank);
     const int qt = CAUSAL ? a.ntile - 1 - rank : rank;  // heaviest first
     const int64_t base = (int64_t)(bh / a.H) * a.stride_b + (int64_t)(bh % a.H) * a.stride_h;
     // grouped-query heads: query head h reads K/V head h / group

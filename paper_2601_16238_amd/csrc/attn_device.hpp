@@ -241,18 +241,48 @@ __device__ __forceinline__ int xcd_contiguous_order(int id, int total)
 // the group, and the launch ends with the tail of the last group, so a launch of only a few
 // rounds of work-groups keeps all heads in one group, heaviest tiles of all heads first
 // (B=8 H=8 S=1024 backward, two rounds: 66 us against 74 us with groups of four).
-// Falls back to the contiguous order when the heads do not divide evenly over the XCDs.
-template <bool CAUSAL>
+// Heads that do not divide evenly over the XCDs: without a mask the contiguous order.  Under a causal
+// mask that order hands one XCD the long work-groups of a head and the next one its short ones; there
+// the BH % 8 heads left over are spread over all XCDs, every eighth of their tiles (heaviest first) to
+// each, and the other heads as above.  In a launch of few rounds the two kinds are interleaved in
+// proportion, so that both run heaviest first; otherwise the tiles of the heads left over come first.
+// (17 heads of 3000 rows, D = 128, dQ 128 -> 91 us, dK/dV 144 -> 100; 20 of 2000, D = 64, forward
+// 38 -> 28.)
+// PAIRED: two work-groups are resident on a compute unit.  A causal launch of at most that many is
+// balanced by giving each unit a heavy and a light one: the second round in reverse order (64 heads of
+// 1024 rows, D = 64, forward 22.5 -> 19.9 us, dK/dV 29.7 -> 28.0).
+template <bool CAUSAL, bool PAIRED = false>
 __device__ __forceinline__ void xcd_tile_order(int id_, int ntile_, int BH_, int &bh, int &rank)
 {
     // (unsigned throughout: nothing here is negative, and an unsigned division by a run-time
     // value is a third shorter than a signed one)
     constexpr unsigned kXcd = 8, kCuPerXcd = 32;
     const unsigned id = id_, ntile = ntile_, BH = BH_;
-    if (BH % kXcd == 0) {
-        const unsigned hpx = BH / kXcd, x = id % kXcd, pos = id / kXcd;
+    const unsigned over = BH % kXcd;  // heads left over
+    if (over == 0 || CAUSAL) {
+        const unsigned hpx = BH / kXcd, x = id % kXcd;
+        unsigned pos = id / kXcd;
+        const unsigned whole = hpx * ntile;  // tiles of the XCD's own heads
+        const unsigned n_over = (over * ntile + kXcd - 1 - x) / kXcd, n = whole + n_over;
+        if (CAUSAL && PAIRED && n <= 2 * kCuPerXcd && pos >= kCuPerXcd) pos = kCuPerXcd + (n - 1 - pos);
+        if (CAUSAL && over) {
+            // how many of the first `pos` (and pos + 1) work-groups are tiles of the heads left over
+            const bool few = n < 4 * kCuPerXcd;
+            auto before = [&](unsigned p) {
+                const unsigned share = few ? p * over / (kXcd * hpx + over) : p;
+                return min(max(share, p > whole ? p - whole : 0u), min(n_over, p));
+            };
+            const unsigned o = before(pos);
+            if (before(pos + 1) > o) {
+                const unsigned j = o * kXcd + x;
+                rank = (int)(j / over);
+                bh = (int)(kXcd * hpx + (j - (j / over) * over));
+                return;
+            }
+            pos -= o;
+        }
         unsigned G = 1;  // heads per group
-        if (CAUSAL) G = hpx * ntile >= 4 * kCuPerXcd ? max(4u, (kCuPerXcd + ntile - 1) / ntile) : hpx;
+        if (CAUSAL) G = whole >= 4 * kCuPerXcd ? max(4u, (kCuPerXcd + ntile - 1) / ntile) : hpx;
         const unsigned group = pos / (G * ntile), within = pos - group * (G * ntile);
         const unsigned heads = min(G, hpx - group * G);  // the last group may be smaller
         const unsigned rk = within / heads;
