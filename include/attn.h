@@ -180,9 +180,10 @@ int attn_bwd_gqa_stages(const void *Q, const void *K, const void *V, const void 
  * chip idle (decoding: Sq = 1), the key range is cut into splits that run as separate
  * work-groups and write fp32 partial results to `workspace`; a second small kernel merges
  * them (log-sum-exp weights).  attn_fwd_rect_workspace_bytes returns what that needs for the
- * problem, 0 when it would not split.  workspace == NULL (with any size) is allowed and
- * means: do not split.  A non-NULL workspace must be 256-byte aligned and at least that
- * large, else ATTN_ERR_WORKSPACE; its contents are undefined on entry and exit.  The split
+ * problem with or without a causal mask (the larger of the two), 0 when neither would split.
+ * workspace == NULL (with any size) is allowed and
+ * means: do not split.  A non-NULL workspace must be 256-byte aligned and large enough for the
+ * split of this call (that size always is), else ATTN_ERR_WORKSPACE; its contents are undefined on entry and exit.  The split
  * plan depends only on the shape and the strides, so results are deterministic.
  *
  * Backward: as attn_bwd_gqa.  Keys that no row sees get zero gradients.  Workspace: the row

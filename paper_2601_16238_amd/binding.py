@@ -355,8 +355,8 @@ def _rect_params_for(q, k, scale, causal):
 
 
 def attn_fwd_rect_workspace_bytes(B, Hq, Hkv, Sq, Sk, D, causal=False):
-    """Bytes attn_fwd_rect needs to split this problem over the keys (0: it would not split).
-    The plan may use fewer splits under a causal mask, never more."""
+    """Bytes attn_fwd_rect needs to split this problem over the keys, causal or not (0: it would
+    not split)."""
     p = make_rect_params(B, Hq, Hkv, Sq, Sk, D, 1.0, causal)
     return int(lib().attn_fwd_rect_workspace_bytes(ctypes.byref(p)))
 

@@ -125,15 +125,25 @@ bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) %
 }  // namespace
 
 // E: element type of Q, K, V, O (__bf16 or _Float16)
-// Workspace of the forward's split over the keys for this problem (0: it would not split).
-static size_t fwd_workspace_bytes(const attn_rect_params_t *p, bool rope)
+// Workspace that the forward's split over the keys takes with this problem's mask (0: it does not split).
+static size_t fwd_split_bytes(const attn_rect_params_t *p, bool rope)
 {
-    if (check_params(p) != ATTN_OK) return 0;
     const FwdView v = fwd_view(*p, rope);
     const int nsplit = attn::fwd_split_plan(v.BH, v.S, p->Sk, kernel_d(p->D), v.causal, nullptr);
     if (nsplit <= 1) return 0;
     const size_t rows = (size_t)p->B * p->Hq * p->Sq;
     return round_ws((size_t)nsplit * rows * (kernel_d(p->D) + 1) * sizeof(float));
+}
+
+// What is asked of the caller: enough for the problem with and without a causal mask, so that a
+// workspace sized with one serves the other.
+static size_t fwd_workspace_bytes(const attn_rect_params_t *p, bool rope)
+{
+    if (check_params(p) != ATTN_OK) return 0;
+    attn_rect_params_t masked = *p, unmasked = *p;
+    masked.causal = p->Sk >= p->Sq;
+    unmasked.causal = 0;
+    return std::max(fwd_split_bytes(&masked, rope), fwd_split_bytes(&unmasked, rope));
 }
 
 // The backward's row statistics: two fp32 values per query row.
@@ -145,9 +155,9 @@ static size_t bwd_stats_bytes(const attn_rect_params_t *p)
 // The fp32 partial results of the dQ kernel's split over the keys and of the dK/dV kernel's split
 // over the query slots (0: not split).  The two kernels run one after the other, each with its
 // merge, so their partial results share one region behind the statistics.
-static size_t dq_part_bytes(const attn_rect_params_t *p)
+static size_t dq_part_bytes(const attn_rect_params_t *p, bool causal)
 {
-    const int nsplit = attn::dq_split_plan(p->B * p->Hq, p->Sq, p->Sk, kernel_d(p->D), p->causal != 0, nullptr);
+    const int nsplit = attn::dq_split_plan(p->B * p->Hq, p->Sq, p->Sk, kernel_d(p->D), causal, nullptr);
     return nsplit > 1 ? round_ws((size_t)nsplit * p->B * p->Hq * p->Sq * kernel_d(p->D) * sizeof(float)) : 0;
 }
 static size_t dkdv_part_bytes(const attn_rect_params_t *p, bool causal)
@@ -192,7 +202,7 @@ static int fwd_impl(const void *Q, const void *K, const void *V, void *O, float 
     int kps = 0;
     int nsplit = workspace ? attn::fwd_split_plan(v.BH, v.S, p->Sk, kernel_d(p->D), v.causal, &kps) : 1;
     if (workspace && (!aligned(workspace, kWsAlign) ||
-                      workspace_bytes < fwd_workspace_bytes(p, rope != nullptr)))
+                      workspace_bytes < fwd_split_bytes(p, rope != nullptr)))
         return ATTN_ERR_WORKSPACE;
     attn::FwdArgsT<E> a;
     a.nsplit = nsplit; a.kps = kps;
@@ -242,7 +252,7 @@ static int bwd_impl(const void *Q, const void *K, const void *V, const void *O, 
     if (stages == 0 || (stages & ~7u)) return ATTN_ERR_SHAPE;
     int dq_kps = 0;
     int dq_nsplit = attn::dq_split_plan(p->B * p->Hq, p->Sq, p->Sk, kernel_d(p->D), p->causal != 0, &dq_kps);
-    if (rope || workspace_bytes < stats_bytes + dq_part_bytes(p)) dq_nsplit = 1;
+    if (rope || workspace_bytes < stats_bytes + dq_part_bytes(p, p->causal != 0)) dq_nsplit = 1;
     int dkdv_chunk = 0;
     const int dkdv_items = attn::dkdv_split_plan(p->B * p->Hkv, p->Hq / p->Hkv, p->Sq, p->Sk, kernel_d(p->D),
                                                  p->causal != 0, &dkdv_chunk);
@@ -376,9 +386,10 @@ int attn_fwd(const void *Q, const void *K, const void *V, void *O, float *LSE,
 size_t attn_bwd_rect_workspace_bytes(const attn_rect_params_t *p)
 {
     if (check_params(p) != ATTN_OK) return 0;
-    // (the larger of the masked and the unmasked plan: a workspace asked for with one serves the other)
-    const size_t dq = dq_part_bytes(p), kv = std::max(dkdv_part_bytes(p, false), p->causal ? dkdv_part_bytes(p, true) : 0);
-    return bwd_stats_bytes(p) + std::max(dq, kv);
+    // (enough with and without a causal mask, as for the forward)
+    size_t part = std::max(dq_part_bytes(p, false), dkdv_part_bytes(p, false));
+    if (p->Sk >= p->Sq) part = std::max(part, std::max(dq_part_bytes(p, true), dkdv_part_bytes(p, true)));
+    return bwd_stats_bytes(p) + part;
 }
 
 size_t attn_bwd_gqa_workspace_bytes(const attn_gqa_params_t *p)

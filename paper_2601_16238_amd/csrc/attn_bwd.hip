@@ -1132,15 +1132,18 @@ static int launch_dq_for(const BwdArgs &a, hipStream_t st)
     if (a.dq_nsplit > 1) return launch_dq_split<D, CAUSAL>(a, st);
     const int blocks32 = (a.S + 31) / 32;
     // 256-row work-groups unless they would leave compute units (256) idle while 128-row
-    // ones would not (few heads and rows against many keys, e.g. chunked prefill).  Under a
+    // ones would not (few heads and rows against many keys, e.g. chunked prefill); at D = 128, where one
+    // work-group fills a unit either way, without a mask also where the 128-row ones would need a second
+    // round (32 heads of 1537 rows 84 -> 64 us, 48 of 1024 61 -> 43).  Under a
     // causal mask 128-row work-groups also balance the unequal tiles better as long as the
-    // launch is small: at D = 128 (one work-group per compute unit either way) up to one
+    // launch is small: at D = 128 up to one
     // 256-row work-group per unit (B=1 H=16 S=4096: 135 -> 117 us, B=1 H=8 S=8192: 256 -> 220 us;
     // with 1.25 per unit already 15 % slower), at D = 64 (two fit a unit) up to four
     // (B=8 H=8 S=1024: 28.9 -> 26.6 us, B=4 H=8 S=2048: 45.4 -> 42.0 us).
-    const int64_t wgs8 = (int64_t)a.BH * ((a.S + 255) / 256);
+    const int64_t wgs8 = (int64_t)a.BH * ((a.S + 255) / 256), wgs4 = (int64_t)a.BH * ((a.S + 127) / 128);
     const bool prefer4 = CAUSAL && (D == 64 ? wgs8 < 1024 : wgs8 <= 256);
-    if (blocks32 >= 8 && wgs8 >= 256 && !prefer4) return launch_dq<D, 8, CAUSAL>(a, st);
+    const bool fill8 = wgs8 >= 256 || (D == 128 && !CAUSAL && wgs4 > 256);
+    if (blocks32 >= 8 && fill8 && !prefer4) return launch_dq<D, 8, CAUSAL>(a, st);
     if (blocks32 >= 4) return launch_dq<D, 4, CAUSAL>(a, st);
     if (blocks32 == 3) return launch_dq<D, 3, CAUSAL>(a, st);
     if (blocks32 == 2 || D == 128) return launch_dq<D, 2, CAUSAL>(a, st);
@@ -1170,15 +1173,13 @@ static int launch_bwd_d(BwdArgs a, bool causal, hipStream_t st, unsigned stages)
     return 0;
 }
 
-// Split the dQ kernel over the keys when its 256-row work-groups would leave compute units
-// (256) idle: aim at one work-group per unit, every split at least eight 64-key tiles (the
-// merge reads and writes one fp32 partial per split and row).  Needs at least 256 query rows
-// per head (a 256-row work-group must have rows to work on) -- decoding shapes have one row per
-// head and many heads, and are not split.
+// Split of the dQ kernel over the keys, by the forward's estimate (see split_plan): D = 128, causal,
+// unsplit -> split, us: 4 heads of 2048 rows 50 -> 35 (8 splits), 8 of 2048 50 -> 37 (4), but 32 of 1024
+// 34 -> 39 (2), 16 of 1024 29 -> 34 (4).  Needs at least 256 query rows per head (a 256-row work-group
+// must have rows to work on) -- decoding shapes have one row per head and many heads, and are not split.
 #ifndef ATTN_F16  // a function of the shape only: defined once, by the bf16 build
 int dq_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps)
 {
-    (void)causal;
     if (D > 128) {  // the kernel for head dimensions above 128 is not split
         if (kps) *kps = (Sk + 63) / 64 * 64;
         return 1;
@@ -1186,11 +1187,10 @@ int dq_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps)
     const int64_t wgs = (int64_t)BH * ((S + 255) / 256);
     const int tiles = (Sk + 63) / 64;
     int nsplit = 1;
-    if (S >= 256 && wgs < 256 && tiles >= 16) {
-        nsplit = (int)((256 + wgs - 1) / wgs);
-        if (nsplit > tiles / 8) nsplit = tiles / 8;
-        if (nsplit > 16) nsplit = 16;
-    }
+    if (S >= 256)
+        // (the unsplit launch has work-groups of 128 rows, the split one of 256)
+        nsplit = split_plan(D > 64 ? SplitCost{7.0f, 1.38f, 1.6f, 2.2f, 256} : SplitCost{7.0f, 0.94f, 1.0f, 1.6f, 512},
+                            wgs, tiles, tiles - S / 128.0f, (size_t)BH * S * D * 4, causal, 16);
     const int tiles_per = (tiles + nsplit - 1) / nsplit;
     nsplit = (tiles + tiles_per - 1) / tiles_per;  // no empty split
     if (kps) *kps = tiles_per * 64;

@@ -30,6 +30,8 @@
 #include "attn_device.hpp"
 #include "attn_launch.hpp"
 
+#include <algorithm>
+
 namespace attn {
 
 template <int D, int NW>
@@ -819,13 +821,43 @@ static int launch_fwd_d(FwdArgs a, bool causal, hipStream_t st)
     return -1;
 }
 
-// Split the keys when the unsplit launch would leave compute units (256) idle: aim at one
-// work-group per unit.  (Measured on the decode shape: 256 work-groups with long key ranges
-// beat 512 or 1024 shorter ones, 0.060 ms against 0.071 and 0.086 -- a work-group streams
-// best when it stays in its pipelined loop, and a second round of work-groups only adds
-// prologues.)  Every split keeps at least four 64-key tiles (the merge reads and writes one
-// fp32 partial result per split and row).
+// Split over the keys.  A launch of few work-groups lasts as long as its longest one; a split shortens
+// that, but every split writes an fp32 partial result that the merge reads: about 5 us and 0.4 us per
+// MB.  The estimate of a launch, in us, with n splits of the key tiles:
+//   - no mask (equal work-groups, as long as all of them are resident at once, one per compute unit):
+//     fixed + tiles / n * per-tile time, which grows from `alone` to `full` as the work-groups fill the
+//     chip;
+//   - causal: the longest work-group, fixed + tiles / n * alone, or the whole work spread evenly over the
+//     compute units, work-groups * (average tiles * full + n * fixed) / 256, whichever is more; and 0.3 of
+//     the longest where not all work-groups are resident at once, so that some long ones start late.
+// The number of splits of which it is least is taken if that is a twentieth below the unsplit launch.
+// Measured, us, unsplit -> split, forward, D = 128, causal: 2 heads of 2048 rows 50 -> 27 (8 splits), 8
+// of 2048 51 -> 35 (4), 8 of 4096 95 -> 67 (2), 6 of 8192 180 -> 123 (2); not split: 32 of 512 19 (27 with
+// two), 16 of 1024 30 (30 with four), 32 of 1536 43 (49 with two).
 #ifndef ATTN_F16  // a function of the shape only: defined once, by the bf16 build
+int split_plan(const SplitCost &c, int64_t wgs, int tiles, float average, size_t part_bytes, bool causal, int most)
+{
+    auto estimate = [&](int n) {
+        const float alone = n > 1 ? c.alone_split : c.alone;
+        const int per = (tiles + n - 1) / n;
+        const float merge = n > 1 ? 5.0f + 0.4e-6f * (float)part_bytes * n : 0.0f;
+        if (!causal) return c.fixed + per * (n > 1 ? c.full : alone) + merge;
+        const float longest = c.fixed + per * alone, load = wgs * (average * c.full + n * c.fixed) / 256.0f;
+        return std::max(longest, load) + (n * wgs > c.resident ? 0.3f * longest : 0.0f) + merge;
+    };
+    int best = 1;
+    float least = 0.95f * estimate(1);
+    for (int n = 2; n <= most && 4 * n <= tiles && n * wgs <= (causal ? 1024 : 256); ++n) {
+        const float t = estimate(n);
+        if (t < least) { least = t; best = n; }
+    }
+    return best;
+}
+
+// The forward.  Decoding (at most 32 rows per head) runs in the streaming kernel and is bound by
+// memory, not by its longest work-group: at least one work-group per compute unit (256 with long key
+// ranges beat 512 or 1024 shorter ones there, 0.060 ms against 0.071 and 0.086 on the decode shape),
+// every split at least four tiles.
 int fwd_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps)
 {
     // (head dimensions above 128: four waves, 128 rows per work-group)
@@ -834,13 +866,19 @@ int fwd_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps)
     const int64_t target = 256;
     const int tiles = (Sk + 63) / 64;
     int nsplit = 1;
-    if (wgs < target && tiles >= 8) {
+    if (S > 32) {
+        const SplitCost cost = D > 128 ? SplitCost{10.0f, 4.3f, 4.3f, 5.0f, 256}
+                               : D > 64 ? SplitCost{7.0f, 1.38f, 1.38f, 1.8f, 256}
+                               : nw == 8 ? SplitCost{7.0f, 0.94f, 0.94f, 1.17f, 256}
+                                         : SplitCost{7.0f, 0.67f, 0.67f, 0.69f, 512};
+        nsplit = split_plan(cost, wgs, tiles, tiles - S / 128.0f, (size_t)BH * S * D * 4, causal, 128);
+    } else if (wgs < target && tiles >= 8) {
         nsplit = (int)((target + wgs - 1) / wgs);
         if (nsplit > tiles / 4) nsplit = tiles / 4;
         if (nsplit > 128) nsplit = 128;
     }
-    // Decoding (at most 32 rows per head) runs in the streaming kernel, of which two work-groups
-    // fit a compute unit: aim at two per unit as far as that leaves every split 8 tiles or more
+    // Two work-groups of the streaming kernel fit a compute unit: aim at two per unit as far as that
+    // leaves every split 8 tiles or more
     // (B=8 Hkv=8 Sk=8192: 8 splits, 55.0 -> 49.5 us; B=16 H=16 Sk=4096: 2 splits, 111 -> 103 us;
     // B=1 Hkv=8 Sk=32768: 64 splits of 8 tiles 28.2 us against 30.0 with 32 of 16; four work-groups
     // per unit are 4-5 % slower again).

@@ -107,7 +107,13 @@ int launch_fwd(const FwdArgsT<_Float16> &a, int D, bool causal, hipStream_t st);
 // 256; called by launch_fwd, which also launches the merge of a split).
 int launch_fwd_wide(const FwdArgsT<__bf16> &a, int D, bool causal, hipStream_t st);
 int launch_fwd_wide(const FwdArgsT<_Float16> &a, int D, bool causal, hipStream_t st);
-// Number of key splits the forward would use for this problem (1: none), and the keys per
+// Number of splits over `tiles` key tiles (`average` over the query rows) with which a launch of `wgs`
+// work-groups ends soonest (1: none); part_bytes: the partial results of one split.  Times in us: what a
+// work-group costs besides its tiles, a tile with the compute unit to itself (unsplit, and in the split
+// kernel), a tile on a full chip; and the work-groups resident at once.  See attn_fwd.hip.
+struct SplitCost { float fixed, alone, alone_split, full; int resident; };
+int split_plan(const SplitCost &c, int64_t wgs, int tiles, float average, size_t part_bytes, bool causal, int most);
+// fwd_split_plan: number of key splits the forward would use for this problem (1: none), and the keys per
 // split; a pure host function of the shape.
 int fwd_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps);
 // `stages`: bit 0 row statistics, bit 1 dK/dV, bit 2 dQ.  With bits 0 and 2 the dQ kernel
