@@ -58,15 +58,25 @@ struct FwdCfg {
     // x 2 halves = 512 contiguous bytes of a piece.
     static constexpr int kVTile = kKTile;                                  // in elements
     static constexpr int kVRows16 = (16 / kKRowsPerDma) * kKPieceBytes;   // 16 rows further, in bytes
-    // V tiles: two, or three for the eight-wave kernel, whose main loop multiplies P of a
-    // sub-tile by V one sub-tile later and therefore still reads tile kt-1 while tile kt+1 is
-    // arriving
-    static constexpr int kVBufs = NW == 8 ? 3 : 2;
+    // The forms with the pipelined main loop: eight waves, and four at D = 64, where it has the
+    // registers.  (At D = 64 the generic form takes a lone wave about 990 cycles per sub-tile, most of
+    // them between its phases, not in arithmetic or waits for memory: 8 heads of 1024 rows, causal,
+    // 18.9 -> 16.4 us, 64 of 2048 59 -> 55, B=32 H=8 S=200 12.3 -> 11.6.)
+    static constexpr bool kMain = NW == 8 || (NW == 4 && D == 64);
+    // V tiles: two, or three for the main loop, which multiplies P of a sub-tile by V one sub-tile
+    // later and therefore still reads tile kt-1 while tile kt+1 is arriving
+    static constexpr int kVBufs = kMain ? 3 : 2;
     // Eight waves: the query rows reach the registers through LDS (see the kernel's prologue):
     // the 64 rows of a pair of waves are staged like a K tile, pair 0 in K buffer 2, pair 1 in
     // V buffer 1 (both free until the first tile barrier), pairs 2 and 3 behind the V buffers.
     static constexpr int kQStage = NW == 8 ? 2 * kKTile : 0;
     static constexpr int kLdsBytes = (3 * kKTile + kVBufs * kVTile + kQStage) * 2;
+    // Four waves: problems of one or two key tiles never enter the main loop and do without its
+    // third V buffer, so that three work-groups fit a compute unit.
+    static constexpr int lds_bytes(int n_kt)
+    {
+        return NW == 4 && kMain && n_kt < 3 ? kLdsBytes - kVTile * 2 : kLdsBytes;
+    }
     static_assert(kLdsBytes <= 160 * 1024, "LDS budget of a gfx950 CU exceeded");
 };
 
@@ -307,7 +317,7 @@ attn_fwd_kernel(const FwdArgs a)
         // ---- V0 (first sub-tile: V(kt+1) -> the buffer freed at the last barrier)
         ld_k(Kn, 0, f0);
         mm_v(f2, p0);
-        if (u == 0) dma_v(kt + 1, vb_fill);
+        if (u == 0 && (NW == 8 || kt + 1 < n_kt)) dma_v(kt + 1, vb_fill);
         ATTN_FENCE();
         // ---- V1
         if (NKQ > 1) ld_k(Kn, 1, f1);
@@ -389,7 +399,7 @@ attn_fwd_kernel(const FwdArgs a)
             }
         }
     }
-    if constexpr (NW == 8) {
+    if (C::kMain && (NW == 8 || n_kt > 2)) {
         // The main loop's first iteration multiplies an all-zero P by the second half of V
         // buffer 2, which nothing has written yet: give it finite contents.
         const u32x4 z = {0u, 0u, 0u, 0u};
@@ -411,7 +421,7 @@ attn_fwd_kernel(const FwdArgs a)
         if (NKQ > 1) ld_k(Ks + C::kKHalf, 1, f1);
     }
 
-    // Main-loop form of a sub-tile (eight-wave kernel, sub-tiles that the wave sees in full):
+    // Main-loop form of a sub-tile (kMain, sub-tiles that the wave sees in full):
     // the probabilities of sub-tile g are multiplied by V one sub-tile LATER.  The iteration
     // then holds three independent pieces of work -- S^T(g+1) = K Q^T, the softmax arithmetic
     // of g, and O^T += V^T P^T(g-1) -- in one basic block with nothing to mask, and the test
@@ -501,7 +511,7 @@ attn_fwd_kernel(const FwdArgs a)
     // third buffer; V(kt+1) replaces the oldest V tile, whose last readers finished before the
     // previous barrier.
     int kt0 = 0;  // first tile of the generic loop below
-    if constexpr (NW == 8) {
+    if constexpr (C::kMain) {
         // Tiles that this wave sees in full (no key past the end, none above its diagonal), in
         // whole groups of three: the loop is unrolled over the three K (and V) buffers so that
         // the buffer of every access is a compile-time constant and the LDS addresses of the
@@ -541,13 +551,13 @@ attn_fwd_kernel(const FwdArgs a)
             subtile(kt, 0, kb1, kb2, vb, vb1, (kb + 32 > Sk) || (CAUSAL && kb + 31 > q0e), sa, sb);
         } else {
             dma_k(kt + 2, kb2);
-            dma_v(kt + 1, vb1);
+            if (NW == 8 || kt + 1 < n_kt) dma_v(kt + 1, vb1);
         }
         if (!CAUSAL || kb + 32 <= q0e + 31)
             subtile(kt, 1, kb1, kb2, vb, vb1, (kb + 64 > Sk) || (CAUSAL && kb + 63 > q0e), sb, sa);
         tile_barrier();
     };
-    if constexpr (NW == 8) {
+    if constexpr (C::kMain) {
         // unrolled over the three buffers like the main loop (kt0 is a multiple of three)
         for (int kt = kt0; kt < n_kt; kt += 3) {  // n_kt is the same for every wave of the work-group
             tile(kt, 1, 2, 0, 1);
@@ -767,7 +777,7 @@ static int launch_fwd_kernel(const FwdArgs &a, hipStream_t st)
         return -1;
     hipLaunchKernelGGL((attn_fwd_kernel<D, NW, CAUSAL, SPLIT>),
                        dim3(a.nqt * a.BH, SPLIT ? a.nsplit : 1), dim3(C::kThreads),
-                       C::kLdsBytes, st, a);
+                       C::lds_bytes((a.Sk + C::kBC - 1) / C::kBC), st, a);
     if (hipGetLastError() != hipSuccess) return -1;
     if (SPLIT) return launch_fwd_merge<D>(a, st);
     return 0;
