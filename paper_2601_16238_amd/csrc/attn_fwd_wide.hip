@@ -15,14 +15,19 @@
 //    reads exactly once, come by non-temporal transfers, and those are requested by the three waves
 //    without rows, so that the computing wave never delays a tile.
 //
-// One barrier per tile of 64 keys.  A tile is processed in four steps whose independent halves
-// sit in one basic block each, so that the matrix pipe and the vector ALU overlap inside a wave:
+// One barrier per tile of 64 keys.  A tile is processed in four phases, in each of which the matrix
+// pipe and the vector ALU overlap inside a wave:
 //   A  S^T(0) = K Q^T                          (D/16 MFMAs)
 //   B  S^T(1) = K Q^T   with   P(0) = exp2(c S(0) - m)
 //   C  O^T += V^T P(0)^T   with   P(1) = exp2(c S(1) - m)
 //   D  O^T += V^T P(1)^T
 // Nothing is carried from one tile to the next except the accumulators, which is what lets
-// two K buffers do.
+// two K buffers do.  With one wave per SIMD (D = 256) nothing else hides a wave's LDS latency, so a
+// phase is written as one step per MFMA, closed by a scheduling fence: the MFMA, the LDS read of the
+// fragment kAhead MFMAs further on (across the phases), one transfer of the next tile every other
+// step, and the step's share of the other sub-tile's probabilities.  Left to the compiler, which reads
+// a fragment right before its MFMA, and with a branch around every transfer, B=4 H=16 S=4096 D=256
+// causal took 632 us; so it takes 583.
 #include "attn_device.hpp"
 #include "attn_launch.hpp"
 
@@ -210,7 +215,6 @@ attn_fwd_wide_kernel(const FwdArgs a)
     for (int j = 0; j < 2; ++j)
         v_lane[j] = C::kOffV + v_at(8 * j + 4 * h + ((l & 15) >> 2), 2 * ((l >> 4) & 1) + ((l >> 1) & 1)) + (l & 1) * 8;
 
-    // S^T of sub-tile u of the tile in buffer buf
     // Per-lane LDS addresses of the current tile's fragments, set once per tile and made opaque
     // to the compiler, so that sub-tile, contraction step and d block are folded into the 16-bit
     // immediate offsets of the LDS instructions instead of into further address arithmetic.
@@ -221,17 +225,21 @@ attn_fwd_wide_kernel(const FwdArgs a)
         v_base1 = v_lane[1] + buf * C::kVTileBytes;
         asm volatile("" : "+v"(k_base), "+v"(v_base0), "+v"(v_base1));
     };
-    // (fetch: -1, or the tensor of tile kt + 1 whose transfers are issued between the MFMAs,
-    // one per two of them -- the chain of dependent MFMAs leaves the issue slots for it)
-    auto scores = [&](int u, f32x16 &s, int fetch = -1, int kt = 0) __attribute__((always_inline)) {
-        const char *Kt = smem + u * C::kKHalfBytes + k_base;
+    // A operand of contraction step ks of sub-tile u's scores, and of MFMA i of its P V (the two 16-key
+    // steps one after the other, d block by d block)
+    auto ld_k = [&](int u, int ks) __attribute__((always_inline)) {
+        return *(const elem8 *)(smem + u * C::kKHalfBytes + k_base + ks * C::kKStepBytes);
+    };
+    auto ld_v = [&](int u, int i) __attribute__((always_inline)) {
+        const char *p = smem + (2 * u + i / DB) * C::kVRows16 + (i % DB) * 4 * PR * 16;  // d block: four chunks further
+        return join8(lds_read_tr((const elem *)(p + v_base0)), lds_read_tr((const elem *)(p + v_base1)));
+    };
+    // S^T of sub-tile u, outside the fast loop
+    auto scores = [&](int u, f32x16 &s) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) s[i] = 0.f;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            s = mfma32(*(const elem8 *)(Kt + ks * C::kKStepBytes), qf[ks], s);
-            if (!NT && fetch >= 0 && (ks & 1) && kt + 1 < n_kt) dma_piece(fetch, kt + 1, (kt & 1) ^ 1, ks >> 1);
-        }
+        for (int ks = 0; ks < KS; ++ks) s = mfma32(ld_k(u, ks), qf[ks], s);
     };
     // ragged tail and causal mask of sub-tile (kt, u); wave-uniform test whether any is needed
     auto mask = [&](int kt, int u, f32x16 &s) __attribute__((always_inline)) {
@@ -291,24 +299,34 @@ attn_fwd_wide_kernel(const FwdArgs a)
             hsum = dot2_acc(p1[2 * i], p1[2 * i + 1], hsum);
         }
     };
-    // O^T += V^T P^T for sub-tile u of the V tile in buffer buf
+    // O^T += V^T P^T for sub-tile u, outside the fast loop
     auto pv = [&](int u, elem8 p0, elem8 p1) __attribute__((always_inline)) {
-        const char *Vt = smem + 2 * u * C::kVRows16;
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
-            const char *Vd = Vt + db * 4 * PR * 16;  // d block db: four chunks further
-            const elem8 f0 = join8(lds_read_tr((const elem *)(Vd + v_base0)),
-                                    lds_read_tr((const elem *)(Vd + v_base1)));
-            const elem8 f1 = join8(lds_read_tr((const elem *)(Vd + C::kVRows16 + v_base0)),
-                                    lds_read_tr((const elem *)(Vd + C::kVRows16 + v_base1)));
-            o[db] = mfma32(f0, p0, o[db]);
-            o[db] = mfma32(f1, p1, o[db]);
+            o[db] = mfma32(ld_v(u, db), p0, o[db]);
+            o[db] = mfma32(ld_v(u, DB + db), p1, o[db]);
         }
+    };
+    // Steps of the fast loop.  A sub-tile's probabilities are formed during the KS or 2 DB steps (the
+    // same number) of a phase, from the second step on, when its scores are complete.
+    constexpr int kSteps = KS;
+    static_assert(2 * DB == KS, "phases have one length");
+    constexpr int kAhead = 4;
+    auto probs_step = [&](int j, const f32x16 &s, float (&e)[16], float &psum) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = j ? 16 * (j - 1) / (kSteps - 1) : 16; i < 16 * j / (kSteps - 1); ++i) {
+            e[i] = fast_exp2(__builtin_fmaf(s[i], c, -m));
+            psum += e[i];
+        }
+    };
+    auto pack16 = [&](const float (&e)[16], elem8 &p0, elem8 &p1) __attribute__((always_inline)) {
+        p0 = pack8(e[0], e[1], e[2], e[3], e[4], e[5], e[6], e[7]);
+        p1 = pack8(e[8], e[9], e[10], e[11], e[12], e[13], e[14], e[15]);
     };
     // Start of iteration kt: K(kt) and V(kt) have been on their way since iteration kt-1.  After
     // the barrier the other buffers (tile kt-1, last read before the barrier) are free and take
-    // tile kt+1.  Its transfers are issued between the MFMAs of the two score steps (see scores):
-    // issued in one burst after the barrier, the waves all queue at the compute unit's
+    // tile kt+1.  Its transfers are issued between the MFMAs of the two score phases, also after the
+    // last tile (they fill a buffer that nobody reads; the epilogue waits): issued in one burst after the barrier, the waves all queue at the compute unit's
     // vector-memory path while the matrix pipes idle (measured: +35 % on the whole kernel).
     auto stage = [&](int kt) __attribute__((always_inline)) {
         (void)kt;
@@ -401,22 +419,74 @@ attn_fwd_wide_kernel(const FwdArgs a)
             set_bases(kt & 1);
             f32x16 sA, sB;
             elem8 pA0, pA1, pB0, pB1;
-            float sumA, sumB;
-            scores(0, sA, 0, kt);                       // A
+            float sumA = 0.f, sumB = 0.f;
+            if constexpr (NT) {
+                // decoding waits for memory; fenced steps cost it 0-4 % (B=8 Hkv=8 Sk=8192 45.8 ->
+                // 47.6 us)
+                scores(0, sA);                              // A
+                mask(kt, 0, sA);
+                scores(1, sB);                              // B
+                probs(sA, pA0, pA1, sumA);
+                __builtin_amdgcn_sched_barrier(0);
+                if (__builtin_expect(overflow(sumA), 0)) { redo = 0; break; }
+                commit(pA0, pA1, sumA);
+                mask(kt, 1, sB);
+                pv(0, pA0, pA1);                            // C
+                probs(sB, pB0, pB1, sumB);
+                __builtin_amdgcn_sched_barrier(0);
+                if (__builtin_expect(overflow(sumB), 0)) { redo = 1; break; }
+                commit(pB0, pB1, sumB);
+                pv(1, pB0, pB1);                            // D
+                __builtin_amdgcn_sched_barrier(0);
+                continue;
+            }
+            elem8 f[4][kSteps];  // the phases' fragments
+            float eA[16], eB[16];
+            auto fetch = [&](int n) __attribute__((always_inline)) {  // fragment of MFMA n of the tile
+                const int ph = n / kSteps, j = n % kSteps;
+                if (ph < 4) f[ph][j] = ph < 2 ? ld_k(ph, j) : ld_v(ph - 2, j);
+            };
+#pragma unroll
+            for (int i = 0; i < 16; ++i) sA[i] = sB[i] = 0.f;
+#pragma unroll
+            for (int n = 0; n < kAhead; ++n) fetch(n);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < kSteps; ++j) {          // A
+                sA = mfma32(f[0][j], qf[j], sA);
+                fetch(j + kAhead);
+                if (j & 1) dma_piece(0, kt + 1, (kt & 1) ^ 1, j >> 1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
             mask(kt, 0, sA);
-            scores(1, sB, 1, kt);                       // B
-            probs(sA, pA0, pA1, sumA);
-            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < kSteps; ++j) {          // B
+                sB = mfma32(f[1][j], qf[j], sB);
+                fetch(kSteps + j + kAhead);
+                if (j & 1) dma_piece(1, kt + 1, (kt & 1) ^ 1, j >> 1);
+                probs_step(j, sA, eA, sumA);
+                __builtin_amdgcn_sched_barrier(0);
+            }
             if (__builtin_expect(overflow(sumA), 0)) { redo = 0; break; }
-            commit(pA0, pA1, sumA);
+            pack16(eA, pA0, pA1);
             mask(kt, 1, sB);
-            pv(0, pA0, pA1);                            // C
-            probs(sB, pB0, pB1, sumB);
-            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < kSteps; ++j) {          // C
+                o[j % DB] = mfma32(f[2][j], j < DB ? pA0 : pA1, o[j % DB]);
+                fetch(2 * kSteps + j + kAhead);
+                probs_step(j, sB, eB, sumB);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            commit(pA0, pA1, sumA);
             if (__builtin_expect(overflow(sumB), 0)) { redo = 1; break; }
+            pack16(eB, pB0, pB1);
+#pragma unroll
+            for (int j = 0; j < kSteps; ++j) {          // D
+                o[j % DB] = mfma32(f[3][j], j < DB ? pB0 : pB1, o[j % DB]);
+                fetch(3 * kSteps + j + kAhead);
+                __builtin_amdgcn_sched_barrier(0);
+            }
             commit(pB0, pB1, sumB);
-            pv(1, pB0, pB1);                            // D
-            __builtin_amdgcn_sched_barrier(0);
         }
         if (redo >= 0) {
             set_bases(kt & 1);
@@ -439,8 +509,10 @@ attn_fwd_wide_kernel(const FwdArgs a)
         fetch_next(kt, 1);
     }
 
-    // no transfer may still be in flight when the work-group's LDS is released
+    // no transfer may still be in flight when the work-group's LDS is released, nor, of any wave, when
+    // the epilogue stages rows in the buffers
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if constexpr (!NT) __syncthreads();
 
     // Epilogue: O = O_acc / l, LSE = ln2 * (m + log2 l).
     const float lt = xhalf_sum(lsum);
