@@ -332,34 +332,52 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
                 const float *st = reinterpret_cast<const float *>(smem + C::kOffStat + rs * C::kStatBytes);
                 const int q_lo = t * C::kRows;
                 f32x16 s, dp;
-                {
-                    // register i <-> query row q_lo + 8*(i/4) + 4h + i%4.  The dP accumulator
-                    // starts from -delta of its row, so that it ends as dP - delta.
-                    f32x16 zero, nd;
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const f32x4 d4 = *(const f32x4 *)(st + 32 + 8 * g + 4 * h);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) nd[4 * g + e] = d4[e];
-                    }
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) zero[i] = 0.f;
-                    s = mfma32(*(const elem8 *)(Qt + lane_off), kf[0], zero);
-                    dp = mfma32(*(const elem8 *)(Qt + C::kTensorBytes + lane_off), vf[0], nd);
-                }
-#pragma unroll
-                for (int ks = 1; ks < KS; ++ks) {
-                    const int off = lane_off ^ (ks * 32);
-                    s = mfma32(*(const elem8 *)(Qt + off), kf[ks], s);
-                    dp = mfma32(*(const elem8 *)(Qt + C::kTensorBytes + off), vf[ks], dp);
-                }
-                // the lane's key is fixed; P = exp2(c S - lse2) per row
+                // register i <-> query row q_lo + 8*(i/4) + 4h + i%4.  The dP accumulator starts
+                // from -delta of its row, so that it ends as dP - delta.  The lane's key is fixed;
+                // P = exp2(c S - lse2) per row.
+                f32x16 zero, nd;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    const f32x4 l4 = *(const f32x4 *)(st + 8 * g + 4 * h);
+                    const f32x4 d4 = *(const f32x4 *)(st + 32 + 8 * g + 4 * h);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        s[4 * g + e] = fast_exp2(__builtin_fmaf(s[4 * g + e], c, -l4[e]));
+                    for (int e = 0; e < 4; ++e) nd[4 * g + e] = d4[e];
+                }
+#pragma unroll
+                for (int i = 0; i < 16; ++i) zero[i] = 0.f;
+                {
+                    // Every MFMA is a step of its own, closed by a scheduling fence, with the read of
+                    // the fragment four MFMAs further on (the compiler reads a fragment right
+                    // before its MFMA and waits); S first, so that its exp2 run next to the
+                    // MFMAs of dP.  us: B=4 H=16 S=4096 D=256 causal 1216 -> 1118 (with the
+                    // consumers' steps), B=1 H=16 S=4096 D=128 causal 142 -> 135, S=16384 1871 -> 1852;
+                    // two or six MFMAs ahead are the same
+                    constexpr int kAhead = 4;
+                    elem8 f[2 * KS];
+                    auto fetch = [&](int n) __attribute__((always_inline)) {
+                        if (n < 2 * KS)
+                            f[n] = *(const elem8 *)(Qt + (n / KS) * C::kTensorBytes + (lane_off ^ ((n % KS) * 32)));
+                    };
+                    f32x4 l4[4];
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) l4[g] = *(const f32x4 *)(st + 8 * g + 4 * h);
+#pragma unroll
+                    for (int n = 0; n < kAhead; ++n) fetch(n);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) {
+                        s = mfma32(f[ks], kf[ks], ks ? s : zero);
+                        fetch(ks + kAhead);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) {
+                        dp = mfma32(f[KS + ks], vf[ks], ks ? dp : nd);
+                        fetch(KS + ks + kAhead);
+#pragma unroll
+                        for (int i = ks < 2 ? 0 : 16 * (ks - 2) / (KS - 2); i < (ks < 2 ? 0 : 16 * (ks - 1) / (KS - 2)); ++i)
+                            s[i] = fast_exp2(__builtin_fmaf(s[i], c, -l4[i / 4][i % 4]));
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
                 if ((q_lo + 32 > S) || (CAUSAL && q_lo + coff < k0 + 31)) {
                     // visible row offsets: >= key - coff - q_lo (causal) and <= S - 1 - q_lo
@@ -428,17 +446,34 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
 #pragma unroll
             for (int i = 0; i < 8; ++i) opB[0][i] = opB[1][i] = 0;
             if (actB) { opB[0] = x[256]; opB[1] = x[256 + 64]; }
+            // MFMA pair n: 16-row step n / DB, d block n % DB (chunks 4db..4db+3: flips bits 6.. of the
+            // swizzled offset)
+            auto frag = [&](int n) __attribute__((always_inline)) {
+                const int o = (n / DB) * 16 * RB, x = (n % DB) << 6;
+                return join8(lds_read_tr((const elem *)(Tt + ((tr_off[0] ^ x) + o))),
+                             lds_read_tr((const elem *)(Tt + ((tr_off[1] ^ x) + o))));
+            };
+            if constexpr (D > 128) {
+                // one wave per SIMD: fenced steps as in the producers (no gain at D <= 128; neither
+                // has requesting slot tf's rows between these MFMAs)
+                constexpr int kAhead = 4;
+                elem8 T[2 * DB];
 #pragma unroll
-            for (int cc = 0; cc < 2; ++cc) {
+                for (int n = 0; n < kAhead; ++n) T[n] = frag(n);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int db = 0; db < DB; ++db) {
-                    // d block db = chunks 4db..4db+3: flips bits 6.. of the swizzled offset
-                    const int o0 = (tr_off[0] ^ (db << 6)) + cc * 16 * RB;
-                    const int o1 = (tr_off[1] ^ (db << 6)) + cc * 16 * RB;
-                    const elem8 T = join8(lds_read_tr((const elem *)(Tt + o0)),
-                                           lds_read_tr((const elem *)(Tt + o1)));
-                    acc[0][db] = mfma32(T, opA[cc], acc[0][db]);
-                    acc[1][db] = mfma32(T, opB[cc], acc[1][db]);
+                for (int n = 0; n < 2 * DB; ++n) {
+                    acc[0][n % DB] = mfma32(T[n], opA[n / DB], acc[0][n % DB]);
+                    if (n + kAhead < 2 * DB) T[n + kAhead] = frag(n + kAhead);
+                    acc[1][n % DB] = mfma32(T[n], opB[n / DB], acc[1][n % DB]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {
+#pragma unroll
+                for (int n = 0; n < 2 * DB; ++n) {
+                    const elem8 T = frag(n);
+                    acc[0][n % DB] = mfma32(T, opA[n / DB], acc[0][n % DB]);
+                    acc[1][n % DB] = mfma32(T, opB[n / DB], acc[1][n % DB]);
                 }
             }
         };
@@ -874,6 +909,81 @@ attn_bwd_dq_kernel(const BwdArgs a)
             }
         }
     };
+    // A sub-tile as one step per MFMA, closed by a scheduling fence, with the LDS read of the fragment
+    // kAhead MFMAs further on: S^T with the transfers of tile kt + 2, dP^T with the exp2 of S, dQ^T, whose
+    // second half waits for the second half of dS next to the MFMAs of the first.  For the forms that
+    // mostly run one wave per SIMD, where nothing else hides the wave's LDS latency, and for eight waves
+    // at D = 64; eight waves at D = 128 are 1 % slower with it.  us: B=4 H=16 S=4096 D=256 causal
+    // 831 -> 802, B=2 H=5 S=3607 310 -> 292; four waves B=1 H=8 S=2048 D=128 50.7 -> 48.0, B=8 H=8 S=1024
+    // D=64 causal 28.9 -> 27.7; B=4 H=16 S=8192 D=64 causal 813 -> 784.
+    constexpr bool kSteps = D > 128 || NW == 4 || (NW == 8 && D == 64);
+    auto tile_steps = [&](int kt, int kb2, int pos, const char *Kt, int rowa, int tra0, int tra1, desc_t Kd, desc_t Vd,
+                          bool fetch) __attribute__((always_inline)) {
+        constexpr int kAhead = 4, N = 2 * KS + 2 * DB;
+        elem8 f[N];
+        auto read = [&](int n) __attribute__((always_inline)) {
+            if (n < 2 * KS) {
+                f[n] = *(const elem8 *)(Kt + (n / KS) * C::kTensorBytes + kb2 * 2 * C::kRows16 +
+                                        (n % KS) * 2 * C::kChunkStep + rowa);
+            } else if (n < N) {
+                const int off = (kb2 * 2 + (n - 2 * KS) / DB) * C::kRows16 + ((n - 2 * KS) % DB) * 4 * C::kChunkStep;
+                f[n] = join8(lds_read_tr((const elem *)(Kt + off + tra0)), lds_read_tr((const elem *)(Kt + off + tra1)));
+            }
+        };
+        const int k_lo = kt * C::kTile + kb2 * 32;
+        constexpr int kEvery = kBetween ? KS / C::kDmaPerWave : 1;
+        f32x16 s, dp, zero;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) zero[i] = 0.f;
+#pragma unroll
+        for (int n = 0; n < kAhead; ++n) read(n);
+        __builtin_amdgcn_sched_barrier(0);
+        if (fetch) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                s = mfma32(f[ks], qf[ks], ks ? s : zero);
+                read(ks + kAhead);
+                if ((ks + 1) % kEvery == 0) dma_piece(kt + 2, pos == 0 ? 2 : pos - 1, (ks + 1) / kEvery - 1, Kd, Vd);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                s = mfma32(f[ks], qf[ks], ks ? s : zero);
+                read(ks + kAhead);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            dp = mfma32(f[KS + ks], gf[ks], ks ? dp : nd);  // ends as dP - delta
+            read(KS + ks + kAhead);
+#pragma unroll
+            for (int i = ks < 2 ? 0 : 16 * (ks - 2) / (KS - 2); i < (ks < 2 ? 0 : 16 * (ks - 1) / (KS - 2)); ++i)
+                s[i] = fast_exp2(__builtin_fmaf(s[i], c, -lse2));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if ((k_lo + 32 > Sk) || (CAUSAL && k_lo + 31 > q0e)) {  // wave-uniform
+            const int lim = (CAUSAL ? qc + coff : Sk - 1) - k_lo - 4 * h;
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                if (8 * (i / 4) + (i % 4) > lim) s[i] = 0.f;
+        }
+        elem8 sb[2];
+        auto half = [&](int i0) __attribute__((always_inline)) {  // dS = P o (dP - delta)
+#pragma unroll
+            for (int i = i0; i < i0 + 8; ++i) dp[i] *= s[i];
+            return pack8(dp[i0], dp[i0 + 1], dp[i0 + 2], dp[i0 + 3], dp[i0 + 4], dp[i0 + 5], dp[i0 + 6], dp[i0 + 7]);
+        };
+        sb[0] = half(0);
+#pragma unroll
+        for (int n = 0; n < 2 * DB; ++n) {
+            dq[n % DB] = mfma32(f[2 * KS + n], sb[n / DB], dq[n % DB]);
+            read(2 * KS + n + kAhead);
+            if (n == 0) sb[1] = half(8);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
     // One tile at ring position `pos`.
     auto tile = [&](int kt, int pos, const char *Kt, int rowa, int tra0, int tra1, desc_t Kd,
                     desc_t Vd) __attribute__((always_inline)) {
@@ -893,6 +1003,10 @@ attn_bwd_dq_kernel(const BwdArgs a)
             if (!(kb2 ? act1 : act0)) continue;
             f32x16 s, dp;
             elem8 sb[2];
+            if constexpr (kSteps) {
+                tile_steps(kt, kb2, pos, Kt, rowa, tra0, tra1, Kd, Vd, fetch && kb2 == 0);
+                continue;
+            }
             if (kBetween && kb2 == 0 && fetch) step_s_fetch(Kt, rowa, s, kt + 2, pos == 0 ? 2 : pos - 1, Kd, Vd);
             else step_s(Kt, rowa, kb2, s);
             step_dp(Kt, rowa, kb2, dp);
