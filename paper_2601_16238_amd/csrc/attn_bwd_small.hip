@@ -4,7 +4,8 @@
 // reading the head's tensors twice; here Q, K, V and dO are brought into LDS once (direct
 // global -> LDS transfers), and nothing is exchanged between work-groups.
 //
-// Wave w (of up to four) owns query block w (32 rows) and key block w (32 keys):
+// Wave w (with twice the waves, waves w and w + NW, one for each part) owns query block w (32 rows)
+// and key block w (32 keys):
 //   as the owner of query block i (the dQ kernel's orientation, one query per lane):
 //     for every key block j:  S^T = K_j Q_i^T,  dP^T = V_j dO_i^T - delta,  P, dS,
 //                             dQ_i^T += K_j^T dS^T
@@ -22,10 +23,12 @@
 
 namespace attn {
 
-template <int D, int NW>
+// DUO: twice the waves, the first half for the query blocks (part 1) and the second for the key blocks
+// (part 2), which then run at the same time.  For launches of at most one work-group per compute unit.
+template <int D, int NW, bool DUO>
 struct SmallCfg {
-    static constexpr int kWaves = NW;                          // 4, or 8 (D = 64 only)
-    static constexpr int kMaxRows = 32 * NW;                   // query rows and keys per head
+    static constexpr int kWaves = DUO ? 2 * NW : NW;
+    static constexpr int kMaxRows = 32 * NW;                   // NW: 4, or 8 (D = 64 only)
     static constexpr int kThreads = kWaves * 64;
     static constexpr int kRowBytes = D * 2;
     static constexpr int kCPR = D / 8;                         // 16-byte chunks per row
@@ -40,20 +43,22 @@ struct SmallCfg {
     static_assert(lds_bytes(kMaxRows) <= 160 * 1024, "LDS budget of a gfx950 CU exceeded");
 };
 
-template <int D, int NW, bool CAUSAL, bool GQA>
+template <int D, int NW, bool CAUSAL, bool GQA, bool DUO>
 // (D = 64, four waves, one query head per K/V head: at most 168 registers, so that three
 // work-groups share a compute unit; with grouped heads the dK/dV accumulators stay live while dQ
 // of the next query head is formed, which takes more)
-__global__ void __launch_bounds__(NW * 64)
-    __attribute__((amdgpu_waves_per_eu(D == 64 ? (NW == 4 && !GQA ? 3 : 2) : 1)))
+__global__ void __launch_bounds__(NW * (DUO ? 128 : 64))
+    __attribute__((amdgpu_waves_per_eu(D == 64 ? (NW == 4 && !GQA && !DUO ? 3 : 2) : DUO ? 2 : 1)))
 attn_bwd_small_kernel(const BwdArgs a)
 {
-    using C = SmallCfg<D, NW>;
+    using C = SmallCfg<D, NW, DUO>;
     constexpr int KS = D / 16, DB = D / 32, PR = C::kPieceRows, CPR = C::kCPR, RB = C::kRowBytes;
     extern __shared__ __attribute__((aligned(1024))) char smem[];
 
     const int tid = threadIdx.x, l = tid & 63, r = l & 31, h = l >> 5;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int w = DUO ? wave % NW : wave;  // the wave's query block and key block
+    const bool part1 = !DUO || wave < NW, part2 = !DUO || wave >= NW;
     const int S = a.S, Sk = a.Sk, Dr = a.Dr;
     const int coff = Sk - S;  // causal: query row i sees keys 0 .. i + coff
     // the work-group owns one K/V head and sums dK, dV over the `group` query heads that read it
@@ -86,7 +91,7 @@ attn_bwd_small_kernel(const BwdArgs a)
         return chunk * 8 < Dr ? (uint32_t)(l / CPR) * row_bytes + ((uint32_t)chunk << 4) : end;
     };
     const int q_pieces = nqb * (32 / PR), k_pieces = nkb * (32 / PR);
-    for (int i = w; i < k_pieces; i += C::kWaves) {
+    for (int i = wave; i < k_pieces; i += C::kWaves) {
         const uint32_t vo = voff(i, k_row, k_bytes);
         dma16(Kd, lds0 + offK + i * 1024, vo, i * PR * k_row);
         dma16(Vd, lds0 + offV + i * 1024, vo, i * PR * k_row);
@@ -108,7 +113,7 @@ attn_bwd_small_kernel(const BwdArgs a)
     if (GQA && gq > 0) __syncthreads();
     {
         const desc_t Qd = make_desc(a.Q + base, q_bytes), Gd = make_desc(a.dO + base, q_bytes);
-        for (int i = w; i < q_pieces; i += C::kWaves) {
+        for (int i = wave; i < q_pieces; i += C::kWaves) {
             const uint32_t vo = voff(i, q_row, q_bytes);
             dma16(Qd, lds0 + offQ + i * 1024, vo, i * PR * q_row);
             dma16(Gd, lds0 + offG + i * 1024, vo, i * PR * q_row);
@@ -118,7 +123,7 @@ attn_bwd_small_kernel(const BwdArgs a)
     // 16 ks + 8 h .. +7) and the row statistics, as in the dQ kernel
     elem8 qf[KS], gf[KS];
     float lse2 = 0.f, ndelta = 0.f;
-    if (w < nqb) {
+    if (part1 && w < nqb) {
         float acc = 0.f;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
@@ -167,7 +172,7 @@ attn_bwd_small_kernel(const BwdArgs a)
     };
 
     // ---- part 1: dQ of query block w
-    if (w < nqb) {
+    if (part1 && w < nqb) {
         f32x16 nd, dq[DB];
 #pragma unroll
         for (int i = 0; i < 16; ++i) nd[i] = ndelta;
@@ -235,7 +240,7 @@ attn_bwd_small_kernel(const BwdArgs a)
     }
 
     // ---- part 2: dK and dV of key block w
-    if (w < nkb) {
+    if (part2 && w < nkb) {
         elem8 kf[KS], vf[KS];  // B operands: lane holds row `key`, columns 16 ks + 8 h .. +7
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
@@ -300,10 +305,10 @@ attn_bwd_small_kernel(const BwdArgs a)
     // space, once every wave is done with the tensors in LDS, and leave whole, 16 bytes per lane
     // (same box: B=32 H=8 S=256 D=64 causal 25.7 -> 24.5 us, B=64 H=8 S=128 D=128 causal 48.2 ->
     // 45.9).
-    constexpr bool kStageOut = !GQA && !(D == 64 && NW == 4);
+    constexpr bool kStageOut = !GQA && !(D == 64 && NW == 4 && !DUO);
     if constexpr (kStageOut) {
         __syncthreads();
-        if (w < nkb) {
+        if (part2 && w < nkb) {
             constexpr int RPI = 64 / CPR;  // rows per store instruction
             char *stg = smem + offQ + w * 32 * RB;
             const int lr = l / CPR, lc = l % CPR;
@@ -332,7 +337,7 @@ attn_bwd_small_kernel(const BwdArgs a)
         }
         return;
     }
-    if (w < nkb) {
+    if (part2 && w < nkb) {
         if (key < Sk) {
             elem *dKp = a.dK + base_kv + (int64_t)key * a.kv_stride_s;
             elem *dVp = a.dV + base_kv + (int64_t)key * a.kv_stride_s;
@@ -352,15 +357,15 @@ attn_bwd_small_kernel(const BwdArgs a)
     }
 }
 
-template <int D, int NW, bool CAUSAL, bool GQA>
+template <int D, int NW, bool CAUSAL, bool GQA, bool DUO>
 static int launch_small_g(const BwdArgs &a, hipStream_t st)
 {
-    using C = SmallCfg<D, NW>;
+    using C = SmallCfg<D, NW, DUO>;
     const int rows_pad = ((a.S > a.Sk ? a.S : a.Sk) + 31) / 32 * 32;
-    if (hipFuncSetAttribute((const void *)attn_bwd_small_kernel<D, NW, CAUSAL, GQA>,
+    if (hipFuncSetAttribute((const void *)attn_bwd_small_kernel<D, NW, CAUSAL, GQA, DUO>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, C::lds_bytes(C::kMaxRows)) != hipSuccess)
         return -1;
-    hipLaunchKernelGGL((attn_bwd_small_kernel<D, NW, CAUSAL, GQA>), dim3(a.BH / a.group), dim3(C::kThreads),
+    hipLaunchKernelGGL((attn_bwd_small_kernel<D, NW, CAUSAL, GQA, DUO>), dim3(a.BH / a.group), dim3(C::kThreads),
                        C::lds_bytes(rows_pad), st, a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
@@ -368,7 +373,13 @@ static int launch_small_g(const BwdArgs &a, hipStream_t st)
 template <int D, int NW, bool CAUSAL>
 static int launch_small(const BwdArgs &a, hipStream_t st)
 {
-    return a.group > 1 ? launch_small_g<D, NW, CAUSAL, true>(a, st) : launch_small_g<D, NW, CAUSAL, false>(a, st);
+    if (a.group > 1) return launch_small_g<D, NW, CAUSAL, true, false>(a, st);
+    // One work-group per compute unit at most: eight waves, four for each part (B=1 H=2 S=128 10.9 ->
+    // 8.6 us, B=32 H=8 S=128 causal 12.7 -> 11.1; larger launches hold three four-wave work-groups per
+    // unit: B=128 H=6 S=65 18.5 against 24.4).  Not at D = 128: the two parts do not fit 256 registers.
+    if constexpr (D == 64 && NW == 4)
+        if (a.BH <= 256) return launch_small_g<D, NW, CAUSAL, false, true>(a, st);
+    return launch_small_g<D, NW, CAUSAL, false, false>(a, st);
 }
 
 #ifndef ATTN_F16  // a function of the head dimension only: defined once, by the bf16 build
