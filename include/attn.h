@@ -181,22 +181,23 @@ int attn_bwd_gqa_stages(const void *Q, const void *K, const void *V, const void 
  * work-groups and write fp32 partial results to `workspace`; a second small kernel merges
  * them (log-sum-exp weights).  attn_fwd_rect_workspace_bytes returns what that needs for the
  * problem with or without a causal mask (the larger of the two), 0 when neither would split.
- * workspace == NULL (with any size) is allowed and
- * means: do not split.  A non-NULL workspace must be 256-byte aligned and large enough for the
- * split of this call (that size always is), else ATTN_ERR_WORKSPACE; its contents are undefined on entry and exit.  The split
- * plan depends only on the shape and the strides, so results are deterministic.
+ * workspace == NULL (with any size) is allowed and means: do not split.  A non-NULL workspace must
+ * be 256-byte aligned and large enough for the split of this call (that size always is) or for a split
+ * into one work-group per compute unit (no split where that would be none), which then bounds the
+ * split, else ATTN_ERR_WORKSPACE; its contents are undefined on entry and exit.  The split plan
+ * depends only on the shape, the strides and that size, so results are deterministic.
  *
  * Backward: as attn_bwd_gqa.  Keys that no row sees get zero gradients.  Workspace: the row
- * statistics (two fp32 per query row, rounded up to 256 bytes) and, when B*Hq*ceil(Sq/256)
- * work-groups of the dQ kernel would leave most of the chip idle (Sq >= 256, at least 1024
- * keys), the fp32 partial dQ of a split of that kernel over the keys ([splits][B*Hq*Sq][64 or
- * 128]); a third small kernel adds them.  The dK/dV kernel is split over the query rows in the
- * same way when the key blocks of the K/V heads (128 keys; 64 above D = 128) leave most of the
- * chip idle and a block has at least 48 x 32 query rows to walk; its partial results (at most
- * 32 MiB) take the place of the partial dQ.  attn_bwd_rect_workspace_bytes(p) covers the
- * statistics and the larger of the two.  A workspace that holds the statistics but not the
- * partial results of a kernel is accepted too: that kernel then runs unsplit.  Either way the
- * plan depends only on the shape and the workspace size, so results are deterministic.
+ * statistics (two fp32 per query row, rounded up to 256 bytes) and, when the dQ kernel's launch
+ * is estimated to end sooner with its work-groups cut over the keys (few heads, long keys), the
+ * fp32 partial dQ of that split ([splits][B*Hq*Sq][64 or 128]); a third small kernel adds them.
+ * The dK/dV kernel is split over the query rows in the same way when the key blocks of the K/V heads
+ * (128 keys; 64 above D = 128) leave most of the chip idle and a block has at least 48 x 32 query rows
+ * to walk; its partial results (at most 32 MiB) take the place of the partial dQ.
+ * attn_bwd_rect_workspace_bytes(p) covers the statistics and the larger of the two.  A workspace
+ * that holds the statistics but not the partial results of a kernel is accepted too: that kernel
+ * then runs unsplit.  Either way the plan depends only on the shape and the workspace size, so
+ * results are deterministic.
  */
 typedef struct {
     int32_t B, Hq, Hkv, Sq, Sk, D;

@@ -125,14 +125,17 @@ bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) %
 }  // namespace
 
 // E: element type of Q, K, V, O (__bf16 or _Float16)
+// The fp32 partial results (O and LSE) of one split of the forward over the keys.
+static size_t fwd_part_bytes(const attn_rect_params_t *p)
+{
+    return (size_t)p->B * p->Hq * p->Sq * (kernel_d(p->D) + 1) * sizeof(float);
+}
 // Workspace that the forward's split over the keys takes with this problem's mask (0: it does not split).
-static size_t fwd_split_bytes(const attn_rect_params_t *p, bool rope)
+static size_t fwd_split_bytes(const attn_rect_params_t *p, bool rope, bool plain = false)
 {
     const FwdView v = fwd_view(*p, rope);
-    const int nsplit = attn::fwd_split_plan(v.BH, v.S, p->Sk, kernel_d(p->D), v.causal, nullptr);
-    if (nsplit <= 1) return 0;
-    const size_t rows = (size_t)p->B * p->Hq * p->Sq;
-    return round_ws((size_t)nsplit * rows * (kernel_d(p->D) + 1) * sizeof(float));
+    const int nsplit = attn::fwd_split_plan(v.BH, v.S, p->Sk, kernel_d(p->D), v.causal, nullptr, 128, plain);
+    return nsplit > 1 ? round_ws(nsplit * fwd_part_bytes(p)) : 0;
 }
 
 // What is asked of the caller: enough for the problem with and without a causal mask, so that a
@@ -197,13 +200,19 @@ static int fwd_impl(const void *Q, const void *K, const void *V, void *O, float 
     if (!aligned(Q, 16) || !aligned(K, 16) || !aligned(V, 16) || !aligned(O, 16) ||
         !aligned(LSE, 4))
         return ATTN_ERR_ALIGN;
-    // No workspace at all: run unsplit.  A workspace that is there must be usable.
+    // No workspace at all: run unsplit.  A workspace that is there must be usable: it holds the plan's
+    // partial results, or at least those of one work-group per compute unit; then the plan is the best
+    // of those that fit.
     const FwdView v = fwd_view(*p, rope != nullptr);
-    int kps = 0;
-    int nsplit = workspace ? attn::fwd_split_plan(v.BH, v.S, p->Sk, kernel_d(p->D), v.causal, &kps) : 1;
-    if (workspace && (!aligned(workspace, kWsAlign) ||
-                      workspace_bytes < fwd_split_bytes(p, rope != nullptr)))
-        return ATTN_ERR_WORKSPACE;
+    int kps = 0, nsplit = 1;
+    if (workspace) {
+        const size_t need = fwd_split_bytes(p, rope != nullptr);
+        if (!aligned(workspace, kWsAlign) ||
+            workspace_bytes < std::min(need, fwd_split_bytes(p, rope != nullptr, true)))
+            return ATTN_ERR_WORKSPACE;
+        const size_t fit = workspace_bytes < need ? workspace_bytes / fwd_part_bytes(p) : 128;
+        nsplit = attn::fwd_split_plan(v.BH, v.S, p->Sk, kernel_d(p->D), v.causal, &kps, (int)fit);
+    }
     attn::FwdArgsT<E> a;
     a.nsplit = nsplit; a.kps = kps;
     a.Opart = static_cast<float *>(workspace);

@@ -867,8 +867,8 @@ int split_plan(const SplitCost &c, int64_t wgs, int tiles, float average, size_t
 // The forward.  Decoding (at most 32 rows per head) runs in the streaming kernel and is bound by
 // memory, not by its longest work-group: at least one work-group per compute unit (256 with long key
 // ranges beat 512 or 1024 shorter ones there, 0.060 ms against 0.071 and 0.086 on the decode shape),
-// every split at least four tiles.
-int fwd_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps)
+// every split at least four tiles (`plain`: the same rule for any number of rows).
+int fwd_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps, int most, bool plain)
 {
     // (head dimensions above 128: four waves, 128 rows per work-group)
     const int nw = D > 128 ? 4 : fwd_waves_for(S, D, BH, causal);
@@ -876,12 +876,12 @@ int fwd_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps)
     const int64_t target = 256;
     const int tiles = (Sk + 63) / 64;
     int nsplit = 1;
-    if (S > 32) {
+    if (S > 32 && !plain) {
         const SplitCost cost = D > 128 ? SplitCost{10.0f, 4.3f, 4.3f, 5.0f, 256}
                                : D > 64 ? SplitCost{7.0f, 1.38f, 1.38f, 1.8f, 256}
                                : nw == 8 ? SplitCost{7.0f, 0.94f, 0.94f, 1.17f, 256}
                                          : SplitCost{7.0f, 0.67f, 0.67f, 0.69f, 512};
-        nsplit = split_plan(cost, wgs, tiles, tiles - S / 128.0f, (size_t)BH * S * D * 4, causal, 128);
+        nsplit = split_plan(cost, wgs, tiles, tiles - S / 128.0f, (size_t)BH * S * D * 4, causal, std::min(most, 128));
     } else if (wgs < target && tiles >= 8) {
         nsplit = (int)((target + wgs - 1) / wgs);
         if (nsplit > tiles / 4) nsplit = tiles / 4;

@@ -115,7 +115,7 @@ struct SplitCost { float fixed, alone, alone_split, full; int resident; };
 int split_plan(const SplitCost &c, int64_t wgs, int tiles, float average, size_t part_bytes, bool causal, int most);
 // fwd_split_plan: number of key splits the forward would use for this problem (1: none), and the keys per
 // split; a pure host function of the shape.
-int fwd_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps);
+int fwd_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps, int most = 128, bool plain = false);
 // `stages`: bit 0 row statistics, bit 1 dK/dV, bit 2 dQ.  With bits 0 and 2 the dQ kernel
 // forms the statistics (and runs first); bit 0 without bit 2 runs the separate kernel.
 // Number of key splits the dQ kernel would use for this problem (1: none) and the keys per
