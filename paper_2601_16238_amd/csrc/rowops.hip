@@ -495,12 +495,13 @@ int bwd_groups(int64_t rows, int V)
 // work-group per row, 24.8 us with 1024 groups, 23.2 us with 768 (three fit a unit).
 int fwd_groups(int64_t rows, int V, bool layernorm)
 {
-    const int per_cu = V == 1 ? 8 : V == 2 ? 4 : V == 4 ? (layernorm ? 3 : 4) : 2;
+    const int per_cu = V == 2 ? 4 : V == 4 ? (layernorm ? 3 : 4) : 2;
     const int64_t g = 256 * per_cu;
     return (int)(rows < g ? rows : g);
 }
 
-// vectors per thread: 1, 2, 4 or 8 with the work-group on a row, 1 .. 4 with a wave on it
+// vectors per thread: 1 (the backward of few rows only), 2, 4 or 8 with the work-group on a row, 1 .. 4
+// with a wave on it
 int vectors_for(int cols)
 {
     const int v = (cols / 8 + kThreads - 1) / kThreads;
@@ -537,7 +538,6 @@ int wave_groups(int64_t rows, int teams, int64_t cap)
 
 #define ROWOPS_DISPATCH(V, CALL)            \
     switch (V) {                            \
-        case 1: { constexpr int kV = 1; CALL; } break; \
         case 2: { constexpr int kV = 2; CALL; } break; \
         case 4: { constexpr int kV = 4; CALL; } break; \
         default: { constexpr int kV = 8; CALL; } break; \
@@ -634,6 +634,9 @@ int rowops_layernorm_bwd(const void *dy, const void *x, const float *w, const fl
             case 2: { constexpr int kV = 2; ROWOPS_LN_BWD(kThreads, 2); } break;
             default: { constexpr int kV = 4; ROWOPS_LN_BWD(kThreads, 2); } break;
         }
+    } else if (V == 1) {
+        constexpr int kV = 1;
+        ROWOPS_LN_BWD(kThreads, 1);
     } else {
         ROWOPS_DISPATCH(V, ROWOPS_LN_BWD(kThreads, 1));
     }
