@@ -3,7 +3,7 @@ forward and backward, rotary forward): argument marshalling only (csrc/marshal.c
 runs in the HIP kernels of libmi355attn.so."""
 import ctypes
 
-from .binding import lib, marshal
+from .binding import _call, lib, marshal
 
 EXPORTS = ("rowops_rmsnorm_fwd", "rowops_layernorm_fwd", "rowops_layernorm_bwd_workspace_bytes",
            "rowops_layernorm_bwd", "rowops_rotary_fwd")
@@ -28,16 +28,12 @@ def _lib():
     return L
 
 
-def _stream(stream):
-    return None if stream is None else stream.cuda_stream
-
-
 def rmsnorm_fwd(x, w, eps, y=None, stream=None):
-    return marshal().rmsnorm_fwd(x, w, eps, y, _stream(stream))
+    return _call(marshal().rmsnorm_fwd, stream, x, w, eps, y)
 
 
 def layernorm_fwd(x, w, b, eps, y=None, mean=None, rstd=None, stream=None):
-    return marshal().layernorm_fwd(x, w, b, eps, y, mean, rstd, _stream(stream))
+    return _call(marshal().layernorm_fwd, stream, x, w, b, eps, y, mean, rstd)
 
 
 def layernorm_bwd_workspace_bytes(rows, cols):
@@ -45,8 +41,8 @@ def layernorm_bwd_workspace_bytes(rows, cols):
 
 
 def layernorm_bwd(dy, x, w, mean, rstd, dx=None, dw=None, db=None, workspace=None, stream=None):
-    return marshal().layernorm_bwd(dy, x, w, mean, rstd, dx, dw, db, workspace, _stream(stream))
+    return _call(marshal().layernorm_bwd, stream, dy, x, w, mean, rstd, dx, dw, db, workspace)
 
 
 def rotary_fwd(x, cos, sin, y=None, stream=None):
-    return marshal().rotary_fwd(x, cos, sin, y, _stream(stream))
+    return _call(marshal().rotary_fwd, stream, x, cos, sin, y)

@@ -1,4 +1,6 @@
 """The native marshalling module: what it refuses, and how torch's own machinery sees the calls."""
+import contextlib
+
 import pytest
 import torch
 
@@ -23,6 +25,59 @@ def half(*shape):
 def test_refused_on_the_host(call, error):
     with pytest.raises(error):
         call()
+
+
+@pytest.mark.parametrize("name,args", [("rmsnorm_fwd", 3), ("layernorm_fwd", 4), ("layernorm_bwd", 5), ("rotary_fwd", 3)])
+def test_row_operations_allocate_on_the_stream_they_run_on(monkeypatch, name, args):
+    """Tensors a call allocates itself (outputs, the LayerNorm backward's workspace, dropped on return) have
+    to belong to the named stream: the native call is made while that stream is torch's current one."""
+    class Named:
+        cuda_stream = 0x40
+
+    current, seen = [], []
+
+    @contextlib.contextmanager
+    def stream(s):
+        current.append(s)
+        yield
+        current.pop()
+
+    class Native:
+        def __getattr__(self, _):
+            return lambda *a: seen.append((a[-1], list(current)))
+
+    side = Named()
+    monkeypatch.setattr(torch.cuda, "stream", stream)
+    monkeypatch.setattr(rowops, "marshal", Native)
+    getattr(rowops, name)(*[None] * args, stream=side)
+    getattr(rowops, name)(*[None] * args)
+    assert seen == [(side.cuda_stream, [side]), (None, [])]
+
+
+@pytest.mark.gpu
+def test_row_operations_on_another_stream():
+    """As on the current stream, while the current stream goes on allocating and writing blocks of the
+    workspace's and the outputs' sizes."""
+    print("case row operations on another stream", flush=True)
+    g = torch.Generator(device="cuda"); g.manual_seed(12)
+    x, dy = (torch.randn((4099, 384), device="cuda", generator=g).to(torch.bfloat16) for _ in range(2))
+    w, b = (torch.randn(384, device="cuda", generator=g) for _ in range(2))
+    t = torch.randn((2, 3, 70, 64), device="cuda", generator=g).to(torch.bfloat16)
+    cos, sin = (torch.randn((70, 32), device="cuda", generator=g) for _ in range(2))
+
+    def calls(stream):
+        y, mean, rstd = rowops.layernorm_fwd(x, w, b, 1e-5, stream=stream)
+        return [rowops.rmsnorm_fwd(x, w, 1e-6, stream=stream), y, mean, rstd,
+                *rowops.layernorm_bwd(dy, x, w, mean, rstd, stream=stream), rowops.rotary_fwd(t, cos, sin, stream=stream)]
+
+    here = calls(None)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    there = calls(side)
+    junk = [torch.full((n,), 0x7F, dtype=torch.uint8, device="cuda")
+            for n in (rowops.layernorm_bwd_workspace_bytes(4099, 384), 4099 * 768, 4099 * 4, 384 * 4) for _ in range(4)]
+    side.synchronize()
+    assert junk and all(torch.equal(p, q) for p, q in zip(here, there))
 
 
 @pytest.mark.gpu
