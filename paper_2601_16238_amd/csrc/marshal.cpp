@@ -8,6 +8,7 @@
 
 #include <c10/hip/HIPStream.h>
 
+#include <algorithm>
 #include <initializer_list>
 #include <optional>
 #include <string>
@@ -335,14 +336,33 @@ const Tensor &rows_of(const Tensor &t, const char *name)
     return t;
 }
 
-const Tensor &f32_of(const Tensor &t, at::IntArrayRef shape, const char *name)
+// An output of the caller's: the library gets only x's rows and columns and writes that many, so there
+// has to be room for them.
+const Tensor &rows_for(const Tensor &x, const Tensor &t, const char *name)
 {
-    if (t.scalar_type() != at::kFloat || !t.is_cuda() || !t.is_contiguous() || t.sizes() != shape) {
+    rows_of(t, name);
+    if (t.size(0) < x.size(0) || t.size(1) < x.size(1) || t.device() != x.device())
+        throw py::value_error(std::string(name) + " must hold x's rows and columns, on x's device");
+    return t;
+}
+
+const Tensor &f32_of(const Tensor &x, const Tensor &t, at::IntArrayRef shape, const char *name)
+{
+    if (t.scalar_type() != at::kFloat || t.device() != x.device() || !t.is_contiguous() || t.sizes() != shape) {
         std::string s = std::string(name) + " must be a contiguous fp32 GPU tensor of shape (";
         for (int64_t n : shape) s += std::to_string(n) + ", ";
-        throw py::value_error(s + ")");
+        throw py::value_error(s + ") on x's device");
     }
     return t;
+}
+
+// Bytes of a workspace: not more than lie between its first element and the end of its storage (an
+// expanded tensor counts elements that it does not have).
+size_t bytes_of(const Tensor &ws, const Tensor &x)
+{
+    require(ws.device() == x.device(), "the workspace must be on the tensors' device");
+    const size_t offset = ws.storage_offset() * ws.itemsize(), end = ws.storage().nbytes();
+    return std::min(ws.nbytes(), end > offset ? end - offset : 0);
 }
 
 float *floats(const Tensor &t) { return static_cast<float *>(t.data_ptr()); }
@@ -351,8 +371,8 @@ Tensor rmsnorm_fwd(const Tensor &x, const Tensor &w, double eps, const OptTensor
 {
     rows_of(x, "x");
     const int64_t rows = x.size(0), cols = x.size(1);
-    f32_of(w, {cols}, "w");
-    const Tensor y = y_in ? rows_of(*y_in, "y") : at::empty_like(x);
+    f32_of(x, w, {cols}, "w");
+    const Tensor y = y_in ? rows_for(x, *y_in, "y") : at::empty_like(x);
     void *const X = x.data_ptr(), *const Y = y.data_ptr(), *const st = stream_ptr(stream);
     check_status(unlocked([&, W = floats(w)] {
         return rowops_rmsnorm_fwd(X, W, Y, rows, cols, x.stride(0), y.stride(0), (float)eps, st);
@@ -366,11 +386,11 @@ std::tuple<Tensor, Tensor, Tensor> layernorm_fwd(const Tensor &x, const Tensor &
 {
     rows_of(x, "x");
     const int64_t rows = x.size(0), cols = x.size(1);
-    f32_of(w, {cols}, "w");
-    f32_of(b, {cols}, "b");
-    const Tensor y = y_in ? rows_of(*y_in, "y") : at::empty_like(x);
+    f32_of(x, w, {cols}, "w");
+    f32_of(x, b, {cols}, "b");
+    const Tensor y = y_in ? rows_for(x, *y_in, "y") : at::empty_like(x);
     auto stat = [&](const OptTensor &t, const char *name) {
-        return t ? f32_of(*t, {rows}, name) : at::empty({rows}, x.options().dtype(at::kFloat));
+        return t ? f32_of(x, *t, {rows}, name) : at::empty({rows}, x.options().dtype(at::kFloat));
     };
     const Tensor mean = stat(mean_in, "mean"), rstd = stat(rstd_in, "rstd");
     void *const X = x.data_ptr(), *const Y = y.data_ptr(), *const st = stream_ptr(stream);
@@ -387,20 +407,21 @@ Grads layernorm_bwd(const Tensor &dy, const Tensor &x, const Tensor &w, const Te
     rows_of(x, "x");
     rows_of(dy, "dy");
     const int64_t rows = x.size(0), cols = x.size(1);
-    require(dy.sizes() == x.sizes(), "dy and x must have one shape");
-    f32_of(w, {cols}, "w");
-    f32_of(mean, {rows}, "mean");
-    f32_of(rstd, {rows}, "rstd");
-    const Tensor dx = dx_in ? rows_of(*dx_in, "dx") : at::empty_like(x);
+    require(dy.sizes() == x.sizes() && dy.device() == x.device(), "dy and x must have one shape and device");
+    f32_of(x, w, {cols}, "w");
+    f32_of(x, mean, {rows}, "mean");
+    f32_of(x, rstd, {rows}, "rstd");
+    const Tensor dx = dx_in ? rows_for(x, *dx_in, "dx") : at::empty_like(x);
     auto column = [&](const OptTensor &t, const char *name) {
-        return t ? f32_of(*t, {cols}, name) : at::empty({cols}, x.options().dtype(at::kFloat));
+        return t ? f32_of(x, *t, {cols}, name) : at::empty({cols}, x.options().dtype(at::kFloat));
     };
     const Tensor dw = column(dw_in, "dw"), db = column(db_in, "db");
     const Tensor ws = ws_in ? *ws_in : bytes_on(rowops_layernorm_bwd_workspace_bytes(rows, cols), x);
+    const size_t ws_bytes = bytes_of(ws, x);
     void *const DY = dy.data_ptr(), *const X = x.data_ptr(), *const DX = dx.data_ptr(), *const WS = ws.data_ptr(),
                *const st = stream_ptr(stream);
     check_status(unlocked([&, W = floats(w), M = floats(mean), R = floats(rstd), DW = floats(dw), DB = floats(db)] {
-        return rowops_layernorm_bwd(DY, X, W, M, R, DX, DW, DB, WS, ws.nbytes(), rows, cols, dy.stride(0),
+        return rowops_layernorm_bwd(DY, X, W, M, R, DX, DW, DB, WS, ws_bytes, rows, cols, dy.stride(0),
                                     x.stride(0), dx.stride(0), st);
     }), "rowops_layernorm_bwd");
     return {dx, dw, db};
@@ -411,10 +432,11 @@ Tensor rotary_fwd(const Tensor &x, const Tensor &cos, const Tensor &sin, const O
     require(x.scalar_type() == at::kBFloat16 && x.is_cuda() && x.dim() == 4 && x.stride(3) == 1,
             "x must be a bf16 [B,H,S,D] GPU tensor with a contiguous D axis");
     const int64_t B = x.size(0), H = x.size(1), S = x.size(2), D = x.size(3);
-    f32_of(cos, {S, D / 2}, "cos");
-    f32_of(sin, {S, D / 2}, "sin");
-    if (y_in) require(y_in->sizes() == x.sizes() && y_in->scalar_type() == x.scalar_type() && y_in->stride(3) == 1,
-                      "y must match x in shape and type");
+    f32_of(x, cos, {S, D / 2}, "cos");
+    f32_of(x, sin, {S, D / 2}, "sin");
+    if (y_in) require(y_in->sizes() == x.sizes() && y_in->scalar_type() == x.scalar_type() &&
+                          y_in->device() == x.device() && y_in->stride(3) == 1,
+                      "y must match x in shape, type and device");
     const Tensor y = y_in ? *y_in : empty_as(x);
     void *const X = x.data_ptr(), *const Y = y.data_ptr(), *const st = stream_ptr(stream);
     check_status(unlocked([&, C = floats(cos), N = floats(sin)] {

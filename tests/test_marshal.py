@@ -3,6 +3,7 @@ import contextlib
 
 import pytest
 import torch
+from torch._subclasses.fake_tensor import FakeTensorMode
 
 import paper_2601_16238_amd as attn
 from paper_2601_16238_amd import rowops
@@ -25,6 +26,58 @@ def half(*shape):
 def test_refused_on_the_host(call, error):
     with pytest.raises(error):
         call()
+
+
+def on_gpu(*shape, dtype=torch.bfloat16, device="cuda"):
+    """A tensor that says it is on a GPU and has no memory: what the checks see, on the host."""
+    with FakeTensorMode():
+        return torch.empty(shape, dtype=dtype, device=device)
+
+
+def f32(*shape, **k):
+    return on_gpu(*shape, dtype=torch.float32, **k)
+
+
+def layernorm_bwd(dy=on_gpu(8, 64), x=on_gpu(8, 64), w=f32(64), mean=f32(8), rstd=f32(8), **out):
+    given = dict(dx=on_gpu(8, 64), dw=f32(64), db=f32(64))   # nothing is allocated before the checks
+    return rowops.layernorm_bwd(dy, x, w, mean, rstd, **{**given, **out})
+
+
+# the kernels write x's rows and columns wherever an output begins
+@pytest.mark.parametrize("call", [
+    lambda: rowops.rmsnorm_fwd(on_gpu(8, 64), f32(64), 1e-6, y=on_gpu(7, 64)),
+    lambda: rowops.rmsnorm_fwd(on_gpu(8, 64), f32(64), 1e-6, y=on_gpu(8, 56)),
+    lambda: rowops.rmsnorm_fwd(on_gpu(8, 64), f32(64), 1e-6, y=on_gpu(8, 64, device="cuda:1")),
+    lambda: rowops.rmsnorm_fwd(on_gpu(8, 64), f32(64, device="cuda:1"), 1e-6),
+    lambda: rowops.layernorm_fwd(on_gpu(8, 64), f32(64), f32(64), 1e-5, y=on_gpu(7, 64)),
+    lambda: rowops.layernorm_fwd(on_gpu(8, 64), f32(64), f32(64), 1e-5, mean=f32(8, device="cuda:1")),
+    lambda: layernorm_bwd(dx=on_gpu(7, 64)),
+    lambda: layernorm_bwd(dx=on_gpu(8, 56)),
+    lambda: layernorm_bwd(dy=on_gpu(8, 64, device="cuda:1")),
+    lambda: layernorm_bwd(rstd=f32(8, device="cuda:1")),
+    lambda: layernorm_bwd(db=f32(64, device="cuda:1")),
+    lambda: layernorm_bwd(workspace=on_gpu(1 << 20, dtype=torch.uint8, device="cpu")),
+    lambda: rowops.rotary_fwd(on_gpu(1, 1, 8, 64), f32(8, 32), f32(8, 32), y=on_gpu(1, 1, 8, 64, device="cuda:1")),
+    lambda: rowops.rotary_fwd(on_gpu(1, 1, 8, 64), f32(8, 32), f32(8, 32, device="cuda:1")),
+])
+def test_row_operations_refuse_outputs_without_room_and_other_devices(call):
+    with pytest.raises(ValueError):
+        call()
+
+
+@pytest.mark.gpu
+def test_row_operations_write_into_larger_outputs():
+    print("case row operations into larger outputs", flush=True)
+    g = torch.Generator(device="cuda"); g.manual_seed(13)
+    x, w = torch.randn((9, 64), device="cuda", generator=g).to(torch.bfloat16), torch.randn(64, device="cuda", generator=g)
+    y = torch.full((11, 80), 3.0, dtype=torch.bfloat16, device="cuda")
+    assert rowops.rmsnorm_fwd(x, w, 1e-6, y=y) is y
+    torch.cuda.synchronize()
+    assert torch.equal(y[:9, :64], rowops.rmsnorm_fwd(x, w, 1e-6))
+    assert bool((y[9:] == 3.0).all()) and bool((y[:, 64:] == 3.0).all())
+    mean, rstd = (torch.ones(9, device="cuda") for _ in range(2))
+    with pytest.raises(attn.AttnError):   # one byte of memory, however many elements it is expanded to
+        rowops.layernorm_bwd(x, x, w, mean, rstd, workspace=torch.zeros(1, dtype=torch.uint8, device="cuda").expand(1 << 20))
 
 
 @pytest.mark.parametrize("name,args", [("rmsnorm_fwd", 3), ("layernorm_fwd", 4), ("layernorm_bwd", 5), ("rotary_fwd", 3)])
