@@ -262,9 +262,9 @@ def _stream_ptr(torch, stream):
     return ctypes.c_void_p(s.cuda_stream)
 
 
-def _check_lse(torch, LSE, shape):
-    if LSE.dtype != torch.float32 or not LSE.is_contiguous() or tuple(LSE.shape) != tuple(shape):
-        raise ValueError("LSE must be a contiguous fp32 [B,Hq,Sq] tensor")
+def _check_lse(torch, LSE, Q):
+    if LSE.dtype != torch.float32 or not LSE.is_contiguous() or LSE.shape != Q.shape[:3] or LSE.device != Q.device:
+        raise ValueError("LSE must be a contiguous fp32 [B,Hq,Sq] tensor on the tensors' device")
 
 
 def _call(entry, stream, *args):
@@ -390,8 +390,9 @@ def attn_bwd_rect_noalloc(Q, K, V, O, dO, LSE, scale, causal, dQ, dK, dV, stream
         raise ValueError("tensors must be bf16 on the GPU")
     _same_layout(Q, O, dO, dQ)
     _same_layout(K, V, dK, dV)
-    B, H, S, D = Q.shape
-    _check_lse(torch, LSE, (B, H, S))
+    if K.dtype != Q.dtype or K.device != Q.device:
+        raise ValueError("all tensors must share dtype and device")
+    _check_lse(torch, LSE, Q)
     p = _rect_params_for(Q, K, scale, causal)
     rc = lib().attn_bwd_rect_noalloc(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(),
                                      dO.data_ptr(), LSE.data_ptr(), dQ.data_ptr(), dK.data_ptr(),

@@ -77,8 +77,9 @@ void check_element_type(const Tensor &q, bool f16_too, const char *what)
 
 void check_lse(const Tensor &lse, const Tensor &q)
 {
-    require(lse.scalar_type() == at::kFloat && lse.is_contiguous() && lse.sizes() == q.sizes().slice(0, 3),
-            "LSE must be a contiguous fp32 [B,Hq,Sq] tensor");
+    require(lse.scalar_type() == at::kFloat && lse.is_contiguous() && lse.sizes() == q.sizes().slice(0, 3) &&
+                lse.device() == q.device(),
+            "LSE must be a contiguous fp32 [B,Hq,Sq] tensor on the tensors' device");
 }
 
 Tensor empty_as(const Tensor &t) { return at::empty_strided(t.sizes(), t.strides(), t.options()); }
@@ -129,7 +130,16 @@ Tensor forward_workspace(size_t need, const OptTensor &given, bool split, const 
 }
 
 void *data_of(const Tensor &t) { return t.defined() ? t.data_ptr() : nullptr; }
-size_t bytes_of(const Tensor &t) { return t.defined() ? t.nbytes() : 0; }
+
+// Bytes of a workspace (none: 0) for a call on x: not more than lie between its first element and the end
+// of its storage (an expanded tensor counts elements that it does not have).
+size_t bytes_of(const Tensor &ws, const Tensor &x)
+{
+    if (!ws.defined()) return 0;
+    require(ws.device() == x.device(), "the workspace must be on the tensors' device");
+    const size_t offset = ws.storage_offset() * ws.itemsize(), end = ws.storage().nbytes();
+    return std::min(ws.nbytes(), end > offset ? end - offset : 0);
+}
 
 std::tuple<Tensor, Tensor> run_forward(const char *where, const attn_rect_params_t &p, const Tensor &q,
                                        const Tensor &k, const Tensor &v, bool f16_too, const OptTensor &o_in,
@@ -139,11 +149,12 @@ std::tuple<Tensor, Tensor> run_forward(const char *where, const attn_rect_params
     Tensor o, lse;
     forward_outputs(q, k, v, f16_too, o, lse, o_in, lse_in);
     const Tensor ws = forward_workspace(split && !ws_in ? attn_fwd_rect_workspace_bytes(&p) : 0, ws_in, split, q);
+    const size_t bytes = bytes_of(ws, q);
     void *const Q = q.data_ptr(), *const K = k.data_ptr(), *const V = v.data_ptr(), *const O = o.data_ptr(),
                *const W = data_of(ws), *const st = stream_ptr(stream);
     float *const L = static_cast<float *>(lse.data_ptr());
     check_status(unlocked([&] {
-        return (q.scalar_type() == at::kHalf ? attn_fwd_rect_f16 : attn_fwd_rect)(Q, K, V, O, L, W, bytes_of(ws), &p, st);
+        return (q.scalar_type() == at::kHalf ? attn_fwd_rect_f16 : attn_fwd_rect)(Q, K, V, O, L, W, bytes, &p, st);
     }), where);
     return {o, lse};
 }
@@ -168,13 +179,13 @@ Grads run_backward(const char *where, const attn_rect_params_t &p, const Tensor 
     };
     const Tensor dq = out(dq_in, q), dk = out(dk_in, k), dv = out(dv_in, k);
     const Tensor ws = ws_in ? *ws_in : bytes_on(attn_bwd_rect_workspace_bytes(&p), q);
+    const size_t bytes = bytes_of(ws, q);
     void *const Q = q.data_ptr(), *const K = k.data_ptr(), *const V = v.data_ptr(), *const O = o.data_ptr(),
                *const G = g.data_ptr(), *const DQ = dq.data_ptr(), *const DK = dk.data_ptr(),
                *const DV = dv.data_ptr(), *const W = ws.data_ptr(), *const st = stream_ptr(stream);
     const float *const L = static_cast<const float *>(lse.data_ptr());
     const float *const C = cos ? static_cast<const float *>(cos->data_ptr()) : nullptr,
                 *const S = sin ? static_cast<const float *>(sin->data_ptr()) : nullptr;
-    const size_t bytes = ws.nbytes();
     check_status(unlocked([&] {
         if (cos) return attn_bwd_rope(Q, K, V, O, G, L, C, S, DQ, DK, DV, W, bytes, &p, st);
         if (stages) {
@@ -254,9 +265,9 @@ Grads attn_bwd_rect_(const Tensor &q, const Tensor &k, const Tensor &v, const Te
 void check_tables(const Tensor &cos, const Tensor &sin, const Tensor &k)
 {
     for (const Tensor *t : {&cos, &sin})
-        require(t->scalar_type() == at::kFloat && t->is_cuda() && t->is_contiguous() && t->dim() == 2 &&
+        require(t->scalar_type() == at::kFloat && t->device() == k.device() && t->is_contiguous() && t->dim() == 2 &&
                     t->size(0) == k.size(2) && t->size(1) == k.size(3) / 2,
-                "cos/sin tables must be contiguous fp32 [Sk, D/2] tensors on the GPU");
+                "cos/sin tables must be contiguous fp32 [Sk, D/2] tensors on the tensors' device");
 }
 
 std::tuple<Tensor, Tensor, OptTensor> attn_fwd_rope_(const Tensor &q, const Tensor &k, const Tensor &v,
@@ -277,7 +288,7 @@ std::tuple<Tensor, Tensor, OptTensor> attn_fwd_rope_(const Tensor &q, const Tens
                *const R = qrot ? qrot->data_ptr() : nullptr, *const W = data_of(ws), *const st = stream_ptr(stream);
     float *const L = static_cast<float *>(lse.data_ptr());
     const float *const C = static_cast<const float *>(cos.data_ptr()), *const S = static_cast<const float *>(sin.data_ptr());
-    check_status(unlocked([&] { return attn_fwd_rope(Q, K, V, C, S, O, L, R, W, bytes_of(ws), &p, st); }),
+    check_status(unlocked([&] { return attn_fwd_rope(Q, K, V, C, S, O, L, R, W, bytes_of(ws, q), &p, st); }),
                  "attn_fwd_rope");
     return {o, lse, qrot};
 }
@@ -354,15 +365,6 @@ const Tensor &f32_of(const Tensor &x, const Tensor &t, at::IntArrayRef shape, co
         throw py::value_error(s + ") on x's device");
     }
     return t;
-}
-
-// Bytes of a workspace: not more than lie between its first element and the end of its storage (an
-// expanded tensor counts elements that it does not have).
-size_t bytes_of(const Tensor &ws, const Tensor &x)
-{
-    require(ws.device() == x.device(), "the workspace must be on the tensors' device");
-    const size_t offset = ws.storage_offset() * ws.itemsize(), end = ws.storage().nbytes();
-    return std::min(ws.nbytes(), end > offset ? end - offset : 0);
 }
 
 float *floats(const Tensor &t) { return static_cast<float *>(t.data_ptr()); }

@@ -43,6 +43,61 @@ def layernorm_bwd(dy=on_gpu(8, 64), x=on_gpu(8, 64), w=f32(64), mean=f32(8), rst
     return rowops.layernorm_bwd(dy, x, w, mean, rstd, **{**given, **out})
 
 
+def heads(H=2, S=8, D=64, **k):
+    return on_gpu(1, H, S, D, **k)
+
+
+def fwd_rect(q=heads(), k=heads(), O=heads(), LSE=f32(1, 2, 8), **out):
+    return attn.attn_fwd_rect(q, k, k, 0.1, False, O=O, LSE=LSE, **out)
+
+
+def bwd_rect(call=attn.attn_bwd_rect, q=heads(), k=heads(), LSE=f32(1, 2, 8), **out):
+    given = dict(dQ=heads(), dK=k, dV=k)
+    return call(q, k, k, q, q, LSE, 0.1, False, **{**given, **out})
+
+
+def fwd_rope(cos=f32(8, 32), sin=f32(8, 32)):
+    return attn.attn_fwd_rope(heads(), heads(), heads(), cos, sin, 0.1, False, O=heads(), LSE=f32(1, 2, 8))
+
+
+ELSEWHERE = [dict(device="cpu"), dict(device="cuda:1")]
+
+
+@pytest.mark.parametrize("where", ELSEWHERE)
+@pytest.mark.parametrize("call", [
+    lambda w: fwd_rect(LSE=f32(1, 2, 8, **w)),
+    lambda w: fwd_rect(workspace=on_gpu(1 << 20, dtype=torch.uint8, **w)),
+    lambda w: bwd_rect(LSE=f32(1, 2, 8, **w)),
+    lambda w: bwd_rect(workspace=on_gpu(1 << 20, dtype=torch.uint8, **w)),
+    lambda w: bwd_rect(attn.attn_bwd_rect_noalloc, LSE=f32(1, 2, 8, **w)),
+    lambda w: bwd_rect(attn.attn_bwd_rect_noalloc, k=heads(**w)),
+    lambda w: fwd_rope(cos=f32(8, 32, **w)),
+    lambda w: fwd_rope(sin=f32(8, 32, **w)),
+])
+def test_attention_refuses_tensors_of_another_device(call, where):
+    with pytest.raises(ValueError):
+        call(where)
+
+
+def test_noalloc_backward_refuses_mixed_types():
+    with pytest.raises(ValueError):
+        bwd_rect(attn.attn_bwd_rect_noalloc, k=heads(dtype=torch.uint8))
+
+
+@pytest.mark.gpu
+def test_attention_workspace_is_counted_to_the_end_of_its_storage():
+    print("case attention workspace storage", flush=True)
+    q = torch.zeros((1, 2, 300, 64), dtype=torch.bfloat16, device="cuda")
+    lse = torch.zeros((1, 2, 300), device="cuda")
+    one = torch.zeros(1, dtype=torch.uint8, device="cuda").expand(1 << 24)
+    with pytest.raises(attn.AttnError):
+        attn.attn_bwd_rect(q, q, q, q, q, lse, 0.1, False, workspace=one)
+    k = torch.zeros((1, 2, 9000, 64), dtype=torch.bfloat16, device="cuda")
+    assert attn.attn_fwd_rect_workspace_bytes(1, 2, 2, 300, 9000, 64)
+    with pytest.raises(attn.AttnError):
+        attn.attn_fwd_rect(q, k, k, 0.1, False, workspace=one)
+
+
 # the kernels write x's rows and columns wherever an output begins
 @pytest.mark.parametrize("call", [
     lambda: rowops.rmsnorm_fwd(on_gpu(8, 64), f32(64), 1e-6, y=on_gpu(7, 64)),
