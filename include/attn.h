@@ -196,7 +196,8 @@ int attn_bwd_gqa_stages(const void *Q, const void *K, const void *V, const void 
  * to walk; its partial results (at most 32 MiB) take the place of the partial dQ.
  * attn_bwd_rect_workspace_bytes(p) covers the statistics and the larger of the two.  A workspace
  * that holds the statistics but not the partial results of a kernel is accepted too: that kernel
- * then runs unsplit.  Either way the plan depends only on the shape and the workspace size, so
+ * then runs with fewer splits, or longer chunks of the query rows, as far as they fit, and unsplit
+ * where no split does.  Either way the plan depends only on the shape and the workspace size, so
  * results are deterministic.
  */
 typedef struct {
@@ -262,9 +263,10 @@ int attn_bwd_rope(const void *Q_rot, const void *K_rot, const void *V, const voi
 /*
  * attn_bwd_rect for callers that cannot allocate device memory or pass a workspace: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  The
- * backward's scratch (two fp32 values per query row) lives in an array inside the library's
- * device image, ATTN_NOALLOC_SCRATCH_BYTES long; each GPU the library runs on holds its own
- * copy until the process ends.  Arguments, validation and stream semantics are those of
+ * backward's scratch (two fp32 values per query row, and in what is left the fp32 partial
+ * results of the splits that fit, as in a workspace of this size) lives in an array inside the
+ * library's device image, ATTN_NOALLOC_SCRATCH_BYTES long; each GPU the library runs on holds its
+ * own copy until the process ends.  Arguments, validation and stream semantics are those of
  * attn_bwd_rect without the workspace pair; results are bit for bit those of attn_bwd_rect
  * called with a workspace of ATTN_NOALLOC_SCRATCH_BYTES bytes.
  *   - Problems with more than ATTN_NOALLOC_SCRATCH_BYTES / 8 query rows (B*Hq*Sq) give

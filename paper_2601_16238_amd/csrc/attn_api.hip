@@ -158,17 +158,24 @@ static size_t bwd_stats_bytes(const attn_rect_params_t *p)
 // The fp32 partial results of the dQ kernel's split over the keys and of the dK/dV kernel's split
 // over the query slots (0: not split).  The two kernels run one after the other, each with its
 // merge, so their partial results share one region behind the statistics.
+static size_t dq_split_bytes(const attn_rect_params_t *p)  // of one split
+{
+    return (size_t)p->B * p->Hq * p->Sq * kernel_d(p->D) * sizeof(float);
+}
 static size_t dq_part_bytes(const attn_rect_params_t *p, bool causal)
 {
     const int nsplit = attn::dq_split_plan(p->B * p->Hq, p->Sq, p->Sk, kernel_d(p->D), causal, nullptr);
-    return nsplit > 1 ? round_ws((size_t)nsplit * p->B * p->Hq * p->Sq * kernel_d(p->D) * sizeof(float)) : 0;
+    return nsplit > 1 ? round_ws(nsplit * dq_split_bytes(p)) : 0;
+}
+static size_t dkdv_chunk_bytes(const attn_rect_params_t *p)  // of one chunk
+{
+    return (size_t)2 * attn::dkdv_split_keys(kernel_d(p->D)) * kernel_d(p->D) * sizeof(float);
 }
 static size_t dkdv_part_bytes(const attn_rect_params_t *p, bool causal)
 {
-    const int D = kernel_d(p->D);
     int chunk = 0;
-    const int items = attn::dkdv_split_plan(p->B * p->Hkv, p->Hq / p->Hkv, p->Sq, p->Sk, D, causal, &chunk);
-    return chunk ? round_ws((size_t)p->B * p->Hkv * items * 2 * attn::dkdv_split_keys(D) * D * sizeof(float)) : 0;
+    const int items = attn::dkdv_split_plan(p->B * p->Hkv, p->Hq / p->Hkv, p->Sq, p->Sk, kernel_d(p->D), causal, &chunk);
+    return chunk ? round_ws((size_t)p->B * p->Hkv * items * dkdv_chunk_bytes(p)) : 0;
 }
 
 // Rotary embedding fused into the call (both tables NULL: none).
@@ -252,20 +259,21 @@ static int bwd_impl(const void *Q, const void *K, const void *V, const void *O, 
         !aligned(dO, 16) || !aligned(dQ, 16) || !aligned(dK, 16) || !aligned(dV, 16) ||
         !aligned(LSE, 4))
         return ATTN_ERR_ALIGN;
-    // The row statistics always; the partial results of a split only if they fit as well (a
-    // smaller workspace runs that kernel unsplit).  No split of dQ with rotary tables: the merge
-    // does not rotate back.
+    // The row statistics always; the rest of the workspace bounds the splits.  (A plan that is dropped
+    // where it does not fit whole costs, in the 8 MiB of the call without workspace, us: one head of 1024
+    // rows on 4096 keys, D = 128, causal 112 against 55 with the splits that fit; 4 -> 1 heads of 2048,
+    // D = 64, causal 180 against 51.)  No split of dQ with rotary tables: the merge does not rotate back.
     const size_t stats_bytes = bwd_stats_bytes(p);
     if (!workspace || !aligned(workspace, kWsAlign) || workspace_bytes < stats_bytes)
         return ATTN_ERR_WORKSPACE;
     if (stages == 0 || (stages & ~7u)) return ATTN_ERR_SHAPE;
-    int dq_kps = 0;
-    int dq_nsplit = attn::dq_split_plan(p->B * p->Hq, p->Sq, p->Sk, kernel_d(p->D), p->causal != 0, &dq_kps);
-    if (rope || workspace_bytes < stats_bytes + dq_part_bytes(p, p->causal != 0)) dq_nsplit = 1;
-    int dkdv_chunk = 0;
+    const size_t room = workspace_bytes - stats_bytes;
+    int dq_kps = 0, dkdv_chunk = 0;
+    const int dq_nsplit = attn::dq_split_plan(p->B * p->Hq, p->Sq, p->Sk, kernel_d(p->D), p->causal != 0, &dq_kps,
+                                              rope ? 1 : (int)std::min<size_t>(16, room / dq_split_bytes(p)));
     const int dkdv_items = attn::dkdv_split_plan(p->B * p->Hkv, p->Hq / p->Hkv, p->Sq, p->Sk, kernel_d(p->D),
-                                                 p->causal != 0, &dkdv_chunk);
-    if (workspace_bytes < stats_bytes + dkdv_part_bytes(p, p->causal != 0)) dkdv_chunk = 0;
+                                                 p->causal != 0, &dkdv_chunk,
+                                                 (int64_t)std::min<size_t>(512, room / dkdv_chunk_bytes(p)));
     attn::BwdArgsT<E> a;
     a.Q = static_cast<const E *>(Q);
     a.K = static_cast<const E *>(K);

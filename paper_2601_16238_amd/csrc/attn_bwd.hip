@@ -1292,7 +1292,7 @@ static int launch_bwd_d(BwdArgs a, bool causal, hipStream_t st, unsigned stages)
 // 34 -> 39 (2), 16 of 1024 29 -> 34 (4).  Needs at least 256 query rows per head (a 256-row work-group
 // must have rows to work on) -- decoding shapes have one row per head and many heads, and are not split.
 #ifndef ATTN_F16  // a function of the shape only: defined once, by the bf16 build
-int dq_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps)
+int dq_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps, int most)
 {
     if (D > 128) {  // the kernel for head dimensions above 128 is not split
         if (kps) *kps = (Sk + 63) / 64 * 64;
@@ -1304,7 +1304,7 @@ int dq_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps)
     if (S >= 256)
         // (the unsplit launch has work-groups of 128 rows, the split one of 256)
         nsplit = split_plan(D > 64 ? SplitCost{7.0f, 1.38f, 1.6f, 2.2f, 256} : SplitCost{7.0f, 0.94f, 1.0f, 1.6f, 512},
-                            wgs, tiles, tiles - S / 128.0f, (size_t)BH * S * D * 4, causal, 16);
+                            wgs, tiles, tiles - S / 128.0f, (size_t)BH * S * D * 4, causal, std::min(most, 16));
     const int tiles_per = (tiles + nsplit - 1) / nsplit;
     nsplit = (tiles + tiles_per - 1) / tiles_per;  // no empty split
     if (kps) *kps = tiles_per * 64;
@@ -1322,7 +1322,7 @@ int dq_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps)
 // the longest block, where the merge (about 5 us) takes most of what is gained and dK and dV keep
 // the one order of their sums that does not depend on the workspace; nor unless a chunk is at most
 // three quarters of the longest block.
-int dkdv_split_plan(int BHkv, int group, int S, int Sk, int D, bool causal, int *chunk)
+int dkdv_split_plan(int BHkv, int group, int S, int Sk, int D, bool causal, int *chunk, int64_t most)
 {
     const int keys = dkdv_split_keys(D), n_block = (Sk + keys - 1) / keys;
     const int64_t resident = D == 64 ? 512 : 256;
@@ -1340,7 +1340,7 @@ int dkdv_split_plan(int BHkv, int group, int S, int Sk, int D, bool causal, int 
             const int64_t n = dkdv_slots(kt, keys, group, S, Sk, causal);
             items += n ? (n + L - 1) / L : 1;
         }
-        if (items * BHkv <= resident) {
+        if (items * BHkv <= std::min(resident, most)) {
             *chunk = (int)L;
             return (int)items;
         }

@@ -120,10 +120,12 @@ int fwd_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps, int most
 // forms the statistics (and runs first); bit 0 without bit 2 runs the separate kernel.
 // Number of key splits the dQ kernel would use for this problem (1: none) and the keys per
 // split; a pure host function of the shape.
-int dq_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps);
+// At most `most` splits.
+int dq_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps, int most = 16);
 // Split of the dK/dV kernel over the query slots: returns the chunks (work-groups) per K/V head and
-// the slots per chunk (0: not split, one work-group per key block); a pure host function of the shape.
-int dkdv_split_plan(int BHkv, int group, int S, int Sk, int D, bool causal, int *chunk);
+// the slots per chunk (0: not split, one work-group per key block), at most `most` chunks in all; a pure
+// host function of the shape.
+int dkdv_split_plan(int BHkv, int group, int S, int Sk, int D, bool causal, int *chunk, int64_t most = 512);
 // Keys per work-group of the split dK/dV kernel, and the 32-row query slots (over all query heads of
 // the group) that key block kt has to walk: all of them, or under a causal mask those from the
 // block's diagonal on.
