@@ -182,10 +182,12 @@ int attn_bwd_gqa_stages(const void *Q, const void *K, const void *V, const void 
  * them (log-sum-exp weights).  attn_fwd_rect_workspace_bytes returns what that needs for the
  * problem with or without a causal mask (the larger of the two), 0 when neither would split.
  * workspace == NULL (with any size) is allowed and means: do not split.  A non-NULL workspace must
- * be 256-byte aligned and large enough for the split of this call (that size always is) or for a split
- * into one work-group per compute unit (no split where that would be none), which then bounds the
- * split, else ATTN_ERR_WORKSPACE; its contents are undefined on entry and exit.  The split plan
- * depends only on the shape, the strides and that size, so results are deterministic.
+ * be 256-byte aligned and large enough for the split of this call (that size always is).  A smaller
+ * one is accepted, and bounds the split, if it is large enough for a split into one work-group per
+ * compute unit or for the split at which the longest work-group is estimated to end first (any size
+ * where either of those would be no split); else ATTN_ERR_WORKSPACE.  Its contents are undefined on
+ * entry and exit.  The split plan depends only on the shape, the strides and that size, so results
+ * are deterministic.
  *
  * Backward: as attn_bwd_gqa.  Keys that no row sees get zero gradients.  Workspace: the row
  * statistics (two fp32 per query row, rounded up to 256 bytes) and, when the dQ kernel's launch

@@ -131,10 +131,10 @@ static size_t fwd_part_bytes(const attn_rect_params_t *p)
     return (size_t)p->B * p->Hq * p->Sq * (kernel_d(p->D) + 1) * sizeof(float);
 }
 // Workspace that the forward's split over the keys takes with this problem's mask (0: it does not split).
-static size_t fwd_split_bytes(const attn_rect_params_t *p, bool rope, bool plain = false)
+static size_t fwd_split_bytes(const attn_rect_params_t *p, bool rope, attn::SplitRule rule = attn::SplitRule::plan)
 {
     const FwdView v = fwd_view(*p, rope);
-    const int nsplit = attn::fwd_split_plan(v.BH, v.S, p->Sk, kernel_d(p->D), v.causal, nullptr, 128, plain);
+    const int nsplit = attn::fwd_split_plan(v.BH, v.S, p->Sk, kernel_d(p->D), v.causal, v.pack_sq != 0, nullptr, 128, rule);
     return nsplit > 1 ? round_ws(nsplit * fwd_part_bytes(p)) : 0;
 }
 
@@ -208,17 +208,22 @@ static int fwd_impl(const void *Q, const void *K, const void *V, void *O, float 
         !aligned(LSE, 4))
         return ATTN_ERR_ALIGN;
     // No workspace at all: run unsplit.  A workspace that is there must be usable: it holds the plan's
-    // partial results, or at least those of one work-group per compute unit; then the plan is the best
+    // partial results, or at least those that one of the other rules asks for; then the plan is the best
     // of those that fit.
     const FwdView v = fwd_view(*p, rope != nullptr);
     int kps = 0, nsplit = 1;
     if (workspace) {
-        const size_t need = fwd_split_bytes(p, rope != nullptr);
-        if (!aligned(workspace, kWsAlign) ||
-            workspace_bytes < std::min(need, fwd_split_bytes(p, rope != nullptr, true)))
-            return ATTN_ERR_WORKSPACE;
-        const size_t fit = workspace_bytes < need ? workspace_bytes / fwd_part_bytes(p) : 128;
-        nsplit = attn::fwd_split_plan(v.BH, v.S, p->Sk, kernel_d(p->D), v.causal, &kps, (int)fit);
+        auto plan = [&](int most) {
+            return attn::fwd_split_plan(v.BH, v.S, p->Sk, kernel_d(p->D), v.causal, v.pack_sq != 0, &kps, most);
+        };
+        if (!aligned(workspace, kWsAlign)) return ATTN_ERR_WORKSPACE;
+        nsplit = plan(128);
+        if (nsplit > 1 && workspace_bytes < round_ws(nsplit * fwd_part_bytes(p))) {
+            if (workspace_bytes < std::min(fwd_split_bytes(p, rope != nullptr, attn::SplitRule::longest),
+                                           fwd_split_bytes(p, rope != nullptr, attn::SplitRule::one_per_unit)))
+                return ATTN_ERR_WORKSPACE;
+            nsplit = plan((int)(workspace_bytes / fwd_part_bytes(p)));
+        }
     }
     attn::FwdArgsT<E> a;
     a.nsplit = nsplit; a.kps = kps;

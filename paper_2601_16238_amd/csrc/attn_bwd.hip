@@ -18,6 +18,8 @@
 #include "attn_device.hpp"
 #include "attn_launch.hpp"
 
+#include <algorithm>
+
 namespace attn {
 
 // ---------------------------------------------------------------------------------------
@@ -1287,11 +1289,39 @@ static int launch_bwd_d(BwdArgs a, bool causal, hipStream_t st, unsigned stages)
     return 0;
 }
 
-// Split of the dQ kernel over the keys, by the forward's estimate (see split_plan): D = 128, causal,
-// unsplit -> split, us: 4 heads of 2048 rows 50 -> 35 (8 splits), 8 of 2048 50 -> 37 (4), but 32 of 1024
-// 34 -> 39 (2), 16 of 1024 29 -> 34 (4).  Needs at least 256 query rows per head (a 256-row work-group
-// must have rows to work on) -- decoding shapes have one row per head and many heads, and are not split.
-#ifndef ATTN_F16  // a function of the shape only: defined once, by the bf16 build
+// Split of the dQ kernel over the keys, by an estimate of the launch, in us, with n splits of the key tiles:
+//   - no mask: fixed + tiles / n * per-tile time, `alone` unsplit and `full` (the rate of a full chip) in
+//     any split, of at most one work-group per compute unit;
+//   - causal: the longest work-group, fixed + tiles / n * alone, or the whole work spread evenly over the
+//     compute units, work-groups * (average tiles * full + n * fixed) / 256, whichever is more; and 0.3 of
+//     the longest where not all work-groups are resident at once, so that some long ones start late;
+//   - the partial results: 5 us and 0.4 us per MB.
+// The number of splits of which it is least is taken if that is a twentieth below the unsplit launch.
+// D = 128, causal, unsplit -> split, us: 4 heads of 2048 rows 50 -> 35 (8 splits), 8 of 2048 50 -> 37 (4),
+// but 32 of 1024 34 -> 39 (2), 16 of 1024 29 -> 34 (4).  Needs at least 256 query rows per head (a 256-row
+// work-group must have rows to work on) -- decoding shapes have one row per head and many heads, and are
+// not split.
+#ifndef ATTN_F16  // functions of the shape only: defined once, by the bf16 build
+int longest_split_plan(const LongestCost &c, int64_t wgs, int tiles, float average, size_t part_bytes, bool causal,
+                       int most)
+{
+    auto estimate = [&](int n) {
+        const float alone = n > 1 ? c.alone_split : c.alone;
+        const int per = (tiles + n - 1) / n;
+        const float merge = n > 1 ? 5.0f + 0.4e-6f * (float)part_bytes * n : 0.0f;
+        if (!causal) return c.fixed + per * (n > 1 ? c.full : alone) + merge;
+        const float longest = c.fixed + per * alone, load = wgs * (average * c.full + n * c.fixed) / 256.0f;
+        return std::max(longest, load) + (n * wgs > c.resident ? 0.3f * longest : 0.0f) + merge;
+    };
+    int best = 1;
+    float least = 0.95f * estimate(1);
+    for (int n = 2; n <= most && 4 * n <= tiles && n * wgs <= (causal ? 1024 : 256); ++n) {
+        const float t = estimate(n);
+        if (t < least) { least = t; best = n; }
+    }
+    return best;
+}
+
 int dq_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps, int most)
 {
     if (D > 128) {  // the kernel for head dimensions above 128 is not split
@@ -1303,8 +1333,8 @@ int dq_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps, int most)
     int nsplit = 1;
     if (S >= 256)
         // (the unsplit launch has work-groups of 128 rows, the split one of 256)
-        nsplit = split_plan(D > 64 ? SplitCost{7.0f, 1.38f, 1.6f, 2.2f, 256} : SplitCost{7.0f, 0.94f, 1.0f, 1.6f, 512},
-                            wgs, tiles, tiles - S / 128.0f, (size_t)BH * S * D * 4, causal, std::min(most, 16));
+        nsplit = longest_split_plan(D > 64 ? LongestCost{7.0f, 1.38f, 1.6f, 2.2f, 256} : LongestCost{7.0f, 0.94f, 1.0f, 1.6f, 512},
+                                    wgs, tiles, tiles - S / 128.0f, (size_t)BH * S * D * 4, causal, std::min(most, 16));
     const int tiles_per = (tiles + nsplit - 1) / nsplit;
     nsplit = (tiles + tiles_per - 1) / tiles_per;  // no empty split
     if (kps) *kps = tiles_per * 64;

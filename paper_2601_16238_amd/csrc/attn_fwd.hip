@@ -31,6 +31,7 @@
 #include "attn_launch.hpp"
 
 #include <algorithm>
+#include <cmath>
 
 namespace attn {
 
@@ -831,33 +832,78 @@ static int launch_fwd_d(FwdArgs a, bool causal, hipStream_t st)
     return -1;
 }
 
+// Which problems go to the kernel of attn_fwd_wide.hip (128-row work-groups, two K/V buffers, two
+// work-groups per compute unit at D <= 128) instead of the one above: head dimensions above 128 and packed
+// rows, whose positions only that kernel knows, and, measured, forward only, graph replay, same box:
+//  - at most 32 query rows per head (decoding; one wave of four has rows, the problem is K/V
+//    streaming): B=8 Hq=32 Hkv=8 Sk=8192 66.7 -> 49.7 us, B=16 H=16 Sk=4096 143 -> 103;
+//  - D = 128 and at most 128 rows: S=96 causal 18.8 -> 14.3 us (the kernel above needs four waves
+//    at D = 128 whatever the length); 128 rows on 1024 keys the same either way.
+// Everything else is faster above: mid-size causal D = 64 launches by 3-5 % (B=8 H=8 S=1024 22.5
+// against 23.6 us), large launches by 7-12 %.
+static bool streams(int S, int D, bool packed) { return D > 128 || S <= 32 || packed || (D == 128 && S <= 128); }
+
+#ifndef ATTN_F16  // functions of the shape only: defined once, by the bf16 build
 // Split over the keys.  A launch of few work-groups lasts as long as its longest one; a split shortens
-// that, but every split writes an fp32 partial result that the merge reads: about 5 us and 0.4 us per
-// MB.  The estimate of a launch, in us, with n splits of the key tiles:
-//   - no mask (equal work-groups, as long as all of them are resident at once, one per compute unit):
-//     fixed + tiles / n * per-tile time, which grows from `alone` to `full` as the work-groups fill the
-//     chip;
-//   - causal: the longest work-group, fixed + tiles / n * alone, or the whole work spread evenly over the
-//     compute units, work-groups * (average tiles * full + n * fixed) / 256, whichever is more; and 0.3 of
-//     the longest where not all work-groups are resident at once, so that some long ones start late.
-// The number of splits of which it is least is taken if that is a twentieth below the unsplit launch.
-// Measured, us, unsplit -> split, forward, D = 128, causal: 2 heads of 2048 rows 50 -> 27 (8 splits), 8
-// of 2048 51 -> 35 (4), 8 of 4096 95 -> 67 (2), 6 of 8192 180 -> 123 (2); not split: 32 of 512 19 (27 with
-// two), 16 of 1024 30 (30 with four), 32 of 1536 43 (49 with two).
-#ifndef ATTN_F16  // a function of the shape only: defined once, by the bf16 build
-int split_plan(const SplitCost &c, int64_t wgs, int tiles, float average, size_t part_bytes, bool causal, int most)
+// that, but every split writes an fp32 partial result that the merge reads.  The launch's time is estimated
+// for every number of splits and the best is taken if it is at least 3 % below the unsplit one.  SplitCost:
+// us that a launch takes besides its tiles, that a further work-group on the same unit takes besides its
+// own; a 64-key tile of a work-group alone on its compute unit, and its share of the unit when several are
+// (no tile takes less than the shares of all of them); work-groups that fit a unit.
+//   - Work-groups of equal length (no mask, or one query tile per head): as many rounds as they need.
+//   - Causal, unsplit: the longest, the whole work spread evenly, or, heaviest first, two (three, ..) of the
+//     length at one (two, ..) launches' worth of resident work-groups.
+//   - Causal, split: the work-groups of a split that lies behind their rows end at once; the others (a query
+//     tile has one per started share of its keys) are dispatched split by split, heaviest first.  Those
+//     that are not resident at once, the lightest of the last split, start when earlier ones end: early
+//     while there are ones that end at their diagonal in an earlier split, else after a whole one.
+// The constants are a fit of this model to the forward's time at every number of splits of 1674 problems
+// (1 .. 96 heads and packed rows, 33 .. 4096 rows, up to 32768 keys, both masks; 9 % rms): the splits it
+// takes are 2.1 % above the best ones on average, against 8.5 % with at least one work-group per compute
+// unit.  us, D = 128 causal: 12 heads of 3143 rows 75 unsplit, 57 with its 2 splits, 74 with 3; 8 heads of
+// 2895 67, 52 with 3; 32 of 512 stay unsplit (19; 27 with 2).  D = 256 causal: 4 of 2524 69, 41 with 4; 12
+// of 3430 unsplit 98 (133 with 2).  D = 64 without mask: 96 heads of 118 rows on 6729 keys 93, 40 with 4.
+struct SplitCost { float fixed, start, tile, share; int per_cu; };
+
+static int fwd_splits(const SplitCost &c, int64_t wgs, int tiles, int S, float part_mb, bool equal, int most)
 {
+    const int64_t resident = 256 * c.per_cu;
+    auto tile_us = [&](int64_t on_a_unit) { return std::max(c.tile, std::min<int64_t>(on_a_unit, c.per_cu) * c.share); };
+    const float diagonal = S / 64.0f;  // tiles over which the rows of a head end
+    const float average = tiles - diagonal / 2, spread = wgs * average * std::max(c.tile / c.per_cu, c.share) / 256;
+    auto unsplit_causal = [&]() {
+        const float on_a_unit = std::min(std::max(wgs / 256.0f, 1.0f), (float)c.per_cu);
+        float t = std::max(c.fixed + tiles * std::max(c.tile, on_a_unit * c.share), spread);
+        for (int64_t j = resident, rounds = 2; j < wgs; j += resident, ++rounds)
+            t = std::max(t, rounds * (c.fixed + tile_us(c.per_cu) * (tiles - diagonal * j / wgs)));
+        return t;
+    };
     auto estimate = [&](int n) {
-        const float alone = n > 1 ? c.alone_split : c.alone;
         const int per = (tiles + n - 1) / n;
-        const float merge = n > 1 ? 5.0f + 0.4e-6f * (float)part_bytes * n : 0.0f;
-        if (!causal) return c.fixed + per * (n > 1 ? c.full : alone) + merge;
-        const float longest = c.fixed + per * alone, load = wgs * (average * c.full + n * c.fixed) / 256.0f;
-        return std::max(longest, load) + (n * wgs > c.resident ? 0.3f * longest : 0.0f) + merge;
+        n = (tiles + per - 1) / per;
+        // (the merge of more than four splits: a thread group per row and eight splits, see launch_fwd_merge)
+        const float merge = n == 1 ? 0.0f : n <= 4 ? 2.7f + 0.46f * part_mb * n : 3.5f + (0.43f * n + 1.1f) * part_mb;
+        if (equal) {
+            const int64_t rounds = (n * wgs + resident - 1) / resident, last = n * wgs - (rounds - 1) * resident;
+            return (rounds - 1) * (c.start + per * tile_us(c.per_cu)) + c.fixed + per * tile_us((last + 255) / 256) + merge;
+        }
+        if (n == 1) return unsplit_causal();
+        const float busy = wgs * std::min((float)n, average / per + 0.5f), late = busy - resident;
+        const float tile = tile_us((int64_t)std::ceil(busy / 256));
+        float t = c.fixed + per * tile;
+        if (late > 0) {
+            const float ends = wgs * std::max(0.0f, 1 - per / diagonal), rest = late - ends;
+            const int last = tiles - (n - 1) * per;
+            const float in_last = wgs * std::min(1.0f, last / diagonal);
+            if (rest <= 0) t *= 1 + 0.3f * late / ends;
+            else if (rest > in_last) t *= 1 + std::ceil(late / resident);
+            else t += c.start + tile * (diagonal >= last ? last * rest / in_last : last - diagonal * (1 - rest / in_last));
+        }
+        return std::max(t, spread + busy * c.start / 256) + merge;
     };
     int best = 1;
-    float least = 0.95f * estimate(1);
-    for (int n = 2; n <= most && 4 * n <= tiles && n * wgs <= (causal ? 1024 : 256); ++n) {
+    float least = 0.97f * estimate(1);
+    for (int n = 2; n <= most && 4 * n <= tiles && n * wgs <= 1024; ++n) {
         const float t = estimate(n);
         if (t < least) { least = t; best = n; }
     }
@@ -867,21 +913,31 @@ int split_plan(const SplitCost &c, int64_t wgs, int tiles, float average, size_t
 // The forward.  Decoding (at most 32 rows per head) runs in the streaming kernel and is bound by
 // memory, not by its longest work-group: at least one work-group per compute unit (256 with long key
 // ranges beat 512 or 1024 shorter ones there, 0.060 ms against 0.071 and 0.086 on the decode shape),
-// every split at least four tiles (`plain`: the same rule for any number of rows).
-int fwd_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps, int most, bool plain)
+// every split at least four tiles.  `rule`: the plan, or the smaller workspaces that are accepted: that
+// rule for any number of rows, or the estimate that dQ uses.
+int fwd_split_plan(int BH, int S, int Sk, int D, bool causal, bool packed, int *kps, int most, SplitRule rule)
 {
-    // (head dimensions above 128: four waves, 128 rows per work-group)
-    const int nw = D > 128 ? 4 : fwd_waves_for(S, D, BH, causal);
-    const int64_t wgs = (int64_t)BH * ((S + nw * 32 - 1) / (nw * 32));
+    const bool wide = streams(S, D, packed);
+    // (rows per work-group: 128 in the streaming kernel)
+    const int nw = D > 128 ? 4 : fwd_waves_for(S, D, BH, causal), tile_rows = wide ? 128 : nw * 32;
+    const int64_t wgs = (int64_t)BH * ((S + tile_rows - 1) / tile_rows);
     const int64_t target = 256;
     const int tiles = (Sk + 63) / 64;
     int nsplit = 1;
-    if (S > 32 && !plain) {
-        const SplitCost cost = D > 128 ? SplitCost{10.0f, 4.3f, 4.3f, 5.0f, 256}
-                               : D > 64 ? SplitCost{7.0f, 1.38f, 1.38f, 1.8f, 256}
-                               : nw == 8 ? SplitCost{7.0f, 0.94f, 0.94f, 1.17f, 256}
-                                         : SplitCost{7.0f, 0.67f, 0.67f, 0.69f, 512};
-        nsplit = split_plan(cost, wgs, tiles, tiles - S / 128.0f, (size_t)BH * S * D * 4, causal, std::min(most, 128));
+    if (S > 32 && rule == SplitRule::plan) {
+        const SplitCost cost = D > 128           ? SplitCost{8.2f, 9.8f, 1.70f, 1.70f, 1}
+                               : D > 64          ? (wide ? SplitCost{4.6f, 1.7f, 1.25f, 1.06f, 2}
+                                                         : SplitCost{6.0f, 1.0f, 1.45f, 1.27f, 1})
+                               : nw == 8         ? SplitCost{6.0f, 0.9f, 0.97f, 0.97f, 2}
+                               : nw == 4 || wide ? SplitCost{4.9f, 1.0f, 0.73f, 0.58f, 2}
+                                                 : SplitCost{4.1f, 0.2f, 0.84f, 0.56f, 3};
+        nsplit = fwd_splits(cost, wgs, tiles, S, (float)BH * S * D * 4e-6f, !causal || S <= tile_rows, std::min(most, 128));
+    } else if (S > 32 && rule == SplitRule::longest) {
+        const LongestCost cost = D > 128 ? LongestCost{10.0f, 4.3f, 4.3f, 5.0f, 256}
+                                 : D > 64 ? LongestCost{7.0f, 1.38f, 1.38f, 1.8f, 256}
+                                 : nw == 8 ? LongestCost{7.0f, 0.94f, 0.94f, 1.17f, 256}
+                                           : LongestCost{7.0f, 0.67f, 0.67f, 0.69f, 512};
+        nsplit = longest_split_plan(cost, wgs, tiles, tiles - S / 128.0f, (size_t)BH * S * D * 4, causal, 128);
     } else if (wgs < target && tiles >= 8) {
         nsplit = (int)((target + wgs - 1) / wgs);
         if (nsplit > tiles / 4) nsplit = tiles / 4;
@@ -905,24 +961,9 @@ int fwd_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps, int most
 }
 #endif
 
-// Which problems of D <= 128 go to the kernel of attn_fwd_wide.hip (128-row work-groups, two K/V
-// buffers, two work-groups per compute unit at D = 128) instead of the one above.  Measured,
-// forward only, graph replay, same box:
-//  - at most 32 query rows per head (decoding; one wave of four has rows, the problem is K/V
-//    streaming): B=8 Hq=32 Hkv=8 Sk=8192 66.7 -> 49.7 us, B=16 H=16 Sk=4096 143 -> 103;
-//  - D = 128 and at most 128 rows: S=96 causal 18.8 -> 14.3 us (the kernel above needs four waves
-//    at D = 128 whatever the length); 128 rows on 1024 keys the same either way.
-// Everything else is faster above: mid-size causal D = 64 launches by 3-5 % (B=8 H=8 S=1024 22.5
-// against 23.6 us), large launches by 7-12 %.
-static bool prefer_streaming_forward(const FwdArgs &a, int D)
-{
-    if (a.S <= 32 || a.pack_sq) return true;  // (packed rows: only that kernel knows their positions)
-    return D == 128 && a.S <= 128;
-}
-
 int launch_fwd(const FwdArgs &a, int D, bool causal, hipStream_t st)
 {
-    if (D == 256 || prefer_streaming_forward(a, D)) {
+    if (streams(a.S, D, a.pack_sq != 0)) {
         if (launch_fwd_wide(a, D, causal, st)) return -1;
         if (a.nsplit <= 1) return 0;
         return D == 256 ? launch_fwd_merge<256>(a, st)

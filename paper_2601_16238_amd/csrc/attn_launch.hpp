@@ -107,15 +107,19 @@ int launch_fwd(const FwdArgsT<_Float16> &a, int D, bool causal, hipStream_t st);
 // 256; called by launch_fwd, which also launches the merge of a split).
 int launch_fwd_wide(const FwdArgsT<__bf16> &a, int D, bool causal, hipStream_t st);
 int launch_fwd_wide(const FwdArgsT<_Float16> &a, int D, bool causal, hipStream_t st);
+// Number of key splits the forward would use for this problem (1: none; at most `most`), and the keys per
+// split; packed: rows packed as pack_sq says.  A pure host function of the shape.  SplitRule: the plan, and
+// two rules whose smaller workspaces are accepted as well (see attn_fwd.hip).
+enum class SplitRule { plan, longest, one_per_unit };
+int fwd_split_plan(int BH, int S, int Sk, int D, bool causal, bool packed, int *kps, int most = 128,
+                   SplitRule rule = SplitRule::plan);
 // Number of splits over `tiles` key tiles (`average` over the query rows) with which a launch of `wgs`
 // work-groups ends soonest (1: none); part_bytes: the partial results of one split.  Times in us: what a
 // work-group costs besides its tiles, a tile with the compute unit to itself (unsplit, and in the split
-// kernel), a tile on a full chip; and the work-groups resident at once.  See attn_fwd.hip.
-struct SplitCost { float fixed, alone, alone_split, full; int resident; };
-int split_plan(const SplitCost &c, int64_t wgs, int tiles, float average, size_t part_bytes, bool causal, int most);
-// fwd_split_plan: number of key splits the forward would use for this problem (1: none), and the keys per
-// split; a pure host function of the shape.
-int fwd_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps, int most = 128, bool plain = false);
+// kernel), a tile on a full chip; and the work-groups resident at once.  See attn_bwd.hip.
+struct LongestCost { float fixed, alone, alone_split, full; int resident; };
+int longest_split_plan(const LongestCost &c, int64_t wgs, int tiles, float average, size_t part_bytes, bool causal,
+                       int most);
 // `stages`: bit 0 row statistics, bit 1 dK/dV, bit 2 dQ.  With bits 0 and 2 the dQ kernel
 // forms the statistics (and runs first); bit 0 without bit 2 runs the separate kernel.
 // Number of key splits the dQ kernel would use for this problem (1: none) and the keys per

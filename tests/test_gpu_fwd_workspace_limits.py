@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("B,Hq,Hkv,Sq,Sk,D,causal,size,refused", [
     (8, 2, 2, 353, 5318, 64, True, 6 * 8 * 2 * 353 * 65 * 4, 256),    # six splits fit of eight
-    (1, 4, 1, 1949, 1949, 64, True, 4 * 4 * 1949 * 65 * 4, 256),    # four of seven
+    (1, 8, 1, 2018, 2018, 64, True, 2 * 8 * 2018 * 65 * 4, 256),    # two of three
     (8, 1, 1, 8373, 8373, 128, False, 256, None),                     # fits none: unsplit
     (1, 8, 8, 5748, 5748, 256, False, 256, None)])
 def test_smaller_workspace(B, Hq, Hkv, Sq, Sk, D, causal, size, refused):

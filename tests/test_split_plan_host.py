@@ -19,3 +19,15 @@ def test_a_workspace_sized_with_one_mask_serves_the_other(B, Hq, Hkv, Sq, Sk, D)
     assert size[0] == size[1] >= 8 * B * Hq * Sq
     # partial results stay small next to what a GPU holds: at most 256 splits' worth of work-groups
     assert size[0] - 8 * B * Hq * Sq <= 1 << 29
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,Sq,Sk,D,nsplit", [
+    (1, 64, 8, 8, 32000, 128, 32), (8, 64, 8, 16, 4000, 128, 4), (4, 32, 8, 16, 8192, 128, 8), (10, 4, 1, 20, 772, 64, 3),
+    (1, 64, 8, 16, 8192, 256, 22), (38, 8, 2, 11, 5537, 256, 3)])
+def test_packed_rows_split_as_measured(B, Hq, Hkv, Sq, Sk, D, nsplit):
+    """Grouped heads with a few new rows each (33 .. 128 packed rows per key/value head) run in the streaming
+    kernel, every row on almost all keys: the number of splits that was measured to be the fastest or
+    within 5 % of it (a work-group per compute unit where that divides evenly, never a few more than one)."""
+    part = B * Hq * Sq * (max(64, D) + 1) * 4
+    for causal in (False, True):
+        assert (attn.attn_fwd_rect_workspace_bytes(B, Hq, Hkv, Sq, Sk, D, causal)) // part == nsplit
