@@ -1238,6 +1238,26 @@ static int launch_dq_split(BwdArgs a, hipStream_t st)
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
+// Waves per work-group of the unsplit dQ kernel (D = 64 or 128): eight, i.e. 256 rows, unless they would
+// leave compute units (256) idle while 128-row ones would not (few heads and rows against many keys, e.g.
+// chunked prefill); at D = 128, where one work-group fills a unit either way, without a mask also where the
+// 128-row ones would need a second round (32 heads of 1537 rows 84 -> 64 us, 48 of 1024 61 -> 43).  Under a
+// causal mask 128-row work-groups also balance the unequal tiles better as long as the launch is small: at
+// D = 128 up to one 256-row work-group per unit (B=1 H=16 S=4096: 135 -> 117 us, B=1 H=8 S=8192: 256 -> 220
+// us; with 1.25 per unit already 15 % slower), at D = 64 (two fit a unit) up to four (B=8 H=8 S=1024: 28.9
+// -> 26.6 us, B=4 H=8 S=2048: 45.4 -> 42.0 us).
+static int dq_waves(int BH, int S, int D, bool causal)
+{
+    const int blocks32 = (S + 31) / 32;
+    const int64_t wgs8 = (int64_t)BH * ((S + 255) / 256), wgs4 = (int64_t)BH * ((S + 127) / 128);
+    const bool prefer4 = causal && (D == 64 ? wgs8 < 1024 : wgs8 <= 256);
+    const bool fill8 = wgs8 >= 256 || (D == 128 && !causal && wgs4 > 256);
+    if (blocks32 >= 8 && fill8 && !prefer4) return 8;
+    if (blocks32 >= 3) return std::min(blocks32, 4);
+    // (one wave: only D = 64; with D = 128 a lone wave would spill while it streams tiles)
+    return D == 128 ? 2 : blocks32;
+}
+
 template <int D, bool CAUSAL>
 static int launch_dq_for(const BwdArgs &a, hipStream_t st)
 {
@@ -1246,24 +1266,11 @@ static int launch_dq_for(const BwdArgs &a, hipStream_t st)
     if constexpr (D > 128) return a.dq_nsplit > 1 ? -1 : launch_dq<D, 4, CAUSAL>(a, st);
     else {
     if (a.dq_nsplit > 1) return launch_dq_split<D, CAUSAL>(a, st);
-    const int blocks32 = (a.S + 31) / 32;
-    // 256-row work-groups unless they would leave compute units (256) idle while 128-row
-    // ones would not (few heads and rows against many keys, e.g. chunked prefill); at D = 128, where one
-    // work-group fills a unit either way, without a mask also where the 128-row ones would need a second
-    // round (32 heads of 1537 rows 84 -> 64 us, 48 of 1024 61 -> 43).  Under a
-    // causal mask 128-row work-groups also balance the unequal tiles better as long as the
-    // launch is small: at D = 128 up to one
-    // 256-row work-group per unit (B=1 H=16 S=4096: 135 -> 117 us, B=1 H=8 S=8192: 256 -> 220 us;
-    // with 1.25 per unit already 15 % slower), at D = 64 (two fit a unit) up to four
-    // (B=8 H=8 S=1024: 28.9 -> 26.6 us, B=4 H=8 S=2048: 45.4 -> 42.0 us).
-    const int64_t wgs8 = (int64_t)a.BH * ((a.S + 255) / 256), wgs4 = (int64_t)a.BH * ((a.S + 127) / 128);
-    const bool prefer4 = CAUSAL && (D == 64 ? wgs8 < 1024 : wgs8 <= 256);
-    const bool fill8 = wgs8 >= 256 || (D == 128 && !CAUSAL && wgs4 > 256);
-    if (blocks32 >= 8 && fill8 && !prefer4) return launch_dq<D, 8, CAUSAL>(a, st);
-    if (blocks32 >= 4) return launch_dq<D, 4, CAUSAL>(a, st);
-    if (blocks32 == 3) return launch_dq<D, 3, CAUSAL>(a, st);
-    if (blocks32 == 2 || D == 128) return launch_dq<D, 2, CAUSAL>(a, st);
-    // one wave: only D = 64 (with D = 128 a lone wave would spill while it streams tiles)
+    const int nw = dq_waves(a.BH, a.S, D, CAUSAL);
+    if (nw == 8) return launch_dq<D, 8, CAUSAL>(a, st);
+    if (nw == 4) return launch_dq<D, 4, CAUSAL>(a, st);
+    if (nw == 3) return launch_dq<D, 3, CAUSAL>(a, st);
+    if (nw == 2) return launch_dq<D, 2, CAUSAL>(a, st);
     if constexpr (D < 128) return launch_dq<D, 1, CAUSAL>(a, st);
     return -1;
     }
@@ -1294,16 +1301,21 @@ static int launch_bwd_d(BwdArgs a, bool causal, hipStream_t st, unsigned stages)
 //     any split, of at most one work-group per compute unit;
 //   - causal: the longest work-group, fixed + tiles / n * alone, or the whole work spread evenly over the
 //     compute units, work-groups * (average tiles * full + n * fixed) / 256, whichever is more; and 0.3 of
-//     the longest where not all work-groups are resident at once, so that some long ones start late;
+//     the longest where not all work-groups with keys to walk (a query tile has one per started share of its
+//     keys) are resident at once, so that some long ones start late.  Unsplit launches, of unsplit_wgs
+//     work-groups heaviest first, take at least twice (three times, ..) the one at one (two, ..) times the
+//     resident number;
 //   - the partial results: 5 us and 0.4 us per MB.
 // The number of splits of which it is least is taken if that is a twentieth below the unsplit launch.
 // D = 128, causal, unsplit -> split, us: 4 heads of 2048 rows 50 -> 35 (8 splits), 8 of 2048 50 -> 37 (4),
-// but 32 of 1024 34 -> 39 (2), 16 of 1024 29 -> 34 (4).  Needs at least 256 query rows per head (a 256-row
-// work-group must have rows to work on) -- decoding shapes have one row per head and many heads, and are
-// not split.
+// but 32 of 1024 34 -> 39 (2), 16 of 1024 29 -> 34 (4).  Whole backward of 8 heads of 2319 rows 53 -> 39 with
+// 4, 44 with 3; of 12 heads of 3358 on 13519 keys 880 -> 797 with 2.  Over 691 problems of 256 .. 4096 rows
+// and up to 20000 keys the splits taken are 1.1 % above the best ones.  Needs at least 256 query rows per
+// head (a 256-row work-group must have rows to work on) -- decoding shapes have one row per head and many
+// heads, and are not split.
 #ifndef ATTN_F16  // functions of the shape only: defined once, by the bf16 build
 int longest_split_plan(const LongestCost &c, int64_t wgs, int tiles, float average, size_t part_bytes, bool causal,
-                       int most)
+                       int most, int S, int64_t unsplit_wgs)
 {
     auto estimate = [&](int n) {
         const float alone = n > 1 ? c.alone_split : c.alone;
@@ -1311,7 +1323,16 @@ int longest_split_plan(const LongestCost &c, int64_t wgs, int tiles, float avera
         const float merge = n > 1 ? 5.0f + 0.4e-6f * (float)part_bytes * n : 0.0f;
         if (!causal) return c.fixed + per * (n > 1 ? c.full : alone) + merge;
         const float longest = c.fixed + per * alone, load = wgs * (average * c.full + n * c.fixed) / 256.0f;
-        return std::max(longest, load) + (n * wgs > c.resident ? 0.3f * longest : 0.0f) + merge;
+        float t = std::max(longest, load);
+        if (!unsplit_wgs) {
+            if (n * wgs > c.resident) t += 0.3f * longest;
+        } else if (n > 1) {
+            if (wgs * std::min((float)n, average / per + 0.5f) > c.resident) t += 0.3f * longest;
+        } else {
+            for (int64_t j = c.resident, rounds = 2; j < unsplit_wgs; j += c.resident, ++rounds)
+                t = std::max(t, rounds * (c.fixed + alone * (tiles - S / 64.0f * j / unsplit_wgs)));
+        }
+        return t + merge;
     };
     int best = 1;
     float least = 0.95f * estimate(1);
@@ -1332,9 +1353,10 @@ int dq_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps, int most)
     const int tiles = (Sk + 63) / 64;
     int nsplit = 1;
     if (S >= 256)
-        // (the unsplit launch has work-groups of 128 rows, the split one of 256)
+        // (the unsplit launch mostly has work-groups of 128 rows, the split one of 256)
         nsplit = longest_split_plan(D > 64 ? LongestCost{7.0f, 1.38f, 1.6f, 2.2f, 256} : LongestCost{7.0f, 0.94f, 1.0f, 1.6f, 512},
-                                    wgs, tiles, tiles - S / 128.0f, (size_t)BH * S * D * 4, causal, std::min(most, 16));
+                                    wgs, tiles, tiles - S / 128.0f, (size_t)BH * S * D * 4, causal, std::min(most, 16),
+                                    S, dq_waves(BH, S, D, causal) == 8 ? wgs : (int64_t)BH * ((S + 127) / 128));
     const int tiles_per = (tiles + nsplit - 1) / nsplit;
     nsplit = (tiles + tiles_per - 1) / tiles_per;  // no empty split
     if (kps) *kps = tiles_per * 64;

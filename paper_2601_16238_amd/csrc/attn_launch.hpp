@@ -116,10 +116,11 @@ int fwd_split_plan(int BH, int S, int Sk, int D, bool causal, bool packed, int *
 // Number of splits over `tiles` key tiles (`average` over the query rows) with which a launch of `wgs`
 // work-groups ends soonest (1: none); part_bytes: the partial results of one split.  Times in us: what a
 // work-group costs besides its tiles, a tile with the compute unit to itself (unsplit, and in the split
-// kernel), a tile on a full chip; and the work-groups resident at once.  See attn_bwd.hip.
+// kernel), a tile on a full chip; and the work-groups resident at once.  S rows in unsplit_wgs work-groups:
+// see attn_bwd.hip (0: not counted).
 struct LongestCost { float fixed, alone, alone_split, full; int resident; };
 int longest_split_plan(const LongestCost &c, int64_t wgs, int tiles, float average, size_t part_bytes, bool causal,
-                       int most);
+                       int most, int S = 0, int64_t unsplit_wgs = 0);
 // `stages`: bit 0 row statistics, bit 1 dK/dV, bit 2 dQ.  With bits 0 and 2 the dQ kernel
 // forms the statistics (and runs first); bit 0 without bit 2 runs the separate kernel.
 // Number of key splits the dQ kernel would use for this problem (1: none) and the keys per

@@ -31,3 +31,11 @@ def test_packed_rows_split_as_measured(B, Hq, Hkv, Sq, Sk, D, nsplit):
     part = B * Hq * Sq * (max(64, D) + 1) * 4
     for causal in (False, True):
         assert (attn.attn_fwd_rect_workspace_bytes(B, Hq, Hkv, Sq, Sk, D, causal)) // part == nsplit
+
+
+@pytest.mark.parametrize("H,Sq,Sk,nsplit", [(12, 3358, 13519, 3), (32, 1038, 10654, 3), (24, 1848, 9348, 2)])
+def test_dq_is_split_where_the_unsplit_launch_takes_two_rounds(H, Sq, Sk, nsplit):
+    """Causal, D = 128, long keys: 288 .. 360 unsplit work-groups of nearly equal length for 256 compute
+    units, of which every second waits for a whole other one; measured 5 .. 16 % faster split."""
+    part = H * Sq * 128 * 4
+    assert (attn.attn_bwd_rect_workspace_bytes(1, H, H, Sq, Sk, 128) - 8 * H * Sq) // part == nsplit
