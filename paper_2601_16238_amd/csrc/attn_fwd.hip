@@ -35,7 +35,9 @@
 
 namespace attn {
 
-template <int D, int NW>
+// MAIN: the form with the pipelined main loop (eight waves always; four waves at D = 64 in launches that
+// four_wave_main chooses).
+template <int D, int NW, bool MAIN>
 struct FwdCfg {
     static constexpr int kThreads = NW * 64;
     static constexpr int kBR = NW * 32;
@@ -59,11 +61,7 @@ struct FwdCfg {
     // x 2 halves = 512 contiguous bytes of a piece.
     static constexpr int kVTile = kKTile;                                  // in elements
     static constexpr int kVRows16 = (16 / kKRowsPerDma) * kKPieceBytes;   // 16 rows further, in bytes
-    // The forms with the pipelined main loop: eight waves, and four at D = 64, where it has the
-    // registers.  (At D = 64 the generic form takes a lone wave about 990 cycles per sub-tile, most of
-    // them between its phases, not in arithmetic or waits for memory: 8 heads of 1024 rows, causal,
-    // 18.9 -> 16.4 us, 64 of 2048 59 -> 55, B=32 H=8 S=200 12.3 -> 11.6.)
-    static constexpr bool kMain = NW == 8 || (NW == 4 && D == 64);
+    static constexpr bool kMain = MAIN;
     // V tiles: two, or three for the main loop, which multiplies P of a sub-tile by V one sub-tile
     // later and therefore still reads tile kt-1 while tile kt+1 is arriving
     static constexpr int kVBufs = kMain ? 3 : 2;
@@ -72,12 +70,6 @@ struct FwdCfg {
     // V buffer 1 (both free until the first tile barrier), pairs 2 and 3 behind the V buffers.
     static constexpr int kQStage = NW == 8 ? 2 * kKTile : 0;
     static constexpr int kLdsBytes = (3 * kKTile + kVBufs * kVTile + kQStage) * 2;
-    // Four waves: problems of one or two key tiles never enter the main loop and do without its
-    // third V buffer, so that three work-groups fit a compute unit.
-    static constexpr int lds_bytes(int n_kt)
-    {
-        return NW == 4 && kMain && n_kt < 3 ? kLdsBytes - kVTile * 2 : kLdsBytes;
-    }
     static_assert(kLdsBytes <= 160 * 1024, "LDS budget of a gfx950 CU exceeded");
 };
 
@@ -86,11 +78,11 @@ struct FwdCfg {
 constexpr float kOverflow = 1024.0f;
 constexpr float kMinusHuge = -1.0e30f;  // initial reference: finite, so masked -inf scores give 0
 
-template <int D, int NW, bool CAUSAL, bool SPLIT>
+template <int D, int NW, bool CAUSAL, bool SPLIT, bool MAIN>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2)))
 attn_fwd_kernel(const FwdArgs a)
 {
-    using C = FwdCfg<D, NW>;
+    using C = FwdCfg<D, NW, MAIN>;
     constexpr int KS = D / 16;  // contraction steps of K Q^T
     constexpr int DB = D / 32;  // 32-row blocks of O^T
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -103,7 +95,7 @@ attn_fwd_kernel(const FwdArgs a)
 
     // (head, query tile) of this work-group; causal tiles are issued heaviest first.
     int bh, rank;
-    xcd_tile_order<CAUSAL, D == 64 && NW == 4>(blockIdx.x, a.nqt, a.BH, bh, rank);
+    xcd_tile_order<CAUSAL, MAIN && NW == 4>(blockIdx.x, a.nqt, a.BH, bh, rank);
     const int qt = CAUSAL ? a.nqt - 1 - rank : rank;
     const int64_t base = (int64_t)(bh / a.H) * a.stride_b + (int64_t)(bh % a.H) * a.stride_h;
     // grouped-query heads: query head h reads K/V head h / group
@@ -769,29 +761,47 @@ static int launch_fwd_merge(const FwdArgs &a, hipStream_t st)
     return launch_fwd_merge_zg<D, (D > 128 ? 4 : 8)>(a, st);
 }
 
-template <int D, int NW, bool CAUSAL, bool SPLIT>
+template <int D, int NW, bool CAUSAL, bool SPLIT, bool MAIN>
 static int launch_fwd_kernel(const FwdArgs &a, hipStream_t st)
 {
-    using C = FwdCfg<D, NW>;
-    if (hipFuncSetAttribute((const void *)attn_fwd_kernel<D, NW, CAUSAL, SPLIT>,
+    using C = FwdCfg<D, NW, MAIN>;
+    if (hipFuncSetAttribute((const void *)attn_fwd_kernel<D, NW, CAUSAL, SPLIT, MAIN>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, C::kLdsBytes) != hipSuccess)
         return -1;
-    hipLaunchKernelGGL((attn_fwd_kernel<D, NW, CAUSAL, SPLIT>),
+    hipLaunchKernelGGL((attn_fwd_kernel<D, NW, CAUSAL, SPLIT, MAIN>),
                        dim3(a.nqt * a.BH, SPLIT ? a.nsplit : 1), dim3(C::kThreads),
-                       C::lds_bytes((a.Sk + C::kBC - 1) / C::kBC), st, a);
+                       C::kLdsBytes, st, a);
     if (hipGetLastError() != hipSuccess) return -1;
     if (SPLIT) return launch_fwd_merge<D>(a, st);
     return 0;
 }
 
-template <int D, int NW>
+template <int D, int NW, bool MAIN>
 static int launch_fwd_nw(const FwdArgs &a, bool causal, hipStream_t st)
 {
     if (a.nsplit > 1)
-        return causal ? launch_fwd_kernel<D, NW, true, true>(a, st)
-                      : launch_fwd_kernel<D, NW, false, true>(a, st);
-    return causal ? launch_fwd_kernel<D, NW, true, false>(a, st)
-                  : launch_fwd_kernel<D, NW, false, false>(a, st);
+        return causal ? launch_fwd_kernel<D, NW, true, true, MAIN>(a, st)
+                      : launch_fwd_kernel<D, NW, false, true, MAIN>(a, st);
+    return causal ? launch_fwd_kernel<D, NW, true, false, MAIN>(a, st)
+                  : launch_fwd_kernel<D, NW, false, false, MAIN>(a, st);
+}
+
+// Whether four waves at D = 64 take the form with the pipelined main loop.  The generic form takes a lone
+// wave about 990 cycles per sub-tile, most of them between its phases, not in arithmetic or waits for
+// memory; the main loop needs a third V buffer and more registers, so that two work-groups fit a compute
+// unit instead of three.  It is entered from three whole tiles on.  Time relative to the generic form:
+// launches of up to two work-groups per unit 0.8 (8 heads of 2048 rows, causal) .. 0.98 (256 of 200, no
+// mask); more of them, sequences below 1024 rows: 1.05 .. 1.27 (384 heads of 135 rows 13.3 -> 15.5 us, 192 of
+// 464 causal 19.3 -> 21.4), except where they fill two rounds: 0.92 .. 1.04 with 897 .. 1024; longer
+// sequences: 1.0 +- 0.08, worst in the second round's lower half (96 heads of 1024 rows 1.09).
+static bool four_wave_main(const FwdArgs &a)
+{
+    if (a.nsplit > 1) return a.kps >= 192;
+    if (a.Sk < 192) return false;
+    const int64_t wgs = (int64_t)a.BH * a.nqt;
+    if (wgs <= 512) return true;
+    if (wgs > 896 && wgs <= 1024) return a.Sk >= 512;
+    return a.S >= 1024 && (a.S >= 2400 || wgs <= 672 || wgs > 1024);
 }
 
 // Waves per work-group: 8 (256 query rows) unless the sequence is too short to fill them.
@@ -803,7 +813,7 @@ static int fwd_waves_for(int S, int D, int BH, bool causal)
 {
     const int blocks32 = (S + 31) / 32;
     // D = 64 under a causal mask with fewer than four 256-row work-groups per compute unit:
-    // 128-row work-groups (three fit a compute unit at D = 64) balance the unequal tiles
+    // 128-row work-groups (two or three fit a compute unit at D = 64) balance the unequal tiles
     // better.  Measured: B=8 H=8 S=1024 26.5 -> 24.3 us, B=16 H=16 S=512 29.5 -> 27.6 us; not
     // so without a mask (+5 %), at D = 128 (+4..33 % on mid-size shapes) or on large problems.
     if (blocks32 >= 8 && D == 64 && causal && (int64_t)BH * ((S + 255) / 256) < 1024) return 4;
@@ -823,12 +833,13 @@ static int launch_fwd_d(FwdArgs a, bool causal, hipStream_t st)
 {
     const int nw = fwd_waves_for(a.S, D, a.BH, causal);
     a.nqt = (a.S + nw * 32 - 1) / (nw * 32);
-    if (nw == 8) return launch_fwd_nw<D, 8>(a, causal, st);
-    if (nw == 4) return launch_fwd_nw<D, 4>(a, causal, st);
+    if (nw == 8) return launch_fwd_nw<D, 8, true>(a, causal, st);
     if constexpr (D < 128) {
-        if (nw == 2) return launch_fwd_nw<D, 2>(a, causal, st);
-        return launch_fwd_nw<D, 1>(a, causal, st);
+        if (nw == 4 && four_wave_main(a)) return launch_fwd_nw<D, 4, true>(a, causal, st);
+        if (nw == 2) return launch_fwd_nw<D, 2, false>(a, causal, st);
+        if (nw == 1) return launch_fwd_nw<D, 1, false>(a, causal, st);
     }
+    if (nw == 4) return launch_fwd_nw<D, 4, false>(a, causal, st);
     return -1;
 }
 
