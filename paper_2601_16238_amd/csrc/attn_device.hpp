@@ -247,7 +247,10 @@ __device__ __forceinline__ int xcd_contiguous_order(int id, int total)
 // each, and the other heads as above.  In a launch of few rounds the two kinds are interleaved in
 // proportion, so that both run heaviest first; otherwise the tiles of the heads left over come first.
 // (17 heads of 3000 rows, D = 128, dQ 128 -> 91 us, dK/dV 144 -> 100; 20 of 2000, D = 64, forward
-// 38 -> 28.)
+// 38 -> 28.)  Not for heads of one tile and launches of at most one work-group per unit, which need no order
+// and start 0.25 us sooner without its divisions; nor for many heads of three tiles, whose contiguous order
+// already gives every unit long and short ones and reads K and V once (330 heads of 600 rows, D = 128,
+// forward 76 us, 83 ordered; 245 of 262 dQ 36, 40).
 // PAIRED: two work-groups are resident on a compute unit.  A causal launch of at most that many is
 // balanced by giving each unit a heavy and a light one: the second round in reverse order (64 heads of
 // 1024 rows, D = 64, forward 22.5 -> 19.9 us, dK/dV 29.7 -> 28.0).
@@ -259,7 +262,9 @@ __device__ __forceinline__ void xcd_tile_order(int id_, int ntile_, int BH_, int
     constexpr unsigned kXcd = 8, kCuPerXcd = 32;
     const unsigned id = id_, ntile = ntile_, BH = BH_;
     const unsigned over = BH % kXcd;  // heads left over
-    if (over == 0 || CAUSAL) {
+    const unsigned units = kXcd * kCuPerXcd;
+    const bool ordered = CAUSAL && ntile > 1 && BH * ntile > units && (ntile != 3 || BH * ntile <= 2 * units);
+    if (over == 0 || ordered) {
         const unsigned hpx = BH / kXcd, x = id % kXcd;
         unsigned pos = id / kXcd;
         const unsigned whole = hpx * ntile;  // tiles of the XCD's own heads
