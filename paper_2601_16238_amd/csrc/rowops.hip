@@ -241,7 +241,8 @@ layernorm_bwd_rows_kernel(const __bf16 *dy, const __bf16 *x, const float *w, con
 {
     constexpr int kWpt = TEAM / 64;  // waves per team
     __shared__ float red[T * kWpt * 2];
-    __shared__ float comb[T == 1 ? 1 : (TEAM == 64 ? T : 1) * 16 * TEAM];
+    // (written as 16-byte vectors with TEAM = 64)
+    __shared__ __attribute__((aligned(16))) float comb[T == 1 ? 1 : (TEAM == 64 ? T : 1) * 16 * TEAM];
     const int t = threadIdx.x % TEAM, team = threadIdx.x / TEAM;
     float wv[V][8], dwp[V][8], dbp[V][8];
 #pragma unroll
