@@ -474,14 +474,15 @@ int check_rows(int64_t rows, int32_t cols, std::initializer_list<int64_t> stride
     return ATTN_OK;
 }
 
-// LayerNorm backward: row teams per work-group, and work-groups.  The launch is one round of
-// resident work-groups.  Up to 4 vectors per thread a work-group is two teams once there are
+// LayerNorm backward with the work-group on a row: row teams per work-group, and work-groups.  The launch is
+// one round of resident work-groups.  Up to 4 vectors per thread a work-group is two teams once there are
 // rows for more than 512 teams: the same waves per unit in half the work-groups, so half the
 // partial rows to write and to sum.  Teams per unit (more cost partial rows, fewer leave
-// latency uncovered), measured on (16384, 1024), (8192, 4096), (4096, 8192), (2048, 16384):
-// V = 1: 4 (33.7 us; 44.8 with 2, 39.1 with 3), V = 2: 2 (38.3 us; 44.7 with 3; 41.3 as
-// single-team work-groups), V = 4: 2, all its registers allow (40.3 us; 44.4 as single-team
-// work-groups in two rounds), V = 8: 1 (50.3 us; 63.4 with 2).
+// latency uncovered), measured on (8192, 4096), (4096, 8192), (2048, 16384): V = 2: 2 (38.3 us; 44.7 with
+// 3; 41.3 as single-team work-groups), V = 4: 2, all its registers allow (40.3 us; 44.4 as single-team
+// work-groups in two rounds), V = 8: 1 (50.3 us; 63.4 with 2).  V = 1 is launched with fewer than 1024 rows
+// (see wave_bwd), a team for each; its cap only sizes the workspace of the launches with a wave per row,
+// which take at most as many work-groups.
 int bwd_teams(int64_t rows, int V) { return rows > kBwdTeams && V <= 4 ? 2 : 1; }
 int bwd_groups(int64_t rows, int V)
 {
@@ -527,6 +528,17 @@ int wave_groups(int64_t rows, int teams, int64_t cap)
 {
     const int64_t per = (rows + cap * teams - 1) / (cap * teams);  // rows per wave
     return (int)((rows + per * teams - 1) / (per * teams));
+}
+
+// The launch of the LayerNorm backward.  The workspace holds a pair of partial rows for each of
+// bwd_groups(rows, vectors_for(cols)) work-groups: no launch takes more.
+struct BwdPlan { bool wave_rows; int V, groups; };
+BwdPlan bwd_plan(int64_t rows, int cols)
+{
+    const int most = bwd_groups(rows, vectors_for(cols));
+    if (!wave_bwd(rows, cols)) return {false, vectors_for(cols), most};
+    const int V = wave_vectors_for(cols), groups = wave_groups(rows, kWaveTeams, wave_bwd_cap(rows, V));
+    return {true, V, groups < most ? groups : most};
 }
 
 #define ROWOPS_WAVE_DISPATCH(V, CALL)       \
@@ -618,16 +630,15 @@ int rowops_layernorm_bwd(const void *dy, const void *x, const float *w, const fl
         workspace_bytes < rowops_layernorm_bwd_workspace_bytes(rows, cols))
         return ATTN_ERR_WORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    const bool wave_rows = wave_bwd(rows, cols);
-    const int V = wave_rows ? wave_vectors_for(cols) : vectors_for(cols);
-    const int groups = wave_rows ? wave_groups(rows, kWaveTeams, wave_bwd_cap(rows, V)) : bwd_groups(rows, V);
+    const BwdPlan plan = bwd_plan(rows, cols);
+    const int V = plan.V, groups = plan.groups;
     float *part = static_cast<float *>(workspace);
 #define ROWOPS_LN_BWD(TEAM, T)                                                                    \
     hipLaunchKernelGGL((layernorm_bwd_rows_kernel<kV, TEAM, T>), dim3(groups), dim3(TEAM * T), 0, \
                        st, static_cast<const __bf16 *>(dy), static_cast<const __bf16 *>(x), w,    \
                        mean, rstd, static_cast<__bf16 *>(dx), part, rows, cols, dy_row_stride,    \
                        x_row_stride, dx_row_stride)
-    if (wave_rows) {
+    if (plan.wave_rows) {
         ROWOPS_WAVE_DISPATCH(V, ROWOPS_LN_BWD(64, kWaveTeams));
     } else if (bwd_teams(rows, V) == 2) {
         switch (V) {
