@@ -23,18 +23,18 @@ CALIB_COPY_BYTES = 256 * 1024 * 1024   # --calib-copy reads this many bytes and 
 # profiles/rowops_hbm_traffic_pmc.txt: FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000 (KiB); for the
 # backward: rows kernel + column kernel.
 MEASURED_TRAFFIC_BYTES = {
-    ("rowops", "rmsnorm_fwd"): int((32927.1 * 2.0 + 65536.0) * 1024),
-    ("rowops", "layernorm_fwd"): int((33062.6 * 2.0 + 65792.4) * 1024),
-    ("rowops", "layernorm_bwd"): int(((65853.2 + 8210.1) * 2.0 + 81920.0 + 64.0) * 1024),
-    ("rowops", "rotary_fwd"): int((8741.5 * 2.0 + 16384.0) * 1024),
+    ("rowops", "rmsnorm_fwd"): int((32923.2 * 2.0 + 65536.0) * 1024),
+    ("rowops", "layernorm_fwd"): int((33058.6 * 2.0 + 65797.4) * 1024),
+    ("rowops", "layernorm_bwd"): int(((65851.8 + 8210.1) * 2.0 + 81920.0 + 64.0) * 1024),
+    ("rowops", "rotary_fwd"): int((8745.5 * 2.0 + 16384.0) * 1024),
 }
 
 
 def measured_traffic_bytes(workload, kernel):
     """HBM bytes per launch of `kernel` on `workload` (read + written, scaled counter readings)
     from the committed rocprofv3 summary of that workload, profiles/<workload>_kernel_trace_and_
-    hbm_traffic.txt; None if there is none.  The summaries are regenerated with the kernels, so
-    the figure cannot outlive the code it was measured on unnoticed."""
+    hbm_traffic.txt; None if there is none.  The figure is of the kernels that the summary was made
+    with, by hand: a change to a kernel's traffic needs a new one."""
     path = os.path.join(ROOT, "profiles", "%s_kernel_trace_and_hbm_traffic.txt" % workload)
     try:
         lines = open(path).read().splitlines()
