@@ -37,6 +37,10 @@ def test_smaller_workspace(B, Hq, Hkv, Sq, Sk, D, causal, size, refused):
     Oref, Lref = attn.attn_fwd_rect(Q, K, V, D ** -0.5, causal, split=False)
     torch.cuda.synchronize()
     assert bool((ws[size:] == 0x5a).all())
-    # both sides round O to bf16 once (2^-9 relative) after sums in fp32 with P rounded to bf16
-    assert (O.float() - Oref.float()).abs().max().item() <= 2 ** -7 * max(1.0, Oref.float().abs().max().item())
+    # Row by row.  Both sides round O to bf16 (a neighbouring value: 2^-7 of it) after fp32 sums over P
+    # rounded to bf16 against different reference maxima: independent errors of 2^-9 / sqrt(3) relative per
+    # key and side, which over V ~ N(0, 1) add up to sqrt(2) 2^-9 / sqrt(3) of O's own size sqrt(sum P^2),
+    # the row's rms; six deviations of that, for 10^5 .. 10^7 values, are below 2^-6 rms
+    diff, o = (O.float() - Oref.float()).abs().amax(-1), Oref.float()
+    assert (diff <= 2 ** -7 * o.abs().amax(-1) + 2 ** -6 * o.square().mean(-1).sqrt()).all()
     assert (LSE - Lref).abs().max().item() <= 2e-5
