@@ -351,7 +351,7 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
                     // the fragment four MFMAs further on (the compiler reads a fragment right
                     // before its MFMA and waits); S first, so that its exp2 run next to the
                     // MFMAs of dP.  us: B=4 H=16 S=4096 D=256 causal 1216 -> 1118 (with the
-                    // consumers' steps), B=1 H=16 S=4096 D=128 causal 142 -> 135, S=16384 1871 -> 1852;
+                    // consumers' steps), B=1 H=16 S=4096 D=128 causal 142 -> 135 (S=16384 the same within noise);
                     // two or six MFMAs ahead are the same
                     constexpr int kAhead = 4;
                     elem8 f[2 * KS];

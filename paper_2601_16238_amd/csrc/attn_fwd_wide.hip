@@ -27,7 +27,7 @@
 // fragment kAhead MFMAs further on (across the phases), one transfer of the next tile every other
 // step, and the step's share of the other sub-tile's probabilities.  Left to the compiler, which reads
 // a fragment right before its MFMA, and with a branch around every transfer, B=4 H=16 S=4096 D=256
-// causal took 632 us; so it takes 583.
+// causal took 632 us; so it takes 577 .. 588.
 #include "attn_device.hpp"
 #include "attn_launch.hpp"
 
@@ -326,8 +326,9 @@ attn_fwd_wide_kernel(const FwdArgs a)
     // Start of iteration kt: K(kt) and V(kt) have been on their way since iteration kt-1.  After
     // the barrier the other buffers (tile kt-1, last read before the barrier) are free and take
     // tile kt+1.  Its transfers are issued between the MFMAs of the two score phases, also after the
-    // last tile (they fill a buffer that nobody reads; the epilogue waits): issued in one burst after the barrier, the waves all queue at the compute unit's
-    // vector-memory path while the matrix pipes idle (measured: +35 % on the whole kernel).
+    // last tile (they fill a buffer that nobody reads; the epilogue waits).  Issued in one burst after
+    // the barrier, the waves all queue at the compute unit's vector-memory path while the matrix pipes
+    // idle (measured: +35 % on the whole kernel).
     auto stage = [&](int kt) __attribute__((always_inline)) {
         (void)kt;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
