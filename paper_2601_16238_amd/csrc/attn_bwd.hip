@@ -1373,10 +1373,12 @@ int dq_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps, int most)
 // 89 -> 74; B=1 H=4 S=8192 D=64 causal 235 -> 192; B=1 H=8 S=2048 D=64 71 -> 67.  Not below 48 slots in
 // the longest block, where the merge (about 5 us) takes most of what is gained and dK and dV keep
 // the one order of their sums that does not depend on the workspace; nor unless a chunk is at most
-// three quarters of the longest block.  At D = 64, where chunks share a unit two by two (each takes 1.75
+// three quarters of the longest block.  At D = 64, where chunks share a unit two by two (each takes 1.7
 // times as long; two unsplit blocks, of unequal length under a mask, 1.1 times), nor unless a chunk and the
 // merge (3 us and 0.4 us per MB of partial results) take less than the longest block, at 0.65 us a slot: split
 // in two, 208 blocks of 50 slots 57 -> 68 us, 240 of 96 101 -> 107; 174 of 640 510 -> 470 (whole backwards).
+// Of 700 problems of 90 blocks and more, timed both ways, two are 3 .. 4 % slower for the choice; split
+// whenever it could be, the 700 were 0.9 % slower on average and single ones up to 19 %.
 int dkdv_split_plan(int BHkv, int group, int S, int Sk, int D, bool causal, int *chunk, int64_t most)
 {
     const int keys = dkdv_split_keys(D), n_block = (Sk + keys - 1) / keys;
@@ -1397,7 +1399,7 @@ int dkdv_split_plan(int BHkv, int group, int S, int Sk, int D, bool causal, int 
         }
         if (items * BHkv <= std::min(resident, most)) {
             const int64_t chunks = items * BHkv;
-            if (D == 64 && 0.65f * L * (chunks > 256 ? 1.75f : 1.0f) + 3.0f + 0.4e-6f * chunks * (2 * 128 * 64 * 4) >=
+            if (D == 64 && 0.65f * L * (chunks > 256 ? 1.7f : 1.0f) + 3.0f + 0.4e-6f * chunks * (2 * 128 * 64 * 4) >=
                                0.65f * longest * ((int64_t)BHkv * n_block > 256 ? 1.1f : 1.0f))
                 return n_block;
             *chunk = (int)L;
