@@ -779,9 +779,11 @@ static int launch_fwd_kernel(const FwdArgs &a, hipStream_t st)
 template <int D, int NW, bool MAIN>
 static int launch_fwd_nw(const FwdArgs &a, bool causal, hipStream_t st)
 {
-    if (a.nsplit > 1)
-        return causal ? launch_fwd_kernel<D, NW, true, true, MAIN>(a, st)
-                      : launch_fwd_kernel<D, NW, false, true, MAIN>(a, st);
+    // (four waves at D = 64 are split in the form with the main loop only, see four_wave_main)
+    if constexpr (MAIN || NW != 4 || D != 64)
+        if (a.nsplit > 1)
+            return causal ? launch_fwd_kernel<D, NW, true, true, MAIN>(a, st)
+                          : launch_fwd_kernel<D, NW, false, true, MAIN>(a, st);
     return causal ? launch_fwd_kernel<D, NW, true, false, MAIN>(a, st)
                   : launch_fwd_kernel<D, NW, false, false, MAIN>(a, st);
 }
@@ -796,7 +798,7 @@ static int launch_fwd_nw(const FwdArgs &a, bool causal, hipStream_t st)
 // sequences: 1.0 +- 0.08, worst in the second round's lower half (96 heads of 1024 rows 1.09).
 static bool four_wave_main(const FwdArgs &a)
 {
-    if (a.nsplit > 1) return a.kps >= 192;
+    if (a.nsplit > 1) return true;  // at least four tiles each
     if (a.Sk < 192) return false;
     const int64_t wgs = (int64_t)a.BH * a.nqt;
     if (wgs <= 512) return true;

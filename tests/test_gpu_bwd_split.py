@@ -31,6 +31,7 @@ def test_dkdv_split_over_the_query_slots(B, Hq, Hkv, Sq, Sk, D, causal, f16):
     Q, K, V, dO = (torch.from_numpy(x[k].view(np.int16)).cuda().view(dt) for k in ("Q", "K", "V", "dO"))
     O, LSE = attn.attn_fwd_rect(Q, K, V, x["scale"], causal)
     full, stats = attn.attn_bwd_rect_workspace_bytes(B, Hq, Hkv, Sq, Sk, D), (8 * B * Hq * Sq + 255) // 256 * 256
+    assert full > stats, "plan does not split"
     ws = torch.full((full,), 0x7F, dtype=torch.uint8, device="cuda")   # poisoned: nothing may be relied on
     got = attn.attn_bwd_rect(Q, K, V, O, dO, LSE, x["scale"], causal, workspace=ws)
     again = attn.attn_bwd_rect(Q, K, V, O, dO, LSE, x["scale"], causal, workspace=ws)
