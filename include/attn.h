@@ -222,6 +222,16 @@ int attn_fwd_rect(const void *Q, const void *K, const void *V, void *O, float *L
 
 size_t attn_bwd_rect_workspace_bytes(const attn_rect_params_t *p);
 
+/*
+ * The workspace with which any of the bf16 and fp16 backward calls is fastest for the problem with its
+ * mask, at least attn_bwd_rect_workspace_bytes(p).  Above D = 64 the dK/dV kernel can store dS (2 bytes
+ * per visible query-key pair) and dQ is then formed from it instead of from Q, K, V and dO once more; this
+ * takes place in any workspace larger than that with room for it, for all heads or a part of them at a time, and
+ * enqueues a kernel for the row statistics, then dK/dV and dQ for each part.  At most 4.5 GiB are
+ * asked for it.  Pure host function; 0 for an invalid problem.
+ */
+size_t attn_bwd_rect_best_workspace_bytes(const attn_rect_params_t *p);
+
 int attn_bwd_rect(const void *Q, const void *K, const void *V, const void *O, const void *dO,
                   const float *LSE, void *dQ, void *dK, void *dV,
                   void *workspace, size_t workspace_bytes,

@@ -178,6 +178,16 @@ static size_t dkdv_part_bytes(const attn_rect_params_t *p, bool causal)
     return chunk ? round_ws((size_t)p->B * p->Hkv * items * dkdv_chunk_bytes(p)) : 0;
 }
 
+// K/V heads whose dS is kept at a time in `room` bytes (see ds_plan), and the bytes for n heads.
+static int ds_heads_in(const attn_rect_params_t *p, size_t room)
+{
+    return attn::ds_plan(p->B * p->Hkv, p->Hq / p->Hkv, p->Sq, p->Sk, kernel_d(p->D), p->causal != 0, room);
+}
+static size_t ds_bytes(const attn_rect_params_t *p, int n)
+{
+    return (size_t)n * (p->Hq / p->Hkv) * attn::ds_head_blocks(p->Sq, p->Sk, p->causal != 0) * (attn::kDsBlock * 2);
+}
+
 // Rotary embedding fused into the call (both tables NULL: none).
 struct Rope {
     const float *cos_table = nullptr, *sin_table = nullptr;
@@ -279,6 +289,10 @@ static int bwd_impl(const void *Q, const void *K, const void *V, const void *O, 
     const int dkdv_items = attn::dkdv_split_plan(p->B * p->Hkv, p->Hq / p->Hkv, p->Sq, p->Sk, kernel_d(p->D),
                                                  p->causal != 0, &dkdv_chunk,
                                                  (int64_t)std::min<size_t>(512, room / dkdv_chunk_bytes(p)));
+    const size_t dkdv_bytes = dkdv_chunk ? round_ws((size_t)p->B * p->Hkv * dkdv_items * dkdv_chunk_bytes(p)) : 0;
+    // (a workspace of the size that attn_bwd_rect_workspace_bytes asks for, or less, keeps the form without dS)
+    int ds_heads = stages == 7u ? ds_heads_in(p, room - dkdv_bytes) : 0;
+    if (ds_heads && workspace_bytes <= attn_bwd_rect_workspace_bytes(p)) ds_heads = 0;
     attn::BwdArgsT<E> a;
     a.Q = static_cast<const E *>(Q);
     a.K = static_cast<const E *>(K);
@@ -291,6 +305,8 @@ static int bwd_impl(const void *Q, const void *K, const void *V, const void *O, 
     a.dQpart = reinterpret_cast<float *>(static_cast<char *>(workspace) + stats_bytes);
     a.dkdv_chunk = dkdv_chunk; a.dkdv_items = dkdv_items;
     a.dKVpart = a.dQpart;
+    a.dS = reinterpret_cast<E *>(reinterpret_cast<char *>(a.dQpart) + dkdv_bytes);
+    a.ds_heads = ds_heads; a.bkv0 = 0; a.nkv = p->B * p->Hkv;
     a.dQ = static_cast<E *>(dQ);
     a.dK = static_cast<E *>(dK);
     a.dV = static_cast<E *>(dV);
@@ -412,6 +428,17 @@ size_t attn_bwd_rect_workspace_bytes(const attn_rect_params_t *p)
     size_t part = std::max(dq_part_bytes(p, false), dkdv_part_bytes(p, false));
     if (p->Sk >= p->Sq) part = std::max(part, std::max(dq_part_bytes(p, true), dkdv_part_bytes(p, true)));
     return bwd_stats_bytes(p) + part;
+}
+
+// dS grows with Sq * Sk: at most 1/64 of the card's 288 GB are asked for it.
+size_t attn_bwd_rect_best_workspace_bytes(const attn_rect_params_t *p)
+{
+    if (check_params(p) != ATTN_OK) return 0;
+    constexpr size_t kMost = ((size_t)288 << 30) / 64;
+    const int n = ds_heads_in(p, kMost);
+    const size_t plain = attn_bwd_rect_workspace_bytes(p);
+    if (!n) return plain;  // (a workspace of that size would not be taken as one for dS)
+    return std::max(bwd_stats_bytes(p) + dkdv_part_bytes(p, p->causal != 0) + ds_bytes(p, n), plain + kWsAlign);
 }
 
 size_t attn_bwd_gqa_workspace_bytes(const attn_gqa_params_t *p)

@@ -5,6 +5,8 @@
 //               accumulate in registers                            (4 GEMMs per tile pair)
 //   3. dQ     : one work-group per block of queries, loops over key tiles, dQ^T
 //               accumulates in registers                           (3 GEMMs per tile pair)
+// or, above D = 64 where the workspace holds dS: 1, 2 (which also stores dS), and
+//   3b. dQ    : the same from the stored dS                        (1 GEMM per tile pair; HBM-bound)
 // With dP = dO V^T and dS = P o (dP - delta):
 //   dV = P^T dO,  dK = scale * dS^T Q,  dQ = scale * dS K.
 //
@@ -136,7 +138,8 @@ __device__ __forceinline__ void dkdv_find_item(const BwdArgs &a, int item, int k
 }
 
 // SPLIT: the work-group takes one chunk of its key block's slots (see dkdv_split_plan).
-template <int D, int P, bool CAUSAL, bool SPLIT>
+// DS: the producers also store dS, for attn_bwd_dq_ds_kernel.
+template <int D, int P, bool CAUSAL, bool SPLIT, bool DS>
 __global__ void __launch_bounds__(P * 128) __attribute__((amdgpu_waves_per_eu(P >= 4 ? P / 2 : 1)))
 attn_bwd_dkdv_kernel(const BwdArgs a)
 {
@@ -153,7 +156,8 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
     // read it (grouped-query attention; group == 1 is multi-head attention).
     const int Hkv = a.H / a.group;
     int bkv, kt;  // causal: key block 0 is the heaviest
-    xcd_tile_order<CAUSAL, D == 64>(blockIdx.x, a.ntile, a.BH / a.group, bkv, kt);
+    xcd_tile_order<CAUSAL, D == 64>(blockIdx.x, a.ntile, a.nkv, bkv, kt);
+    bkv += a.bkv0;
     int item = 0, z = 0;  // SPLIT: chunk of the head, and of the key block
     if (SPLIT) {
         item = __builtin_amdgcn_readfirstlane(kt);
@@ -195,12 +199,14 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
     const uint32_t head_bytes = (uint32_t)(((int64_t)(S - 1) * a.stride_s + Dr) * 2);
     desc_t Qd, Gd;  // Q and dO of the current query head
     rsrc_t Wr;      // its row statistics
+    desc_t Wd;      // (DS: issued from assembly, as the compiler would wait for the stores with it)
     const uint32_t lds0 = lds_address(smem);
     auto set_head = [&](int bh) {
         const int64_t base = (int64_t)(bh / a.H) * a.stride_b + (int64_t)(bh % a.H) * a.stride_h;
         Qd = make_desc(a.Q + base, head_bytes);
         Gd = make_desc(a.dO + base, head_bytes);
-        Wr = make_rsrc(a.delta + (int64_t)bh * 2 * S, (uint32_t)S * 8u);
+        if (DS) Wd = make_desc(a.delta + (int64_t)bh * 2 * S, (uint32_t)S * 8u);
+        else Wr = make_rsrc(a.delta + (int64_t)bh * 2 * S, (uint32_t)S * 8u);
     };
     const uint32_t row_bytes = (uint32_t)a.stride_s * 2u;
     uint32_t dma_voff[C::kDmaPerWave];
@@ -221,7 +227,10 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
     // that nobody reads before a later barrier.  (Spread between the consumers' MFMAs instead they
     // measured the same or up to 2.5 % slower.)
     auto dma_stat = [&](int t, int rs) __attribute__((always_inline)) {
-        if (w == C::kStatWave)
+        if (w != C::kStatWave) return;
+        if (DS)
+            dma4(Wd, lds0 + C::kOffStat + rs * C::kStatBytes, stat_voff, (uint32_t)(t * C::kRows * 4));
+        else
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
                 Wr, (void __attribute__((address_space(3))) *)(smem + C::kOffStat + rs * C::kStatBytes),
                 4, (int)stat_voff, t * C::kRows * 4, 0, 0);
@@ -244,8 +253,9 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
     // kAhead-1 newer slots may stay in flight) and everyone must be done with slot t-2.
     auto slot_barrier = [&]() {
         if (producer) {
-            if (w == C::kStatWave) wait_vm_and_barrier<C::kAhead - 1>();
-            else wait_vm_and_barrier<0>();
+            // (DS: a slot's two stores follow its transfer and need no wait of their own)
+            if (w == C::kStatWave) wait_vm_and_barrier<DS ? 3 * C::kAhead - 1 : C::kAhead - 1>();
+            else wait_vm_and_barrier<DS ? 63 : 0>();
         } else if (C::kDmaPerTensor % C::kPairs != 0 && !extra) {
             wait_vm_and_barrier<(C::kAhead - 1) * (C::kDmaPerWave - 2)>();
         } else {
@@ -324,6 +334,20 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
 
         int rs = 0;  // ring position of the current slot
         int t = t_first;  // its rows: slot t of the current head
+        // DS: the 2 KB block of (slot, 32 keys), see ds_row_blocks; the row of blocks of slot t starts at
+        // ds_row and has ds_len of them.  One store holds 16 queries of every key: 128-byte runs.
+        elem *ds_head = DS ? a.dS + ((int64_t)(bh0 + g_first) - (int64_t)a.bkv0 * a.group) *
+                                        ds_head_blocks(S, Sk, CAUSAL) * kDsBlock : nullptr;
+        elem *ds_row = ds_head + (DS ? ds_row_blocks(t, Sk, coff, CAUSAL) * kDsBlock : 0);
+        int ds_len = ds_row_len(t, Sk, coff, CAUSAL);
+        const uint32_t ds_voff = (uint32_t)k0 * 64u + (uint32_t)(((r >> 2) * 16 + h * 4 + (r & 3)) * 16);
+        constexpr int kNt = 2;  // non-temporal (plain: dQ 3 .. 10 % longer)
+        auto store_ds = [&](elem8 d0, elem8 d1) __attribute__((always_inline)) {
+            // (blocks that no row of the slot sees, and keys past the last, lie past the row's end: not stored)
+            const rsrc_t row = make_rsrc(ds_row, (uint32_t)ds_len * (kDsBlock * 2u));
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, d0), row, (int)ds_voff, 0, kNt);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, d1), row, (int)ds_voff, 128, kNt);
+        };
         for (int g = 0; g < n_seq; ++g) {
             slot_barrier();
             int rd = rs + C::kAhead;
@@ -396,12 +420,30 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
                 elem8 *x = Xs + (g & 1) * (C::kPairs * 256);
                 x[0] = pack8(s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7]);
                 x[64] = pack8(s[8], s[9], s[10], s[11], s[12], s[13], s[14], s[15]);
-                x[128] = pack8(dp[0], dp[1], dp[2], dp[3], dp[4], dp[5], dp[6], dp[7]);
-                x[192] = pack8(dp[8], dp[9], dp[10], dp[11], dp[12], dp[13], dp[14], dp[15]);
+                const elem8 d0 = pack8(dp[0], dp[1], dp[2], dp[3], dp[4], dp[5], dp[6], dp[7]);
+                const elem8 d1 = pack8(dp[8], dp[9], dp[10], dp[11], dp[12], dp[13], dp[14], dp[15]);
+                x[128] = d0;
+                x[192] = d1;
+                if (DS) store_ds(d0, d1);
+            } else if (DS) {  // (past the row's end: only counted by the waits)
+                const elem8 none = {};
+                store_ds(none, none);
             }
             advance_fetch();
             rs = ring_next(rs);
-            if (++t == n_slot) t = t0;
+            ++t;
+            if (DS) {
+                ds_row += (CAUSAL ? ds_len : ds_len | 1) * kDsBlock;
+                if (CAUSAL) ds_len = ds_row_len(t, Sk, coff, true);
+            }
+            if (t == n_slot) {
+                t = t0;
+                if (DS) {
+                    ds_head += ds_head_blocks(S, Sk, CAUSAL) * kDsBlock;
+                    ds_row = ds_head + ds_row_blocks(t, Sk, coff, CAUSAL) * kDsBlock;
+                    ds_len = ds_row_len(t, Sk, coff, CAUSAL);
+                }
+            }
         }
         wait_vm_and_barrier<0>();  // the consumers' last slot
     } else {
@@ -670,6 +712,60 @@ struct DqCfg {
     static_assert(16 % kPieceRows == 0, "sub-tiles start at piece boundaries");
     static_assert(kLdsBytes <= 160 * 1024, "LDS budget of a gfx950 CU exceeded");
 };
+
+// A wave's 32 finished dQ rows from row q0 on (accumulators dq, in the layout of the MFMA), scaled, to
+// memory through its staging area stg.
+template <typename C, int D>
+__device__ __forceinline__ void dq_rows_out(const BwdArgs &a, f32x16 (&dq)[D / 32], char *stg, int64_t base, int q0, int l)
+{
+    constexpr int DB = D / 32, CPR = D / 8, RPI = 64 / CPR;
+    const int r = l & 31, h = l >> 5, lr = l / CPR, lc = l % CPR, S = a.S, Dr = a.Dr;
+    const int qc = min(q0 + r, S - 1);
+    auto at = [](int row, int chunk) {
+        return C::piece_base(row / C::kPieceRows) + (chunk * C::kPieceRows + row % C::kPieceRows) * 16;
+    };
+    if (a.rope_cos) {
+        // Q was rotated before the forward: what has been accumulated is the gradient of the
+        // rotated rows; the gradient of the unrotated ones is its image under the transpose of
+        // the rotation (head dimension == D only; column d pairs with d + D/2, i.e. d block db
+        // with db + DB/2, same register).
+        const int64_t pos = (int64_t)(qc + a.rope_pos0) * (D / 2);
+#pragma unroll
+        for (int db = 0; db < DB / 2; ++db)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const f32x4 c4 = *(const f32x4 *)(a.rope_cos + pos + 32 * db + 8 * g + 4 * h);
+                const f32x4 s4 = *(const f32x4 *)(a.rope_sin + pos + 32 * db + 8 * g + 4 * h);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float y1 = dq[db][4 * g + e], y2 = dq[db + DB / 2][4 * g + e];
+                    dq[db][4 * g + e] = __builtin_fmaf(y1, c4[e], y2 * s4[e]);
+                    dq[db + DB / 2][4 * g + e] = __builtin_fmaf(y2, c4[e], -(y1 * s4[e]));
+                }
+            }
+    }
+    {
+        // The accumulator holds 4 consecutive columns of one row per register group: stored
+        // directly, every instruction writes 8-byte pieces of 32 rows.  The rows go through the
+        // wave's staging area in LDS instead and leave whole, 16 bytes per lane.  The areas that
+        // lie in ring position 2 move to the position that the last two tiles did not use (other
+        // waves may still be reading those).
+        const float sc = a.scale;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                *(elem4 *)(stg + at(r, 4 * db + g) + 8 * h) =
+                    pack4(dq[db][4 * g] * sc, dq[db][4 * g + 1] * sc, dq[db][4 * g + 2] * sc, dq[db][4 * g + 3] * sc);
+        asm volatile("" ::: "memory");  // a wave's LDS accesses execute in order
+#pragma unroll
+        for (int j = 0; j < 32 / RPI; ++j) {
+            const u32x4 v = *(const u32x4 *)(stg + at(RPI * j + lr, lc));
+            const int row = q0 + RPI * j + lr;
+            if (row < S && lc * 8 < Dr) *(u32x4 *)(a.dQ + base + (int64_t)row * a.stride_s + lc * 8) = v;
+        }
+    }
+}
 
 template <int D, int NW, bool CAUSAL, bool SPLIT>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D > 128 ? 1 : 2)))
@@ -1073,47 +1169,122 @@ attn_bwd_dq_kernel(const BwdArgs a)
         }
         return;
     }
-    if (a.rope_cos) {
-        // Q was rotated before the forward: what has been accumulated is the gradient of the
-        // rotated rows; the gradient of the unrotated ones is its image under the transpose of
-        // the rotation (head dimension == D only; column d pairs with d + D/2, i.e. d block db
-        // with db + DB/2, same register).
-        const int64_t pos = (int64_t)(qc + a.rope_pos0) * (D / 2);
+    dq_rows_out<C, D>(a, dq, stg, base, q0, l);
+}
+
+// ---------------------------------------------------------------------------------------
+// 3b. dQ from the dS that the dK/dV kernel stored: one product instead of three, bound by reading dS
+// (2 bytes a score) from HBM.  Work-group = NW waves, wave = 32 queries, loop over tiles of 32 keys.
+// The K tile (in the layout above, shared) and the waves' dS blocks (each read by its wave alone) go
+// global -> LDS directly, kRing - 1 tiles ahead: about 100 KB in flight per unit.
+// A dS block holds 8-byte groups of 4 consecutive queries of a key; in the order in which the producers
+// store them the 64 lanes of a transpose read (8 keys x 32 queries) cover 512 contiguous bytes.
+// ---------------------------------------------------------------------------------------
+template <int D, int NW>
+struct DqsCfg : DqCfg<D, 4> {
+    using T = DqCfg<D, 4>;  // (for the layout of a piece)
+    static constexpr int kBlk = NW * 32;
+    static constexpr int kTile = 32;
+    static constexpr int kPieces = kTile / T::kPieceRows;
+    static constexpr int kKBytes = T::piece_base(kPieces);
+    static constexpr int kTileBytes = kKBytes + NW * kDsBlock * 2;
+    static constexpr int kRing = 160 * 1024 / kTileBytes < 6 ? 160 * 1024 / kTileBytes : 6;
+    static constexpr int kStage = T::piece_base(32 / T::kPieceRows);
+    static constexpr int kLdsBytes = kRing * kTileBytes > NW * kStage ? kRing * kTileBytes : NW * kStage;
+    static constexpr int kDmaK = (kPieces + NW - 1) / NW;     // transfers of a wave per tile: K, then dS
+    static constexpr int kDma = kDmaK + 2;
+    static_assert(kPieces % NW == 0, "every wave has the same number of transfers in flight");
+    static_assert(kRing >= 3 && kLdsBytes <= 160 * 1024, "LDS layout");
+};
+
+template <int D, int NW, bool CAUSAL>
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW > 4 ? 2 : 1)))
+attn_bwd_dq_ds_kernel(const BwdArgs a)
+{
+    using C = DqsCfg<D, NW>;
+    constexpr int DB = D / 32, PR = C::kPieceRows;
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+
+    const int tid = threadIdx.x, l = tid & 63, h = l >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int S = a.S, Sk = a.Sk, coff = Sk - S;
+    int bh, rank;
+    xcd_tile_order<CAUSAL>(blockIdx.x, a.ntile, a.nkv * a.group, bh, rank);
+    const int qt = CAUSAL ? a.ntile - 1 - rank : rank;  // heaviest first
+    const int64_t ds_head = bh * ds_head_blocks(S, Sk, CAUSAL);  // (of the launch's heads)
+    bh += a.bkv0 * a.group;
+    const int64_t base = (int64_t)(bh / a.H) * a.stride_b + (int64_t)(bh % a.H) * a.stride_h;
+    const int64_t base_kv = (int64_t)(bh / a.H) * a.kv_stride_b + (int64_t)((bh % a.H) / a.group) * a.kv_stride_h;
+    const int t = qt * NW + w;  // the wave's slot
+    const int q0 = t * 32;
+    const int n_row = t * 32 < S ? ds_row_len(t, Sk, coff, CAUSAL) : 0;  // key blocks that it sees
+    const int q_end = min(S, (qt + 1) * C::kBlk);
+    const int n_kt = ((CAUSAL ? min(Sk, q_end + coff) : Sk) + 31) / 32;  // ... and that some wave sees
+
+    const int Dr = a.Dr;
+    const uint32_t head_bytes = (uint32_t)(((int64_t)(Sk - 1) * a.kv_stride_s + Dr) * 2);
+    const desc_t Kd = make_desc(a.K + base_kv, head_bytes);
+    const desc_t Sd = make_desc(a.dS + (ds_head + ds_row_blocks(min(t, (S + 31) / 32 - 1), Sk, coff, CAUSAL)) * kDsBlock,
+                                (uint32_t)n_row * (kDsBlock * 2u));
+    const uint32_t row_bytes = (uint32_t)a.kv_stride_s * 2u;
+    const uint32_t lds0 = lds_address(smem);
+    const uint32_t voff = (l / PR) * 8 < Dr ? (l % PR) * row_bytes + ((l / PR) << 4) : head_bytes;
+    // (tiles past the last read as zero, or are keys that nobody uses)
+    auto fetch = [&](int kt, int pos) __attribute__((always_inline)) {
+        const uint32_t dst = lds0 + pos * C::kTileBytes;
 #pragma unroll
-        for (int db = 0; db < DB / 2; ++db)
+        for (int n = 0; n < 2; ++n)
+            dma16_between_nt(Sd, dst + C::kKBytes + w * (kDsBlock * 2) + n * 1024, l * 16, kt * (kDsBlock * 2) + n * 1024);
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const f32x4 c4 = *(const f32x4 *)(a.rope_cos + pos + 32 * db + 8 * g + 4 * h);
-                const f32x4 s4 = *(const f32x4 *)(a.rope_sin + pos + 32 * db + 8 * g + 4 * h);
+        for (int n = 0; n < C::kDmaK; ++n) {
+            const int piece = w + n * NW;
+            dma16_between(Kd, dst + C::piece_base(piece), voff, (kt * 32 + piece * PR) * row_bytes);
+        }
+    };
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float y1 = dq[db][4 * g + e], y2 = dq[db + DB / 2][4 * g + e];
-                    dq[db][4 * g + e] = __builtin_fmaf(y1, c4[e], y2 * s4[e]);
-                    dq[db + DB / 2][4 * g + e] = __builtin_fmaf(y2, c4[e], -(y1 * s4[e]));
+    for (int i = 0; i < C::kRing - 1; ++i) fetch(i, i);
+
+    // transpose reads: of K, rows 4h+e (+8) and the 64 bytes of d block 0; of dS, the same keys and
+    // the 4 queries of the lane's chunk
+    int tr[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int row = 8 * j + 4 * h + ((l & 15) >> 2), chunk = 2 * ((l >> 4) & 1) + ((l >> 1) & 1);
+        tr[j] = C::piece_base(row / PR) + (chunk * PR + row % PR) * 16 + (l & 1) * 8;
+    }
+    int ds = C::kKBytes + w * (kDsBlock * 2) + h * 256 + (((l >> 4) & 1) * 2 + (l & 1)) * 64 + ((l & 15) >> 2) * 16 +
+             ((l >> 1) & 1) * 8;
+    asm volatile("" : "+v"(tr[0]), "+v"(tr[1]), "+v"(ds));
+
+    f32x16 dq[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) dq[db][i] = 0.f;
+
+    int pos = 0;
+    for (int kt = 0; kt < n_kt; ++kt) {
+        wait_vm_and_barrier<(C::kRing - 2) * C::kDma>();
+        fetch(kt + C::kRing - 1, pos == 0 ? C::kRing - 1 : pos - 1);
+        if (kt < n_row) {
+            const char *const T = smem + pos * C::kTileBytes;
+#pragma unroll
+            for (int cc = 0; cc < 2; ++cc) {
+                const elem8 b = join8(lds_read_tr((const elem *)(T + ds + cc * 1024)),
+                                      lds_read_tr((const elem *)(T + ds + cc * 1024 + 512)));
+#pragma unroll
+                for (int db = 0; db < DB; ++db) {
+                    const int off = cc * C::kRows16 + db * 4 * C::kChunkStep;
+                    const elem8 kT = join8(lds_read_tr((const elem *)(T + off + tr[0])),
+                                           lds_read_tr((const elem *)(T + off + tr[1])));
+                    dq[db] = mfma32(kT, b, dq[db]);
                 }
             }
-    }
-    {
-        // The accumulator holds 4 consecutive columns of one row per register group: stored
-        // directly, every instruction writes 8-byte pieces of 32 rows.  The rows go through the
-        // wave's staging area in LDS instead and leave whole, 16 bytes per lane.  The areas that
-        // lie in ring position 2 move to the position that the last two tiles did not use (other
-        // waves may still be reading those).
-        const float sc = a.scale;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-                *(elem4 *)(stg + at(r, 4 * db + g) + 8 * h) =
-                    pack4(dq[db][4 * g] * sc, dq[db][4 * g + 1] * sc, dq[db][4 * g + 2] * sc, dq[db][4 * g + 3] * sc);
-        asm volatile("" ::: "memory");  // a wave's LDS accesses execute in order
-#pragma unroll
-        for (int j = 0; j < 32 / RPI; ++j) {
-            const u32x4 v = *(const u32x4 *)(stg + at(RPI * j + lr, lc));
-            const int row = q0 + RPI * j + lr;
-            if (row < S && lc * 8 < Dr) *(u32x4 *)(a.dQ + base + (int64_t)row * a.stride_s + lc * 8) = v;
         }
+        pos = pos + 1 == C::kRing ? 0 : pos + 1;
     }
+    wait_vm_and_barrier<0>();  // (everyone's transfers have landed: the LDS is free)
+    dq_rows_out<C, D>(a, dq, smem + w * C::kStage, base, q0, l);
 }
 
 // Sum of the per-split partial dQ, times scale, rounded: one thread per (row, 4 consecutive d);
@@ -1159,19 +1330,19 @@ static bool allow_lds(K kernel, int bytes)
                                bytes) == hipSuccess;
 }
 
-template <int D, int P, bool CAUSAL>
+template <int D, int P, bool CAUSAL, bool DS = false>
 static int launch_dkdv_p(BwdArgs a, hipStream_t st)
 {
     using C = DkdvCfg<D, P>;
     a.ntile = (a.Sk + C::kBlk - 1) / C::kBlk;
-    if (!allow_lds(attn_bwd_dkdv_kernel<D, P, CAUSAL, false>, C::kLdsBytes)) return -1;
-    hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, P, CAUSAL, false>), dim3(a.ntile * (a.BH / a.group)),
+    if (!allow_lds(attn_bwd_dkdv_kernel<D, P, CAUSAL, false, DS>, C::kLdsBytes)) return -1;
+    hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, P, CAUSAL, false, DS>), dim3(a.ntile * a.nkv),
                        dim3(C::kThreads), C::kLdsBytes, st, a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 // Split over the query slots: one work-group per chunk, then the merge.
-template <int D, bool CAUSAL>
+template <int D, bool CAUSAL, bool DS>
 static int launch_dkdv_split(BwdArgs a, hipStream_t st)
 {
     constexpr int P = D > 128 ? 2 : 4, keys = dkdv_split_keys(D);
@@ -1179,8 +1350,8 @@ static int launch_dkdv_split(BwdArgs a, hipStream_t st)
     static_assert(C::kBlk == keys, "keys per work-group");
     const int BHkv = a.BH / a.group;
     a.ntile = a.dkdv_items;
-    if (!allow_lds(attn_bwd_dkdv_kernel<D, P, CAUSAL, true>, C::kLdsBytes)) return -1;
-    hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, P, CAUSAL, true>), dim3(a.ntile * BHkv), dim3(C::kThreads),
+    if (!allow_lds(attn_bwd_dkdv_kernel<D, P, CAUSAL, true, DS>, C::kLdsBytes)) return -1;
+    hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, P, CAUSAL, true, DS>), dim3(a.ntile * BHkv), dim3(C::kThreads),
                        C::kLdsBytes, st, a);
     if (hipGetLastError() != hipSuccess) return -1;
     const int n_block = (a.Sk + keys - 1) / keys;
@@ -1194,19 +1365,19 @@ static int launch_dkdv_split(BwdArgs a, hipStream_t st)
 // registers: three per SIMD hide more of each other's latencies).  Measured: -2.5..4 % on the
 // large shapes; slower on small launches (more of a 192-key block is padding) and at D = 64
 // (the larger work-group no longer fits a compute unit twice).
-template <int D, bool CAUSAL>
+template <int D, bool CAUSAL, bool DS = false>
 static int launch_dkdv(const BwdArgs &a, hipStream_t st)
 {
-    if (a.dkdv_chunk) return launch_dkdv_split<D, CAUSAL>(a, st);
+    if (a.dkdv_chunk) return launch_dkdv_split<D, CAUSAL, DS>(a, st);
     // D = 256: two pairs, one wave per SIMD (a consumer's two 32 x 256 accumulators alone are
     // 256 registers), 64 keys per work-group
-    if constexpr (D > 128) return launch_dkdv_p<D, 2, CAUSAL>(a, st);
+    if constexpr (D > 128) return launch_dkdv_p<D, 2, CAUSAL, DS>(a, st);
     else {
         if constexpr (D == 128) {
-            const int64_t wgs6 = (int64_t)(a.BH / a.group) * ((a.Sk + 191) / 192);
-            if (wgs6 >= 512) return launch_dkdv_p<D, 6, CAUSAL>(a, st);
+            const int64_t wgs6 = (int64_t)a.nkv * ((a.Sk + 191) / 192);
+            if (wgs6 >= 512) return launch_dkdv_p<D, 6, CAUSAL, DS>(a, st);
         }
-        return launch_dkdv_p<D, 4, CAUSAL>(a, st);
+        return launch_dkdv_p<D, 4, CAUSAL, DS>(a, st);
     }
 }
 
@@ -1276,12 +1447,61 @@ static int launch_dq_for(const BwdArgs &a, hipStream_t st)
     }
 }
 
+template <int D, int NW, bool CAUSAL>
+static int launch_dq_ds(BwdArgs a, hipStream_t st)
+{
+    using C = DqsCfg<D, NW>;
+    a.ntile = (a.S + C::kBlk - 1) / C::kBlk;
+    if (!allow_lds(attn_bwd_dq_ds_kernel<D, NW, CAUSAL>, C::kLdsBytes)) return -1;
+    hipLaunchKernelGGL((attn_bwd_dq_ds_kernel<D, NW, CAUSAL>), dim3(a.ntile * a.nkv * a.group), dim3(NW * 64),
+                       C::kLdsBytes, st, a);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+// Waves (of 32 rows) per work-group: eight, which read K least often, unless smaller work-groups still
+// fill the compute units in one round.  us, whole backward, 8 | 4 | 2: 11 heads of 1166 rows 61 | 55 | 53,
+// 4 of 5599 causal 173 | 147 | 152, 10 of 1876 D=256 causal 116 | 105 | 105; 8 of 4384 248 | 267 | 284,
+// 32 of 4096 and 16384 five per cent faster with eight.  Long causal heads, whose eight-wave work-groups
+// are the most unequal, take four for longer: 4 of 10802 460 | 427 | 458, 4 of 12527 550 | 530 | 569, but
+// 114 of 321 46 | 51.
+static int dq_ds_waves(int64_t heads, int S, bool causal)
+{
+    if (heads * ((S + 127) / 128) > (causal && S > 4096 ? 512 : 256)) return 8;
+    return heads * ((S + 63) / 64) > 256 ? 4 : 2;
+}
+
+// The backward with dS kept: statistics, then dK/dV and dQ for as many K/V heads at a time as the
+// workspace holds dS of.
+template <int D, bool CAUSAL>
+static int launch_bwd_ds(BwdArgs a, hipStream_t st)
+{
+    constexpr int RPB = 256 / (D / 8);
+    const int64_t rows = (int64_t)a.BH * a.S;
+    hipLaunchKernelGGL((attn_bwd_delta_kernel<D>), dim3((unsigned)((rows + RPB - 1) / RPB)), dim3(256), 0, st, a);
+    if (hipGetLastError() != hipSuccess) return -1;
+    const int BHkv = a.BH / a.group, n_chunk = (BHkv + a.ds_heads - 1) / a.ds_heads;
+    for (int i = 0; i < n_chunk; ++i) {
+        a.bkv0 = (int)((int64_t)BHkv * i / n_chunk);
+        a.nkv = (int)((int64_t)BHkv * (i + 1) / n_chunk) - a.bkv0;
+        if (launch_dkdv<D, CAUSAL, true>(a, st)) return -1;
+        const int nw = dq_ds_waves((int64_t)a.nkv * a.group, a.S, CAUSAL);
+        if (nw == 8 ? launch_dq_ds<D, 8, CAUSAL>(a, st) : nw == 4 ? launch_dq_ds<D, 4, CAUSAL>(a, st)
+                                                                  : launch_dq_ds<D, 2, CAUSAL>(a, st)) return -1;
+    }
+    return 0;
+}
+
 // Order of a full backward: dQ (which also forms the row statistics and stores them), then
 // dK/dV (which reads them).  The separate statistics kernel runs only when they are asked for
 // without dQ.
 template <int D>
 static int launch_bwd_d(BwdArgs a, bool causal, hipStream_t st, unsigned stages)
 {
+    a.bkv0 = 0;
+    a.nkv = a.BH / a.group;
+    if constexpr (D >= 128) {
+        if (stages == 7u && a.ds_heads) return causal ? launch_bwd_ds<D, true>(a, st) : launch_bwd_ds<D, false>(a, st);
+    }
     a.stats_in_dq = (stages & 5u) == 5u;
     if (stages & 4u) {
         if (causal ? launch_dq_for<D, true>(a, st) : launch_dq_for<D, false>(a, st)) return -1;
@@ -1294,6 +1514,15 @@ static int launch_bwd_d(BwdArgs a, bool causal, hipStream_t st, unsigned stages)
     }
     if (stages & 2u) return causal ? launch_dkdv<D, true>(a, st) : launch_dkdv<D, false>(a, st);
     return 0;
+}
+
+// Short heads, the full backward: one fused launch.  With grouped-query heads its work-group
+// walks the query heads of a K/V head one after the other, which pays once there is a K/V
+// head for every compute unit (measured: 10-26 % faster from 256 K/V heads on, slower below,
+// where the two-kernel form spreads the query heads over the chip)
+static bool takes_bwd_small(int BHkv, int group, int S, int Sk, int D)
+{
+    return std::max(S, Sk) <= bwd_small_max_rows(D) && (group == 1 || BHkv >= 256);
 }
 
 // Split of the dQ kernel over the keys, by an estimate of the launch, in us, with n splits of the key tiles:
@@ -1408,17 +1637,32 @@ int dkdv_split_plan(int BHkv, int group, int S, int Sk, int D, bool causal, int 
     }
     return n_block;
 }
+
+// dS kept for dQ (above D = 64): K/V heads whose dS is held at a time in `room` bytes, 0: dS is not kept.
+// The dK/dV kernel stores it once (3 .. 7 % longer: the stores) and the dQ kernel then has one product per
+// tile instead of three, at the rate at which dS comes from HBM (5.2 .. 5.9 TB/s).  Whole backward, before
+// -> after, us: B=4 H=32 S=4096 D=128 3220 -> 3075, causal 1760 -> 1670; B=1 H=16 S=16384 causal 3245 ->
+// 2940; B=4 H=16 S=4096 D=256 causal 2000 -> 1660; 8 heads of 1683 rows 64 -> 54; 4 of 2415 D=256 144 -> 97.
+// At D = 64 dQ's products are half as long and dS as large: 64 heads of 8192 rows causal have 4.3 GB of
+// it, 0.75 ms to read against 0.78 for the whole dQ kernel that does not.
+// Not for one or two long heads at D <= 128, whose dQ is better split over the keys (one of 12784 rows
+// causal 181 -> 212, two of 4842 108 -> 110), nor in parts of fewer than 1024 key blocks (four rounds): each
+// part ends with a launch's tail, two launches over (16 heads of 16384 rows, causal, eight at a time 3055,
+// four 3350; 128 heads of 4096 32 at a time 3115, causal 1710, sixteen 3050 and 1900).
+int ds_plan(int BHkv, int group, int S, int Sk, int D, bool causal, size_t room)
+{
+    if (D < 128 || takes_bwd_small(BHkv, group, S, Sk, D)) return 0;
+    if (D == 128 && S >= 2048 && (int64_t)BHkv * group * ((S + 127) / 128) <= 128) return 0;
+    const size_t n = std::min<size_t>(BHkv, room / ((size_t)group * ds_head_blocks(S, Sk, causal) * (kDsBlock * 2)));
+    if (n == 0 || n == (size_t)BHkv) return (int)n;
+    const int parts = (int)((BHkv + n - 1) / n), keys = dkdv_split_keys(D);
+    return (int64_t)(BHkv / parts) * ((Sk + keys - 1) / keys) < 1024 ? 0 : (BHkv + parts - 1) / parts;
+}
 #endif
 
 int launch_bwd(const BwdArgs &a, int D, bool causal, hipStream_t st, unsigned stages)
 {
-    // short heads, the full backward: one fused launch.  With grouped-query heads its work-group
-    // walks the query heads of a K/V head one after the other, which pays once there is a K/V
-    // head for every compute unit (measured: 10-26 % faster from 256 K/V heads on, slower below,
-    // where the two-kernel form spreads the query heads over the chip)
-    if (stages == 7u && (a.S > a.Sk ? a.S : a.Sk) <= bwd_small_max_rows(D) &&
-        (a.group == 1 || a.BH / a.group >= 256))
-        return launch_bwd_small(a, D, causal, st);
+    if (stages == 7u && takes_bwd_small(a.BH / a.group, a.group, a.S, a.Sk, D)) return launch_bwd_small(a, D, causal, st);
     return D == 256 ? launch_bwd_d<256>(a, causal, st, stages)
          : D == 128 ? launch_bwd_d<128>(a, causal, st, stages)
                     : launch_bwd_d<64>(a, causal, st, stages);

@@ -89,6 +89,10 @@ struct BwdArgsT {
     // dkdv_chunk == 0: not split.
     int dkdv_chunk, dkdv_items;
     float *dKVpart;          // [B*Hkv][dkdv_items][dV, dK][keys of a block][D]
+    // dS kept from the dK/dV kernel for dQ (see ds_row_blocks): K/V heads that the region holds
+    // at a time (0: not kept), and the K/V heads bkv0 .. bkv0 + nkv - 1 of the launch
+    E *dS;
+    int ds_heads, bkv0, nkv;
     // Rotary embedding: Q holds ROTATED rows; dQ is rotated back (by the transpose of the
     // rotation) before it is stored, so that it is the gradient of the unrotated rows.  NULL
     // tables: none.
@@ -131,6 +135,9 @@ int dq_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps, int most 
 // the slots per chunk (0: not split, one work-group per key block), at most `most` chunks in all; a pure
 // host function of the shape.
 int dkdv_split_plan(int BHkv, int group, int S, int Sk, int D, bool causal, int *chunk, int64_t most = 512);
+// K/V heads whose dS the backward keeps at a time in `room` bytes (0: it recomputes it for dQ); a pure host
+// function of the shape and the room.
+int ds_plan(int BHkv, int group, int S, int Sk, int D, bool causal, size_t room);
 // Keys per work-group of the split dK/dV kernel, and the 32-row query slots (over all query heads of
 // the group) that key block kt has to walk: all of them, or under a causal mask those from the
 // block's diagonal on.
@@ -140,6 +147,27 @@ __host__ __device__ inline int dkdv_slots(int kt, int keys, int group, int S, in
     const int n_slot = (S + 31) / 32, first = kt * keys - (Sk - S);
     const int t0 = causal && first > 0 ? first / 32 : 0;
     return n_slot > t0 ? group * (n_slot - t0) : 0;
+}
+// Stored dS: 2 KB blocks of 32 query rows (a slot) x 32 keys; per query head, for slot 0, 1, .. the row of its
+// key blocks.  Under a causal mask (Sk >= S, coff = Sk - S) a row has only the blocks that hold a visible
+// pair, one more than the row before; without one an odd number, so that the rows, which the dQ kernel's
+// waves read side by side, start in different memory channels.  ds_row_len: blocks that slot t sees;
+// ds_row_blocks: blocks before its row.
+constexpr int kDsBlock = 1024;  // elements
+__host__ __device__ inline int ds_row_len(int t, int Sk, int coff, bool causal)
+{
+    const int all = (Sk + 31) / 32, seen = t + (coff + 31) / 32 + 1;
+    return causal && seen < all ? seen : all;
+}
+__host__ __device__ inline int64_t ds_row_blocks(int t, int Sk, int coff, bool causal)
+{
+    // (only the last slot's row can be cut at the last key)
+    return causal ? (int64_t)t * ((coff + 31) / 32 + 1) + (int64_t)t * (t - 1) / 2 : (int64_t)t * ((Sk + 31) / 32 | 1);
+}
+__host__ __device__ inline int64_t ds_head_blocks(int S, int Sk, bool causal)
+{
+    const int last = (S + 31) / 32 - 1;
+    return ds_row_blocks(last, Sk, Sk - S, causal) + ds_row_len(last, Sk, Sk - S, causal);
 }
 // The whole backward in one launch for heads of at most bwd_small_max_rows(D) query rows and keys
 // (attn_bwd_small.hip; called by launch_bwd when all three stages are asked for).

@@ -161,6 +161,20 @@ std::tuple<Tensor, Tensor> run_forward(const char *where, const attn_rect_params
 
 using Grads = std::tuple<Tensor, Tensor, Tensor>;
 
+// A workspace with room for dS (whole backwards), or without it where the device has no memory for that.
+Tensor backward_workspace(const attn_rect_params_t &p, const Tensor &q, bool whole)
+{
+    if (whole) {
+        const size_t best = attn_bwd_rect_best_workspace_bytes(&p);
+        try {
+            return bytes_on(best, q);
+        } catch (const c10::OutOfMemoryError &) {
+            if (best == attn_bwd_rect_workspace_bytes(&p)) throw;
+        }
+    }
+    return bytes_on(attn_bwd_rect_workspace_bytes(&p), q);
+}
+
 // cos, sin: the rotary form; stages: restricted to those stages (square problems)
 Grads run_backward(const char *where, const attn_rect_params_t &p, const Tensor &q, const Tensor &k,
                    const Tensor &v, const Tensor &o, const Tensor &g, const Tensor &lse, bool f16_too,
@@ -178,7 +192,7 @@ Grads run_backward(const char *where, const attn_rect_params_t &p, const Tensor 
         return given ? *given : empty_as(like);
     };
     const Tensor dq = out(dq_in, q), dk = out(dk_in, k), dv = out(dv_in, k);
-    const Tensor ws = ws_in ? *ws_in : bytes_on(attn_bwd_rect_workspace_bytes(&p), q);
+    const Tensor ws = ws_in ? *ws_in : backward_workspace(p, q, !stages);
     const size_t bytes = bytes_of(ws, q);
     void *const Q = q.data_ptr(), *const K = k.data_ptr(), *const V = v.data_ptr(), *const O = o.data_ptr(),
                *const G = g.data_ptr(), *const DQ = dq.data_ptr(), *const DK = dk.data_ptr(),

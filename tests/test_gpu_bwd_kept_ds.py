@@ -1,0 +1,66 @@
+"""dQ from the dS that the dK/dV kernel stores: against the fp64 oracle, against the form that recomputes
+dS, and in parts of the heads."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2601_16238_amd as attn
+from paper_2601_16238_amd import workloads as wl
+from parity_util import bf16_round, check_grad, f16_round, to_f64
+
+pytestmark = pytest.mark.gpu
+
+# work-groups of 64, 128 and 256 rows; last slot and last key block ragged, one row or key over; a causal
+# offset off the 32-key blocks; key blocks that no row of a slot sees; grouped heads; padded head
+# dimensions; fp16; with and without the split of dK/dV
+CASES = [(1, 2, 2, 257, 257, 128, True, False), (1, 3, 1, 385, 609, 96, True, True),
+         (1, 4, 2, 290, 321, 200, False, False), (2, 3, 3, 513, 513, 256, True, True),
+         (1, 40, 20, 500, 545, 128, True, False), (2, 33, 33, 289, 417, 256, False, False),
+         (1, 90, 90, 300, 300, 128, False, False), (2, 48, 48, 300, 331, 80, True, False),
+         (1, 6, 3, 1601, 70, 128, False, False)]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,Sq,Sk,D,causal,f16", CASES)
+def test_dq_from_the_stored_ds(B, Hq, Hkv, Sq, Sk, D, causal, f16):
+    print("case kept_ds", B, Hq, Hkv, Sq, Sk, D, causal, f16, flush=True)
+    draw = wl.random_rect_inputs_f16 if f16 else wl.random_rect_inputs
+    x = draw(B, Hq, Hkv, Sq, Sk, D, seed=5200 + Sq + D)
+    rnd = f16_round if f16 else bf16_round
+    ref = oracle.attn_bwd(x["Q"], x["K"], x["V"], x["dO"], x["scale"], causal, dtype="f16" if f16 else "bf16")
+    dt = torch.float16 if f16 else torch.bfloat16
+    Q, K, V, dO = (torch.from_numpy(x[k].view(np.int16)).cuda().view(dt) for k in ("Q", "K", "V", "dO"))
+    O, LSE = attn.attn_fwd_rect(Q, K, V, x["scale"], causal)
+    best = attn.attn_bwd_rect_best_workspace_bytes(B, Hq, Hkv, Sq, Sk, D, causal)
+    assert best > attn.attn_bwd_rect_workspace_bytes(B, Hq, Hkv, Sq, Sk, D), "dS is not kept"
+    ws = torch.full((best + 4096,), 0xFF, dtype=torch.uint8, device="cuda")   # NaN: nothing may be relied on
+    got = attn.attn_bwd_rect(Q, K, V, O, dO, LSE, x["scale"], causal, workspace=ws[:best])
+    again = attn.attn_bwd_rect(Q, K, V, O, dO, LSE, x["scale"], causal)
+    torch.cuda.synchronize()
+    assert bool((ws[best:] == 0xFF).all()), "written past the workspace"
+    for name, g, a, r in zip(("dQ", "dK", "dV"), got, again, ref):
+        check_grad(name, to_f64(g), r, rnd=rnd)
+        assert torch.equal(g.view(torch.int16), a.view(torch.int16)), name
+
+
+@pytest.mark.parametrize("H,Hkv,S,D,causal", [(702, 351, 330, 128, True), (400, 400, 333, 256, False)])
+def test_ds_of_a_part_of_the_heads_at_a_time(H, Hkv, S, D, causal):
+    """A workspace for the dS of some of the heads: bit for bit the result of the whole one.  (The
+    recomputed form adds the same products in another order: one rounding step, or the fp32 rounding
+    of the sums where the terms cancel.)"""
+    print("case kept_ds parts", H, Hkv, S, D, causal, flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(S)
+    Q, dO = (torch.randn((2, H, S, D), generator=g, device="cuda").bfloat16() for _ in range(2))
+    K, V = (torch.randn((2, Hkv, S, D), generator=g, device="cuda").bfloat16() for _ in range(2))
+    O, LSE = attn.attn_fwd_rect(Q, K, V, D ** -0.5, causal)
+    best = attn.attn_bwd_rect_best_workspace_bytes(2, H, Hkv, S, S, D, causal)
+    ws = torch.full((best,), 0xFF, dtype=torch.uint8, device="cuda")
+    whole, part, none = (attn.attn_bwd_rect(Q, K, V, O, dO, LSE, D ** -0.5, causal, workspace=ws[:n])
+                         for n in (best, int(best * 0.6), 16 * H * S + 256))
+    torch.cuda.synchronize()
+    for w, p, n in zip(whole, part, none):
+        assert torch.equal(w.view(torch.int16), p.view(torch.int16))
+        w, n = w.double(), n.double()
+        assert bool(((w - n).abs() <= n.abs() * 2.0 ** -7 + 1e-3 * n.abs().max()).all())
+    assert not torch.equal(whole[0].view(torch.int16), none[0].view(torch.int16)), "dS is not kept"
