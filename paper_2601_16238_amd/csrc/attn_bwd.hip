@@ -139,12 +139,13 @@ __device__ __forceinline__ void dkdv_find_item(const BwdArgs &a, int item, int k
 
 // SPLIT: the work-group takes one chunk of its key block's slots (see dkdv_split_plan).
 // DS: the producers also store dS, for attn_bwd_dq_ds_kernel.
-template <int D, int P, bool CAUSAL, bool SPLIT, bool DS>
+// U: columns that the products run over (a multiple of 32 up to D; the others are zeros).
+template <int D, int U, int P, bool CAUSAL, bool SPLIT, bool DS>
 __global__ void __launch_bounds__(P * 128) __attribute__((amdgpu_waves_per_eu(P >= 4 ? P / 2 : 1)))
 attn_bwd_dkdv_kernel(const BwdArgs a)
 {
     using C = DkdvCfg<D, P>;
-    constexpr int KS = D / 16, DB = D / 32, CPR = D / 8, RB = C::kRowBytes;
+    constexpr int KS = U / 16, DB = U / 32, CPR = D / 8, RB = C::kRowBytes;
     extern __shared__ __attribute__((aligned(1024))) char smem[];
 
     const int tid = threadIdx.x, l = tid & 63, r = l & 31, h = l >> 5;
@@ -300,11 +301,11 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
         // issued for; chunks XOR-swizzled by the row like the slots.
         elem8 kf[KS], vf[KS];
         {
-            constexpr int RPI = 64 / CPR;  // rows per load instruction
+            constexpr int RPI = 64 / CPR, kLoads = 32 / RPI;  // rows per load instruction
             const int lr = l / CPR, lc = l % CPR;
-            u32x4 tk[KS], tv[KS];
+            u32x4 tk[kLoads], tv[kLoads];
 #pragma unroll
-            for (int j = 0; j < KS; ++j) {
+            for (int j = 0; j < kLoads; ++j) {
                 const int64_t off = base_kv + (int64_t)min(k0 + RPI * j + lr, Sk - 1) * a.kv_stride_s;
                 tk[j] = ld_row16(a.K + off, lc * 8, Dr);
                 tv[j] = ld_row16(a.V + off, lc * 8, Dr);
@@ -316,9 +317,9 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
                 return D <= 128 ? (row >> 4) * (C::kPairs * 4096) + (row & 15) * RB + ((chunk ^ swz(row & 15)) << 4)
                                 : row * RB + ((chunk ^ swz(row)) << 4);
             };
-            auto sort_rows = [&](const u32x4 (&t)[KS], elem8 (&f)[KS]) __attribute__((always_inline)) {
+            auto sort_rows = [&](const u32x4 (&t)[kLoads], elem8 (&f)[KS]) __attribute__((always_inline)) {
 #pragma unroll
-                for (int j = 0; j < KS; ++j) *(u32x4 *)(mine + slot_of(RPI * j + lr, lc)) = t[j];
+                for (int j = 0; j < kLoads; ++j) *(u32x4 *)(mine + slot_of(RPI * j + lr, lc)) = t[j];
                 asm volatile("" ::: "memory");  // a wave's LDS accesses execute in order
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) f[ks] = *(const elem8 *)(mine + slot_of(r, 2 * ks + h));
@@ -400,7 +401,7 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
                         dp = mfma32(f[KS + ks], vf[ks], ks ? dp : nd);
                         fetch(KS + ks + kAhead);
 #pragma unroll
-                        for (int i = ks < 2 ? 0 : 16 * (ks - 2) / (KS - 2); i < (ks < 2 ? 0 : 16 * (ks - 1) / (KS - 2)); ++i)
+                        for (int i = exps_before(ks, KS); i < exps_before(ks + 1, KS); ++i)
                             s[i] = fast_exp2(__builtin_fmaf(s[i], c, -l4[i / 4][i % 4]));
                         __builtin_amdgcn_sched_barrier(0);
                     }
@@ -568,15 +569,16 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                    for (int hp = 0; hp < 2; ++hp) {
+                    for (int hp = 0; hp < 2; ++hp) {  // (columns past U: anything; the merge drops them)
+                        constexpr int HB = D / 64;
 #pragma unroll
-                        for (int db = hp * (DB / 2); db < (hp + 1) * (DB / 2); ++db)
+                        for (int db = hp * HB; db < (hp + 1) * HB && db < DB; ++db)
 #pragma unroll
                             for (int g = 0; g < 4; ++g) {
                                 f32x4 v;
 #pragma unroll
                                 for (int e = 0; e < 4; ++e) v[e] = acc[kb][db][4 * g + e];
-                                const int chunk = (db % (DB / 2)) * 8 + 2 * g + h;
+                                const int chunk = (db % HB) * 8 + 2 * g + h;
                                 *(f32x4 *)(stg + r * RB + ((chunk ^ swz(r)) << 4)) = v;
                             }
                         asm volatile("" ::: "memory");  // a wave's LDS accesses execute in order
@@ -715,16 +717,16 @@ struct DqCfg {
 
 // A wave's 32 finished dQ rows from row q0 on (accumulators dq, in the layout of the MFMA), scaled, to
 // memory through its staging area stg.
-template <typename C, int D>
-__device__ __forceinline__ void dq_rows_out(const BwdArgs &a, f32x16 (&dq)[D / 32], char *stg, int64_t base, int q0, int l)
+template <typename C, int D, int U>
+__device__ __forceinline__ void dq_rows_out(const BwdArgs &a, f32x16 (&dq)[U / 32], char *stg, int64_t base, int q0, int l)
 {
-    constexpr int DB = D / 32, CPR = D / 8, RPI = 64 / CPR;
+    constexpr int DB = U / 32, CPR = D / 8, RPI = 64 / CPR;
     const int r = l & 31, h = l >> 5, lr = l / CPR, lc = l % CPR, S = a.S, Dr = a.Dr;
     const int qc = min(q0 + r, S - 1);
     auto at = [](int row, int chunk) {
         return C::piece_base(row / C::kPieceRows) + (chunk * C::kPieceRows + row % C::kPieceRows) * 16;
     };
-    if (a.rope_cos) {
+    if (U == D && a.rope_cos) {
         // Q was rotated before the forward: what has been accumulated is the gradient of the
         // rotated rows; the gradient of the unrotated ones is its image under the transpose of
         // the rotation (head dimension == D only; column d pairs with d + D/2, i.e. d block db
@@ -767,16 +769,16 @@ __device__ __forceinline__ void dq_rows_out(const BwdArgs &a, f32x16 (&dq)[D / 3
     }
 }
 
-template <int D, int NW, bool CAUSAL, bool SPLIT>
+template <int D, int U, int NW, bool CAUSAL, bool SPLIT>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D > 128 ? 1 : 2)))
 attn_bwd_dq_kernel(const BwdArgs a)
 {
     using C = DqCfg<D, NW>;
-    constexpr int KS = D / 16, DB = D / 32, PR = C::kPieceRows;
+    constexpr int KS = U / 16, DB = U / 32, PR = C::kPieceRows;
     // A wave's transfers per tile are issued between the MFMAs of the tile's first step instead of
     // in a burst after the barrier wherever their number divides that of the MFMAs (measured at
     // D = 128: long causal shapes 2-3 % faster)
-    constexpr bool kBetween = KS % C::kDmaPerWave == 0;
+    constexpr bool kBetween = KS % C::kDmaPerWave == 0 || (U < D && KS >= C::kDmaPerWave);
     extern __shared__ __attribute__((aligned(1024))) char smem[];
 
     const int tid = threadIdx.x, l = tid & 63, r = l & 31, h = l >> 5;
@@ -854,11 +856,11 @@ attn_bwd_dq_kernel(const BwdArgs a)
     // the fragment layout through the wave's staging area in LDS, one tensor after the other.
     elem8 qf[KS], gf[KS], of[KS];
     if constexpr (C::kStageRows) {
-        constexpr int CPR = D / 8, RPI = 64 / CPR;  // chunks per row; rows per load instruction
+        constexpr int CPR = D / 8, RPI = 64 / CPR, kLoads = 32 / RPI;  // chunks per row; rows per load instruction
         const int lr = l / CPR, lc = l % CPR;
-        u32x4 tq[KS], tg[KS], to[KS];
+        u32x4 tq[kLoads], tg[kLoads], to[kLoads];
 #pragma unroll
-        for (int j = 0; j < KS; ++j) {
+        for (int j = 0; j < kLoads; ++j) {
             const int64_t off = base + (int64_t)min(q0 + RPI * j + lr, S - 1) * a.stride_s;
             tq[j] = ld_row16(a.Q + off, lc * 8, Dr);
             tg[j] = ld_row16(a.dO + off, lc * 8, Dr);
@@ -866,9 +868,9 @@ attn_bwd_dq_kernel(const BwdArgs a)
         }
         char *stage = smem + 2 * C::kTileBytes + w * C::kStageBytes;
         const int rd = at(r, h);  // chunk h of row r; contraction step ks: 2 ks chunks further
-        auto sort_rows = [&](const u32x4 (&t)[KS], elem8 (&f)[KS]) __attribute__((always_inline)) {
+        auto sort_rows = [&](const u32x4 (&t)[kLoads], elem8 (&f)[KS]) __attribute__((always_inline)) {
 #pragma unroll
-            for (int j = 0; j < KS; ++j) *(u32x4 *)(stage + at(RPI * j + lr, lc)) = t[j];
+            for (int j = 0; j < kLoads; ++j) *(u32x4 *)(stage + at(RPI * j + lr, lc)) = t[j];
             asm volatile("" ::: "memory");  // a wave's LDS accesses execute in order
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) f[ks] = *(const elem8 *)(stage + rd + ks * 2 * C::kChunkStep);
@@ -967,7 +969,7 @@ attn_bwd_dq_kernel(const BwdArgs a)
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             s = mfma32(*(const elem8 *)(Kt + ks * 2 * C::kChunkStep + rowa), qf[ks], ks ? s : zero);
-            if ((ks + 1) % kEvery == 0) dma_piece(kt_next, pos_next, (ks + 1) / kEvery - 1, Kd, Vd);
+            if ((ks + 1) % kEvery == 0 && (ks + 1) / kEvery <= C::kDmaPerWave) dma_piece(kt_next, pos_next, (ks + 1) / kEvery - 1, Kd, Vd);
         }
     };
     auto step_dp = [&](const char *Kt, int rowa, int kb2, f32x16 &dp) __attribute__((always_inline)) {
@@ -1041,7 +1043,7 @@ attn_bwd_dq_kernel(const BwdArgs a)
             for (int ks = 0; ks < KS; ++ks) {
                 s = mfma32(f[ks], qf[ks], ks ? s : zero);
                 read(ks + kAhead);
-                if ((ks + 1) % kEvery == 0) dma_piece(kt + 2, pos == 0 ? 2 : pos - 1, (ks + 1) / kEvery - 1, Kd, Vd);
+                if ((ks + 1) % kEvery == 0 && (ks + 1) / kEvery <= C::kDmaPerWave) dma_piece(kt + 2, pos == 0 ? 2 : pos - 1, (ks + 1) / kEvery - 1, Kd, Vd);
                 __builtin_amdgcn_sched_barrier(0);
             }
         } else {
@@ -1057,7 +1059,7 @@ attn_bwd_dq_kernel(const BwdArgs a)
             dp = mfma32(f[KS + ks], gf[ks], ks ? dp : nd);  // ends as dP - delta
             read(KS + ks + kAhead);
 #pragma unroll
-            for (int i = ks < 2 ? 0 : 16 * (ks - 2) / (KS - 2); i < (ks < 2 ? 0 : 16 * (ks - 1) / (KS - 2)); ++i)
+            for (int i = exps_before(ks, KS); i < exps_before(ks + 1, KS); ++i)
                 s[i] = fast_exp2(__builtin_fmaf(s[i], c, -lse2));
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -1148,15 +1150,16 @@ attn_bwd_dq_kernel(const BwdArgs a)
         // fp32 row is twice as long as the staging area's, so it goes in two halves
         const int64_t row0 = ((int64_t)blockIdx.y * a.BH + bh) * S;
 #pragma unroll
-        for (int hp = 0; hp < 2; ++hp) {
+        for (int hp = 0; hp < 2; ++hp) {  // (columns past U: anything; the merge drops them)
+            constexpr int HB = D / 64;
 #pragma unroll
-            for (int db = hp * (DB / 2); db < (hp + 1) * (DB / 2); ++db)
+            for (int db = hp * HB; db < (hp + 1) * HB && db < DB; ++db)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     f32x4 v;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) v[e] = dq[db][4 * g + e];
-                    *(f32x4 *)(stg + at(r, (db % (DB / 2)) * 8 + 2 * g + h)) = v;
+                    *(f32x4 *)(stg + at(r, (db % HB) * 8 + 2 * g + h)) = v;
                 }
             asm volatile("" ::: "memory");  // a wave's LDS accesses execute in order
 #pragma unroll
@@ -1169,7 +1172,7 @@ attn_bwd_dq_kernel(const BwdArgs a)
         }
         return;
     }
-    dq_rows_out<C, D>(a, dq, stg, base, q0, l);
+    dq_rows_out<C, D, U>(a, dq, stg, base, q0, l);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1197,12 +1200,12 @@ struct DqsCfg : DqCfg<D, 4> {
     static_assert(kRing >= 3 && kLdsBytes <= 160 * 1024, "LDS layout");
 };
 
-template <int D, int NW, bool CAUSAL>
+template <int D, int U, int NW, bool CAUSAL>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW > 4 ? 2 : 1)))
 attn_bwd_dq_ds_kernel(const BwdArgs a)
 {
     using C = DqsCfg<D, NW>;
-    constexpr int DB = D / 32, PR = C::kPieceRows;
+    constexpr int DB = U / 32, PR = C::kPieceRows;
     extern __shared__ __attribute__((aligned(1024))) char smem[];
 
     const int tid = threadIdx.x, l = tid & 63, h = l >> 5;
@@ -1284,7 +1287,7 @@ attn_bwd_dq_ds_kernel(const BwdArgs a)
         pos = pos + 1 == C::kRing ? 0 : pos + 1;
     }
     wait_vm_and_barrier<0>();  // (everyone's transfers have landed: the LDS is free)
-    dq_rows_out<C, D>(a, dq, smem + w * C::kStage, base, q0, l);
+    dq_rows_out<C, D, U>(a, dq, smem + w * C::kStage, base, q0, l);
 }
 
 // Sum of the per-split partial dQ, times scale, rounded: one thread per (row, 4 consecutive d);
@@ -1330,19 +1333,19 @@ static bool allow_lds(K kernel, int bytes)
                                bytes) == hipSuccess;
 }
 
-template <int D, int P, bool CAUSAL, bool DS = false>
+template <int D, int U, int P, bool CAUSAL, bool DS>
 static int launch_dkdv_p(BwdArgs a, hipStream_t st)
 {
     using C = DkdvCfg<D, P>;
     a.ntile = (a.Sk + C::kBlk - 1) / C::kBlk;
-    if (!allow_lds(attn_bwd_dkdv_kernel<D, P, CAUSAL, false, DS>, C::kLdsBytes)) return -1;
-    hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, P, CAUSAL, false, DS>), dim3(a.ntile * a.nkv),
+    if (!allow_lds(attn_bwd_dkdv_kernel<D, U, P, CAUSAL, false, DS>, C::kLdsBytes)) return -1;
+    hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, U, P, CAUSAL, false, DS>), dim3(a.ntile * a.nkv),
                        dim3(C::kThreads), C::kLdsBytes, st, a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 // Split over the query slots: one work-group per chunk, then the merge.
-template <int D, bool CAUSAL, bool DS>
+template <int D, int U, bool CAUSAL, bool DS>
 static int launch_dkdv_split(BwdArgs a, hipStream_t st)
 {
     constexpr int P = D > 128 ? 2 : 4, keys = dkdv_split_keys(D);
@@ -1350,8 +1353,8 @@ static int launch_dkdv_split(BwdArgs a, hipStream_t st)
     static_assert(C::kBlk == keys, "keys per work-group");
     const int BHkv = a.BH / a.group;
     a.ntile = a.dkdv_items;
-    if (!allow_lds(attn_bwd_dkdv_kernel<D, P, CAUSAL, true, DS>, C::kLdsBytes)) return -1;
-    hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, P, CAUSAL, true, DS>), dim3(a.ntile * BHkv), dim3(C::kThreads),
+    if (!allow_lds(attn_bwd_dkdv_kernel<D, U, P, CAUSAL, true, DS>, C::kLdsBytes)) return -1;
+    hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, U, P, CAUSAL, true, DS>), dim3(a.ntile * BHkv), dim3(C::kThreads),
                        C::kLdsBytes, st, a);
     if (hipGetLastError() != hipSuccess) return -1;
     const int n_block = (a.Sk + keys - 1) / keys;
@@ -1365,41 +1368,48 @@ static int launch_dkdv_split(BwdArgs a, hipStream_t st)
 // registers: three per SIMD hide more of each other's latencies).  Measured: -2.5..4 % on the
 // large shapes; slower on small launches (more of a 192-key block is padding) and at D = 64
 // (the larger work-group no longer fits a compute unit twice).
-template <int D, bool CAUSAL, bool DS = false>
-static int launch_dkdv(const BwdArgs &a, hipStream_t st)
+template <int D, int U, bool CAUSAL, bool DS>
+static int launch_dkdv_u(const BwdArgs &a, hipStream_t st)
 {
-    if (a.dkdv_chunk) return launch_dkdv_split<D, CAUSAL, DS>(a, st);
+    if (a.dkdv_chunk) return launch_dkdv_split<D, U, CAUSAL, DS>(a, st);
     // D = 256: two pairs, one wave per SIMD (a consumer's two 32 x 256 accumulators alone are
     // 256 registers), 64 keys per work-group
-    if constexpr (D > 128) return launch_dkdv_p<D, 2, CAUSAL, DS>(a, st);
+    if constexpr (D > 128) return launch_dkdv_p<D, U, 2, CAUSAL, DS>(a, st);
     else {
         if constexpr (D == 128) {
             const int64_t wgs6 = (int64_t)a.nkv * ((a.Sk + 191) / 192);
-            if (wgs6 >= 512) return launch_dkdv_p<D, 6, CAUSAL, DS>(a, st);
+            if (wgs6 >= 512) return launch_dkdv_p<D, U, 6, CAUSAL, DS>(a, st);
         }
-        return launch_dkdv_p<D, 4, CAUSAL, DS>(a, st);
+        return launch_dkdv_p<D, U, 4, CAUSAL, DS>(a, st);
     }
 }
 
-template <int D, int NW, bool CAUSAL>
+template <int D, bool CAUSAL, bool DS = false>
+static int launch_dkdv(const BwdArgs &a, hipStream_t st)
+{
+    constexpr int U = narrow_columns(D);
+    return a.Dr <= U ? launch_dkdv_u<D, U, CAUSAL, DS>(a, st) : launch_dkdv_u<D, D, CAUSAL, DS>(a, st);
+}
+
+template <int D, int U, int NW, bool CAUSAL>
 static int launch_dq(BwdArgs a, hipStream_t st)
 {
     using C = DqCfg<D, NW>;
     a.ntile = (a.S + C::kBlk - 1) / C::kBlk;
-    if (!allow_lds(attn_bwd_dq_kernel<D, NW, CAUSAL, false>, C::kLdsBytes)) return -1;
-    hipLaunchKernelGGL((attn_bwd_dq_kernel<D, NW, CAUSAL, false>), dim3(a.ntile * a.BH),
+    if (!allow_lds(attn_bwd_dq_kernel<D, U, NW, CAUSAL, false>, C::kLdsBytes)) return -1;
+    hipLaunchKernelGGL((attn_bwd_dq_kernel<D, U, NW, CAUSAL, false>), dim3(a.ntile * a.BH),
                        dim3(C::kThreads), C::kLdsBytes, st, a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 // Split over the keys: 256-row work-groups, one grid row per split, then the merge.
-template <int D, bool CAUSAL>
+template <int D, int U, bool CAUSAL>
 static int launch_dq_split(BwdArgs a, hipStream_t st)
 {
     using C = DqCfg<D, 8>;
     a.ntile = (a.S + C::kBlk - 1) / C::kBlk;
-    if (!allow_lds(attn_bwd_dq_kernel<D, 8, CAUSAL, true>, C::kLdsBytes)) return -1;
-    hipLaunchKernelGGL((attn_bwd_dq_kernel<D, 8, CAUSAL, true>), dim3(a.ntile * a.BH, a.dq_nsplit),
+    if (!allow_lds(attn_bwd_dq_kernel<D, U, 8, CAUSAL, true>, C::kLdsBytes)) return -1;
+    hipLaunchKernelGGL((attn_bwd_dq_kernel<D, U, 8, CAUSAL, true>), dim3(a.ntile * a.BH, a.dq_nsplit),
                        dim3(C::kThreads), C::kLdsBytes, st, a);
     if (hipGetLastError() != hipSuccess) return -1;
     const int64_t rows = (int64_t)a.BH * a.S;
@@ -1429,33 +1439,47 @@ static int dq_waves(int BH, int S, int D, bool causal)
     return D == 128 ? 2 : blocks32;
 }
 
-template <int D, bool CAUSAL>
-static int launch_dq_for(const BwdArgs &a, hipStream_t st)
+template <int D, int U, bool CAUSAL>
+static int launch_dq_u(const BwdArgs &a, hipStream_t st)
 {
     // D = 256: always four waves, one per SIMD (Q and dO fragments plus the accumulator are
     // 256 registers); never split
-    if constexpr (D > 128) return a.dq_nsplit > 1 ? -1 : launch_dq<D, 4, CAUSAL>(a, st);
+    if constexpr (D > 128) return a.dq_nsplit > 1 ? -1 : launch_dq<D, U, 4, CAUSAL>(a, st);
     else {
-    if (a.dq_nsplit > 1) return launch_dq_split<D, CAUSAL>(a, st);
+    if (a.dq_nsplit > 1) return launch_dq_split<D, U, CAUSAL>(a, st);
     const int nw = dq_waves(a.BH, a.S, D, CAUSAL);
-    if (nw == 8) return launch_dq<D, 8, CAUSAL>(a, st);
-    if (nw == 4) return launch_dq<D, 4, CAUSAL>(a, st);
-    if (nw == 3) return launch_dq<D, 3, CAUSAL>(a, st);
-    if (nw == 2) return launch_dq<D, 2, CAUSAL>(a, st);
-    if constexpr (D < 128) return launch_dq<D, 1, CAUSAL>(a, st);
+    if (nw == 8) return launch_dq<D, U, 8, CAUSAL>(a, st);
+    if (nw == 4) return launch_dq<D, U, 4, CAUSAL>(a, st);
+    if (nw == 3) return launch_dq<D, U, 3, CAUSAL>(a, st);
+    if (nw == 2) return launch_dq<D, U, 2, CAUSAL>(a, st);
+    if constexpr (D < 128) return launch_dq<D, U, 1, CAUSAL>(a, st);
     return -1;
     }
 }
 
-template <int D, int NW, bool CAUSAL>
-static int launch_dq_ds(BwdArgs a, hipStream_t st)
+template <int D, bool CAUSAL>
+static int launch_dq_for(const BwdArgs &a, hipStream_t st)
+{
+    constexpr int U = narrow_columns(D);
+    return a.Dr <= U ? launch_dq_u<D, U, CAUSAL>(a, st) : launch_dq_u<D, D, CAUSAL>(a, st);
+}
+
+template <int D, int U, int NW, bool CAUSAL>
+static int launch_dq_ds_u(BwdArgs a, hipStream_t st)
 {
     using C = DqsCfg<D, NW>;
     a.ntile = (a.S + C::kBlk - 1) / C::kBlk;
-    if (!allow_lds(attn_bwd_dq_ds_kernel<D, NW, CAUSAL>, C::kLdsBytes)) return -1;
-    hipLaunchKernelGGL((attn_bwd_dq_ds_kernel<D, NW, CAUSAL>), dim3(a.ntile * a.nkv * a.group), dim3(NW * 64),
+    if (!allow_lds(attn_bwd_dq_ds_kernel<D, U, NW, CAUSAL>, C::kLdsBytes)) return -1;
+    hipLaunchKernelGGL((attn_bwd_dq_ds_kernel<D, U, NW, CAUSAL>), dim3(a.ntile * a.nkv * a.group), dim3(NW * 64),
                        C::kLdsBytes, st, a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+template <int D, int NW, bool CAUSAL>
+static int launch_dq_ds(const BwdArgs &a, hipStream_t st)
+{
+    constexpr int U = narrow_columns(D);
+    return a.Dr <= U ? launch_dq_ds_u<D, U, NW, CAUSAL>(a, st) : launch_dq_ds_u<D, D, NW, CAUSAL>(a, st);
 }
 
 // Waves (of 32 rows) per work-group: eight, which read K least often, unless smaller work-groups still

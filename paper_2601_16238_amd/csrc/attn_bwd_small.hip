@@ -43,7 +43,8 @@ struct SmallCfg {
     static_assert(lds_bytes(kMaxRows) <= 160 * 1024, "LDS budget of a gfx950 CU exceeded");
 };
 
-template <int D, int NW, bool CAUSAL, bool GQA, bool DUO>
+// U: columns that the products run over (a multiple of 32 up to D; the others are zeros).
+template <int D, int U, int NW, bool CAUSAL, bool GQA, bool DUO>
 // (D = 64, four waves, one query head per K/V head: at most 168 registers, so that three
 // work-groups share a compute unit; with grouped heads the dK/dV accumulators stay live while dQ
 // of the next query head is formed, which takes more)
@@ -52,7 +53,7 @@ __global__ void __launch_bounds__(NW * (DUO ? 128 : 64))
 attn_bwd_small_kernel(const BwdArgs a)
 {
     using C = SmallCfg<D, NW, DUO>;
-    constexpr int KS = D / 16, DB = D / 32, PR = C::kPieceRows, CPR = C::kCPR, RB = C::kRowBytes;
+    constexpr int KS = U / 16, DB = U / 32, PR = C::kPieceRows, CPR = C::kCPR, RB = C::kRowBytes;
     extern __shared__ __attribute__((aligned(1024))) char smem[];
 
     const int tid = threadIdx.x, l = tid & 63, r = l & 31, h = l >> 5;
@@ -205,7 +206,7 @@ attn_bwd_small_kernel(const BwdArgs a)
 #pragma unroll
                 for (int db = 0; db < DB; ++db) dq[db] = mfma32(tr_frag(offK, j, cc, db), sb[cc], dq[db]);
         }
-        if (a.rope_cos) {
+        if (U == D && a.rope_cos) {
             // Q was rotated before the forward: what has been accumulated is the gradient of the
             // rotated rows; the gradient of the unrotated ones is its image under the transpose of
             // the rotation (head dimension == D; column d pairs with d + D/2, i.e. d block db with
@@ -357,17 +358,24 @@ attn_bwd_small_kernel(const BwdArgs a)
     }
 }
 
-template <int D, int NW, bool CAUSAL, bool GQA, bool DUO>
-static int launch_small_g(const BwdArgs &a, hipStream_t st)
+template <int D, int U, int NW, bool CAUSAL, bool GQA, bool DUO>
+static int launch_small_u(const BwdArgs &a, hipStream_t st)
 {
     using C = SmallCfg<D, NW, DUO>;
     const int rows_pad = ((a.S > a.Sk ? a.S : a.Sk) + 31) / 32 * 32;
-    if (hipFuncSetAttribute((const void *)attn_bwd_small_kernel<D, NW, CAUSAL, GQA, DUO>,
+    if (hipFuncSetAttribute((const void *)attn_bwd_small_kernel<D, U, NW, CAUSAL, GQA, DUO>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, C::lds_bytes(C::kMaxRows)) != hipSuccess)
         return -1;
-    hipLaunchKernelGGL((attn_bwd_small_kernel<D, NW, CAUSAL, GQA, DUO>), dim3(a.BH / a.group), dim3(C::kThreads),
+    hipLaunchKernelGGL((attn_bwd_small_kernel<D, U, NW, CAUSAL, GQA, DUO>), dim3(a.BH / a.group), dim3(C::kThreads),
                        C::lds_bytes(rows_pad), st, a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+template <int D, int NW, bool CAUSAL, bool GQA, bool DUO>
+static int launch_small_g(const BwdArgs &a, hipStream_t st)
+{
+    constexpr int U = narrow_columns(D);
+    return a.Dr <= U ? launch_small_u<D, U, NW, CAUSAL, GQA, DUO>(a, st) : launch_small_u<D, D, NW, CAUSAL, GQA, DUO>(a, st);
 }
 
 template <int D, int NW, bool CAUSAL>

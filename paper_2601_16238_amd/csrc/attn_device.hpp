@@ -37,6 +37,13 @@ __device__ __forceinline__ f32x16 mfma32(elem8 a, elem8 b, f32x16 c)
 // Row of a 32x32 accumulator block held in register i by a lane of half h = lane/32.
 __device__ __forceinline__ constexpr int acc_row(int i, int h) { return 8 * (i / 4) + 4 * h + (i % 4); }
 
+// How many of a score block's sixteen exp2 lie before step ks of the KS MFMAs that they are spread over: none
+// before the third (the scores come from the MFMA just issued), then evenly.
+__device__ __forceinline__ constexpr int exps_before(int ks, int KS)
+{
+    return ks < 2 ? 0 : KS > 2 ? 16 * (ks - 2) / (KS - 2) : 16;
+}
+
 // Exchange between lane l and lane l^32: returns {value of the lower-half partner or self,
 // value of the upper-half partner or self}; max/sum of the pair is symmetric in the two.
 __device__ __forceinline__ float xhalf_max(float x)

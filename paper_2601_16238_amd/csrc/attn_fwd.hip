@@ -78,13 +78,15 @@ struct FwdCfg {
 constexpr float kOverflow = 1024.0f;
 constexpr float kMinusHuge = -1.0e30f;  // initial reference: finite, so masked -inf scores give 0
 
-template <int D, int NW, bool CAUSAL, bool SPLIT, bool MAIN>
+// U: columns that the products run over, a multiple of 32 up to D; the others are zeros (tensors of a
+// smaller head dimension).  The layouts are those of D.
+template <int D, int U, int NW, bool CAUSAL, bool SPLIT, bool MAIN>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2)))
 attn_fwd_kernel(const FwdArgs a)
 {
     using C = FwdCfg<D, NW, MAIN>;
-    constexpr int KS = D / 16;  // contraction steps of K Q^T
-    constexpr int DB = D / 32;  // 32-row blocks of O^T
+    constexpr int KS = U / 16;  // contraction steps of K Q^T
+    constexpr int DB = U / 32;  // 32-row blocks of O^T
     extern __shared__ __attribute__((aligned(16))) char smem[];
     elem *Ks = reinterpret_cast<elem *>(smem);  // [3][64][D] swizzled
     elem *Vs = Ks + 3 * C::kKTile;              // [kVBufs] tiles in the K tile's layout
@@ -183,7 +185,7 @@ attn_fwd_kernel(const FwdArgs a)
     // (one 32x32 score block per wave).  One step is four (D=128) MFMAs whose A fragments
     // are fetched a step ahead into the other of two fragment sets, so the LDS latency hides
     // behind the previous step's MFMAs.
-    constexpr int NKQ = KS / 4;  // K Q^T steps per sub-tile, four contraction steps each
+    constexpr int NKQ = (KS + 3) / 4;  // K Q^T steps per sub-tile, up to four contraction steps each
     // element offset of this lane's fragment for contraction step 0 within a 32-row half
     // tile: chunk h of row r
     // The per-lane parts of the LDS addresses are kept in one register each and made opaque to
@@ -202,12 +204,12 @@ attn_fwd_kernel(const FwdArgs a)
     asm volatile("" : "+v"(k_lane), "+v"(v_lane0), "+v"(v_lane1));
     auto ld_k = [&](const elem *Kt, int kq, elem8 (&f)[4]) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+        for (int t = 0; t < 4 && 4 * kq + t < KS; ++t)
             f[t] = *(const elem8 *)((const char *)(Kt + (4 * kq + t) * C::kKStep) + k_lane);
     };
     auto mm_k = [&](int kq, const elem8 (&f)[4], f32x16 &t0) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) t0 = mfma32(f[t], qf[4 * kq + t], t0);
+        for (int t = 0; t < 4 && 4 * kq + t < KS; ++t) t0 = mfma32(f[t], qf[4 * kq + t], t0);
     };
     // V^T fragment: lane (d = 32*db + l%32, half h) gets the 8 keys of contraction step cc
     // that its half owns, from two transpose reads.  Vt: byte offset of tile and sub-tile
@@ -350,7 +352,8 @@ attn_fwd_kernel(const FwdArgs a)
     // would have written to memory as bf16.  The table rows are requested here, after the first
     // K and V tiles, so that all of them are in flight together, and used further down.
     f32x4 rc[KS][2], rs[KS][2];  // [ks][half of the 8 columns]; only ks < KS/2 is used
-    if (a.rope_cos) {
+    const bool rope = U == D && a.rope_cos;
+    if (rope) {
         const int64_t pos = (int64_t)(qc * a.rope_row_step + a.rope_pos0) * (D / 2);
 #pragma unroll
         for (int ks = 0; ks < KS / 2; ++ks)
@@ -364,7 +367,7 @@ attn_fwd_kernel(const FwdArgs a)
         // the wave's own query rows have landed once at most the later transfers (K(0), K(1),
         // V(0)) are outstanding; with the rotary table rows in flight as well, whose place in the
         // order of issue is the compiler's choice, everything is awaited
-        if (a.rope_cos) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (rope) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * C::kKDmaPerWave) : "memory");
         const char *Qs = smem + q_stage + ((r / PR) * C::kKPieceBytes + (h * PR + r % PR) * 16);
 #pragma unroll
@@ -372,7 +375,7 @@ attn_fwd_kernel(const FwdArgs a)
         // ... and are in registers before anybody may overwrite the staging space
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
-    if (a.rope_cos) {
+    if (rope) {
         elem *qr = a.Qrot ? a.Qrot + base + (int64_t)qc * a.stride_s : nullptr;
 #pragma unroll
         for (int ks = 0; ks < KS / 2; ++ks) {
@@ -592,16 +595,18 @@ attn_fwd_kernel(const FwdArgs a)
             // through LDS like O below; an fp32 row is twice as long, so it goes in two halves
             constexpr int CPR = D / 8, RPI = 64 / CPR;
             const int lr_ = l / CPR, lc = l % CPR;
+            // (columns past U: whatever the staging space holds; the merge reads and drops them)
+            constexpr int HB = D / 64;
 #pragma unroll
             for (int hp = 0; hp < 2; ++hp) {
 #pragma unroll
-                for (int db = hp * (DB / 2); db < (hp + 1) * (DB / 2); ++db)
+                for (int db = hp * HB; db < (hp + 1) * HB && db < DB; ++db)
 #pragma unroll
                     for (int g = 0; g < 4; ++g) {
                         f32x4 ov;
 #pragma unroll
                         for (int e = 0; e < 4; ++e) ov[e] = o[db][4 * g + e] * inv;
-                        *(f32x4 *)(stg + at(r, (db % (DB / 2)) * 8 + 2 * g + h)) = ov;
+                        *(f32x4 *)(stg + at(r, (db % HB) * 8 + 2 * g + h)) = ov;
                     }
                 asm volatile("" ::: "memory");  // a wave's LDS accesses execute in order
 #pragma unroll
@@ -761,14 +766,14 @@ static int launch_fwd_merge(const FwdArgs &a, hipStream_t st)
     return launch_fwd_merge_zg<D, (D > 128 ? 4 : 8)>(a, st);
 }
 
-template <int D, int NW, bool CAUSAL, bool SPLIT, bool MAIN>
+template <int D, int U, int NW, bool CAUSAL, bool SPLIT, bool MAIN>
 static int launch_fwd_kernel(const FwdArgs &a, hipStream_t st)
 {
     using C = FwdCfg<D, NW, MAIN>;
-    if (hipFuncSetAttribute((const void *)attn_fwd_kernel<D, NW, CAUSAL, SPLIT, MAIN>,
+    if (hipFuncSetAttribute((const void *)attn_fwd_kernel<D, U, NW, CAUSAL, SPLIT, MAIN>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, C::kLdsBytes) != hipSuccess)
         return -1;
-    hipLaunchKernelGGL((attn_fwd_kernel<D, NW, CAUSAL, SPLIT, MAIN>),
+    hipLaunchKernelGGL((attn_fwd_kernel<D, U, NW, CAUSAL, SPLIT, MAIN>),
                        dim3(a.nqt * a.BH, SPLIT ? a.nsplit : 1), dim3(C::kThreads),
                        C::kLdsBytes, st, a);
     if (hipGetLastError() != hipSuccess) return -1;
@@ -776,16 +781,16 @@ static int launch_fwd_kernel(const FwdArgs &a, hipStream_t st)
     return 0;
 }
 
-template <int D, int NW, bool MAIN>
+template <int D, int U, int NW, bool MAIN>
 static int launch_fwd_nw(const FwdArgs &a, bool causal, hipStream_t st)
 {
     // (four waves at D = 64 are split in the form with the main loop only, see four_wave_main)
     if constexpr (MAIN || NW != 4 || D != 64)
         if (a.nsplit > 1)
-            return causal ? launch_fwd_kernel<D, NW, true, true, MAIN>(a, st)
-                          : launch_fwd_kernel<D, NW, false, true, MAIN>(a, st);
-    return causal ? launch_fwd_kernel<D, NW, true, false, MAIN>(a, st)
-                  : launch_fwd_kernel<D, NW, false, false, MAIN>(a, st);
+            return causal ? launch_fwd_kernel<D, U, NW, true, true, MAIN>(a, st)
+                          : launch_fwd_kernel<D, U, NW, false, true, MAIN>(a, st);
+    return causal ? launch_fwd_kernel<D, U, NW, true, false, MAIN>(a, st)
+                  : launch_fwd_kernel<D, U, NW, false, false, MAIN>(a, st);
 }
 
 // Whether four waves at D = 64 take the form with the pipelined main loop.  The generic form takes a lone
@@ -830,18 +835,18 @@ static int fwd_waves_for(int S, int D, int BH, bool causal)
     return blocks32;  // 1 or 2
 }
 
-template <int D>
+template <int D, int U = D>
 static int launch_fwd_d(FwdArgs a, bool causal, hipStream_t st)
 {
     const int nw = fwd_waves_for(a.S, D, a.BH, causal);
     a.nqt = (a.S + nw * 32 - 1) / (nw * 32);
-    if (nw == 8) return launch_fwd_nw<D, 8, true>(a, causal, st);
+    if (nw == 8) return launch_fwd_nw<D, U, 8, true>(a, causal, st);
     if constexpr (D < 128) {
-        if (nw == 4 && four_wave_main(a)) return launch_fwd_nw<D, 4, true>(a, causal, st);
-        if (nw == 2) return launch_fwd_nw<D, 2, false>(a, causal, st);
-        if (nw == 1) return launch_fwd_nw<D, 1, false>(a, causal, st);
+        if (nw == 4 && four_wave_main(a)) return launch_fwd_nw<D, U, 4, true>(a, causal, st);
+        if (nw == 2) return launch_fwd_nw<D, U, 2, false>(a, causal, st);
+        if (nw == 1) return launch_fwd_nw<D, U, 1, false>(a, causal, st);
     }
-    if (nw == 4) return launch_fwd_nw<D, 4, false>(a, causal, st);
+    if (nw == 4) return launch_fwd_nw<D, U, 4, false>(a, causal, st);
     return -1;
 }
 
@@ -982,7 +987,9 @@ int launch_fwd(const FwdArgs &a, int D, bool causal, hipStream_t st)
         return D == 256 ? launch_fwd_merge<256>(a, st)
              : D == 128 ? launch_fwd_merge<128>(a, st) : launch_fwd_merge<64>(a, st);
     }
-    return D == 128 ? launch_fwd_d<128>(a, causal, st) : launch_fwd_d<64>(a, causal, st);
+    constexpr int U128 = narrow_columns(128), U64 = narrow_columns(64);
+    if (D == 128) return a.Dr <= U128 ? launch_fwd_d<128, U128>(a, causal, st) : launch_fwd_d<128>(a, causal, st);
+    return a.Dr <= U64 ? launch_fwd_d<64, U64>(a, causal, st) : launch_fwd_d<64>(a, causal, st);
 }
 
 }  // namespace attn

@@ -138,6 +138,13 @@ int dkdv_split_plan(int BHkv, int group, int S, int Sk, int D, bool causal, int 
 // K/V heads whose dS the backward keeps at a time in `room` bytes (0: it recomputes it for dQ); a pure host
 // function of the shape and the room.
 int ds_plan(int BHkv, int group, int S, int Sk, int D, bool causal, size_t room);
+// Columns that the products run over in the narrow instances of the kernels for D columns, for tensors of at
+// most that many; the columns past them are zeros and cost their share of the matrix instructions, LDS
+// reads and registers.  The products summed are the same.  us, all columns -> narrow, forward |
+// backward: 140 heads of 1477 rows D = 80 causal 104 -> 90 | 289 -> 275, 68 of 2529 D = 96 208 -> 181 |
+// 737 -> 637 (with dS kept in both); 240 of 1226 D = 32 causal 88 -> 61 | 227 -> 173.  (No further steps:
+// at D = 64 an instance of 48 columns would leave the 32-column blocks of dQ, dK, dV and O as they are.)
+constexpr int narrow_columns(int D) { return D > 64 ? D / 4 * 3 : D / 2; }
 // Keys per work-group of the split dK/dV kernel, and the 32-row query slots (over all query heads of
 // the group) that key block kt has to walk: all of them, or under a causal mask those from the
 // block's diagonal on.
