@@ -228,7 +228,9 @@ size_t attn_bwd_rect_workspace_bytes(const attn_rect_params_t *p);
  * per visible query-key pair) and dQ is then formed from it instead of from Q, K, V and dO once more; this
  * takes place in any workspace larger than that with room for it, for all heads or a part of them at a time, and
  * enqueues a kernel for the row statistics, then dK/dV and dQ for each part.  At most 4.5 GiB are
- * asked for it.  Pure host function; 0 for an invalid problem.
+ * asked for it.  Calls of few work-groups run dK/dV and dQ side by side instead, in one kernel after the
+ * statistics and before a merge, also in any workspace larger than that.  Pure host function; 0 for an
+ * invalid problem.
  */
 size_t attn_bwd_rect_best_workspace_bytes(const attn_rect_params_t *p);
 

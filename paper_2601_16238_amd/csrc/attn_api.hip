@@ -188,6 +188,18 @@ static size_t ds_bytes(const attn_rect_params_t *p, int n)
     return (size_t)n * (p->Hq / p->Hkv) * attn::ds_head_blocks(p->Sq, p->Sk, p->causal != 0) * (attn::kDsBlock * 2);
 }
 
+// dK/dV and dQ in one launch, in `room` bytes (see pair_plan), and the bytes of its partial results.
+static attn::PairPlan pair_in(const attn_rect_params_t *p, size_t room)
+{
+    return attn::pair_plan(p->B * p->Hkv, p->Hq / p->Hkv, p->Sq, p->Sk, kernel_d(p->D), p->causal != 0, room);
+}
+static size_t pair_bytes(const attn_rect_params_t *p, const attn::PairPlan &plan)
+{
+    if (!plan.dkdv_chunk) return 0;
+    return (kernel_d(p->D) > 128 ? 0 : round_ws(plan.dq_nsplit * dq_split_bytes(p))) +
+           round_ws((size_t)p->B * p->Hkv * plan.items * dkdv_chunk_bytes(p));
+}
+
 // Rotary embedding fused into the call (both tables NULL: none).
 struct Rope {
     const float *cos_table = nullptr, *sin_table = nullptr;
@@ -277,7 +289,7 @@ static int bwd_impl(const void *Q, const void *K, const void *V, const void *O, 
     // The row statistics always; the rest of the workspace bounds the splits.  (A plan that is dropped
     // where it does not fit whole costs, in the 8 MiB of the call without workspace, us: one head of 1024
     // rows on 4096 keys, D = 128, causal 112 against 55 with the splits that fit; 4 -> 1 heads of 2048,
-    // D = 64, causal 180 against 51.)  No split of dQ with rotary tables: the merge does not rotate back.
+    // D = 64, causal 180 against 51.)  dQ with rotary tables is split only where it runs next to dK/dV.
     const size_t stats_bytes = bwd_stats_bytes(p);
     if (!workspace || !aligned(workspace, kWsAlign) || workspace_bytes < stats_bytes)
         return ATTN_ERR_WORKSPACE;
@@ -293,6 +305,8 @@ static int bwd_impl(const void *Q, const void *K, const void *V, const void *O, 
     // (a workspace of the size that attn_bwd_rect_workspace_bytes asks for, or less, keeps the form without dS)
     int ds_heads = stages == 7u ? ds_heads_in(p, room - dkdv_bytes) : 0;
     if (ds_heads && workspace_bytes <= attn_bwd_rect_workspace_bytes(p)) ds_heads = 0;
+    attn::PairPlan pair = {};  // (nor with it the two kernels side by side)
+    if (stages == 7u && workspace_bytes > attn_bwd_rect_workspace_bytes(p)) pair = pair_in(p, room);
     attn::BwdArgsT<E> a;
     a.Q = static_cast<const E *>(Q);
     a.K = static_cast<const E *>(K);
@@ -307,6 +321,12 @@ static int bwd_impl(const void *Q, const void *K, const void *V, const void *O, 
     a.dKVpart = a.dQpart;
     a.dS = reinterpret_cast<E *>(reinterpret_cast<char *>(a.dQpart) + dkdv_bytes);
     a.ds_heads = ds_heads; a.bkv0 = 0; a.nkv = p->B * p->Hkv;
+    a.pair = pair.taken; a.pair_dkdv = a.pair_dq = 0;
+    if (pair.taken) {
+        a.dq_nsplit = pair.dq_nsplit; a.dq_kps = pair.dq_kps;
+        a.dkdv_chunk = pair.dkdv_chunk; a.dkdv_items = pair.items;
+        if (kernel_d(p->D) <= 128) a.dKVpart += round_ws(pair.dq_nsplit * dq_split_bytes(p)) / sizeof(float);
+    }
     a.dQ = static_cast<E *>(dQ);
     a.dK = static_cast<E *>(dK);
     a.dV = static_cast<E *>(dV);
@@ -435,8 +455,10 @@ size_t attn_bwd_rect_best_workspace_bytes(const attn_rect_params_t *p)
 {
     if (check_params(p) != ATTN_OK) return 0;
     constexpr size_t kMost = ((size_t)288 << 30) / 64;
-    const int n = ds_heads_in(p, kMost);
     const size_t plain = attn_bwd_rect_workspace_bytes(p);
+    const attn::PairPlan pair = pair_in(p, kMost);
+    if (pair.taken) return std::max(bwd_stats_bytes(p) + pair_bytes(p, pair), plain + kWsAlign);
+    const int n = ds_heads_in(p, kMost);
     if (!n) return plain;  // (a workspace of that size would not be taken as one for dS)
     return std::max(bwd_stats_bytes(p) + dkdv_part_bytes(p, p->causal != 0) + ds_bytes(p, n), plain + kWsAlign);
 }

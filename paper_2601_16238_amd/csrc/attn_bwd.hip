@@ -7,6 +7,7 @@
 //               accumulates in registers                           (3 GEMMs per tile pair)
 // or, above D = 64 where the workspace holds dS: 1, 2 (which also stores dS), and
 //   3b. dQ    : the same from the stored dS                        (1 GEMM per tile pair; HBM-bound)
+// or, for calls of few work-groups: 1, then 2 and 3 side by side in one launch.
 // With dP = dO V^T and dS = P o (dP - delta):
 //   dV = P^T dO,  dK = scale * dS^T Q,  dQ = scale * dS K.
 //
@@ -140,9 +141,9 @@ __device__ __forceinline__ void dkdv_find_item(const BwdArgs &a, int item, int k
 // SPLIT: the work-group takes one chunk of its key block's slots (see dkdv_split_plan).
 // DS: the producers also store dS, for attn_bwd_dq_ds_kernel.
 // U: columns that the products run over (a multiple of 32 up to D; the others are zeros).
+// block, ntile: the work-group among those of the kernel, and its key blocks (or chunks) per K/V head.
 template <int D, int U, int P, bool CAUSAL, bool SPLIT, bool DS>
-__global__ void __launch_bounds__(P * 128) __attribute__((amdgpu_waves_per_eu(P >= 4 ? P / 2 : 1)))
-attn_bwd_dkdv_kernel(const BwdArgs a)
+__device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
 {
     using C = DkdvCfg<D, P>;
     constexpr int KS = U / 16, DB = U / 32, CPR = D / 8, RB = C::kRowBytes;
@@ -157,7 +158,7 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
     // read it (grouped-query attention; group == 1 is multi-head attention).
     const int Hkv = a.H / a.group;
     int bkv, kt;  // causal: key block 0 is the heaviest
-    xcd_tile_order<CAUSAL, D == 64>(blockIdx.x, a.ntile, a.nkv, bkv, kt);
+    xcd_tile_order<CAUSAL, D == 64>(block, ntile, a.nkv, bkv, kt);
     bkv += a.bkv0;
     int item = 0, z = 0;  // SPLIT: chunk of the head, and of the key block
     if (SPLIT) {
@@ -618,16 +619,23 @@ attn_bwd_dkdv_kernel(const BwdArgs a)
     }
 }
 
+template <int D, int U, int P, bool CAUSAL, bool SPLIT, bool DS>
+__global__ void __launch_bounds__(P * 128) __attribute__((amdgpu_waves_per_eu(P >= 4 ? P / 2 : 1)))
+attn_bwd_dkdv_kernel(const BwdArgs a)
+{
+    bwd_dkdv<D, U, P, CAUSAL, SPLIT, DS>(a, blockIdx.x, a.ntile);
+}
+
 // Sum of the partial dK and dV of the key blocks that were cut into several chunks, in the order of
 // the chunks, dK times scale, rounded.  A work-group owns 1024 / D keys of one block and tensor,
 // a thread 4 consecutive columns of one key; HBM-bound and small.
 template <int D, bool CAUSAL>
-__global__ void __launch_bounds__(256) attn_bwd_dkdv_merge_kernel(const BwdArgs a)
+__device__ __forceinline__ void bwd_dkdv_merge(const BwdArgs &a, int block, int kind)
 {
     constexpr int keys = dkdv_split_keys(D), kRows = 1024 / D, kSub = keys / kRows;
     const int n_block = (a.Sk + keys - 1) / keys;
-    const int sub = blockIdx.x % kSub, kind = blockIdx.y;
-    const int kt = (blockIdx.x / kSub) % n_block, bkv = blockIdx.x / (kSub * n_block);
+    const int sub = block % kSub;
+    const int kt = (block / kSub) % n_block, bkv = block / (kSub * n_block);
     const int n = dkdv_chunks(a, kt, keys, CAUSAL);
     if (n < 2) return;  // (written by its one work-group)
     int first = 0;  // the block's first chunk: the chunks of the blocks before it, summed over the lanes
@@ -656,6 +664,12 @@ __global__ void __launch_bounds__(256) attn_bwd_dkdv_merge_kernel(const BwdArgs 
     elem *out = (kind ? a.dK : a.dV) + (int64_t)(bkv / Hkv) * a.kv_stride_b + (int64_t)(bkv % Hkv) * a.kv_stride_h +
                 (int64_t)key * a.kv_stride_s + d0;
     *(elem4 *)out = pack4(acc[0] * sc, acc[1] * sc, acc[2] * sc, acc[3] * sc);
+}
+
+template <int D, bool CAUSAL>
+__global__ void __launch_bounds__(256) attn_bwd_dkdv_merge_kernel(const BwdArgs a)
+{
+    bwd_dkdv_merge<D, CAUSAL>(a, blockIdx.x, blockIdx.y);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -769,9 +783,9 @@ __device__ __forceinline__ void dq_rows_out(const BwdArgs &a, f32x16 (&dq)[U / 3
     }
 }
 
+// block, ntile: the work-group among those of a split, and its query tiles per head; part: the split.
 template <int D, int U, int NW, bool CAUSAL, bool SPLIT>
-__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D > 128 ? 1 : 2)))
-attn_bwd_dq_kernel(const BwdArgs a)
+__device__ __forceinline__ void bwd_dq(const BwdArgs &a, int block, int ntile, int part)
 {
     using C = DqCfg<D, NW>;
     constexpr int KS = U / 16, DB = U / 32, PR = C::kPieceRows;
@@ -785,8 +799,8 @@ attn_bwd_dq_kernel(const BwdArgs a)
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int S = a.S;
     int bh, rank;
-    xcd_tile_order<CAUSAL, D == 64 && NW == 4>(blockIdx.x, a.ntile, a.BH, bh, rank);
-    const int qt = CAUSAL ? a.ntile - 1 - rank : rank;  // heaviest first
+    xcd_tile_order<CAUSAL, D == 64 && NW == 4>(block, ntile, a.BH, bh, rank);
+    const int qt = CAUSAL ? ntile - 1 - rank : rank;  // heaviest first
     const int64_t base = (int64_t)(bh / a.H) * a.stride_b + (int64_t)(bh % a.H) * a.stride_h;
     // grouped-query heads: query head h reads K/V head h / group
     const int64_t base_kv = (int64_t)(bh / a.H) * a.kv_stride_b +
@@ -802,7 +816,7 @@ attn_bwd_dq_kernel(const BwdArgs a)
     int coff = Sk - S;  // causal: query row i sees keys 0 .. i + coff
     int64_t kv_first = 0;
     if (SPLIT) {
-        const int k_begin = blockIdx.y * a.dq_kps;  // < Sk by the launcher's plan
+        const int k_begin = part * a.dq_kps;  // < Sk by the launcher's plan
         kv_first = (int64_t)k_begin * a.kv_stride_s;
         Sk = min(Sk - k_begin, a.dq_kps);
         coff -= k_begin;
@@ -905,7 +919,7 @@ attn_bwd_dq_kernel(const BwdArgs a)
         }
         ndelta = -xhalf_sum(acc);
         lse2 = a.LSE[(int64_t)bh * S + qc] * kLog2e;
-        if (q < S && h == 0 && (!SPLIT || blockIdx.y == 0)) {
+        if (q < S && h == 0 && (!SPLIT || part == 0)) {
             a.delta[(int64_t)bh * 2 * S + q] = ndelta;
             a.delta[(int64_t)bh * 2 * S + S + q] = lse2;
         }
@@ -1148,7 +1162,7 @@ attn_bwd_dq_kernel(const BwdArgs a)
     if (SPLIT) {
         // unscaled fp32 partial of this key range (zeros if the range had no visible key); an
         // fp32 row is twice as long as the staging area's, so it goes in two halves
-        const int64_t row0 = ((int64_t)blockIdx.y * a.BH + bh) * S;
+        const int64_t row0 = ((int64_t)part * a.BH + bh) * S;
 #pragma unroll
         for (int hp = 0; hp < 2; ++hp) {  // (columns past U: anything; the merge drops them)
             constexpr int HB = D / 64;
@@ -1173,6 +1187,13 @@ attn_bwd_dq_kernel(const BwdArgs a)
         return;
     }
     dq_rows_out<C, D, U>(a, dq, stg, base, q0, l);
+}
+
+template <int D, int U, int NW, bool CAUSAL, bool SPLIT>
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D > 128 ? 1 : 2)))
+attn_bwd_dq_kernel(const BwdArgs a)
+{
+    bwd_dq<D, U, NW, CAUSAL, SPLIT>(a, blockIdx.x, a.ntile, blockIdx.y);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1293,34 +1314,87 @@ attn_bwd_dq_ds_kernel(const BwdArgs a)
 // Sum of the per-split partial dQ, times scale, rounded: one thread per (row, 4 consecutive d);
 // HBM-bound and small.
 template <int D>
-__global__ void __launch_bounds__(256) attn_bwd_dq_merge_kernel(const BwdArgs a)
+__device__ __forceinline__ void bwd_dq_merge(const BwdArgs &a, int block)
 {
     constexpr int TPR = D / 4;  // threads per row
     const int64_t rows = (int64_t)a.BH * a.S;
-    const int64_t row = (int64_t)blockIdx.x * (256 / TPR) + threadIdx.x / TPR;
+    const int64_t row = (int64_t)block * (256 / TPR) + threadIdx.x / TPR;
     if (row >= rows) return;
     const int d0 = (threadIdx.x % TPR) * 4;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     // four splits per step, their loads issued together (one dependent load per split costs a
     // memory latency each); added in the order of the splits
     const int n = a.dq_nsplit;
-    for (int z0 = 0; z0 < n; z0 += 4) {
-        f32x4 v[4];
+    auto sum = [&](int d) __attribute__((always_inline)) {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int z0 = 0; z0 < n; z0 += 4) {
+            f32x4 v[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            v[k] = *(const f32x4 *)(a.dQpart + ((int64_t)(z0 + k < n ? z0 + k : z0) * rows + row) * D + d0);
+            for (int k = 0; k < 4; ++k)
+                v[k] = *(const f32x4 *)(a.dQpart + ((int64_t)(z0 + k < n ? z0 + k : z0) * rows + row) * D + d);
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (z0 + k < n) {
+            for (int k = 0; k < 4; ++k)
+                if (z0 + k < n) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[e] += v[k][e];
-            }
-    }
+                    for (int e = 0; e < 4; ++e) acc[e] += v[k][e];
+                }
+        }
+        return acc;
+    };
+    f32x4 acc = sum(d0);
     const int bh = (int)(row / a.S), q = (int)(row % a.S);
+    if (a.rope_cos) {  // rotated back, as in dq_rows_out; d0 pairs with d0 -+ D/2
+        const f32x4 other = sum(d0 ^ (D / 2));
+        const int64_t pos = (int64_t)(q + a.rope_pos0) * (D / 2) + d0 % (D / 2);
+        const f32x4 c4 = *(const f32x4 *)(a.rope_cos + pos), s4 = *(const f32x4 *)(a.rope_sin + pos);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            acc[e] = __builtin_fmaf(acc[e], c4[e], d0 < D / 2 ? other[e] * s4[e] : -(other[e] * s4[e]));
+    }
     elem *dQp = a.dQ + (int64_t)(bh / a.H) * a.stride_b + (int64_t)(bh % a.H) * a.stride_h +
                 (int64_t)q * a.stride_s + d0;
     const float sc = a.scale;
     if (d0 < a.Dr) *(elem4 *)dQp = pack4(acc[0] * sc, acc[1] * sc, acc[2] * sc, acc[3] * sc);
+}
+
+template <int D>
+__global__ void __launch_bounds__(256) attn_bwd_dq_merge_kernel(const BwdArgs a) { bwd_dq_merge<D>(a, blockIdx.x); }
+
+// ---------------------------------------------------------------------------------------
+// 2 + 3. dK/dV and dQ in one launch, for calls whose work-groups leave compute units idle: the first
+// pair_dkdv work-groups are those of the dK/dV kernel, the others those of the dQ kernel (the statistics,
+// which both read, come from the kernel above).  Bound by the longest work-group, so both are cut until
+// the units are taken (see pair_plan), and one launch merges both.
+// ---------------------------------------------------------------------------------------
+template <int D>
+struct PairCfg {  // as many waves for dQ as for dK/dV; above D = 128 one per SIMD
+    static constexpr int kPairs = D > 128 ? 2 : 4, kWaves = 2 * kPairs;
+    using Dkdv = DkdvCfg<D, kPairs>;
+    using Dq = DqCfg<D, kWaves>;
+    static constexpr int kLdsBytes = Dkdv::kLdsBytes > Dq::kLdsBytes ? Dkdv::kLdsBytes : Dq::kLdsBytes;
+    static constexpr int kMergeRows = 256 / (D / 4);  // dQ rows of a merging work-group
+    static_assert(Dkdv::kThreads == Dq::kThreads, "one launch");
+};
+
+template <int D, int U, bool CAUSAL, bool SPLIT>
+__global__ void __launch_bounds__(PairCfg<D>::Dq::kThreads) __attribute__((amdgpu_waves_per_eu(D > 128 ? 1 : 2)))
+attn_bwd_pair_kernel(const BwdArgs a)
+{
+    using C = PairCfg<D>;
+    if ((int)blockIdx.x < a.pair_dkdv) {
+        bwd_dkdv<D, U, C::kPairs, CAUSAL, SPLIT, false>(a, blockIdx.x, a.ntile);
+    } else {
+        const int i = (int)blockIdx.x - a.pair_dkdv, n = a.pair_dq * a.BH;
+        // (above D = 128 dQ is not split)
+        bwd_dq<D, U, C::kWaves, CAUSAL, SPLIT && D <= 128>(a, D > 128 ? i : i % n, a.pair_dq, D > 128 ? 0 : i / n);
+    }
+}
+
+template <int D, bool CAUSAL>
+__global__ void __launch_bounds__(256) attn_bwd_pair_merge_kernel(const BwdArgs a)
+{
+    const int i = (int)blockIdx.x - a.pair_dkdv;  // first the two tensors of the key blocks, then dQ
+    if (i < 0) bwd_dkdv_merge<D, CAUSAL>(a, blockIdx.x >> 1, blockIdx.x & 1);
+    else bwd_dq_merge<D>(a, i);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1494,15 +1568,21 @@ static int dq_ds_waves(int64_t heads, int S, bool causal)
     return heads * ((S + 63) / 64) > 256 ? 4 : 2;
 }
 
+template <int D>
+static int launch_delta(const BwdArgs &a, hipStream_t st)
+{
+    constexpr int RPB = 256 / (D / 8);
+    const int64_t rows = (int64_t)a.BH * a.S;
+    hipLaunchKernelGGL((attn_bwd_delta_kernel<D>), dim3((unsigned)((rows + RPB - 1) / RPB)), dim3(256), 0, st, a);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
 // The backward with dS kept: statistics, then dK/dV and dQ for as many K/V heads at a time as the
 // workspace holds dS of.
 template <int D, bool CAUSAL>
 static int launch_bwd_ds(BwdArgs a, hipStream_t st)
 {
-    constexpr int RPB = 256 / (D / 8);
-    const int64_t rows = (int64_t)a.BH * a.S;
-    hipLaunchKernelGGL((attn_bwd_delta_kernel<D>), dim3((unsigned)((rows + RPB - 1) / RPB)), dim3(256), 0, st, a);
-    if (hipGetLastError() != hipSuccess) return -1;
+    if (launch_delta<D>(a, st)) return -1;
     const int BHkv = a.BH / a.group, n_chunk = (BHkv + a.ds_heads - 1) / a.ds_heads;
     for (int i = 0; i < n_chunk; ++i) {
         a.bkv0 = (int)((int64_t)BHkv * i / n_chunk);
@@ -1515,6 +1595,38 @@ static int launch_bwd_ds(BwdArgs a, hipStream_t st)
     return 0;
 }
 
+// dK/dV and dQ in one launch.
+template <int D, int U, bool CAUSAL, bool SPLIT>
+static int launch_bwd_pair_u(BwdArgs a, hipStream_t st)
+{
+    using C = PairCfg<D>;
+    const int n_block = (a.Sk + C::Dkdv::kBlk - 1) / C::Dkdv::kBlk, nsplit = SPLIT && D <= 128 ? a.dq_nsplit : 1;
+    a.ntile = SPLIT ? a.dkdv_items : n_block;
+    a.pair_dkdv = a.ntile * a.nkv;
+    a.pair_dq = (a.S + C::Dq::kBlk - 1) / C::Dq::kBlk;
+    a.stats_in_dq = 0;
+    if (!allow_lds(attn_bwd_pair_kernel<D, U, CAUSAL, SPLIT>, C::kLdsBytes)) return -1;
+    hipLaunchKernelGGL((attn_bwd_pair_kernel<D, U, CAUSAL, SPLIT>), dim3(a.pair_dkdv + a.pair_dq * a.BH * nsplit),
+                       dim3(C::Dq::kThreads), C::kLdsBytes, st, a);
+    if (hipGetLastError() != hipSuccess) return -1;
+    if (!SPLIT) return 0;
+    const int64_t rows = D <= 128 ? (int64_t)a.BH * a.S : 0;
+    a.pair_dkdv = 2 * a.nkv * n_block * (C::Dkdv::kBlk * D / 1024);
+    hipLaunchKernelGGL((attn_bwd_pair_merge_kernel<D, CAUSAL>),
+                       dim3((unsigned)(a.pair_dkdv + (rows + C::kMergeRows - 1) / C::kMergeRows)), dim3(256), 0, st, a);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+template <int D, bool CAUSAL>
+static int launch_bwd_pair(const BwdArgs &a, hipStream_t st)
+{
+    constexpr int U = narrow_columns(D);
+    if (launch_delta<D>(a, st)) return -1;
+    if (a.dkdv_chunk)
+        return a.Dr <= U ? launch_bwd_pair_u<D, U, CAUSAL, true>(a, st) : launch_bwd_pair_u<D, D, CAUSAL, true>(a, st);
+    return a.Dr <= U ? launch_bwd_pair_u<D, U, CAUSAL, false>(a, st) : launch_bwd_pair_u<D, D, CAUSAL, false>(a, st);
+}
+
 // Order of a full backward: dQ (which also forms the row statistics and stores them), then
 // dK/dV (which reads them).  The separate statistics kernel runs only when they are asked for
 // without dQ.
@@ -1523,6 +1635,7 @@ static int launch_bwd_d(BwdArgs a, bool causal, hipStream_t st, unsigned stages)
 {
     a.bkv0 = 0;
     a.nkv = a.BH / a.group;
+    if (stages == 7u && a.pair) return causal ? launch_bwd_pair<D, true>(a, st) : launch_bwd_pair<D, false>(a, st);
     if constexpr (D >= 128) {
         if (stages == 7u && a.ds_heads) return causal ? launch_bwd_ds<D, true>(a, st) : launch_bwd_ds<D, false>(a, st);
     }
@@ -1530,11 +1643,7 @@ static int launch_bwd_d(BwdArgs a, bool causal, hipStream_t st, unsigned stages)
     if (stages & 4u) {
         if (causal ? launch_dq_for<D, true>(a, st) : launch_dq_for<D, false>(a, st)) return -1;
     } else if (stages & 1u) {
-        constexpr int RPB = 256 / (D / 8);
-        const int64_t rows = (int64_t)a.BH * a.S;
-        hipLaunchKernelGGL((attn_bwd_delta_kernel<D>), dim3((unsigned)((rows + RPB - 1) / RPB)),
-                           dim3(256), 0, st, a);
-        if (hipGetLastError() != hipSuccess) return -1;
+        if (launch_delta<D>(a, st)) return -1;
     }
     if (stages & 2u) return causal ? launch_dkdv<D, true>(a, st) : launch_dkdv<D, false>(a, st);
     return 0;
@@ -1681,6 +1790,82 @@ int ds_plan(int BHkv, int group, int S, int Sk, int D, bool causal, size_t room)
     if (n == 0 || n == (size_t)BHkv) return (int)n;
     const int parts = (int)((BHkv + n - 1) / n), keys = dkdv_split_keys(D);
     return (int64_t)(BHkv / parts) * ((Sk + keys - 1) / keys) < 1024 ? 0 : (BHkv + parts - 1) / parts;
+}
+
+// dK/dV and dQ in one launch, when all work-groups of both kernels find a compute unit of their own: one
+// kernel after the other leaves most units idle twice, and three launches (four with the statistics where
+// dS is kept, two merges) cost more than the products of such calls.  Both are cut, dQ over the keys and
+// dK/dV over the query slots, as long as the chunks still have a unit each.  The launch takes as long as its
+// longest work-group: fixed + slots * slot or dq_fixed + tiles * dq_tile us, and, cut, a merge; the cut
+// with the least is compared with the same estimate of the two kernels one after the other (constants of
+// both: a fit to 160 problems of up to 256 work-groups, 3 .. 9 % rms).  Whole backward, us: 6 heads of 940
+// rows D = 64 causal 35 -> 19, 12 of 1037 44 -> 33, 1 of 1181 D = 96 45 -> 23, 3 of 2099 D = 128 causal 58 ->
+// 36, 9 of 329 D = 64 causal 22 -> 15, 3 of 134 D = 256 causal 23 -> 16; 0.75 on average over 200 random
+// problems, one of them slower by more than 2 % (36 -> 9 heads of 75 rows D = 256: 30.5 -> 33).  Not beyond a
+// work-group per unit: 26 heads of 1776 rows D = 128 causal 101 -> 110, 13 of 4773 D = 64 175 -> 198 (uncut).
+PairPlan pair_plan(int BHkv, int group, int S, int Sk, int D, bool causal, size_t room)
+{
+    PairPlan best = {};
+    if (takes_bwd_small(BHkv, group, S, Sk, D)) return best;
+    constexpr int64_t units = 256;
+    const int keys = dkdv_split_keys(D), n_block = (Sk + keys - 1) / keys;
+    const int dq_rows = D > 128 ? 128 : 256, dq_keys = D > 128 ? 32 : 64, tiles = (Sk + dq_keys - 1) / dq_keys;
+    const int64_t heads = (int64_t)BHkv * group, wgs = (int64_t)BHkv * n_block, dq_wgs = heads * ((S + dq_rows - 1) / dq_rows);
+    if (wgs + dq_wgs > units) return best;
+    // all slots of a head, and the chunks of L slots that they make (causal: every block has fewer than the one before)
+    auto over_blocks = [&](auto &&f) {
+        int64_t sum = 0;
+        if (!causal) return (int64_t)n_block * f(std::max(1, dkdv_slots(0, keys, group, S, Sk, false)));
+        for (int kt = 0; kt < n_block; ++kt) sum += f(std::max(1, dkdv_slots(kt, keys, group, S, Sk, true)));
+        return sum;
+    };
+    const size_t dq_bytes = (size_t)heads * S * D * 4, chunk_bytes = (size_t)2 * keys * D * 4;
+    const PairCost c = D > 128  ? PairCost{11.0f, 0.87f, 11.0f, 1.10f, 3.0f, 0.35e-6f}
+                       : D > 64 ? PairCost{9.1f, 0.67f, 9.5f, 1.65f, 3.7f, 0.34e-6f}
+                                : PairCost{7.9f, 0.57f, 8.0f, 1.03f, 3.1f, 0.43e-6f};
+    best.items = n_block; best.dq_nsplit = 1; best.dq_kps = tiles * dq_keys;
+    const int longest = std::max(1, dkdv_slots(0, keys, group, S, Sk, causal));
+    const int64_t slots = BHkv * over_blocks([](int s) { return s; });
+    float least = std::max(c.fixed + longest * c.slot, c.dq_fixed + tiles * c.dq_tile);
+    for (int n = 1; n <= (D > 128 ? 1 : 16) && (n == 1 || 4 * n <= tiles) && n * dq_wgs < units; ++n) {
+        const int per = (tiles + n - 1) / n;
+        if ((tiles + per - 1) / per != n) continue;
+        const float dq_us = c.dq_fixed + per * c.dq_tile + c.merge;
+        if (dq_us >= least) continue;
+        const int64_t left = units - n * dq_wgs;
+        int L = (int)std::max<int64_t>((slots + left - 1) / left, std::min(8, longest));
+        int64_t items = 0;
+        for (; L <= longest; L += (L + 15) / 16) {
+            items = BHkv * over_blocks([L](int s) { return (s + L - 1) / L; });
+            if (items <= left) break;
+        }
+        if (L > longest) continue;
+        const size_t part = (D > 128 ? 0 : (n * dq_bytes + 255) / 256 * 256) + items * chunk_bytes;
+        const float t = std::max(c.fixed + L * c.slot + c.merge, dq_us) + c.byte * part;
+        if (part > room || t >= least) continue;
+        least = t;
+        best.dq_nsplit = n; best.dq_kps = per * dq_keys;
+        best.dkdv_chunk = L; best.items = (int)(items / BHkv);
+    }
+    // the two kernels one after the other
+    int chunk = 0, kps = 0;
+    const int64_t items = (int64_t)BHkv * dkdv_split_plan(BHkv, group, S, Sk, D, causal, &chunk);
+    const float walk = chunk ? chunk : longest;
+    size_t part = chunk ? items * chunk_bytes : 0;
+    int merges = chunk ? 1 : 0;
+    float t;
+    if (ds_plan(BHkv, group, S, Sk, D, causal, ~(size_t)0)) {  // (not by the room: the same choice in the best size)
+        t = D > 128 ? 16.5f + 0.87f * walk + 9.9f * merges + 0.47f * ((Sk + 31) / 32)
+                    : 12.2f + 0.75f * walk + 9.3f * merges + 0.23e-6f * part + 0.256f * ((Sk + 31) / 32);
+    } else {
+        const int n = dq_split_plan((int)heads, S, Sk, D, causal, &kps);
+        const float per = n > 1 ? kps / dq_keys : tiles;
+        if (n > 1) { ++merges; part += n * dq_bytes; }
+        t = D > 64 ? 8.7f + 0.39f * walk + 7.9f * merges + 0.24e-6f * part + 2.95f * per
+                   : 9.9f + 0.59f * walk * (items > 256 ? 1.4f : 1.0f) + 4.1f * merges + 0.47e-6f * part + 0.8f * per;
+    }
+    best.taken = least < 0.95f * t;
+    return best;
 }
 #endif
 

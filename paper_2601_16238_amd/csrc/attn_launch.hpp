@@ -93,6 +93,9 @@ struct BwdArgsT {
     // at a time (0: not kept), and the K/V heads bkv0 .. bkv0 + nkv - 1 of the launch
     E *dS;
     int ds_heads, bkv0, nkv;
+    // dK/dV and dQ in one launch (see pair_plan), if `pair`: the work-groups of dK/dV, which come first,
+    // and the query tiles per head
+    int pair, pair_dkdv, pair_dq;
     // Rotary embedding: Q holds ROTATED rows; dQ is rotated back (by the transpose of the
     // rotation) before it is stored, so that it is the gradient of the unrotated rows.  NULL
     // tables: none.
@@ -138,6 +141,12 @@ int dkdv_split_plan(int BHkv, int group, int S, int Sk, int D, bool causal, int 
 // K/V heads whose dS the backward keeps at a time in `room` bytes (0: it recomputes it for dQ); a pure host
 // function of the shape and the room.
 int ds_plan(int BHkv, int group, int S, int Sk, int D, bool causal, size_t room);
+// dK/dV and dQ in one launch, with both splits (dkdv_chunk == 0: neither is split) in `room` bytes: first the
+// partial results of dQ, rounded up to 256 bytes, then those of dK/dV.
+struct PairPlan { bool taken; int dq_nsplit, dq_kps, dkdv_chunk, items; };
+// PairCost: us (see attn_bwd.hip).
+struct PairCost { float fixed, slot, dq_fixed, dq_tile, merge, byte; };
+PairPlan pair_plan(int BHkv, int group, int S, int Sk, int D, bool causal, size_t room);
 // Columns that the products run over in the narrow instances of the kernels for D columns, for tensors of at
 // most that many; the columns past them are zeros and cost their share of the matrix instructions, LDS
 // reads and registers.  The products summed are the same.  us, all columns -> narrow, forward |
