@@ -280,7 +280,8 @@ def _call(entry, stream, *args):
 
 
 def attn_fwd(Q, K, V, scale, causal, O=None, LSE=None, stream=None):
-    """O, LSE = attention forward.  Q,K,V: bf16 device tensors [B,H,S,D] with equal strides.
+    """O, LSE = attention forward.  Q,K,V: bf16 device tensors [B,H,S,D] with equal strides.  Few heads of
+    more than 768 rows are split over the keys (see attn_fwd_rect), if the device has the memory.
     Enqueues on `stream` (default: torch's current stream); does not synchronise."""
     return _call(marshal().attn_fwd, stream, Q, K, V, float(scale), bool(causal), O, LSE)
 

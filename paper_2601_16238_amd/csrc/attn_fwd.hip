@@ -920,6 +920,10 @@ static int fwd_splits(const SplitCost &c, int64_t wgs, int tiles, int S, float p
         return std::max(t, spread + busy * c.start / 256) + merge;
     };
     int best = 1;
+    // Causal rows beyond those of the fit: the heavy work-groups of a split that nearly fills the chip run
+    // longer than estimated.  us, unsplit -> two splits: 9 heads of 8690 rows D = 96 182 -> 204, 5 of 5555
+    // D = 256 148 -> 166, 6 of 9829 D = 80 185 -> 197; with fewer work-groups it pays, 6 of 5161 (126) 97 -> 73.
+    if (!equal && S > 4096 && wgs > 160) return 1;
     float least = 0.97f * estimate(1);
     for (int n = 2; n <= most && 4 * n <= tiles && n * wgs <= 1024; ++n) {
         const float t = estimate(n);

@@ -121,12 +121,28 @@ void forward_outputs(const Tensor &q, const Tensor &k, const Tensor &v, bool f16
     else lse = at::empty(q.sizes().slice(0, 3), q.options().dtype(at::kFloat));
 }
 
-// The workspace of a forward's split over the keys: the caller's, else one of the planned size.
-Tensor forward_workspace(size_t need, const OptTensor &given, bool split, const Tensor &q)
+// What a forward call does about its split over the keys.  spare: the square calls, whose C entry points have
+// no workspace; they take one (of the rectangular call) where the device has the memory for it.
+enum class Split { no, yes, spare };
+
+// The workspace of that split: the caller's, else one of the planned size.
+// Square calls of up to 768 keys are not split: it saves at most 6 us there (2 heads of 768 rows, D = 128
+// causal), and their rows stay bit for bit those of a rectangular call that is not split.  Above that,
+// us, one kernel -> split: one head of 1957 rows D = 128 49 -> 23, 2 of 1287 D = 32 21 -> 13, 3 of 5199 D = 80
+// causal 96 -> 43, 4 of 4829 D = 128 causal 111 -> 53, 8 of 4139 D = 32 causal 40 -> 36; over 170 random calls that
+// the plan splits 0.62 on average, three of them 2 .. 7 % slower (16 of 1158 D = 80 causal 28 -> 30).
+constexpr int kSquareUnsplitKeys = 768;
+Tensor forward_workspace(size_t need, const OptTensor &given, Split split, const Tensor &q)
 {
-    if (!split) return Tensor();
+    if (split == Split::no) return Tensor();
     if (given) return *given;
-    return need ? bytes_on(need, q) : Tensor();
+    if (!need) return Tensor();
+    try {
+        return bytes_on(need, q);
+    } catch (const c10::OutOfMemoryError &) {
+        if (split == Split::yes) throw;
+    }
+    return Tensor();
 }
 
 void *data_of(const Tensor &t) { return t.defined() ? t.data_ptr() : nullptr; }
@@ -143,12 +159,13 @@ size_t bytes_of(const Tensor &ws, const Tensor &x)
 
 std::tuple<Tensor, Tensor> run_forward(const char *where, const attn_rect_params_t &p, const Tensor &q,
                                        const Tensor &k, const Tensor &v, bool f16_too, const OptTensor &o_in,
-                                       const OptTensor &lse_in, const OptTensor &ws_in, bool split,
+                                       const OptTensor &lse_in, const OptTensor &ws_in, Split split,
                                        const OptStream &stream)
 {
     Tensor o, lse;
     forward_outputs(q, k, v, f16_too, o, lse, o_in, lse_in);
-    const Tensor ws = forward_workspace(split && !ws_in ? attn_fwd_rect_workspace_bytes(&p) : 0, ws_in, split, q);
+    const bool plan = !ws_in && (split == Split::yes || (split == Split::spare && p.Sk > kSquareUnsplitKeys));
+    const Tensor ws = forward_workspace(plan ? attn_fwd_rect_workspace_bytes(&p) : 0, ws_in, split, q);
     const size_t bytes = bytes_of(ws, q);
     void *const Q = q.data_ptr(), *const K = k.data_ptr(), *const V = v.data_ptr(), *const O = o.data_ptr(),
                *const W = data_of(ws), *const st = stream_ptr(stream);
@@ -222,7 +239,8 @@ std::tuple<Tensor, Tensor> attn_fwd_(const Tensor &q, const Tensor &k, const Ten
                                      const OptTensor &o, const OptTensor &lse, const OptStream &stream)
 {
     same_layout(q, {&k, &v});
-    return run_forward("attn_fwd", rect_params(q, k, scale, causal), q, k, v, false, o, lse, {}, false, stream);
+    return run_forward("attn_fwd", rect_params(q, k, scale, causal), q, k, v, false, o, lse, {}, Split::spare,
+                       stream);
 }
 
 Grads attn_bwd_(const OptStages &stages, const Tensor &q, const Tensor &k, const Tensor &v, const Tensor &o, const Tensor &g,
@@ -246,7 +264,8 @@ attn_rect_params_t gqa_params(const Tensor &q, const Tensor &k, double scale, bo
 std::tuple<Tensor, Tensor> attn_fwd_gqa_(const Tensor &q, const Tensor &k, const Tensor &v, double scale, bool causal,
                                          const OptTensor &o, const OptTensor &lse, const OptStream &stream)
 {
-    return run_forward("attn_fwd_gqa", gqa_params(q, k, scale, causal), q, k, v, false, o, lse, {}, false, stream);
+    return run_forward("attn_fwd_gqa", gqa_params(q, k, scale, causal), q, k, v, false, o, lse, {}, Split::spare,
+                       stream);
 }
 
 Grads attn_bwd_gqa_(const OptStages &stages, const Tensor &q, const Tensor &k, const Tensor &v, const Tensor &o,
@@ -263,7 +282,8 @@ std::tuple<Tensor, Tensor> attn_fwd_rect_(const Tensor &q, const Tensor &k, cons
                                           const OptTensor &o, const OptTensor &lse, const OptTensor &ws, bool split,
                                           const OptStream &stream)
 {
-    return run_forward("attn_fwd_rect", rect_params(q, k, scale, causal), q, k, v, true, o, lse, ws, split, stream);
+    return run_forward("attn_fwd_rect", rect_params(q, k, scale, causal), q, k, v, true, o, lse, ws,
+                       split ? Split::yes : Split::no, stream);
 }
 
 Grads attn_bwd_rect_(const Tensor &q, const Tensor &k, const Tensor &v, const Tensor &o, const Tensor &g,
@@ -297,7 +317,7 @@ std::tuple<Tensor, Tensor, OptTensor> attn_fwd_rope_(const Tensor &q, const Tens
     OptTensor qrot = qrot_in;
     if (qrot) same_layout(q, {&*qrot});
     else if (want_q_rot) qrot = empty_as(q);
-    const Tensor ws = forward_workspace(split ? attn_fwd_rope_workspace_bytes(&p) : 0, {}, split, q);
+    const Tensor ws = forward_workspace(split ? attn_fwd_rope_workspace_bytes(&p) : 0, {}, split ? Split::yes : Split::no, q);
     void *const Q = q.data_ptr(), *const K = k.data_ptr(), *const V = v.data_ptr(), *const O = o.data_ptr(),
                *const R = qrot ? qrot->data_ptr() : nullptr, *const W = data_of(ws), *const st = stream_ptr(stream);
     float *const L = static_cast<float *>(lse.data_ptr());
@@ -341,7 +361,7 @@ std::tuple<Tensor, Tensor, Tensor, Tensor, Tensor> fused_forward(const Tensor &q
                                                                  double scale, bool causal)
 {
     const Tensor q = dense(q_), k = dense(k_), v = like(k, dense(v_));
-    auto [o, lse] = run_forward("attn_fwd_rect", rect_params(q, k, scale, causal), q, k, v, true, {}, {}, {}, true, {});
+    auto [o, lse] = run_forward("attn_fwd_rect", rect_params(q, k, scale, causal), q, k, v, true, {}, {}, {}, Split::yes, {});
     return {q, k, v, o, lse};
 }
 
