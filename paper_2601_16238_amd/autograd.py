@@ -2,29 +2,13 @@
 stand where a framework's scaled-dot-product attention stands in a training step (the paper
 trains its ViT and miniGPT examples through its fused attention this way).
 
-Marshalling only: the forward calls attn_fwd_rect and keeps (Q, K, V, O, LSE) for the
-backward, which calls attn_bwd_rect.  No arithmetic happens here, and there is no fallback:
-tensors the kernels cannot take (wrong device or type) raise.
+Marshalling only, in native code (csrc/marshal.cpp): the forward calls attn_fwd_rect and keeps
+(Q, K, V, O, LSE) for the backward, which calls attn_bwd_rect.  No arithmetic happens here, and
+there is no fallback: tensors the kernels cannot take (wrong device or type) raise.
 """
 import torch
 
 from . import binding
-
-
-class _FusedAttention(torch.autograd.Function):
-    @staticmethod
-    def forward(ctx, q, k, v, scale, causal):
-        # (layouts the library does not take are copied to ones it does; what is saved is what ran)
-        q, k, v, O, LSE = binding.marshal().fused_forward(q, k, v, scale, causal)
-        ctx.save_for_backward(q, k, v, O, LSE)
-        ctx.scale, ctx.causal = scale, causal
-        return O
-
-    @staticmethod
-    def backward(ctx, dO):
-        q, k, v, O, LSE = ctx.saved_tensors
-        dQ, dK, dV = binding.marshal().fused_backward(q, k, v, O, LSE, dO, ctx.scale, ctx.causal)
-        return dQ, dK, dV, None, None
 
 
 def fused_attention(q, k, v, causal=False, scale=None):
@@ -32,6 +16,8 @@ def fused_attention(q, k, v, causal=False, scale=None):
     [B, Hkv, Sk, D] with Hkv dividing Hq; bf16 or fp16 tensors on the GPU; D a multiple of 8 up
     to 128.  scale defaults to D ** -0.5.  With causal=True query row i sees keys
     0 .. i + Sk - Sq (needs Sk >= Sq)."""
+    if torch._C._are_functorch_transforms_active():
+        raise RuntimeError("fused_attention has no rule for function transforms (vmap, grad, jvp, ...)")
     if scale is None:
         scale = float(q.shape[-1]) ** -0.5
-    return _FusedAttention.apply(q, k, v, float(scale), bool(causal))
+    return binding.marshal().fused_attention(q, k, v, float(scale), bool(causal))
