@@ -816,7 +816,8 @@ static bool four_wave_main(const FwdArgs &a)
 // but still take part in the staging): the one- and two-wave forms are only built for D = 64,
 // and short problems at D = 128 go to the kernel of attn_fwd_wide.hip unless the rotary
 // embedding is fused into the call.
-static int fwd_waves_for(int S, int D, int BH, bool causal)
+// split_keys: the keys of a launch that may be split, else 0.
+static int fwd_waves_for(int S, int D, int BH, bool causal, int split_keys)
 {
     const int blocks32 = (S + 31) / 32;
     // D = 64 under a causal mask with fewer than four 256-row work-groups per compute unit:
@@ -825,6 +826,14 @@ static int fwd_waves_for(int S, int D, int BH, bool causal)
     // so without a mask (+5 %), at D = 128 (+4..33 % on mid-size shapes) or on large problems.
     if (blocks32 >= 8 && D == 64 && causal && (int64_t)BH * ((S + 255) / 256) < 1024) return 4;
     if (blocks32 >= 8) return 8;
+    // Five to seven blocks at D = 128, where a work-group fills a unit whatever its waves: two work-groups of
+    // four waves per head stage K and V twice and half fill the second, one of eight has the pipelined main
+    // loop.  Eight where the heads' pairs do not fit the units at once, or the split of long keys makes as many
+    // of them; us, four -> eight: 140 heads of 150 rows on 998 keys 53 -> 33, 176 of 154 causal 18 -> 13, 224 of
+    // 215 on 3497 causal 156 -> 102, 64 of 190 on 3243 causal 49 -> 40, 120 of 179 on 5326 D = 96 93 -> 75; with fewer
+    // four waves are quicker (100 of 148 causal 10 | 13, 32 of 132 on 1776 23 | 25).  At D = 64, where two or
+    // three of the smaller ones share a unit, eight take 1.1 times as long on average.
+    if (D == 128 && blocks32 >= 5 && (BH > 128 || (int64_t)BH * split_keys >= 131072)) return 8;
     // Three 32-row blocks also take four waves; the fourth has no rows and only stages K and V.
     // Measured at B=128 H=6 S=65: 13.6 -> 10.4 us, S=96: 15.4 -> 12.5 us.  The three-wave
     // kernel needs 177 registers at D = 64 (two waves per SIMD, two work-groups per compute
@@ -838,7 +847,7 @@ static int fwd_waves_for(int S, int D, int BH, bool causal)
 template <int D, int U = D>
 static int launch_fwd_d(FwdArgs a, bool causal, hipStream_t st)
 {
-    const int nw = fwd_waves_for(a.S, D, a.BH, causal);
+    const int nw = fwd_waves_for(a.S, D, a.BH, causal, a.nsplit > 1 ? a.Sk : 0);
     a.nqt = (a.S + nw * 32 - 1) / (nw * 32);
     if (nw == 8) return launch_fwd_nw<D, U, 8, true>(a, causal, st);
     if constexpr (D < 128) {
@@ -941,7 +950,7 @@ int fwd_split_plan(int BH, int S, int Sk, int D, bool causal, bool packed, int *
 {
     const bool wide = streams(S, D, packed);
     // (rows per work-group: 128 in the streaming kernel)
-    const int nw = D > 128 ? 4 : fwd_waves_for(S, D, BH, causal), tile_rows = wide ? 128 : nw * 32;
+    const int nw = D > 128 ? 4 : fwd_waves_for(S, D, BH, causal, Sk), tile_rows = wide ? 128 : nw * 32;
     const int64_t wgs = (int64_t)BH * ((S + tile_rows - 1) / tile_rows);
     const int64_t target = 256;
     const int tiles = (Sk + 63) / 64;

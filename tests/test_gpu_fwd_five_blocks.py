@@ -1,0 +1,26 @@
+"""The forward at D = 128 with 129 .. 224 rows a head, in one eight-wave work-group a head, against the fp64
+oracle: first and last of its row blocks, ragged keys, padded columns, split and whole, both masks."""
+import pytest
+import torch
+
+import oracle
+import paper_2601_16238_amd as attn
+from paper_2601_16238_amd import workloads as wl
+from parity_util import check_bf16, to_dev, to_f64
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("Hq,Hkv,Sq,Sk,D,causal", [(132, 132, 129, 129, 128, True), (130, 65, 224, 225, 96, False),
+                                                   (136, 17, 161, 700, 128, True), (48, 12, 193, 2800, 128, True),
+                                                   (44, 44, 150, 3001, 80, False)])
+def test_five_to_seven_row_blocks(Hq, Hkv, Sq, Sk, D, causal):
+    print("case five blocks", Hq, Hkv, Sq, Sk, D, causal, flush=True)
+    x = wl.random_rect_inputs(1, Hq, Hkv, Sq, Sk, D, seed=7100 + Sq)
+    Q, K, V = (to_dev(x[k]) for k in ("Q", "K", "V"))
+    Oref, Lref = oracle.attn_fwd(x["Q"], x["K"], x["V"], x["scale"], causal)
+    for split in (True, False):
+        O, LSE = attn.attn_fwd_rect(Q, K, V, x["scale"], causal, O=torch.full_like(Q, float("nan")), split=split)
+        torch.cuda.synchronize()
+        check_bf16("O split=%s" % split, to_f64(O), Oref)
+        assert abs(to_f64(LSE) - Lref).max() <= 1e-5
