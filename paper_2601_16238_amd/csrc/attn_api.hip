@@ -241,8 +241,9 @@ static int fwd_impl(const void *Q, const void *K, const void *V, void *O, float 
         if (!aligned(workspace, kWsAlign)) return ATTN_ERR_WORKSPACE;
         nsplit = plan(128);
         if (nsplit > 1 && workspace_bytes < round_ws(nsplit * fwd_part_bytes(p))) {
-            if (workspace_bytes < std::min(fwd_split_bytes(p, rope != nullptr, attn::SplitRule::longest),
-                                           fwd_split_bytes(p, rope != nullptr, attn::SplitRule::one_per_unit)))
+            if (workspace_bytes < std::min({fwd_split_bytes(p, rope != nullptr, attn::SplitRule::longest),
+                                            fwd_split_bytes(p, rope != nullptr, attn::SplitRule::one_per_unit),
+                                            fwd_split_bytes(p, rope != nullptr, attn::SplitRule::four_waves)}))
                 return ATTN_ERR_WORKSPACE;
             nsplit = plan((int)(workspace_bytes / fwd_part_bytes(p)));
         }

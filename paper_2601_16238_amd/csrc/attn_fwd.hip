@@ -945,17 +945,19 @@ static int fwd_splits(const SplitCost &c, int64_t wgs, int tiles, int S, float p
 // memory, not by its longest work-group: at least one work-group per compute unit (256 with long key
 // ranges beat 512 or 1024 shorter ones there, 0.060 ms against 0.071 and 0.086 on the decode shape),
 // every split at least four tiles.  `rule`: the plan, or the smaller workspaces that are accepted: that
-// rule for any number of rows, or the estimate that dQ uses.
+// rule for any number of rows, the estimate that dQ uses, or the plan for work-groups of four waves.
 int fwd_split_plan(int BH, int S, int Sk, int D, bool causal, bool packed, int *kps, int most, SplitRule rule)
 {
     const bool wide = streams(S, D, packed);
     // (rows per work-group: 128 in the streaming kernel)
-    const int nw = D > 128 ? 4 : fwd_waves_for(S, D, BH, causal, Sk), tile_rows = wide ? 128 : nw * 32;
+    // (the smaller workspaces of heads of five to seven blocks at D = 128: those of four waves)
+    const int nw = D > 128 || (rule != SplitRule::plan && D == 128 && S <= 224) ? 4 : fwd_waves_for(S, D, BH, causal, Sk);
+    const int tile_rows = wide ? 128 : nw * 32;
     const int64_t wgs = (int64_t)BH * ((S + tile_rows - 1) / tile_rows);
     const int64_t target = 256;
     const int tiles = (Sk + 63) / 64;
     int nsplit = 1;
-    if (S > 32 && rule == SplitRule::plan) {
+    if (S > 32 && (rule == SplitRule::plan || rule == SplitRule::four_waves)) {
         const SplitCost cost = D > 128           ? SplitCost{8.2f, 9.8f, 1.70f, 1.70f, 1}
                                : D > 64          ? (wide ? SplitCost{4.6f, 1.7f, 1.25f, 1.06f, 2}
                                                          : SplitCost{6.0f, 1.0f, 1.45f, 1.27f, 1})

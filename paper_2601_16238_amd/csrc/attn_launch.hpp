@@ -116,8 +116,8 @@ int launch_fwd_wide(const FwdArgsT<__bf16> &a, int D, bool causal, hipStream_t s
 int launch_fwd_wide(const FwdArgsT<_Float16> &a, int D, bool causal, hipStream_t st);
 // Number of key splits the forward would use for this problem (1: none; at most `most`), and the keys per
 // split; packed: rows packed as pack_sq says.  A pure host function of the shape.  SplitRule: the plan, and
-// two rules whose smaller workspaces are accepted as well (see attn_fwd.hip).
-enum class SplitRule { plan, longest, one_per_unit };
+// three rules whose smaller workspaces are accepted as well (see attn_fwd.hip).
+enum class SplitRule { plan, longest, one_per_unit, four_waves };
 int fwd_split_plan(int BH, int S, int Sk, int D, bool causal, bool packed, int *kps, int most = 128,
                    SplitRule rule = SplitRule::plan);
 // Number of splits over `tiles` key tiles (`average` over the query rows) with which a launch of `wgs`

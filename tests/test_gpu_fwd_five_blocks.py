@@ -24,3 +24,23 @@ def test_five_to_seven_row_blocks(Hq, Hkv, Sq, Sk, D, causal):
         torch.cuda.synchronize()
         check_bf16("O split=%s" % split, to_f64(O), Oref)
         assert abs(to_f64(LSE) - Lref).max() <= 1e-5
+
+
+def test_the_workspace_of_four_wave_work_groups_is_accepted():
+    """Three splits' partial results, which two work-groups of four waves a head take where one of eight takes seven."""
+    H, Sq, Sk, D = 34, 184, 4957, 128
+    print("case five blocks, smaller workspace", flush=True)
+    part = H * Sq * (D + 1) * 4
+    need = (3 * part + 255) // 256 * 256
+    assert attn.attn_fwd_rect_workspace_bytes(1, H, H, Sq, Sk, D, True) > need
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    Q = torch.randn((1, H, Sq, D), generator=g, device="cuda").bfloat16()
+    K, V = (torch.randn((1, H, Sk, D), generator=g, device="cuda").bfloat16() for _ in range(2))
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    O, LSE = attn.attn_fwd_rect(Q, K, V, D ** -0.5, True, workspace=ws)
+    O1, LSE1 = attn.attn_fwd_rect(Q, K, V, D ** -0.5, True, split=False)
+    torch.cuda.synchronize()
+    assert (LSE - LSE1).abs().max() <= 2e-5   # (each within 1e-5 of the exact one)
+    # two roundings of one result, each within the rounding of P of the exact one
+    assert (O.double() - O1.double()).norm() <= 5e-3 * O1.double().norm()
