@@ -11,6 +11,22 @@ import torch
 from . import binding
 
 
+class _RecordedAttention(torch.autograd.Function):
+    """The same two calls as a Python function, which a tracer records as one operation and calls again.
+    (It would record of the native node only the allocations, and replay those without the kernels.)"""
+
+    @staticmethod
+    def forward(ctx, q, k, v, scale, causal):
+        q, k, v, O, LSE = binding.marshal().fused_forward(q, k, v, scale, causal)
+        ctx.save_for_backward(q, k, v, O, LSE)
+        ctx.scale, ctx.causal = scale, causal
+        return O
+
+    @staticmethod
+    def backward(ctx, dO):
+        return (*binding.marshal().fused_backward(*ctx.saved_tensors, dO, ctx.scale, ctx.causal), None, None)
+
+
 def fused_attention(q, k, v, causal=False, scale=None):
     """softmax(scale * q k^T [+ causal mask]) v with gradients.  q: [B, Hq, Sq, D]; k, v:
     [B, Hkv, Sk, D] with Hkv dividing Hq; bf16 or fp16 tensors on the GPU; D a multiple of 8 up
@@ -20,4 +36,6 @@ def fused_attention(q, k, v, causal=False, scale=None):
         raise RuntimeError("fused_attention has no rule for function transforms (vmap, grad, jvp, ...)")
     if scale is None:
         scale = float(q.shape[-1]) ** -0.5
+    if torch.jit.is_tracing():
+        return _RecordedAttention.apply(q, k, v, float(scale), bool(causal))
     return binding.marshal().fused_attention(q, k, v, float(scale), bool(causal))

@@ -360,16 +360,30 @@ Tensor like(const Tensor &ref, const Tensor &t)
     return out;
 }
 
+std::tuple<Tensor, Tensor, Tensor, Tensor, Tensor> fused_forward(const Tensor &q_, const Tensor &k_, const Tensor &v_,
+                                                                 double scale, bool causal)
+{
+    // (layouts the library does not take are copied to ones it does; what is saved is what ran)
+    const Tensor q = dense(q_), k = dense(k_), v = like(k, dense(v_));
+    auto [o, lse] = run_forward("attn_fwd_rect", rect_params(q, k, scale, causal), q, k, v, true, {}, {}, {},
+                                Split::yes, {});
+    return {q, k, v, o, lse};
+}
+
+Grads fused_backward(const Tensor &q, const Tensor &k, const Tensor &v, const Tensor &o, const Tensor &lse,
+                     const Tensor &g, double scale, bool causal)
+{
+    return run_backward("attn_bwd_rect", rect_params(q, k, scale, causal), q, k, v, o, like(o, g), lse, true, {}, {},
+                        {}, {}, {});
+}
+
 // A native node: the backward runs in the engine's thread without the interpreter (us per step, Python
 // function -> this: 128 x 6 heads of 65 rows 77 -> 61, 8 x 8 of 1024 rows causal 79 -> 69, D = 64).
 struct FusedAttention : torch::autograd::Function<FusedAttention> {
     static Tensor forward(torch::autograd::AutogradContext *ctx, const Tensor &q_, const Tensor &k_, const Tensor &v_,
                           double scale, bool causal)
     {
-        // (layouts the library does not take are copied to ones it does; what is saved is what ran)
-        const Tensor q = dense(q_), k = dense(k_), v = like(k, dense(v_));
-        auto [o, lse] = run_forward("attn_fwd_rect", rect_params(q, k, scale, causal), q, k, v, true, {}, {}, {},
-                                    Split::yes, {});
+        auto [q, k, v, o, lse] = fused_forward(q_, k_, v_, scale, causal);
         ctx->save_for_backward({q, k, v, o, lse});
         ctx->saved_data["scale"] = scale;
         ctx->saved_data["causal"] = causal;
@@ -380,12 +394,10 @@ struct FusedAttention : torch::autograd::Function<FusedAttention> {
                                                    torch::autograd::variable_list grads)
     {
         const torch::autograd::variable_list saved = ctx->get_saved_variables();
-        const Tensor &q = saved[0], &k = saved[1], &v = saved[2], &o = saved[3], &lse = saved[4];
         const double scale = ctx->saved_data["scale"].toDouble();
         const bool causal = ctx->saved_data["causal"].toBool();
         try {
-            auto [dq, dk, dv] = run_backward("attn_bwd_rect", rect_params(q, k, scale, causal), q, k, v, o,
-                                             like(o, grads[0]), lse, true, {}, {}, {}, {}, {});
+            auto [dq, dk, dv] = fused_backward(saved[0], saved[1], saved[2], saved[3], saved[4], grads[0], scale, causal);
             return {dq, dk, dv, Tensor(), Tensor()};
         } catch (py::error_already_set &e) {  // to the form that the engine carries over to its caller
             py::gil_scoped_acquire gil;
@@ -526,6 +538,8 @@ PYBIND11_MODULE(_marshal, m)
     m.def("attn_fwd_rope", &attn_fwd_rope_);
     m.def("attn_bwd_rope", &attn_bwd_rope_);
     m.def("fused_attention", &fused_attention);
+    m.def("fused_forward", &fused_forward);
+    m.def("fused_backward", &fused_backward);
     m.def("rmsnorm_fwd", &rmsnorm_fwd);
     m.def("layernorm_fwd", &layernorm_fwd);
     m.def("layernorm_bwd", &layernorm_bwd);

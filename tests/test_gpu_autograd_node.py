@@ -57,6 +57,22 @@ def test_errors_keep_their_type():
     assert q.grad is not None
 
 
+@pytest.mark.parametrize("grad", [True, False])
+def test_a_traced_call_runs_the_kernels_on_other_inputs(grad):
+    print("case traced", grad, flush=True)
+    example = [(t * 0.5).detach().requires_grad_(grad) for t in inputs(False)]
+    f = torch.jit.trace(lambda q, k, v: attn.fused_attention(q, k, v, causal=True), example, check_trace=False)
+    x = inputs(grad)
+    want = attn.fused_attention(*x, causal=True)
+    for _ in range(2):
+        got = f(*x)
+        assert torch.equal(got, want) and got.requires_grad == grad
+        if grad:
+            pairs = zip(torch.autograd.grad(got, x, want.detach()),
+                        torch.autograd.grad(want, x, want.detach(), retain_graph=True))
+            assert all(torch.equal(a, b) for a, b in pairs)
+
+
 def test_threads_and_streams():
     q, k, v = inputs(False)
     want = None
