@@ -411,6 +411,8 @@ struct FusedAttention : torch::autograd::Function<FusedAttention> {
 
 Tensor fused_attention(const Tensor &q, const Tensor &k, const Tensor &v, double scale, bool causal)
 {
+    for (const Tensor *t : {&q, &k, &v})
+        TORCH_CHECK_NOT_IMPLEMENTED(!t->_fw_grad(0).defined(), "fused_attention has no rule for forward mode");
     return FusedAttention::apply(q, k, v, scale, causal);
 }
 

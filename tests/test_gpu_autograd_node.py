@@ -33,7 +33,7 @@ def test_graph_rules():
     with torch.no_grad():
         assert not attn.fused_attention(q, k, v).requires_grad
     assert not attn.fused_attention(*inputs(False)).requires_grad
-    with pytest.raises(RuntimeError):  # forward mode
+    with pytest.raises(NotImplementedError):  # forward mode
         with torch.autograd.forward_ad.dual_level():
             attn.fused_attention(torch.autograd.forward_ad.make_dual(q.detach(), q.detach()), k, v)
     with pytest.raises(RuntimeError):
