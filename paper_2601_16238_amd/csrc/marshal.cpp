@@ -396,15 +396,22 @@ struct FusedAttention : torch::autograd::Function<FusedAttention> {
         const torch::autograd::variable_list saved = ctx->get_saved_variables();
         const double scale = ctx->saved_data["scale"].toDouble();
         const bool causal = ctx->saved_data["causal"].toBool();
+        // (Python's exceptions to the form in which the engine carries them over to its caller; it would
+        // make a RuntimeError of any other)
+        auto carried = [](const auto &set_error) {
+            py::gil_scoped_acquire gil;
+            set_error();
+            python_error err;
+            err.persist();
+            return err;
+        };
         try {
             auto [dq, dk, dv] = fused_backward(saved[0], saved[1], saved[2], saved[3], saved[4], grads[0], scale, causal);
             return {dq, dk, dv, Tensor(), Tensor()};
-        } catch (py::error_already_set &e) {  // to the form that the engine carries over to its caller
-            py::gil_scoped_acquire gil;
-            e.restore();
-            python_error err;
-            err.persist();
-            throw err;
+        } catch (py::error_already_set &e) {
+            throw carried([&] { e.restore(); });
+        } catch (const py::builtin_exception &e) {
+            throw carried([&] { e.set_error(); });
         }
     }
 };

@@ -52,6 +52,12 @@ def test_errors_keep_their_type():
         bad = attn.fused_attention(q, k, v)
     with pytest.raises(KeyError):
         bad.sum().backward()
+    # tensors that the kernels cannot take: the exception of a direct call with them
+    for changed in (lambda t: t.float(), lambda t: t.cpu()):
+        with torch.autograd.graph.saved_tensors_hooks(lambda t: t, changed):
+            bad = attn.fused_attention(q, k, v)
+        with pytest.raises(ValueError, match="on the GPU"):
+            bad.sum().backward()
     o.sum().backward()
     torch.cuda.synchronize()
     assert q.grad is not None
