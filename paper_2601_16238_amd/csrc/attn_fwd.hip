@@ -929,12 +929,16 @@ static int fwd_splits(const SplitCost &c, int64_t wgs, int tiles, int S, float p
         return std::max(t, spread + busy * c.start / 256) + merge;
     };
     int best = 1;
-    // Causal rows beyond those of the fit: the heavy work-groups of a split that nearly fills the chip run
-    // longer than estimated.  us, unsplit -> two splits: 9 heads of 8690 rows D = 96 182 -> 204, 5 of 5555
-    // D = 256 148 -> 166, 6 of 9829 D = 80 185 -> 197; with fewer work-groups it pays, 6 of 5161 (126) 97 -> 73.
-    if (!equal && S > 4096 && wgs > 160) return 1;
+    // Causal rows beyond those of the fit, one work-group per unit: two splits whose heavy work-groups nearly fill
+    // the chip run longer than estimated.  us, unsplit | two | three: 13 heads of 4335 rows D = 96 (221 work-groups)
+    // 84 | 108 | 97, 9 of 6061 D = 128 (216) 142 | 172 | 143, 5 of 5535 D = 256 (220) 144 | 161 | 147.  Over 340
+    // problems of 120 .. 512 work-groups at D = 80 .. 128 the plan without two splits here takes 0.977 of the time
+    // that it takes with them, over 200 above D = 128 0.989, none more than 1.12.  With fewer two splits pay, 5 of
+    // 9329 D = 96 (185) 172 | 117, and with more, where the unsplit launch takes a second round: 8 of 8394 D = 128
+    // (264) 201 | 175; three pay for longer, 4 of 13775 D = 128 (216) 309 | 304 | 259.
+    const bool no_two = !equal && S > 4096 && c.per_cu == 1 && wgs > 188 && wgs <= 256;
     float least = 0.97f * estimate(1);
-    for (int n = 2; n <= most && 4 * n <= tiles && n * wgs <= 1024; ++n) {
+    for (int n = no_two ? 3 : 2; n <= most && 4 * n <= tiles && n * wgs <= 1024; ++n) {
         const float t = estimate(n);
         if (t < least) { least = t; best = n; }
     }

@@ -39,3 +39,11 @@ def test_dq_is_split_where_the_unsplit_launch_takes_two_rounds(H, Sq, Sk, nsplit
     units, of which every second waits for a whole other one; measured 5 .. 16 % faster split."""
     part = H * Sq * 128 * 4
     assert (attn.attn_bwd_rect_workspace_bytes(1, H, H, Sq, Sk, 128) - 8 * H * Sq) // part == nsplit
+
+
+@pytest.mark.parametrize("H,S,D,nsplit", [(3, 7903, 64, 4), (5, 4667, 64, 4), (5, 5787, 64, 4), (5, 9064, 128, 3), (5, 10000, 128, 3),
+                                          (4, 13775, 128, 3)])
+def test_long_causal_heads_are_split_as_measured(H, S, D, nsplit):
+    """160 .. 240 work-groups of more than 4096 rows: 1.1 .. 1.6 times as long unsplit."""
+    part = H * S * (D + 1) * 4
+    assert attn.attn_fwd_rect_workspace_bytes(1, H, H, S, S, D, True) // part == nsplit
