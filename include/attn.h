@@ -100,8 +100,10 @@ size_t attn_bwd_workspace_bytes(const attn_params_t *p);
  *   workspace  : device scratch of at least attn_bwd_workspace_bytes(p) bytes, 256-byte
  *                aligned; contents undefined on entry and on exit (the library initialises
  *                everything it reads)
- * Enqueues two kernels on hip_stream: dQ (which also forms the row statistics delta and
- * rescaled LSE and stores them in the workspace), then dK/dV (which reads them).
+ * Enqueues, in a workspace of that size, dQ (which also forms the row statistics delta and rescaled
+ * LSE and stores them in the workspace), then dK/dV (which reads them), each followed by a merge
+ * where it is split; short heads take one kernel.  In a larger workspace a kernel for the statistics
+ * can come first, see attn_bwd_rect_best_workspace_bytes.
  */
 int attn_bwd(const void *Q, const void *K, const void *V, const void *O, const void *dO,
              const float *LSE, void *dQ, void *dK, void *dV,
@@ -229,8 +231,9 @@ size_t attn_bwd_rect_workspace_bytes(const attn_rect_params_t *p);
  * takes place in any workspace larger than that with room for it, for all heads or a part of them at a time, and
  * enqueues a kernel for the row statistics, then dK/dV and dQ for each part.  At most 4.5 GiB are
  * asked for it.  Calls of few work-groups run dK/dV and dQ side by side instead, in one kernel after the
- * statistics and before a merge, also in any workspace larger than that.  Pure host function; 0 for an
- * invalid problem.
+ * statistics and before a merge, also in any workspace larger than that.  Each form adds in an order of its
+ * own, so results depend on the workspace size in their last bits; for one size they are deterministic.
+ * Pure host function; 0 for an invalid problem.
  */
 size_t attn_bwd_rect_best_workspace_bytes(const attn_rect_params_t *p);
 

@@ -30,8 +30,8 @@ class _RecordedAttention(torch.autograd.Function):
 def fused_attention(q, k, v, causal=False, scale=None):
     """softmax(scale * q k^T [+ causal mask]) v with gradients.  q: [B, Hq, Sq, D]; k, v:
     [B, Hkv, Sk, D] with Hkv dividing Hq; bf16 or fp16 tensors on the GPU; D a multiple of 8 up
-    to 128.  scale defaults to D ** -0.5.  With causal=True query row i sees keys
-    0 .. i + Sk - Sq (needs Sk >= Sq)."""
+    to 256.  scale defaults to D ** -0.5.  With causal=True query row i sees keys
+    0 .. i + Sk - Sq (needs Sk >= Sq).  The backward's workspace is that of attn_bwd without one."""
     if torch._C._are_functorch_transforms_active():
         raise RuntimeError("fused_attention has no rule for function transforms (vmap, grad, jvp, ...)")
     if scale is None:

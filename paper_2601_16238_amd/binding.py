@@ -281,7 +281,7 @@ def _call(entry, stream, *args):
 
 def attn_fwd(Q, K, V, scale, causal, O=None, LSE=None, stream=None):
     """O, LSE = attention forward.  Q,K,V: bf16 device tensors [B,H,S,D] with equal strides.  Few heads of
-    more than 768 rows are split over the keys (see attn_fwd_rect), if the device has the memory.
+    more than 768 rows are split over the keys (see attn_fwd_rect), if there is memory to spare (see attn_bwd).
     Enqueues on `stream` (default: torch's current stream); does not synchronise."""
     return _call(marshal().attn_fwd, stream, Q, K, V, float(scale), bool(causal), O, LSE)
 
@@ -295,7 +295,12 @@ def attn_bwd(Q, K, V, O, dO, LSE, scale, causal, dQ=None, dK=None, dV=None, work
              stream=None, stages=None):
     """dQ, dK, dV = attention backward for upstream gradient dO (all bf16, same strides).
     `stages` (profiling aid) restricts the call to a subset of its kernels through
-    attn_bwd_stages; None calls attn_bwd."""
+    attn_bwd_stages; None calls attn_bwd.
+    Without `workspace` every backward call allocates one of the best size (see
+    attn_bwd_rect_best_workspace_bytes) where there is memory to spare: up to 64 MiB always, more if the allocator
+    has it idle or if it is at most an eighth of what the process may still get; else one of the plain size.  The
+    two forms add the same products in different orders, so that the last bits of a call without `workspace` can
+    depend on the free memory; under torch.use_deterministic_algorithms it always takes the plain size."""
     return _call(marshal().attn_bwd, stream, None if stages is None else int(stages), Q, K, V, O, dO, LSE,
                  float(scale), bool(causal), dQ, dK, dV, workspace)
 
@@ -315,7 +320,7 @@ def make_gqa_params(B, Hq, Hkv, S, D, scale, causal, q_strides=None, kv_strides=
 
 
 def attn_fwd_gqa(Q, K, V, scale, causal, O=None, LSE=None, stream=None):
-    """O [B,Hq,S,D], LSE [B,Hq,S] = grouped-query attention forward; K, V: [B,Hkv,S,D]."""
+    """O [B,Hq,S,D], LSE [B,Hq,S] = grouped-query attention forward; K, V: [B,Hkv,S,D].  Split as attn_fwd."""
     return _call(marshal().attn_fwd_gqa, stream, Q, K, V, float(scale), bool(causal), O, LSE)
 
 
@@ -379,8 +384,8 @@ def attn_bwd_rect_workspace_bytes(B, Hq, Hkv, Sq, Sk, D):
 
 
 def attn_bwd_rect_best_workspace_bytes(B, Hq, Hkv, Sq, Sk, D, causal):
-    """Bytes of the workspace with which the backward is fastest; what a call without one allocates, if
-    the device has the memory."""
+    """Bytes of the workspace with which the backward is fastest; what a call without one allocates, if there is
+    memory to spare (see attn_bwd)."""
     p = make_rect_params(B, Hq, Hkv, Sq, Sk, D, 1.0, causal)
     return int(lib().attn_bwd_rect_best_workspace_bytes(ctypes.byref(p)))
 

@@ -6,7 +6,11 @@
 // times slower.
 #include <torch/extension.h>
 
+#include <ATen/Context.h>
+#include <c10/core/DeviceGuard.h>
+#include <c10/hip/HIPCachingAllocator.h>
 #include <c10/hip/HIPStream.h>
+#include <hip/hip_runtime_api.h>
 #include <torch/csrc/Exceptions.h>
 
 #include <algorithm>
@@ -124,8 +128,38 @@ void forward_outputs(const Tensor &q, const Tensor &k, const Tensor &v, bool f16
     else lse = at::empty(q.sizes().slice(0, 3), q.options().dtype(at::kFloat));
 }
 
+// Whether a call takes `bytes` more than it needs for the sake of speed.  Not under
+// torch.use_deterministic_algorithms: the result would depend on the free memory through the order of its sums.
+// Up to 64 MiB always; more only if the allocator has a block of that size idle or if it is at most an eighth of
+// what the process may still get, so that no allocation fails for it (before an allocation fails, the allocator waits
+// for the device and gives back everything it holds).  Under 1 us, 6 where the device is asked.
+constexpr size_t kFreely = (size_t)64 << 20, kShare = 8;
+bool to_spare(size_t bytes, const Tensor &x)
+{
+    if (at::globalContext().deterministicAlgorithms()) return false;
+    if (bytes <= kFreely) return true;
+    namespace allocator = c10::hip::HIPCachingAllocator;
+    const c10::DeviceIndex device = x.get_device();
+    try {
+        size_t idle = 1;  // (not 0, for which it would ask the device)
+        allocator::cacheInfo(device, &idle);
+        if (idle >= bytes) return true;
+        const c10::DeviceGuard guard(x.device());
+        size_t left = 0, total = 0;
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // (the question is no part of a captured graph)
+        if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return false;
+        const hipError_t rc = hipMemGetInfo(&left, &total);
+        if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess || rc != hipSuccess) return false;
+        const double may = allocator::getMemoryFraction(device) * (double)total;
+        const double held = allocator::getDeviceStats(device).reserved_bytes[0].current;
+        return bytes <= std::min((double)left, may - held) / kShare;
+    } catch (const c10::Error &) {  // (an allocator that does not answer these questions)
+        return false;
+    }
+}
+
 // What a forward call does about its split over the keys.  spare: the square calls, whose C entry points have
-// no workspace; they take one (of the rectangular call) where the device has the memory for it.
+// no workspace; they take one (of the rectangular call) where there is memory to spare.
 enum class Split { no, yes, spare };
 
 // The workspace of that split: the caller's, else one of the planned size.
@@ -139,7 +173,7 @@ Tensor forward_workspace(size_t need, const OptTensor &given, Split split, const
 {
     if (split == Split::no) return Tensor();
     if (given) return *given;
-    if (!need) return Tensor();
+    if (!need || (split == Split::spare && !to_spare(need, q))) return Tensor();
     try {
         return bytes_on(need, q);
     } catch (const c10::OutOfMemoryError &) {
@@ -181,18 +215,17 @@ std::tuple<Tensor, Tensor> run_forward(const char *where, const attn_rect_params
 
 using Grads = std::tuple<Tensor, Tensor, Tensor>;
 
-// A workspace with room for dS (whole backwards), or without it where the device has no memory for that.
+// The workspace of the fastest form (whole backwards), or the plain one where there is no memory to spare for that.
 Tensor backward_workspace(const attn_rect_params_t &p, const Tensor &q, bool whole)
 {
-    if (whole) {
-        const size_t best = attn_bwd_rect_best_workspace_bytes(&p);
+    const size_t plain = attn_bwd_rect_workspace_bytes(&p), best = whole ? attn_bwd_rect_best_workspace_bytes(&p) : plain;
+    if (best > plain && to_spare(best, q)) {
         try {
             return bytes_on(best, q);
         } catch (const c10::OutOfMemoryError &) {
-            if (best == attn_bwd_rect_workspace_bytes(&p)) throw;
         }
     }
-    return bytes_on(attn_bwd_rect_workspace_bytes(&p), q);
+    return bytes_on(plain, q);
 }
 
 // cos, sin: the rotary form; stages: restricted to those stages (square problems)
