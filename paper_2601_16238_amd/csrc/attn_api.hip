@@ -303,11 +303,11 @@ static int bwd_impl(const void *Q, const void *K, const void *V, const void *O, 
                                                  p->causal != 0, &dkdv_chunk,
                                                  (int64_t)std::min<size_t>(512, room / dkdv_chunk_bytes(p)));
     const size_t dkdv_bytes = dkdv_chunk ? round_ws((size_t)p->B * p->Hkv * dkdv_items * dkdv_chunk_bytes(p)) : 0;
-    // (a workspace of the size that attn_bwd_rect_workspace_bytes asks for, or less, keeps the form without dS)
-    int ds_heads = stages == 7u ? ds_heads_in(p, room - dkdv_bytes) : 0;
-    if (ds_heads && workspace_bytes <= attn_bwd_rect_workspace_bytes(p)) ds_heads = 0;
-    attn::PairPlan pair = {};  // (nor with it the two kernels side by side)
-    if (stages == 7u && workspace_bytes > attn_bwd_rect_workspace_bytes(p)) pair = pair_in(p, room);
+    // (a workspace of the size that attn_bwd_rect_workspace_bytes asks for, or less, keeps the form without dS,
+    // and with one kernel after the other)
+    const bool more = stages == 7u && workspace_bytes > attn_bwd_rect_workspace_bytes(p);
+    const int ds_heads = more ? ds_heads_in(p, room - dkdv_bytes) : 0;
+    const attn::PairPlan pair = more ? pair_in(p, room) : attn::PairPlan{};
     attn::BwdArgsT<E> a;
     a.Q = static_cast<const E *>(Q);
     a.K = static_cast<const E *>(K);

@@ -1725,6 +1725,36 @@ int dq_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps, int most)
     return nsplit;
 }
 
+// Sum of floor((a i + b) / m) for i = 0 .. n - 1 (all of them >= 0, m > 0): the whole parts of the quotients at
+// once, and of what is left, below the line, the lattice points counted the other way round.
+static int64_t floor_sum(int64_t n, int64_t m, int64_t a, int64_t b)
+{
+    if (n <= 0) return 0;
+    const int64_t whole = n * (n - 1) / 2 * (a / m) + n * (b / m);
+    a %= m; b %= m;
+    const int64_t top = (a * (n - 1) + b) / m;  // the last term
+    // (value j is reached from i = ceil((m j - b) / a) on)
+    return top ? whole + top * n - floor_sum(top, a, m, m - b + a - 1) : whole;
+}
+
+// Chunks of at most L slots that the key blocks of a K/V head are cut into.  The plans try many L: a loop over the
+// blocks for each took up to 48 us (one head of 471 rows on 16714 keys), this 1.
+struct BlockChunks {
+    int64_t flat, falling, longest, shortest, step;  // blocks with all slots, and with `step` fewer each to the last
+    BlockChunks(int n_block, int keys, int group, int S, int Sk, bool causal)
+        : longest(dkdv_slots(0, keys, group, S, Sk, causal)), shortest(dkdv_slots(n_block - 1, keys, group, S, Sk, causal)),
+          step((int64_t)group * (keys / 32))
+    {
+        // (causal: block kt starts at slot (kt * keys - (Sk - S)) / 32, keys being a multiple of 32)
+        flat = causal ? std::min<int64_t>(n_block, (Sk - S) / keys + 1) : n_block;
+        falling = n_block - flat;
+    }
+    int64_t of(int64_t L) const
+    {
+        return flat * ((longest + L - 1) / L) + floor_sum(falling, L, step, shortest + L - 1);
+    }
+};
+
 // Split the dK/dV kernel over the query slots when its work-groups (one per key block of a K/V head)
 // leave compute units idle: few K/V heads, e.g. grouped-query heads, whose one work-group per block
 // walks the slots of every query head of the group.  The slots of a key block are cut into chunks of
@@ -1749,16 +1779,11 @@ int dkdv_split_plan(int BHkv, int group, int S, int Sk, int D, bool causal, int 
     if ((int64_t)BHkv * n_block >= resident) return n_block;
     const int longest = dkdv_slots(0, keys, group, S, Sk, causal);
     if (longest < 48) return n_block;
-    int64_t slots = 0;
-    for (int kt = 0; kt < n_block; ++kt) slots += dkdv_slots(kt, keys, group, S, Sk, causal);
-    int64_t L = (slots * BHkv + resident - 1) / resident;
+    const BlockChunks head(n_block, keys, group, S, Sk, causal);
+    int64_t L = (head.of(1) * BHkv + resident - 1) / resident;
     if (L < 16) L = 16;
     for (; 4 * L <= 3 * (int64_t)longest; L += (L + 31) / 32) {
-        int64_t items = 0;
-        for (int kt = 0; kt < n_block; ++kt) {
-            const int64_t n = dkdv_slots(kt, keys, group, S, Sk, causal);
-            items += n ? (n + L - 1) / L : 1;
-        }
+        const int64_t items = head.of(L);
         if (items * BHkv <= std::min(resident, most)) {
             const int64_t chunks = items * BHkv;
             if (D == 64 && 0.65f * L * (chunks > 256 ? 1.7f : 1.0f) + 3.0f + 0.4e-6f * chunks * (2 * 128 * 64 * 4) >=
@@ -1812,20 +1837,14 @@ PairPlan pair_plan(int BHkv, int group, int S, int Sk, int D, bool causal, size_
     const int dq_rows = D > 128 ? 128 : 256, dq_keys = D > 128 ? 32 : 64, tiles = (Sk + dq_keys - 1) / dq_keys;
     const int64_t heads = (int64_t)BHkv * group, wgs = (int64_t)BHkv * n_block, dq_wgs = heads * ((S + dq_rows - 1) / dq_rows);
     if (wgs + dq_wgs > units) return best;
-    // all slots of a head, and the chunks of L slots that they make (causal: every block has fewer than the one before)
-    auto over_blocks = [&](auto &&f) {
-        int64_t sum = 0;
-        if (!causal) return (int64_t)n_block * f(std::max(1, dkdv_slots(0, keys, group, S, Sk, false)));
-        for (int kt = 0; kt < n_block; ++kt) sum += f(std::max(1, dkdv_slots(kt, keys, group, S, Sk, true)));
-        return sum;
-    };
+    const BlockChunks head(n_block, keys, group, S, Sk, causal);
     const size_t dq_bytes = (size_t)heads * S * D * 4, chunk_bytes = (size_t)2 * keys * D * 4;
     const PairCost c = D > 128  ? PairCost{11.0f, 0.87f, 11.0f, 1.10f, 3.0f, 0.35e-6f}
                        : D > 64 ? PairCost{9.1f, 0.67f, 9.5f, 1.65f, 3.7f, 0.34e-6f}
                                 : PairCost{7.9f, 0.57f, 8.0f, 1.03f, 3.1f, 0.43e-6f};
     best.items = n_block; best.dq_nsplit = 1; best.dq_kps = tiles * dq_keys;
-    const int longest = std::max(1, dkdv_slots(0, keys, group, S, Sk, causal));
-    const int64_t slots = BHkv * over_blocks([](int s) { return s; });
+    const int longest = (int)head.longest;
+    const int64_t slots = BHkv * head.of(1);
     float least = std::max(c.fixed + longest * c.slot, c.dq_fixed + tiles * c.dq_tile);
     for (int n = 1; n <= (D > 128 ? 1 : 16) && (n == 1 || 4 * n <= tiles) && n * dq_wgs < units; ++n) {
         const int per = (tiles + n - 1) / n;
@@ -1833,15 +1852,17 @@ PairPlan pair_plan(int BHkv, int group, int S, int Sk, int D, bool causal, size_
         const float dq_us = c.dq_fixed + per * c.dq_tile + c.merge;
         if (dq_us >= least) continue;
         const int64_t left = units - n * dq_wgs;
+        if (left < wgs) break;  // (not a chunk for every block)
         int L = (int)std::max<int64_t>((slots + left - 1) / left, std::min(8, longest));
         int64_t items = 0;
-        for (; L <= longest; L += (L + 15) / 16) {
-            items = BHkv * over_blocks([L](int s) { return (s + L - 1) / L; });
+        auto walk_us = [&] { return c.fixed + L * c.slot + c.merge; };
+        for (; L <= longest && walk_us() < least; L += (L + 15) / 16) {
+            items = BHkv * head.of(L);
             if (items <= left) break;
         }
-        if (L > longest) continue;
+        if (L > longest || walk_us() >= least) continue;
         const size_t part = (D > 128 ? 0 : (n * dq_bytes + 255) / 256 * 256) + items * chunk_bytes;
-        const float t = std::max(c.fixed + L * c.slot + c.merge, dq_us) + c.byte * part;
+        const float t = std::max(walk_us(), dq_us) + c.byte * part;
         if (part > room || t >= least) continue;
         least = t;
         best.dq_nsplit = n; best.dq_kps = per * dq_keys;

@@ -1,5 +1,6 @@
 """Workspace sizes of the split plans (host only): what is asked for with one mask serves the other."""
 import ctypes
+import time
 
 import pytest
 
@@ -47,3 +48,36 @@ def test_long_causal_heads_are_split_as_measured(H, S, D, nsplit):
     """160 .. 240 work-groups of more than 4096 rows: 1.1 .. 1.6 times as long unsplit."""
     part = H * S * (D + 1) * 4
     assert attn.attn_fwd_rect_workspace_bytes(1, H, H, S, S, D, True) // part == nsplit
+
+
+@pytest.mark.parametrize("Hq,Hkv,Sq,Sk,D", [(1, 1, 471, 16714, 64), (8, 1, 225, 19549, 128), (2, 1, 12560, 13659, 256)])
+def test_a_plan_takes_a_few_microseconds(Hq, Hkv, Sq, Sk, D):
+    """Every backward call makes them (a loop over the key blocks for each cut took 30 .. 53 us here; now at most 4)."""
+    p = ctypes.byref(binding.make_rect_params(1, Hq, Hkv, Sq, Sk, D, 1.0, True))
+    f, least = binding.lib().attn_bwd_rect_best_workspace_bytes, 1.0
+    for _ in range(200):
+        t = time.perf_counter()
+        f(p)
+        least = min(least, time.perf_counter() - t)
+    assert least < 12e-6
+
+
+@pytest.mark.parametrize("Hq,Hkv,Sq,Sk", [(1, 1, 9000, 9007), (2, 1, 5000, 6001), (4, 1, 2000, 2063), (3, 3, 1601, 3000),
+                                          (2, 2, 3000, 3001), (16, 2, 225, 3200), (1, 1, 1537, 4096)])
+def test_chunks_of_dk_dv_cover_the_key_blocks(Hq, Hkv, Sq, Sk):
+    """The chunks that the plan counts in closed form, block by block, D = 256 (where dQ has no partial results)."""
+    def chunks(causal):
+        group, n_block, n_slot = Hq // Hkv, (Sk + 63) // 64, (Sq + 31) // 32
+        slots = [group * (n_slot - max(0, 64 * kt - (Sk - Sq)) // 32 * causal) for kt in range(n_block)]
+        if Hkv * n_block >= 256 or slots[0] < 48:
+            return 0
+        L = max(16, (sum(slots) * Hkv + 255) // 256)
+        while 4 * L <= 3 * slots[0]:
+            items = sum((s + L - 1) // L for s in slots) * Hkv
+            if items <= 256:
+                return items
+            L += (L + 31) // 32
+        return 0
+    part = max(chunks(0), chunks(1)) * 2 * 64 * 256 * 4
+    assert part > 0
+    assert attn.attn_bwd_rect_workspace_bytes(1, Hq, Hkv, Sq, Sk, 256) == (8 * Hq * Sq + 255) // 256 * 256 + part
