@@ -237,6 +237,20 @@ size_t attn_bwd_rect_workspace_bytes(const attn_rect_params_t *p);
  */
 size_t attn_bwd_rect_best_workspace_bytes(const attn_rect_params_t *p);
 
+/*
+ * The kernels that a whole bf16 or fp16 backward without rotary tables takes in a workspace of that size: one
+ * for short heads; dQ, then dK/dV; dK/dV with dS stored, then dQ from it; or dK/dV and dQ side by side; and
+ * whether dK/dV is cut into chunks and dQ over the keys.  Pure host function, for tests and profiles; an
+ * ATTN_ERR_* (negative) for an invalid problem or too small a workspace.
+ */
+#define ATTN_BWD_FORM_APART 0
+#define ATTN_BWD_FORM_SHORT 1
+#define ATTN_BWD_FORM_STORED_DS 2
+#define ATTN_BWD_FORM_SIDE_BY_SIDE 3
+#define ATTN_BWD_FORM_DKDV_CUT 16
+#define ATTN_BWD_FORM_DQ_CUT 32
+int attn_bwd_rect_form(const attn_rect_params_t *p, size_t workspace_bytes);
+
 int attn_bwd_rect(const void *Q, const void *K, const void *V, const void *O, const void *dO,
                   const float *LSE, void *dQ, void *dK, void *dV,
                   void *workspace, size_t workspace_bytes,

@@ -25,7 +25,8 @@ EXPORTS = ("attn_params_contiguous", "attn_fwd", "attn_bwd_workspace_bytes", "at
            "attn_bwd_stages", "attn_gqa_params_contiguous", "attn_fwd_gqa",
            "attn_bwd_gqa_workspace_bytes", "attn_bwd_gqa", "attn_bwd_gqa_stages",
            "attn_rect_params_contiguous", "attn_fwd_rect_workspace_bytes", "attn_fwd_rect",
-           "attn_bwd_rect_workspace_bytes", "attn_bwd_rect_best_workspace_bytes", "attn_bwd_rect", "attn_fwd_rect_f16",
+           "attn_bwd_rect_workspace_bytes", "attn_bwd_rect_best_workspace_bytes", "attn_bwd_rect_form",
+           "attn_bwd_rect", "attn_fwd_rect_f16",
            "attn_bwd_rect_f16", "attn_bwd_rect_noalloc", "attn_fwd_rope_workspace_bytes", "attn_fwd_rope",
            "attn_bwd_rope", "attn_probe_mfma_bf16",
            "attn_probe_atomic_f32", "attn_probe_stream",
@@ -123,6 +124,8 @@ def lib():
         L.attn_bwd_rect_workspace_bytes.restype = ctypes.c_size_t
         L.attn_bwd_rect_best_workspace_bytes.argtypes = [rp]
         L.attn_bwd_rect_best_workspace_bytes.restype = ctypes.c_size_t
+        L.attn_bwd_rect_form.argtypes = [rp, ctypes.c_size_t]
+        L.attn_bwd_rect_form.restype = ctypes.c_int
         L.attn_bwd_rect.argtypes = [vp] * 9 + [vp, ctypes.c_size_t, rp, vp]
         L.attn_bwd_rect.restype = ctypes.c_int
         L.attn_fwd_rect_f16.argtypes = L.attn_fwd_rect.argtypes

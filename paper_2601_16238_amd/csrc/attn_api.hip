@@ -272,6 +272,34 @@ static int fwd_impl(const void *Q, const void *K, const void *V, void *O, float 
                ? ATTN_OK : ATTN_ERR_LAUNCH;
 }
 
+// The kernels of a backward call: what a workspace has room for beyond the row statistics bounds the splits.  (A
+// plan that is dropped where it does not fit whole costs, in the 8 MiB of the call without workspace, us: one head
+// of 1024 rows on 4096 keys, D = 128, causal 112 against 55 with the splits that fit; 4 -> 1 heads of 2048,
+// D = 64, causal 180 against 51.)  dQ with rotary tables is split only where it runs next to dK/dV.
+struct BwdPlan {
+    int dq_nsplit, dq_kps, dkdv_chunk, dkdv_items, ds_heads;
+    size_t dkdv_bytes;
+    attn::PairPlan pair;
+};
+static BwdPlan bwd_plan(const attn_rect_params_t *p, size_t workspace_bytes, bool rope, uint32_t stages)
+{
+    const size_t room = workspace_bytes - bwd_stats_bytes(p);
+    BwdPlan r = {};
+    r.dq_nsplit = attn::dq_split_plan(p->B * p->Hq, p->Sq, p->Sk, kernel_d(p->D), p->causal != 0, &r.dq_kps,
+                                      rope ? 1 : (int)std::min<size_t>(16, room / dq_split_bytes(p)));
+    r.dkdv_items = attn::dkdv_split_plan(p->B * p->Hkv, p->Hq / p->Hkv, p->Sq, p->Sk, kernel_d(p->D),
+                                         p->causal != 0, &r.dkdv_chunk,
+                                         (int64_t)std::min<size_t>(512, room / dkdv_chunk_bytes(p)));
+    r.dkdv_bytes = r.dkdv_chunk ? round_ws((size_t)p->B * p->Hkv * r.dkdv_items * dkdv_chunk_bytes(p)) : 0;
+    // (a workspace of the size that attn_bwd_rect_workspace_bytes asks for, or less, keeps the form without dS,
+    // and with one kernel after the other)
+    if (stages == 7u && workspace_bytes > attn_bwd_rect_workspace_bytes(p)) {
+        r.ds_heads = ds_heads_in(p, room - r.dkdv_bytes);
+        r.pair = pair_in(p, room);
+    }
+    return r;
+}
+
 template <typename E>
 static int bwd_impl(const void *Q, const void *K, const void *V, const void *O, const void *dO,
                     const float *LSE, void *dQ, void *dK, void *dV,
@@ -287,27 +315,12 @@ static int bwd_impl(const void *Q, const void *K, const void *V, const void *O, 
         !aligned(dO, 16) || !aligned(dQ, 16) || !aligned(dK, 16) || !aligned(dV, 16) ||
         !aligned(LSE, 4))
         return ATTN_ERR_ALIGN;
-    // The row statistics always; the rest of the workspace bounds the splits.  (A plan that is dropped
-    // where it does not fit whole costs, in the 8 MiB of the call without workspace, us: one head of 1024
-    // rows on 4096 keys, D = 128, causal 112 against 55 with the splits that fit; 4 -> 1 heads of 2048,
-    // D = 64, causal 180 against 51.)  dQ with rotary tables is split only where it runs next to dK/dV.
     const size_t stats_bytes = bwd_stats_bytes(p);
     if (!workspace || !aligned(workspace, kWsAlign) || workspace_bytes < stats_bytes)
         return ATTN_ERR_WORKSPACE;
     if (stages == 0 || (stages & ~7u)) return ATTN_ERR_SHAPE;
-    const size_t room = workspace_bytes - stats_bytes;
-    int dq_kps = 0, dkdv_chunk = 0;
-    const int dq_nsplit = attn::dq_split_plan(p->B * p->Hq, p->Sq, p->Sk, kernel_d(p->D), p->causal != 0, &dq_kps,
-                                              rope ? 1 : (int)std::min<size_t>(16, room / dq_split_bytes(p)));
-    const int dkdv_items = attn::dkdv_split_plan(p->B * p->Hkv, p->Hq / p->Hkv, p->Sq, p->Sk, kernel_d(p->D),
-                                                 p->causal != 0, &dkdv_chunk,
-                                                 (int64_t)std::min<size_t>(512, room / dkdv_chunk_bytes(p)));
-    const size_t dkdv_bytes = dkdv_chunk ? round_ws((size_t)p->B * p->Hkv * dkdv_items * dkdv_chunk_bytes(p)) : 0;
-    // (a workspace of the size that attn_bwd_rect_workspace_bytes asks for, or less, keeps the form without dS,
-    // and with one kernel after the other)
-    const bool more = stages == 7u && workspace_bytes > attn_bwd_rect_workspace_bytes(p);
-    const int ds_heads = more ? ds_heads_in(p, room - dkdv_bytes) : 0;
-    const attn::PairPlan pair = more ? pair_in(p, room) : attn::PairPlan{};
+    const BwdPlan plan = bwd_plan(p, workspace_bytes, rope != nullptr, stages);
+    const attn::PairPlan &pair = plan.pair;
     attn::BwdArgsT<E> a;
     a.Q = static_cast<const E *>(Q);
     a.K = static_cast<const E *>(K);
@@ -316,12 +329,12 @@ static int bwd_impl(const void *Q, const void *K, const void *V, const void *O, 
     a.dO = static_cast<const E *>(dO);
     a.LSE = LSE;
     a.delta = static_cast<float *>(workspace);
-    a.dq_nsplit = dq_nsplit; a.dq_kps = dq_kps;
+    a.dq_nsplit = plan.dq_nsplit; a.dq_kps = plan.dq_kps;
     a.dQpart = reinterpret_cast<float *>(static_cast<char *>(workspace) + stats_bytes);
-    a.dkdv_chunk = dkdv_chunk; a.dkdv_items = dkdv_items;
+    a.dkdv_chunk = plan.dkdv_chunk; a.dkdv_items = plan.dkdv_items;
     a.dKVpart = a.dQpart;
-    a.dS = reinterpret_cast<E *>(reinterpret_cast<char *>(a.dQpart) + dkdv_bytes);
-    a.ds_heads = ds_heads; a.bkv0 = 0; a.nkv = p->B * p->Hkv;
+    a.dS = reinterpret_cast<E *>(reinterpret_cast<char *>(a.dQpart) + plan.dkdv_bytes);
+    a.ds_heads = plan.ds_heads; a.bkv0 = 0; a.nkv = p->B * p->Hkv;
     a.pair = pair.taken; a.pair_dkdv = a.pair_dq = 0;
     if (pair.taken) {
         a.dq_nsplit = pair.dq_nsplit; a.dq_kps = pair.dq_kps;
@@ -462,6 +475,21 @@ size_t attn_bwd_rect_best_workspace_bytes(const attn_rect_params_t *p)
     const int n = ds_heads_in(p, kMost);
     if (!n) return plain;  // (a workspace of that size would not be taken as one for dS)
     return std::max(bwd_stats_bytes(p) + dkdv_part_bytes(p, p->causal != 0) + ds_bytes(p, n), plain + kWsAlign);
+}
+
+int attn_bwd_rect_form(const attn_rect_params_t *p, size_t workspace_bytes)
+{
+    const int rc = check_params(p);
+    if (rc != ATTN_OK) return rc;
+    if (workspace_bytes < bwd_stats_bytes(p)) return ATTN_ERR_WORKSPACE;
+    if (attn::bwd_is_small(p->B * p->Hkv, p->Hq / p->Hkv, p->Sq, p->Sk, kernel_d(p->D))) return ATTN_BWD_FORM_SHORT;
+    const BwdPlan plan = bwd_plan(p, workspace_bytes, false, 7u);
+    if (plan.pair.taken)
+        return ATTN_BWD_FORM_SIDE_BY_SIDE | (plan.pair.dkdv_chunk ? ATTN_BWD_FORM_DKDV_CUT : 0) |
+               (plan.pair.dq_nsplit > 1 ? ATTN_BWD_FORM_DQ_CUT : 0);
+    const int cut = plan.dkdv_chunk ? ATTN_BWD_FORM_DKDV_CUT : 0;
+    if (plan.ds_heads) return ATTN_BWD_FORM_STORED_DS | cut;
+    return ATTN_BWD_FORM_APART | cut | (plan.dq_nsplit > 1 ? ATTN_BWD_FORM_DQ_CUT : 0);
 }
 
 size_t attn_bwd_gqa_workspace_bytes(const attn_gqa_params_t *p)

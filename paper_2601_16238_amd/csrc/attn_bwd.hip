@@ -1796,6 +1796,8 @@ int dkdv_split_plan(int BHkv, int group, int S, int Sk, int D, bool causal, int 
     return n_block;
 }
 
+bool bwd_is_small(int BHkv, int group, int S, int Sk, int D) { return takes_bwd_small(BHkv, group, S, Sk, D); }
+
 // dS kept for dQ (above D = 64): K/V heads whose dS is held at a time in `room` bytes, 0: dS is not kept.
 // The dK/dV kernel stores it once (3 .. 7 % longer: the stores) and the dQ kernel then has one product per
 // tile instead of three, at the rate at which dS comes from HBM (5.2 .. 5.9 TB/s).  Whole backward, before

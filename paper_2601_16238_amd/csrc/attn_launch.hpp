@@ -188,6 +188,7 @@ __host__ __device__ inline int64_t ds_head_blocks(int S, int Sk, bool causal)
 // The whole backward in one launch for heads of at most bwd_small_max_rows(D) query rows and keys
 // (attn_bwd_small.hip; called by launch_bwd when all three stages are asked for).
 int bwd_small_max_rows(int D);
+bool bwd_is_small(int BHkv, int group, int S, int Sk, int D);  // whether a whole backward is that launch
 int launch_bwd_small(const BwdArgsT<__bf16> &a, int D, bool causal, hipStream_t st);
 int launch_bwd_small(const BwdArgsT<_Float16> &a, int D, bool causal, hipStream_t st);
 int launch_bwd(const BwdArgsT<__bf16> &a, int D, bool causal, hipStream_t st, unsigned stages);

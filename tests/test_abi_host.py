@@ -340,3 +340,14 @@ def test_rowops_validation_without_a_gpu():
                                                    4 * 64 * 128, 64 * 128, ss, 4 * 64 * 128, 64 * 128, 128, None)
     assert rot(D=24) == binding.ATTN_ERR_SHAPE                # halves must be multiples of 8
     assert rot(ss=64) == binding.ATTN_ERR_STRIDE
+
+
+def test_form_of_the_backward():
+    def form(size, B=1, Hq=6, Hkv=6, Sq=1037, Sk=1037, D=64, causal=True):
+        p = attn.make_rect_params(B, Hq, Hkv, Sq, Sk, D, 1.0, causal)
+        return attn.lib().attn_bwd_rect_form(ctypes.byref(p), size)
+    assert form(1 << 32) % 16 == 3 and form(attn.attn_bwd_rect_workspace_bytes(1, 6, 6, 1037, 1037, 64)) % 16 == 0
+    assert form(1 << 32, Hq=64, Hkv=64, Sq=4096, Sk=4096, D=128) == 2
+    assert form(1 << 20, Sq=65, Sk=65) == 1
+    assert form(8) == binding.ATTN_ERR_WORKSPACE
+    assert form(1 << 32, D=100) == form(1 << 32, Sk=8) == binding.ATTN_ERR_SHAPE
