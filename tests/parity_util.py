@@ -1,10 +1,12 @@
 """Helpers for the GPU parity tests: host<->device marshalling and error metrics."""
+import ctypes
+
 import numpy as np
 import torch
 
-from paper_2601_16238_amd import workloads as wl
+from paper_2601_16238_amd import binding, workloads as wl
 
-# Tolerances of the benchmark spec: bf16 outputs within max-abs 2e-2 and mean-abs 2e-3
+# Tolerances: bf16 outputs within max-abs 2e-2 and mean-abs 2e-3
 # of the fp64 oracle, fp32 LSE within 1e-5.
 TOL_MAX, TOL_MEAN, TOL_LSE = 2e-2, 2e-3, 1e-5
 
@@ -108,3 +110,23 @@ def check_lse_allclose(got, ref, atol=TOL_LSE, rtol=TOL_LSE):
     print("LSE: literal max %.3e | fp32 rounding floor %.3e | max(|err| - rtol|ref|) %.3e | max|ref| %.4g"
           % (float(d.max()), f32floor, worst, float(np.abs(ref).max())), flush=True)
     assert worst <= atol
+
+
+# which kernels a backward takes (attn_bwd_rect_form in include/attn.h)
+APART, SHORT, STORED_DS, SIDE_BY_SIDE, DKDV_CUT, DQ_CUT = 0, 1, 2, 3, 16, 32
+
+
+def backward_form(B, Hq, Hkv, Sq, Sk, D, causal, workspace_bytes):
+    p = binding.make_rect_params(B, Hq, Hkv, Sq, Sk, D, 1.0, causal)
+    return binding.lib().attn_bwd_rect_form(ctypes.byref(p), workspace_bytes)
+
+
+def in_layout(t, layout):
+    """t [B,H,S,D] with the same values in [B,S,H,D] storage, or ("padded") with 8 unused columns after every
+    row, 3 unused rows after every head and an unused head after every batch entry, all NaN."""
+    B, H, S, D = t.shape
+    if layout == "BSHD":
+        return t.transpose(1, 2).contiguous().transpose(1, 2)
+    out = t.new_full((B, H + 1, S + 3, D + 8), float("nan"))[:, :H, :S, :D]
+    out.copy_(t)
+    return out

@@ -7,22 +7,23 @@ import torch
 import oracle
 import paper_2601_16238_amd as attn
 from paper_2601_16238_amd import workloads as wl
-from parity_util import bf16_round, check_grad, f16_round, to_f64
+from parity_util import DKDV_CUT, STORED_DS, backward_form, bf16_round, check_grad, f16_round, in_layout, to_f64
 
 pytestmark = pytest.mark.gpu
 
-# work-groups of 64, 128 and 256 rows; last slot and last key block ragged, one row or key over; a causal
-# offset off the 32-key blocks; key blocks that no row of a slot sees; grouped heads; padded head
-# dimensions; fp16; with and without the split of dK/dV
-CASES = [(1, 2, 2, 257, 257, 128, True, False), (1, 3, 1, 385, 609, 96, True, True),
-         (1, 4, 2, 290, 321, 200, False, False), (2, 3, 3, 513, 513, 256, True, True),
-         (1, 40, 20, 500, 545, 128, True, False), (2, 33, 33, 289, 417, 256, False, False),
-         (1, 90, 90, 300, 300, 128, False, False), (2, 48, 48, 300, 331, 80, True, False),
-         (1, 6, 3, 1601, 70, 128, False, False)]
+# (last: dK/dV cut into chunks)  work-groups of 64, 128 and 256 rows; last slot and last key block ragged,
+# one row; a causal offset off the 32-key blocks; key blocks that no row of a slot sees; grouped heads; padded head
+# dimensions; fp16; four and six pairs
+CASES = [(2, 2, 2, 92, 1039, 128, True, False, 0), (1, 33, 33, 1, 900, 128, True, True, 0), (1, 70, 70, 1, 500, 256, False, False, 0),
+         (1, 96, 24, 400, 400, 96, True, True, 1), (2, 48, 12, 385, 609, 128, True, False, 1),
+         (1, 36, 12, 700, 733, 128, True, False, 1), (1, 72, 9, 290, 321, 200, False, False, 1),
+         (1, 56, 14, 400, 433, 256, True, True, 1), (2, 33, 33, 289, 417, 256, False, False, 0),
+         (1, 90, 90, 300, 300, 128, False, False, 0), (2, 48, 48, 300, 331, 80, True, False, 0),
+         (1, 120, 120, 513, 70, 128, False, False, 0), (2, 256, 256, 40, 161, 128, True, False, 0)]
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,Sq,Sk,D,causal,f16", CASES)
-def test_dq_from_the_stored_ds(B, Hq, Hkv, Sq, Sk, D, causal, f16):
+@pytest.mark.parametrize("B,Hq,Hkv,Sq,Sk,D,causal,f16,cut", CASES)
+def test_dq_from_the_stored_ds(B, Hq, Hkv, Sq, Sk, D, causal, f16, cut):
     print("case kept_ds", B, Hq, Hkv, Sq, Sk, D, causal, f16, flush=True)
     draw = wl.random_rect_inputs_f16 if f16 else wl.random_rect_inputs
     x = draw(B, Hq, Hkv, Sq, Sk, D, seed=5200 + Sq + D)
@@ -32,7 +33,7 @@ def test_dq_from_the_stored_ds(B, Hq, Hkv, Sq, Sk, D, causal, f16):
     Q, K, V, dO = (torch.from_numpy(x[k].view(np.int16)).cuda().view(dt) for k in ("Q", "K", "V", "dO"))
     O, LSE = attn.attn_fwd_rect(Q, K, V, x["scale"], causal)
     best = attn.attn_bwd_rect_best_workspace_bytes(B, Hq, Hkv, Sq, Sk, D, causal)
-    assert best > attn.attn_bwd_rect_workspace_bytes(B, Hq, Hkv, Sq, Sk, D), "dS is not kept"
+    assert backward_form(B, Hq, Hkv, Sq, Sk, D, causal, best) == STORED_DS + DKDV_CUT * cut
     ws = torch.full((best + 4096,), 0xFF, dtype=torch.uint8, device="cuda")   # NaN: nothing may be relied on
     got = attn.attn_bwd_rect(Q, K, V, O, dO, LSE, x["scale"], causal, workspace=ws[:best])
     again = attn.attn_bwd_rect(Q, K, V, O, dO, LSE, x["scale"], causal)
@@ -55,6 +56,7 @@ def test_ds_of_a_part_of_the_heads_at_a_time(H, Hkv, S, D, causal):
     K, V = (torch.randn((2, Hkv, S, D), generator=g, device="cuda").bfloat16() for _ in range(2))
     O, LSE = attn.attn_fwd_rect(Q, K, V, D ** -0.5, causal)
     best = attn.attn_bwd_rect_best_workspace_bytes(2, H, Hkv, S, S, D, causal)
+    assert [backward_form(2, H, Hkv, S, S, D, causal, n) for n in (best, int(best * 0.6))] == [STORED_DS] * 2
     ws = torch.full((best,), 0xFF, dtype=torch.uint8, device="cuda")
     whole, part, none = (attn.attn_bwd_rect(Q, K, V, O, dO, LSE, D ** -0.5, causal, workspace=ws[:n])
                          for n in (best, int(best * 0.6), 16 * H * S + 256))
@@ -64,3 +66,22 @@ def test_ds_of_a_part_of_the_heads_at_a_time(H, Hkv, S, D, causal):
         w, n = w.double(), n.double()
         assert bool(((w - n).abs() <= n.abs() * 2.0 ** -7 + 1e-3 * n.abs().max()).all())
     assert not torch.equal(whole[0].view(torch.int16), none[0].view(torch.int16)), "dS is not kept"
+
+
+@pytest.mark.parametrize("layout", ["BSHD", "padded"])
+@pytest.mark.parametrize("B,Hq,Hkv,Sq,Sk,D,causal,f16,cut", [c for c in CASES if c[:3] in ((2, 48, 12), (1, 96, 24), (2, 33, 33))])
+def test_stored_ds_in_other_layouts(B, Hq, Hkv, Sq, Sk, D, causal, f16, cut, layout):
+    """[B,S,H,D] storage, and rows and heads with gaps: bit for bit the contiguous result."""
+    print("case kept_ds layout", Hq, Hkv, Sq, Sk, D, layout, flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(Sq)
+    dt = torch.float16 if f16 else torch.bfloat16
+    Q, dO = (torch.randn((B, Hq, Sq, D), generator=g, device="cuda").to(dt) for _ in range(2))
+    K, V = (torch.randn((B, Hkv, Sk, D), generator=g, device="cuda").to(dt) for _ in range(2))
+    O, LSE = attn.attn_fwd_rect(Q, K, V, D ** -0.5, causal)
+    want = attn.attn_bwd_rect(Q, K, V, O, dO, LSE, D ** -0.5, causal)
+    t = [in_layout(x, layout) for x in (Q, K, V, O, dO)]
+    out = [in_layout(torch.full_like(x, float("nan")), layout) for x in (Q, K, V)]
+    attn.attn_bwd_rect(*t, LSE, D ** -0.5, causal, dQ=out[0], dK=out[1], dV=out[2])
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(out, want))

@@ -6,7 +6,7 @@ import torch
 import oracle
 import paper_2601_16238_amd as attn
 from paper_2601_16238_amd import workloads as wl
-from parity_util import check_bf16, to_dev, to_f64
+from parity_util import check_bf16, in_layout, to_dev, to_f64
 
 pytestmark = pytest.mark.gpu
 
@@ -44,3 +44,19 @@ def test_the_workspace_of_four_wave_work_groups_is_accepted():
     assert (LSE - LSE1).abs().max() <= 2e-5   # (each within 1e-5 of the exact one)
     # two roundings of one result, each within the rounding of P of the exact one
     assert (O.double() - O1.double()).norm() <= 5e-3 * O1.double().norm()
+
+
+@pytest.mark.parametrize("layout", ["BSHD", "padded"])
+@pytest.mark.parametrize("Hq,Hkv,Sq,Sk,D,causal", [(130, 65, 224, 225, 96, False), (48, 12, 193, 2800, 128, True)])
+def test_five_to_seven_row_blocks_in_other_layouts(Hq, Hkv, Sq, Sk, D, causal, layout):
+    """[B,S,H,D] storage, and rows and heads with gaps: bit for bit the contiguous result."""
+    print("case five blocks layout", Hq, Hkv, Sq, Sk, D, layout, flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(Sq)
+    Q = torch.randn((1, Hq, Sq, D), generator=g, device="cuda").bfloat16()
+    K, V = (torch.randn((1, Hkv, Sk, D), generator=g, device="cuda").bfloat16() for _ in range(2))
+    O, LSE = attn.attn_fwd_rect(Q, K, V, D ** -0.5, causal)
+    out = in_layout(torch.full_like(Q, float("nan")), layout)
+    _, LSE2 = attn.attn_fwd_rect(*(in_layout(t, layout) for t in (Q, K, V)), D ** -0.5, causal, O=out)
+    torch.cuda.synchronize()
+    assert torch.equal(out, O) and torch.equal(LSE2, LSE)
