@@ -33,8 +33,9 @@ MEASURED_TRAFFIC_BYTES = {
 def measured_traffic_bytes(workload, kernel):
     """HBM bytes per launch of `kernel` on `workload` (read + written, scaled counter readings)
     from the committed rocprofv3 summary of that workload, profiles/<workload>_kernel_trace_and_
-    hbm_traffic.txt; None if there is none.  The figure is of the kernels that the summary was made
-    with, by hand: a change to a kernel's traffic needs a new one."""
+    hbm_traffic.txt; None if there is none.  The first line of the kernel counts: the summary lists the stage-wise
+    instances first.  The figure is of the kernels that the summary was made with, by hand: a change to a
+    kernel's traffic needs a new one."""
     path = os.path.join(ROOT, "profiles", "%s_kernel_trace_and_hbm_traffic.txt" % workload)
     try:
         lines = open(path).read().splitlines()
@@ -101,6 +102,20 @@ def graph_ms(torch, fn, n):
     return time_calls(torch, graph.replay, 3) / n
 
 
+def best_backward_workspace(torch, attn, *problem):
+    """The workspace that a backward call without one takes (where there is memory to spare).  The stage-wise
+    timings of `measure` are of dK/dV and dQ one after the other, whatever form the whole call takes in it."""
+    return torch.empty(attn.attn_bwd_rect_best_workspace_bytes(*problem), dtype=torch.uint8, device="cuda")
+
+
+def backward_form(binding, workspace_bytes, *problem):
+    import ctypes
+    B, Hq, Hkv, Sq, Sk, D, causal = problem
+    p = binding.make_rect_params(B, Hq, Hkv, Sq, Sk, D, 1.0, causal)
+    return ("dQ, then dK/dV", "one kernel", "dK/dV storing dS, then dQ from it", "dK/dV and dQ side by side")[
+        binding.lib().attn_bwd_rect_form(ctypes.byref(p), workspace_bytes) % 16]
+
+
 def measure(torch, attn, wl, w, steps, warmup):
     import numpy as np
     from paper_2601_16238_amd import binding
@@ -117,8 +132,7 @@ def measure(torch, attn, wl, w, steps, warmup):
     O = torch.empty_like(Q)
     LSE = torch.empty((w.B, H, w.S), dtype=torch.float32, device="cuda")
     dQ, dK, dV = torch.empty_like(Q), torch.empty_like(K), torch.empty_like(K)
-    ws = torch.empty(attn.attn_bwd_gqa_workspace_bytes(w.B, H, Hkv, w.S, w.D), dtype=torch.uint8,
-                     device="cuda")
+    ws = best_backward_workspace(torch, attn, w.B, H, Hkv, w.S, w.S, w.D, causal)
     fwd_call, bwd_call = (attn.attn_fwd_gqa, attn.attn_bwd_gqa) if gqa else (attn.attn_fwd, attn.attn_bwd)
 
     def fwd():
@@ -161,6 +175,8 @@ def measure(torch, attn, wl, w, steps, warmup):
     b_fwd, b_bwd = 2 * t_q + 2 * t_kv + lse_b, 4 * t_q + 4 * t_kv + lse_b
     res = {
         "ms_per_step": ms_step, "ms": ms, "wall_s": wall,
+        "backward": {"form": backward_form(binding, ws.numel(), w.B, H, Hkv, w.S, w.S, w.D, causal),
+                     "workspace_bytes": ws.numel()},
         "tflops_fwdbwd": (f_fwd + f_bwd) / (ms_step * 1e-3) / 1e12,
         "tflops_fwd": f_fwd / (ms["fwd"] * 1e-3) / 1e12,
         "tflops_bwd": f_bwd / (ms["bwd"] * 1e-3) / 1e12,
@@ -218,7 +234,7 @@ def measure_cold(torch, attn, wl, w, steps):
     Q, K, V, dO = mk(), mk(), mk(), mk()
     O, dQ, dK, dV = (torch.empty_like(Q) for _ in range(4))
     LSE = torch.empty((nsets, w.B, w.H, w.S), dtype=torch.float32, device="cuda")
-    ws = torch.empty(attn.attn_bwd_workspace_bytes(w.B, w.H, w.S, w.D), dtype=torch.uint8, device="cuda")
+    ws = best_backward_workspace(torch, attn, w.B, w.H, w.H, w.S, w.S, w.D, w.causal)
     scale = wl.default_scale(w.D)
     state = {"i": 0}
 
@@ -266,7 +282,7 @@ def measure_rect(torch, attn, wl, w, steps, warmup):
     shape = (w.B, w.Hq, w.Hkv, w.Sq, w.Sk, w.D)
     fws_bytes = attn.attn_fwd_rect_workspace_bytes(*shape)
     fws = torch.empty(max(fws_bytes, 256), dtype=torch.uint8, device="cuda")
-    bws = torch.empty(attn.attn_bwd_rect_workspace_bytes(*shape), dtype=torch.uint8, device="cuda")
+    bws = best_backward_workspace(torch, attn, *shape, causal)
 
     def fwd():
         attn.attn_fwd_rect(Q, K, V, scale, causal, O=O, LSE=LSE, workspace=fws)
@@ -598,7 +614,7 @@ def main():
                               "fwd_bwd": r["tflops_fwdbwd"] / PEAK_BF16_TFLOPS,
                               "peak_tflops": PEAK_BF16_TFLOPS},
         "tflops": {"fwd": r["tflops_fwd"], "bwd": r["tflops_bwd"], "fwd_bwd": r["tflops_fwdbwd"]},
-        "ms": r["ms"],
+        "ms": r["ms"], "backward": r["backward"],
         "algorithmic_gbs": {"fwd": r["gbs_fwd"], "bwd": r["gbs_bwd"], "hbm_peak": PEAK_HBM_GBS},
         "roofline": {"kernel": dom, "bound": "mfma", "achieved": r["kernels"][dom]["achieved_tflops"],
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": r["kernels"][dom]["frac"],
@@ -648,8 +664,7 @@ def main():
         sc = wl.default_scale(w.D)
         o16, l16 = attn.attn_fwd_rect(q16, k16, v16, sc, w.causal)
         bufs = [torch.empty_like(q16) for _ in range(3)]
-        ws16 = torch.empty(attn.attn_bwd_rect_workspace_bytes(w.B, H, H, w.S, w.S, w.D),
-                           dtype=torch.uint8, device="cuda")
+        ws16 = best_backward_workspace(torch, attn, w.B, H, H, w.S, w.S, w.D, w.causal)
         f16_fwd = time_calls(torch, lambda: attn.attn_fwd_rect(q16, k16, v16, sc, w.causal, O=o16, LSE=l16), 10)
         f16_bwd = time_calls(torch, lambda: attn.attn_bwd_rect(q16, k16, v16, o16, do16, l16, sc, w.causal,
                                                                 dQ=bufs[0], dK=bufs[1], dV=bufs[2],
