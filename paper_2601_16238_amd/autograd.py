@@ -12,8 +12,8 @@ from . import binding
 
 
 class _RecordedAttention(torch.autograd.Function):
-    """The same two calls as a Python function, which a tracer records as one operation and calls again.
-    (It would record of the native node only the allocations, and replay those without the kernels.)"""
+    """The same two calls as a Python function, which a tracer records as one operation and calls again: of
+    the native node it would record only the allocations, and replay those without the kernels."""
 
     @staticmethod
     def forward(ctx, q, k, v, scale, causal):
@@ -36,6 +36,5 @@ def fused_attention(q, k, v, causal=False, scale=None):
         raise RuntimeError("fused_attention has no rule for function transforms (vmap, grad, jvp, ...)")
     if scale is None:
         scale = float(q.shape[-1]) ** -0.5
-    if torch.jit.is_tracing():
-        return _RecordedAttention.apply(q, k, v, float(scale), bool(causal))
-    return binding.marshal().fused_attention(q, k, v, float(scale), bool(causal))
+    out = binding.marshal().fused_attention(q, k, v, float(scale), bool(causal))
+    return _RecordedAttention.apply(q, k, v, float(scale), bool(causal)) if out is None else out

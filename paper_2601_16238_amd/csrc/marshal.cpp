@@ -12,6 +12,7 @@
 #include <c10/hip/HIPStream.h>
 #include <hip/hip_runtime_api.h>
 #include <torch/csrc/Exceptions.h>
+#include <torch/csrc/jit/frontend/tracer.h>
 
 #include <algorithm>
 #include <initializer_list>
@@ -449,8 +450,10 @@ struct FusedAttention : torch::autograd::Function<FusedAttention> {
     }
 };
 
-Tensor fused_attention(const Tensor &q, const Tensor &k, const Tensor &v, double scale, bool causal)
+// (none while a tracer records: it would keep the allocations and not the kernels)
+OptTensor fused_attention(const Tensor &q, const Tensor &k, const Tensor &v, double scale, bool causal)
 {
+    if (torch::jit::tracer::isTracing()) return {};
     for (const Tensor *t : {&q, &k, &v})
         TORCH_CHECK_NOT_IMPLEMENTED(!t->_fw_grad(0).defined(), "fused_attention has no rule for forward mode");
     return FusedAttention::apply(q, k, v, scale, causal);
