@@ -186,8 +186,9 @@ int attn_bwd_gqa_stages(const void *Q, const void *K, const void *V, const void 
  * workspace == NULL (with any size) is allowed and means: do not split.  A non-NULL workspace must
  * be 256-byte aligned and large enough for the split of this call (that size always is).  A smaller
  * one is accepted, and bounds the split, if it is large enough for a split into one work-group per
- * compute unit or for the split at which the longest work-group is estimated to end first (any size
- * where either of those would be no split); else ATTN_ERR_WORKSPACE.  Its contents are undefined on
+ * compute unit, for the split at which the longest work-group is estimated to end first, or for the plan
+ * with four-wave work-groups (129 .. 224 rows above D = 64), any size where one of those would be no
+ * split; else ATTN_ERR_WORKSPACE.  Its contents are undefined on
  * entry and exit.  The split plan depends only on the shape, the strides and that size, so results
  * are deterministic.
  *
@@ -294,7 +295,7 @@ int attn_bwd_rope(const void *Q_rot, const void *K_rot, const void *V, const voi
 /*
  * attn_bwd_rect for callers that cannot allocate device memory or pass a workspace: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  The
- * backward's scratch (two fp32 values per query row, and in what is left the fp32 partial
+ * backward's scratch (two fp32 values per query row, and in what is left dS or the fp32 partial
  * results of the splits that fit, as in a workspace of this size) lives in an array inside the
  * library's device image, ATTN_NOALLOC_SCRATCH_BYTES long; each GPU the library runs on holds its
  * own copy until the process ends.  Arguments, validation and stream semantics are those of

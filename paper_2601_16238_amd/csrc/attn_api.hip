@@ -570,7 +570,7 @@ int attn_bwd_stages(const void *Q, const void *K, const void *V, const void *O, 
 
 }  // extern "C"
 
-// Scratch of attn_bwd_rect_noalloc: the backward's row statistics, in an array that lives in
+// Scratch of attn_bwd_rect_noalloc: the workspace of the call, in an array that lives in
 // the library's device image instead of in memory the caller allocates.  Every GPU the library
 // runs on holds its own copy at its own address, so the address is looked up once per device
 // (with that device current) and kept; host code uses that pointer, never the array's name.
@@ -610,9 +610,10 @@ int attn_bwd_rect_noalloc(const void *Q, const void *K, const void *V, const voi
     if (need > (size_t)ATTN_NOALLOC_SCRATCH_BYTES) return ATTN_ERR_WORKSPACE;
     void *ws = scratch_of_current_device();
     if (!ws) return ATTN_ERR_LAUNCH;
-    // Every value of the scratch that a kernel reads is written earlier in the same call (the
-    // dQ kernel stores the statistics of every query row, the dK/dV kernel reads only those),
-    // so nothing has to be cleared although the array keeps the last call's contents.
+    // Every value of the scratch that a kernel reads is written earlier in the same call (the statistics of every
+    // query row by the dQ kernel or, in the forms with dS kept or both kernels side by side, by their own; partial
+    // results and dS by the kernel before the one that reads them), so nothing has to be cleared although the array
+    // keeps the last call's contents.
     return bwd_impl<__bf16>(Q, K, V, O, dO, LSE, dQ, dK, dV, ws, ATTN_NOALLOC_SCRATCH_BYTES, p,
                             hip_stream,
                             ATTN_BWD_STAGE_DELTA | ATTN_BWD_STAGE_DKDV | ATTN_BWD_STAGE_DQ);

@@ -6,7 +6,7 @@
 //   3. dQ     : one work-group per block of queries, loops over key tiles, dQ^T
 //               accumulates in registers                           (3 GEMMs per tile pair)
 // or, above D = 64 where the workspace holds dS: 1, 2 (which also stores dS), and
-//   3b. dQ    : the same from the stored dS                        (1 GEMM per tile pair; HBM-bound)
+//   3b. dQ    : the same from the stored dS                        (1 GEMM per tile pair; waits for dS)
 // or, for calls of few work-groups: 1, then 2 and 3 side by side in one launch.
 // With dP = dO V^T and dS = P o (dP - delta):
 //   dV = P^T dO,  dK = scale * dS^T Q,  dQ = scale * dS K.
@@ -763,9 +763,9 @@ __device__ __forceinline__ void dq_rows_out(const BwdArgs &a, f32x16 (&dq)[U / 3
     {
         // The accumulator holds 4 consecutive columns of one row per register group: stored
         // directly, every instruction writes 8-byte pieces of 32 rows.  The rows go through the
-        // wave's staging area in LDS instead and leave whole, 16 bytes per lane.  The areas that
-        // lie in ring position 2 move to the position that the last two tiles did not use (other
-        // waves may still be reading those).
+        // wave's staging area stg instead and leave whole, 16 bytes per lane.  (From dQ's ring the areas that
+        // lie in ring position 2 have moved to the position that the last two tiles did not use: other
+        // waves may still be reading those.)
         const float sc = a.scale;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
@@ -1198,7 +1198,8 @@ attn_bwd_dq_kernel(const BwdArgs a)
 
 // ---------------------------------------------------------------------------------------
 // 3b. dQ from the dS that the dK/dV kernel stored: one product instead of three, bound by reading dS
-// (2 bytes a score) from HBM.  Work-group = NW waves, wave = 32 queries, loop over tiles of 32 keys.
+// (2 bytes a score) from HBM where the launch is long (rates: see ds_plan).  Work-group = NW waves, wave = 32
+// queries, loop over tiles of 32 keys.
 // The K tile (in the layout above, shared) and the waves' dS blocks (each read by its wave alone) go
 // global -> LDS directly, kRing - 1 tiles ahead: about 100 KB in flight per unit.
 // A dS block holds 8-byte groups of 4 consecutive queries of a key; in the order in which the producers
@@ -1799,10 +1800,11 @@ int dkdv_split_plan(int BHkv, int group, int S, int Sk, int D, bool causal, int 
 bool bwd_is_small(int BHkv, int group, int S, int Sk, int D) { return takes_bwd_small(BHkv, group, S, Sk, D); }
 
 // dS kept for dQ (above D = 64): K/V heads whose dS is held at a time in `room` bytes, 0: dS is not kept.
-// The dK/dV kernel stores it once (3 .. 7 % longer: the stores) and the dQ kernel then has one product per
-// tile instead of three, at the rate at which dS comes from HBM (5.2 .. 5.9 TB/s).  Whole backward, before
-// -> after, us: B=4 H=32 S=4096 D=128 3220 -> 3075, causal 1760 -> 1670; B=1 H=16 S=16384 causal 3245 ->
-// 2940; B=4 H=16 S=4096 D=256 causal 2000 -> 1660; 8 heads of 1683 rows 64 -> 54; 4 of 2415 D=256 144 -> 97.
+// The dK/dV kernel stores it once (11 .. 15 % longer: the stores) and the dQ kernel then has one product per
+// tile instead of three and waits for dS: by the counters it reads 6.1 TB/s with 16 heads of 16384 rows, 4.4 .. 5.2 with
+// many of 2048 .. 4096 (D = 256: 4.8), 3.0 .. 3.5 in the short launches of few rows on long keys.  Whole backward, before ->
+// after, us: B=4 H=32 S=4096 D=128 3322 -> 3186, causal 1818 -> 1722; B=1 H=16 S=16384 causal 3270 -> 3083; B=4 H=16
+// S=4096 D=256 causal 2046 -> 1707; 8 heads of 1683 rows 78 -> 62; 4 of 2415 D=256 161 -> 102.
 // At D = 64 dQ's products are half as long and dS as large: 64 heads of 8192 rows causal have 4.3 GB of
 // it, 0.75 ms to read against 0.78 for the whole dQ kernel that does not.
 // Not for one or two long heads at D <= 128, whose dQ is better split over the keys (one of 12784 rows
@@ -1828,7 +1830,8 @@ int ds_plan(int BHkv, int group, int S, int Sk, int D, bool causal, size_t room)
 // both: a fit to 160 problems of up to 256 work-groups, 3 .. 9 % rms).  Whole backward, us: 6 heads of 940
 // rows D = 64 causal 35 -> 19, 12 of 1037 44 -> 33, 1 of 1181 D = 96 45 -> 23, 3 of 2099 D = 128 causal 58 ->
 // 36, 9 of 329 D = 64 causal 22 -> 15, 3 of 134 D = 256 causal 23 -> 16; 0.75 on average over 200 random
-// problems, one of them slower by more than 2 % (36 -> 9 heads of 75 rows D = 256: 30.5 -> 33).  Not beyond a
+// problems; against dS kept one of them is slower by more than 2 % (36 -> 9 heads of 75 rows D = 256: 30.5 -> 33), against
+// dQ, then dK/dV none of 1600 by more than 1.3 %.  Not beyond a
 // work-group per unit: 26 heads of 1776 rows D = 128 causal 101 -> 110, 13 of 4773 D = 64 175 -> 198 (uncut).
 PairPlan pair_plan(int BHkv, int group, int S, int Sk, int D, bool causal, size_t room)
 {
