@@ -229,7 +229,6 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
     // that nobody reads before a later barrier.  (Spread between the consumers' MFMAs instead they
     // measured the same or up to 2.5 % slower.)
     auto dma_stat = [&](int t, int rs) __attribute__((always_inline)) {
-        if (w != C::kStatWave) return;
         if (DS)
             dma4(Wd, lds0 + C::kOffStat + rs * C::kStatBytes, stat_voff, (uint32_t)(t * C::kRows * 4));
         else
@@ -255,9 +254,13 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
     // kAhead-1 newer slots may stay in flight) and everyone must be done with slot t-2.
     auto slot_barrier = [&]() {
         if (producer) {
-            // (DS: a slot's two stores follow its transfer and need no wait of their own)
-            if (w == C::kStatWave) wait_vm_and_barrier<DS ? 3 * C::kAhead - 1 : C::kAhead - 1>();
-            else wait_vm_and_barrier<DS ? 63 : 0>();
+            // (DS: nobody waits for a producer's stores)
+            if (DS) wait_vm_and_barrier<63>();
+            else if (w == C::kStatWave) wait_vm_and_barrier<C::kAhead - 1>();
+            else wait_vm_and_barrier<0>();
+        } else if (DS && pair == C::kPairs - 1) {
+            constexpr int own = C::kDmaPerTensor % C::kPairs != 0 ? C::kDmaPerWave - 2 : C::kDmaPerWave;
+            wait_vm_and_barrier<(C::kAhead - 1) * (own + 1)>();
         } else if (C::kDmaPerTensor % C::kPairs != 0 && !extra) {
             wait_vm_and_barrier<(C::kAhead - 1) * (C::kDmaPerWave - 2)>();
         } else {
@@ -287,11 +290,13 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
     if (producer) {
         // The statistics of the first kAhead slots are requested before anything else (the
         // consumers request the rows meanwhile).
-        set_head(bh0 + g_first);
+        if (!DS) {
+            set_head(bh0 + g_first);
 #pragma unroll
-        for (int i = 0; i < C::kAhead; ++i) {
-            dma_stat(tf, i);
-            advance_fetch();
+            for (int i = 0; i < C::kAhead; ++i) {
+                if (w == C::kStatWave) dma_stat(tf, i);
+                advance_fetch();
+            }
         }
         // K and V fragments (B operands): lane holds K[key][16ks + 8h .. +7].
         // The 32 rows are fetched whole (an instruction covers 64 / (D/8) consecutive rows instead
@@ -354,7 +359,7 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
             slot_barrier();
             int rd = rs + C::kAhead;
             rd = rd >= C::kRing ? rd - C::kRing : rd;
-            dma_stat(tf, rd);
+            if (!DS && w == C::kStatWave) dma_stat(tf, rd);
             if (active(t)) {
                 const char *Qt = smem + rs * C::kSlotBytes;
                 const float *st = reinterpret_cast<const float *>(smem + C::kOffStat + rs * C::kStatBytes);
@@ -427,11 +432,8 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
                 x[128] = d0;
                 x[192] = d1;
                 if (DS) store_ds(d0, d1);
-            } else if (DS) {  // (past the row's end: only counted by the waits)
-                const elem8 none = {};
-                store_ds(none, none);
             }
-            advance_fetch();
+            if (!DS) advance_fetch();
             rs = ring_next(rs);
             ++t;
             if (DS) {
@@ -447,7 +449,7 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
                 }
             }
         }
-        wait_vm_and_barrier<0>();  // the consumers' last slot
+        wait_vm_and_barrier<DS ? 63 : 0>();  // the consumers' last slot
     } else {
         // Consumers.  Wave 4+cw accumulates ONE output for the 64 keys of two producers
         // (2*(cw>>1) and the next): dV^T += dO^T P for even cw, dK^T += Q^T dS for odd cw.
@@ -529,6 +531,7 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
 #pragma unroll
         for (int i = 0; i < C::kAhead; ++i) {
             dma_pieces(tf, i);
+            if (DS && pair == C::kPairs - 1) dma_stat(tf, i);
             advance_fetch();
         }
         int rs = 0;  // ring position of the producers' slot; the consumers' is one behind
@@ -539,6 +542,7 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
             int rd = rs + C::kAhead;
             rd = rd >= C::kRing ? rd - C::kRing : rd;
             dma_pieces(tf, rd);
+            if (DS && pair == C::kPairs - 1) dma_stat(tf, rd);
             advance_fetch();
             if (g > 0) consume(tp, g - 1, rs == 0 ? C::kRing - 1 : rs - 1);
             rs = ring_next(rs);
