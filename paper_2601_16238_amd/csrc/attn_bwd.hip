@@ -681,19 +681,11 @@ __global__ void __launch_bounds__(256) attn_bwd_dkdv_merge_kernel(const BwdArgs 
 // accumulator in registers), loop over key tiles of 64 rows.  K and V tiles go global -> LDS
 // directly, two tiles ahead, into a ring of three.
 //
-// LDS layout of a tile tensor.  One wave-wide transfer fills 1 KB in lane order, and a lane
-// may fetch any 16-byte chunk, so within such a piece (P rows of a tile: 4 at D = 128, 8 at
-// D = 64) the chunks are stored chunk-major: chunk c of row r sits at 16 * (c * P + r % P),
-// and consecutive pieces are P * 16 bytes apart more than their size.  Then
-//  - the address of a fragment is a per-lane constant plus compile-time terms for the
-//    contraction step, the d block, the sub-tile and the ring position: with the loop unrolled
-//    over the ring positions every LDS access is one register plus an immediate offset and the
-//    loop has no vector instruction for addressing (it had 16 per sub-tile with a row-major,
-//    XOR-swizzled tile);
-//  - 16 consecutive rows at a fixed chunk fall into 16 different 16-byte bank groups (the row
-//    reads for S^T = K Q^T and dP^T = V dO^T), and the 64 lanes of a transpose read (4 rows x
-//    4 chunks x 2 halves per half-wave, for dQ^T += K^T dS^T) cover 512 contiguous bytes:
-//    both are conflict free.
+// LDS layout of a tile tensor: pieces (see Pieces).  The address of a fragment is a per-lane constant
+// plus compile-time terms for the contraction step, the d block, the sub-tile and the ring position: with
+// the loop unrolled over the ring positions every LDS access is one register plus an immediate offset and
+// the loop has no vector instruction for addressing (it had 16 per sub-tile with a row-major,
+// XOR-swizzled tile).
 // ---------------------------------------------------------------------------------------
 template <int D, int NW>
 struct DqCfg {
@@ -703,32 +695,21 @@ struct DqCfg {
     static constexpr int kSub = kTile / 32;          // 32-key sub-tiles per tile
     static constexpr int kRing = 3;
     static constexpr int kRowBytes = D * 2;
-    static constexpr int kPieceRows = 1024 / kRowBytes;       // rows one 1 KB transfer fills
-    static constexpr int kPieceBytes = 1024 + kPieceRows * 16;
+    using L = Pieces<D>;
+    static constexpr int kPieceRows = L::kRows;               // rows one 1 KB transfer fills
     static constexpr int kPieces = kTile / kPieceRows;        // per tensor
-    // D = 256 (two rows per piece): the uniform piece distance that spreads the row reads over
-    // the banks puts the four rows of a transpose read into overlapping banks.  Pieces are laid
-    // out in pairs instead: the second of a pair 1024 + 128 bytes after the first (the two pieces
-    // a transpose read touches then fall into different halves of the banks), pairs 2 * 1024 +
-    // 128 + 160 bytes apart (16 consecutive rows at a fixed chunk: 16 different 16-byte bank groups).
-    static constexpr int kPairBytes = 2 * 1024 + 128 + 160;
-    static constexpr int piece_base(int piece)
-    {
-        return D > 128 ? (piece >> 1) * kPairBytes + (piece & 1) * (1024 + 128) : piece * kPieceBytes;
-    }
-    static constexpr int kTensorBytes = piece_base(kPieces);     // K part of a tile; V follows
+    static constexpr int kTensorBytes = L::base(kPieces);        // K part of a tile; V follows
     static constexpr int kTileBytes = 2 * kTensorBytes;
     // D <= 128: the rows of Q, dO and O reach the fragment registers through a per-wave staging
     // area of 32 rows in the tile tensors' layout (see the kernel's prologue).  The areas start
     // at ring position 2, which is free until the first barrier of the key loop.
     static constexpr bool kStageRows = true;
-    static constexpr int kStageBytes = kStageRows ? piece_base(32 / kPieceRows) : 0;
+    static constexpr int kStageBytes = kStageRows ? L::base(32 / kPieceRows) : 0;
     static constexpr int kLdsBytes = kRing * kTileBytes > 2 * kTileBytes + NW * kStageBytes
                                          ? kRing * kTileBytes : 2 * kTileBytes + NW * kStageBytes;
     static constexpr int kDmaPerTile = 2 * kPieces;           // wave-wide 1 KB transfers
     static constexpr int kDmaPerWave = (kDmaPerTile + NW - 1) / NW;
-    static constexpr int kChunkStep = kPieceRows * 16;        // next 16-byte chunk of a row
-    static constexpr int kRows16 = piece_base(16 / kPieceRows);      // 16 rows further
+    static constexpr int kRows16 = L::kRows16;                // 16 rows further
     static_assert(16 % kPieceRows == 0, "sub-tiles start at piece boundaries");
     static_assert(kLdsBytes <= 160 * 1024, "LDS budget of a gfx950 CU exceeded");
 };
@@ -741,9 +722,7 @@ __device__ __forceinline__ void dq_rows_out(const BwdArgs &a, f32x16 (&dq)[U / 3
     constexpr int DB = U / 32, CPR = D / 8, RPI = 64 / CPR;
     const int r = l & 31, h = l >> 5, lr = l / CPR, lc = l % CPR, S = a.S, Dr = a.Dr;
     const int qc = min(q0 + r, S - 1);
-    auto at = [](int row, int chunk) {
-        return C::piece_base(row / C::kPieceRows) + (chunk * C::kPieceRows + row % C::kPieceRows) * 16;
-    };
+    auto at = [](int row, int chunk) { return Pieces<D>::at(row, chunk); };
     if (U == D && a.rope_cos) {
         // Q was rotated before the forward: what has been accumulated is the gradient of the
         // rotated rows; the gradient of the unrotated ones is its image under the transpose of
@@ -792,6 +771,7 @@ template <int D, int U, int NW, bool CAUSAL, bool SPLIT>
 __device__ __forceinline__ void bwd_dq(const BwdArgs &a, int block, int ntile, int part)
 {
     using C = DqCfg<D, NW>;
+    using L = Pieces<D>;
     constexpr int KS = U / 16, DB = U / 32, PR = C::kPieceRows;
     // A wave's transfers per tile are issued between the MFMAs of the tile's first step instead of
     // in a burst after the barrier wherever their number divides that of the MFMAs (measured at
@@ -831,9 +811,7 @@ __device__ __forceinline__ void bwd_dq(const BwdArgs &a, int block, int ntile, i
     const int n_kt = max(0, (CAUSAL ? min(Sk, q_end + coff) : Sk) + C::kTile - 1) / C::kTile;
 
     // byte offset of 16-byte chunk `chunk` of row `row` within a tile tensor
-    auto at = [](int row, int chunk) {
-        return C::piece_base(row / PR) + (chunk * PR + row % PR) * 16;
-    };
+    auto at = [](int row, int chunk) { return L::at(row, chunk); };
 
     // ---- streaming of tile kt into ring position pos; rows past S-1 read as zero
     const int Dr = a.Dr;  // columns Dr..D-1 read as zero (offset past the end of the resource)
@@ -844,16 +822,15 @@ __device__ __forceinline__ void bwd_dq(const BwdArgs &a, int block, int ntile, i
     const uint32_t lds0 = lds_address(smem);
     // (the descriptors are passed by value: captured by reference through two levels of
     // lambdas the compiler no longer proves them wave-uniform)
-    // lane l lands at byte 16 * l of a piece: chunk l / PR of the piece's row l % PR.  The
-    // piece's first row goes into the scalar offset (which takes part in the range check like
+    // lane l lands at byte 16 * l of a piece.  The piece's first row goes into the scalar offset (which takes part in the range check like
     // the per-lane one), so one per-lane offset serves every transfer.
-    const uint32_t voff = (l / PR) * 8 < Dr ? (l % PR) * row_bytes + ((l / PR) << 4) : head_bytes;
+    const uint32_t voff = Pieces<D>::lane_offset(l, row_bytes, Dr, head_bytes);
     auto dma_piece = [&](int kt, int pos, int n, desc_t Kd, desc_t Vd) __attribute__((always_inline)) {
         // wave-uniform 1 KB piece; a wave with nothing left repeats an earlier piece so
         // that every wave has the same number of transfers in flight
         const int i = (w + n * NW) % C::kDmaPerTile;
         const int tensor = i / C::kPieces, piece = i % C::kPieces;
-        const uint32_t dst = lds0 + pos * C::kTileBytes + tensor * C::kTensorBytes + C::piece_base(piece);
+        const uint32_t dst = lds0 + pos * C::kTileBytes + tensor * C::kTensorBytes + L::base(piece);
         const uint32_t soff = (kt * C::kTile + piece * PR) * row_bytes;
         if (kBetween) dma16_between(tensor ? Vd : Kd, dst, voff, soff);
         else dma16(tensor ? Vd : Kd, dst, voff, soff);
@@ -885,13 +862,13 @@ __device__ __forceinline__ void bwd_dq(const BwdArgs &a, int block, int ntile, i
             if (a.stats_in_dq) to[j] = ld_row16(a.O + off, lc * 8, Dr);
         }
         char *stage = smem + 2 * C::kTileBytes + w * C::kStageBytes;
-        const int rd = at(r, h);  // chunk h of row r; contraction step ks: 2 ks chunks further
+        const int rd = at(r, h);  // chunk h of row r
         auto sort_rows = [&](const u32x4 (&t)[kLoads], elem8 (&f)[KS]) __attribute__((always_inline)) {
 #pragma unroll
             for (int j = 0; j < kLoads; ++j) *(u32x4 *)(stage + at(RPI * j + lr, lc)) = t[j];
             asm volatile("" ::: "memory");  // a wave's LDS accesses execute in order
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) f[ks] = *(const elem8 *)(stage + rd + ks * 2 * C::kChunkStep);
+            for (int ks = 0; ks < KS; ++ks) f[ks] = *(const elem8 *)(stage + rd + L::step(ks));
             asm volatile("" ::: "memory");
         };
         sort_rows(tq, qf);
@@ -944,8 +921,7 @@ __device__ __forceinline__ void bwd_dq(const BwdArgs &a, int block, int ntile, i
 
     const float c = a.scale_log2e;
     // Per-lane LDS addresses within ring position 0 (lo) and 2 (hi): row fragment = chunk h of
-    // row r (contraction step ks: 2 ks chunks further); transpose reads = rows 4h+e (+8), the
-    // 64 bytes of d block 0 of each row (d block db: 4 db chunks further).  Everything else --
+    // row r; transpose reads = rows 4h+e (+8), the 64 bytes of d block 0 of each row.  Everything else --
     // ring position, tensor, sub-tile, 16-row step -- is a compile-time offset.  Position 2
     // gets registers of its own because an LDS instruction's immediate reaches 64 KB and the
     // ring is longer than that at D = 128.  The values are made opaque so that the compiler
@@ -975,7 +951,7 @@ __device__ __forceinline__ void bwd_dq(const BwdArgs &a, int block, int ntile, i
         s = mfma32(*(const elem8 *)(Kt + kb2 * 2 * C::kRows16 + rowa), qf[0], zero);
 #pragma unroll
         for (int ks = 1; ks < KS; ++ks)
-            s = mfma32(*(const elem8 *)(Kt + kb2 * 2 * C::kRows16 + ks * 2 * C::kChunkStep + rowa), qf[ks], s);
+            s = mfma32(*(const elem8 *)(Kt + kb2 * 2 * C::kRows16 + L::step(ks) + rowa), qf[ks], s);
     };
     // the same with the transfers of tile kt_next (into ring position pos_next) between the MFMAs
     auto step_s_fetch = [&](const char *Kt, int rowa, f32x16 &s, int kt_next, int pos_next, desc_t Kd,
@@ -986,7 +962,7 @@ __device__ __forceinline__ void bwd_dq(const BwdArgs &a, int block, int ntile, i
         for (int i = 0; i < 16; ++i) zero[i] = 0.f;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            s = mfma32(*(const elem8 *)(Kt + ks * 2 * C::kChunkStep + rowa), qf[ks], ks ? s : zero);
+            s = mfma32(*(const elem8 *)(Kt + L::step(ks) + rowa), qf[ks], ks ? s : zero);
             if ((ks + 1) % kEvery == 0 && (ks + 1) / kEvery <= C::kDmaPerWave) dma_piece(kt_next, pos_next, (ks + 1) / kEvery - 1, Kd, Vd);
         }
     };
@@ -995,7 +971,7 @@ __device__ __forceinline__ void bwd_dq(const BwdArgs &a, int block, int ntile, i
         dp = mfma32(*(const elem8 *)(Vt + kb2 * 2 * C::kRows16 + rowa), gf[0], nd);  // ends as dP - delta
 #pragma unroll
         for (int ks = 1; ks < KS; ++ks)
-            dp = mfma32(*(const elem8 *)(Vt + kb2 * 2 * C::kRows16 + ks * 2 * C::kChunkStep + rowa), gf[ks], dp);
+            dp = mfma32(*(const elem8 *)(Vt + kb2 * 2 * C::kRows16 + L::step(ks) + rowa), gf[ks], dp);
     };
     auto step_p = [&](int k_lo, f32x16 &s) __attribute__((always_inline)) {  // S -> P
         const bool need_mask = (k_lo + 32 > Sk) || (CAUSAL && k_lo + 31 > q0e);
@@ -1020,7 +996,7 @@ __device__ __forceinline__ void bwd_dq(const BwdArgs &a, int block, int ntile, i
         for (int cc = 0; cc < 2; ++cc) {
 #pragma unroll
             for (int db = 0; db < DB; ++db) {
-                const int off = (kb2 * 2 + cc) * C::kRows16 + db * 4 * C::kChunkStep;
+                const int off = (kb2 * 2 + cc) * C::kRows16 + db * L::kBlock;
                 const elem8 kT = join8(lds_read_tr((const elem *)(Kt + off + tra0)),
                                        lds_read_tr((const elem *)(Kt + off + tra1)));
                 dq[db] = mfma32(kT, sb[cc], dq[db]);
@@ -1042,9 +1018,9 @@ __device__ __forceinline__ void bwd_dq(const BwdArgs &a, int block, int ntile, i
         auto read = [&](int n) __attribute__((always_inline)) {
             if (n < 2 * KS) {
                 f[n] = *(const elem8 *)(Kt + (n / KS) * C::kTensorBytes + kb2 * 2 * C::kRows16 +
-                                        (n % KS) * 2 * C::kChunkStep + rowa);
+                                        L::step(n % KS) + rowa);
             } else if (n < N) {
-                const int off = (kb2 * 2 + (n - 2 * KS) / DB) * C::kRows16 + ((n - 2 * KS) % DB) * 4 * C::kChunkStep;
+                const int off = (kb2 * 2 + (n - 2 * KS) / DB) * C::kRows16 + ((n - 2 * KS) % DB) * L::kBlock;
                 f[n] = join8(lds_read_tr((const elem *)(Kt + off + tra0)), lds_read_tr((const elem *)(Kt + off + tra1)));
             }
         };
@@ -1211,14 +1187,14 @@ attn_bwd_dq_kernel(const BwdArgs a)
 // ---------------------------------------------------------------------------------------
 template <int D, int NW>
 struct DqsCfg : DqCfg<D, 4> {
-    using T = DqCfg<D, 4>;  // (for the layout of a piece)
     static constexpr int kBlk = NW * 32;
     static constexpr int kTile = 32;
-    static constexpr int kPieces = kTile / T::kPieceRows;
-    static constexpr int kKBytes = T::piece_base(kPieces);
+    using L = Pieces<D>;
+    static constexpr int kPieces = kTile / L::kRows;
+    static constexpr int kKBytes = L::base(kPieces);
     static constexpr int kTileBytes = kKBytes + NW * kDsBlock * 2;
     static constexpr int kRing = 160 * 1024 / kTileBytes < 6 ? 160 * 1024 / kTileBytes : 6;
-    static constexpr int kStage = T::piece_base(32 / T::kPieceRows);
+    static constexpr int kStage = L::base(32 / L::kRows);
     static constexpr int kLdsBytes = kRing * kTileBytes > NW * kStage ? kRing * kTileBytes : NW * kStage;
     static constexpr int kDmaK = (kPieces + NW - 1) / NW;     // transfers of a wave per tile: K, then dS
     static constexpr int kDma = kDmaK + 2;
@@ -1231,6 +1207,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW
 attn_bwd_dq_ds_kernel(const BwdArgs a)
 {
     using C = DqsCfg<D, NW>;
+    using L = Pieces<D>;
     constexpr int DB = U / 32, PR = C::kPieceRows;
     extern __shared__ __attribute__((aligned(1024))) char smem[];
 
@@ -1257,7 +1234,7 @@ attn_bwd_dq_ds_kernel(const BwdArgs a)
                                 (uint32_t)n_row * (kDsBlock * 2u));
     const uint32_t row_bytes = (uint32_t)a.kv_stride_s * 2u;
     const uint32_t lds0 = lds_address(smem);
-    const uint32_t voff = (l / PR) * 8 < Dr ? (l % PR) * row_bytes + ((l / PR) << 4) : head_bytes;
+    const uint32_t voff = Pieces<D>::lane_offset(l, row_bytes, Dr, head_bytes);
     // (tiles past the last read as zero, or are keys that nobody uses)
     auto fetch = [&](int kt, int pos) __attribute__((always_inline)) {
         const uint32_t dst = lds0 + pos * C::kTileBytes;
@@ -1267,7 +1244,7 @@ attn_bwd_dq_ds_kernel(const BwdArgs a)
 #pragma unroll
         for (int n = 0; n < C::kDmaK; ++n) {
             const int piece = w + n * NW;
-            dma16_between(Kd, dst + C::piece_base(piece), voff, (kt * 32 + piece * PR) * row_bytes);
+            dma16_between(Kd, dst + L::base(piece), voff, (kt * 32 + piece * PR) * row_bytes);
         }
     };
 #pragma unroll
@@ -1279,7 +1256,7 @@ attn_bwd_dq_ds_kernel(const BwdArgs a)
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
         const int row = 8 * j + 4 * h + ((l & 15) >> 2), chunk = 2 * ((l >> 4) & 1) + ((l >> 1) & 1);
-        tr[j] = C::piece_base(row / PR) + (chunk * PR + row % PR) * 16 + (l & 1) * 8;
+        tr[j] = L::at(row, chunk) + (l & 1) * 8;
     }
     int ds = C::kKBytes + w * (kDsBlock * 2) + h * 256 + (((l >> 4) & 1) * 2 + (l & 1)) * 64 + ((l & 15) >> 2) * 16 +
              ((l >> 1) & 1) * 8;
@@ -1303,7 +1280,7 @@ attn_bwd_dq_ds_kernel(const BwdArgs a)
                                       lds_read_tr((const elem *)(T + ds + cc * 1024 + 512)));
 #pragma unroll
                 for (int db = 0; db < DB; ++db) {
-                    const int off = cc * C::kRows16 + db * 4 * C::kChunkStep;
+                    const int off = cc * C::kRows16 + db * L::kBlock;
                     const elem8 kT = join8(lds_read_tr((const elem *)(T + off + tr[0])),
                                            lds_read_tr((const elem *)(T + off + tr[1])));
                     dq[db] = mfma32(kT, b, dq[db]);

@@ -194,6 +194,46 @@ __device__ __forceinline__ void dma4(desc_t desc, uint32_t lds_addr, uint32_t vo
                  : "memory", "m0");
 }
 #pragma clang diagnostic pop
+// Layout of a tile's rows in LDS as the direct transfers write them.  One wave-wide transfer of 16 bytes per lane
+// fills a piece of 1 KB, kRows rows of D columns, in lane order; which 16-byte chunk a lane fetches is free.  Four
+// neighbouring lanes fetch 64 contiguous bytes of a row (the rows of a piece one after the other, then the next
+// 64 bytes of each): a transfer then passes the compute unit's vector-memory path in 16 cycles.  With neighbouring
+// lanes in different rows it takes 64, one per lane (tiles from the L2: 38 B/ns per unit against 130).
+//  - Row reads: 16 lanes take one chunk of 16 consecutive rows.  The rows of a piece are 64 bytes apart, and the
+//    distances of the pieces put those of the others into the 16-byte bank groups between: conflict free.  (D = 64:
+//    rows 4 .. 7 of a piece hold the chunks of a pair in exchanged order.)
+//  - Transpose reads: 32 lanes take 4 rows x 64 bytes, 256 contiguous bytes (D = 256: 128 in either piece of a pair,
+//    in different halves of the banks).
+//  - Contraction step, 32-column block, sub-tile and 16-row step are compile-time distances.
+template <int D>
+struct Pieces {
+    static constexpr int kRows = 1024 / (D * 2);
+    static constexpr int kBlock = 4 * kRows * 16;  // the next 32 columns
+    __host__ __device__ static constexpr int base(int piece)
+    {
+        return D > 128 ? (piece >> 1) * (2 * 1024 + 128 + 144) + (piece & 1) * (1024 + 128)
+                       : piece * (1024 + (D > 64 ? 16 : 32));
+    }
+    __host__ __device__ static constexpr int turn(int row) { return D == 64 ? (row >> 2) & 1 : 0; }
+    // byte offset of chunk `chunk` of row `row`
+    __host__ __device__ static constexpr int at(int row, int chunk)
+    {
+        return base(row / kRows) + (chunk / 4) * kBlock + (row % kRows) * 64 + ((chunk % 4) ^ turn(row)) * 16;
+    }
+    // at(row, 2 ks + h) - at(row, h) for h = 0, 1
+    __host__ __device__ static constexpr int step(int ks) { return (ks / 2) * kBlock + (ks % 2) * 32; }
+    static constexpr int kRows16 = base(16 / kRows);  // 16 rows further
+    // what lane l of a transfer fetches: row of the piece, and chunk
+    __device__ static int lane_row(int l) { return (l / 4) % kRows; }
+    __device__ static int lane_chunk(int l) { return l / (4 * kRows) * 4 + ((l % 4) ^ turn(lane_row(l))); }
+    // ... as a byte offset into a raw buffer of rows row_bytes apart of which dr columns are real; other columns:
+    // `past`, an offset past its end
+    __device__ static uint32_t lane_offset(int l, uint32_t row_bytes, int dr, uint32_t past)
+    {
+        return lane_chunk(l) * 8 < dr ? lane_row(l) * row_bytes + lane_chunk(l) * 16 : past;
+    }
+};
+
 // Wait until at most N of this wave's vector-memory operations are outstanding and all its
 // LDS operations are done, then join the work-group barrier.  Unlike __syncthreads this
 // leaves the newest global -> LDS transfers in flight across the barrier.

@@ -42,25 +42,18 @@ struct FwdCfg {
     static constexpr int kThreads = NW * 64;
     static constexpr int kBR = NW * 32;
     static constexpr int kBC = 64;
-    // K tile: one wave-wide transfer of 16 B per lane fills a 1 KB piece of kKRowsPerDma
-    // rows; within a piece the 16-byte chunks are stored chunk-major (chunk c of row r at
-    // 16 * (c * rows + r % rows)) and consecutive pieces lie 16 * rows bytes further apart than
-    // their size.  The fragment a lane needs for contraction step ks is then at a per-lane
-    // constant plus ks * kKStep -- one address register instead of one per step -- and the 16
-    // rows that one quarter of a wave reads at a fixed chunk fall into 16 different 16-byte
-    // bank groups.
-    static constexpr int kKRowsPerDma = 1024 / (D * 2);        // rows one wave-wide 16 B/lane load fills
-    static constexpr int kKPieceBytes = 1024 + kKRowsPerDma * 16;
-    static constexpr int kKDmas = kBC / kKRowsPerDma;          // such loads per tile
-    static constexpr int kKTile = kKDmas * kKPieceBytes / 2;   // in elements
+    // K tile: in pieces (see Pieces), one wave-wide transfer each.  The fragment a lane needs for
+    // contraction step ks is at a per-lane constant plus a distance that is known at compile time --
+    // one address register instead of one per step.
+    using L = Pieces<D>;
+    static constexpr int kKDmas = kBC / L::kRows;              // transfers per tile
+    static constexpr int kKTile = L::base(kKDmas) / 2;         // in elements
     static constexpr int kKHalf = kKTile / 2;                  // 32 rows further
-    static constexpr int kKStep = 2 * kKRowsPerDma * 16 / 2;   // next contraction step, in elements
     static constexpr int kKDmaPerWave = (kKDmas + NW - 1) / NW;
-    // V tile: the same transfers and layout as the K tile (row-major rows in chunk-major pieces);
-    // it is transposed by the reads (LDS transpose read), whose 64 lanes fetch 4 rows x 4 chunks
-    // x 2 halves = 512 contiguous bytes of a piece.
-    static constexpr int kVTile = kKTile;                                  // in elements
-    static constexpr int kVRows16 = (16 / kKRowsPerDma) * kKPieceBytes;   // 16 rows further, in bytes
+    // V tile: the same transfers and layout as the K tile; it is transposed by the reads (LDS transpose
+    // read).
+    static constexpr int kVTile = kKTile;                      // in elements
+    static constexpr int kVRows16 = L::kRows16;                // 16 rows further, in bytes
     static constexpr bool kMain = MAIN;
     // V tiles: two, or three for the main loop, which multiplies P of a sub-tile by V one sub-tile
     // later and therefore still reads tile kt-1 while tile kt+1 is arriving
@@ -149,20 +142,21 @@ attn_fwd_kernel(const FwdArgs a)
     const uint32_t tile_bytes = C::kBC * row_bytes;
     // K and V go global -> LDS directly (no registers): one wave-wide transfer of 16 B per lane
     // fills 1 KB of LDS in lane order; lane l fetches the chunk that belongs at its position of the
-    // piece, chunk l / rows of row l % rows.  The piece's first row goes into the scalar
+    // piece.  The piece's first row goes into the scalar
     // offset (which takes part in the range check like the per-lane one).  The transfers are
     // issued from assembly, out of the compiler's sight (it would otherwise make the wave wait for
     // all of them before its next transpose read of LDS); tile_barrier() orders them against the
     // reads.  They fill buffers that nobody reads before the next barrier.
-    constexpr int PR = C::kKRowsPerDma;
-    const uint32_t k_voff = (l / PR) * 8 < Dr ? (l % PR) * row_bytes + ((l / PR) << 4) : head_bytes;
+    using L = typename C::L;
+    constexpr int PR = L::kRows;
+    const uint32_t k_voff = L::lane_offset(l, row_bytes, Dr, head_bytes);
     auto dma_tile = [&](desc_t desc, uint32_t lds_tile, int kt) __attribute__((always_inline)) {
 #pragma unroll
         for (int n = 0; n < C::kKDmaPerWave; ++n) {
             // which 1 KB piece of the tile: wave-uniform
             const int ii = __builtin_amdgcn_readfirstlane(w) + n * NW;
             if (C::kKDmas % NW == 0 || ii < C::kKDmas)
-                dma16_between(desc, lds_tile + ii * C::kKPieceBytes, k_voff, kt * tile_bytes + ii * PR * row_bytes);
+                dma16_between(desc, lds_tile + L::base(ii), k_voff, kt * tile_bytes + ii * PR * row_bytes);
         }
     };
     auto dma_k = [&](int kt, int buf) __attribute__((always_inline)) {
@@ -192,20 +186,17 @@ attn_fwd_kernel(const FwdArgs a)
     // the compiler, so that buffer, sub-tile and step are folded into the 16-bit immediate
     // offset of the LDS instruction instead of into further address registers.  (The V region
     // starts beyond what an immediate reaches from zero, so its registers include its base.)
-    int k_lane = ((r / PR) * (C::kKPieceBytes / 2) + (h * PR + r % PR) * 8) * 2;
+    int k_lane = L::at(r, h);
     // transpose reads of a V tile: the 16-lane group reads rows 4h + e (e = 0..3; +8 for the
     // second read), 64 bytes of d block 0 of each row -- the keys of contraction half h in the
     // order the accumulator of S^T holds them
-    auto v_at = [](int row, int chunk) {
-        return (row / PR) * C::kKPieceBytes + (chunk * PR + row % PR) * 16;
-    };
-    int v_lane0 = 3 * C::kKTile * 2 + v_at(4 * h + ((l & 15) >> 2), 2 * ((l >> 4) & 1) + ((l >> 1) & 1)) + (l & 1) * 8;
-    int v_lane1 = 3 * C::kKTile * 2 + v_at(8 + 4 * h + ((l & 15) >> 2), 2 * ((l >> 4) & 1) + ((l >> 1) & 1)) + (l & 1) * 8;
+    int v_lane0 = 3 * C::kKTile * 2 + L::at(4 * h + ((l & 15) >> 2), 2 * ((l >> 4) & 1) + ((l >> 1) & 1)) + (l & 1) * 8;
+    int v_lane1 = 3 * C::kKTile * 2 + L::at(8 + 4 * h + ((l & 15) >> 2), 2 * ((l >> 4) & 1) + ((l >> 1) & 1)) + (l & 1) * 8;
     asm volatile("" : "+v"(k_lane), "+v"(v_lane0), "+v"(v_lane1));
     auto ld_k = [&](const elem *Kt, int kq, elem8 (&f)[4]) {
 #pragma unroll
         for (int t = 0; t < 4 && 4 * kq + t < KS; ++t)
-            f[t] = *(const elem8 *)((const char *)(Kt + (4 * kq + t) * C::kKStep) + k_lane);
+            f[t] = *(const elem8 *)((const char *)Kt + L::step(4 * kq + t) + k_lane);
     };
     auto mm_k = [&](int kq, const elem8 (&f)[4], f32x16 &t0) {
 #pragma unroll
@@ -217,7 +208,7 @@ attn_fwd_kernel(const FwdArgs a)
     auto ld_v = [&](int Vt, int cc, elem8 (&f)[4]) {
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
-            const char *p = smem + Vt + cc * C::kVRows16 + db * 4 * PR * 16;  // d block db: four chunks further
+            const char *p = smem + Vt + cc * C::kVRows16 + db * L::kBlock;
             f[db] = join8(lds_read_tr((const elem *)(p + v_lane0)), lds_read_tr((const elem *)(p + v_lane1)));
         }
     };
@@ -337,10 +328,10 @@ attn_fwd_kernel(const FwdArgs a)
         const uint32_t q_bytes = rows > 0 ? (uint32_t)(((int64_t)(rows - 1) * a.stride_s + Dr) * 2) : 0u;
         const desc_t Qd = make_desc(Qp + (int64_t)(rows > 0 ? row0 : 0) * a.stride_s, q_bytes);
         const uint32_t q_row_bytes = (uint32_t)a.stride_s * 2u;
-        const uint32_t q_voff = (l / PR) * 8 < Dr ? (l % PR) * q_row_bytes + ((l / PR) << 4) : q_bytes;
+        const uint32_t q_voff = L::lane_offset(l, q_row_bytes, Dr, q_bytes);
 #pragma unroll
         for (int n = 0; n < C::kKDmas / 2; ++n)
-            dma16_between(Qd, lds0 + q_stage + n * C::kKPieceBytes, q_voff,
+            dma16_between(Qd, lds0 + q_stage + L::base(n), q_voff,
                           (half * (C::kKDmas / 2) + n) * PR * q_row_bytes);
     }
     dma_k(0, 0);
@@ -369,9 +360,9 @@ attn_fwd_kernel(const FwdArgs a)
         // order of issue is the compiler's choice, everything is awaited
         if (rope) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * C::kKDmaPerWave) : "memory");
-        const char *Qs = smem + q_stage + ((r / PR) * C::kKPieceBytes + (h * PR + r % PR) * 16);
+        const char *Qs = smem + q_stage + L::at(r, h);
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const elem8 *)(Qs + ks * (C::kKStep * 2));
+        for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const elem8 *)(Qs + L::step(ks));
         // ... and are in registers before anybody may overwrite the staging space
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
@@ -583,9 +574,7 @@ attn_fwd_kernel(const FwdArgs a)
     constexpr int kWaveBytes = C::kKHalf * 2;
     char *const stg = smem + (NW != 8 ? 0 : w < 6 ? w * kWaveBytes
                                                   : (3 * C::kKTile + 3 * C::kVTile) * 2 + (w - 6) * kWaveBytes);
-    auto at = [](int row, int chunk) {
-        return (row / PR) * C::kKPieceBytes + (chunk * PR + row % PR) * 16;
-    };
+    auto at = [](int row, int chunk) { return L::at(row, chunk); };
     if (SPLIT) {
         // normalised fp32 partial result of this key range; a row that saw no key of the
         // range contributes O = 0 with LSE = -inf

@@ -40,26 +40,15 @@ struct WideCfg {
     static constexpr int kThreads = kNW * 64;
     static constexpr int kBR = kNW * 32;
     static constexpr int kBC = 64;
-    // K tile: wave-wide transfers of 16 B per lane fill 1 KB pieces of kPR rows, chunk-major
-    // inside a piece (chunk c of row r at 16 * (kPR c + r % kPR)), pieces 16 kPR bytes further
-    // apart than their size: the 16 rows a quarter wave reads at a fixed chunk fall into 16
-    // different 16-byte bank groups.
-    static constexpr int kPR = 1024 / (D * 2);
-    static constexpr int kKPieceBytes = 1024 + kPR * 16;
+    // K and V tiles: in pieces (see Pieces), one wave-wide transfer each.  V is only read with the LDS
+    // transpose read (the A operand of O^T += V^T P^T is V^T).
+    using L = Pieces<D>;
+    static constexpr int kPR = L::kRows;
     static constexpr int kKPieces = kBC / kPR;
-    static constexpr int kKTileBytes = kKPieces * kKPieceBytes;
+    static constexpr int kKTileBytes = L::base(kKPieces);
     static constexpr int kKHalfBytes = kKTileBytes / 2;     // 32 rows further
-    static constexpr int kKStepBytes = 2 * kPR * 16;        // next contraction step
     static constexpr int kKDmaPerWave = kKPieces / kNW;
-    // V tile: the same transfers and chunk-major pieces.  The tile is only read with the LDS
-    // transpose read (the A operand of O^T += V^T P^T is V^T), whose 32 lanes per half wave fetch
-    // 4 rows x 64 bytes.  With four or eight rows per piece those lie in one piece and the K
-    // tile's piece distance serves; with two rows per piece (D = 256) they are 128 contiguous
-    // bytes in each of two neighbouring pieces, which a distance of 1024 + 128 bytes puts into
-    // disjoint banks.
-    static constexpr int kVPieceBytes = D > 128 ? 1024 + 128 : kKPieceBytes;
-    static constexpr int kVTileBytes = kKPieces * kVPieceBytes;
-    static constexpr int kVRows16 = (16 / kPR) * kVPieceBytes;   // 16 rows further
+    static constexpr int kVTileBytes = kKTileBytes;
     static constexpr int kOffV = 2 * kKTileBytes;
     static constexpr int kLdsBytes = 2 * (kKTileBytes + kVTileBytes);
     static_assert(kKPieces % kNW == 0 && 2 * kKDmaPerWave == D / 16, "staging divides evenly");
@@ -77,6 +66,7 @@ __global__ void __launch_bounds__(WideCfg<D>::kThreads)
 attn_fwd_wide_kernel(const FwdArgs a)
 {
     using C = WideCfg<D>;
+    using L = typename C::L;
     constexpr int KS = D / 16, DB = D / 32, PR = C::kPR;
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
@@ -171,16 +161,14 @@ attn_fwd_wide_kernel(const FwdArgs a)
     const uint32_t lds0 = lds_address(smem);
     const uint32_t row_bytes = (uint32_t)a.kv_stride_s * 2u;
     const uint32_t tile_bytes = C::kBC * row_bytes;
-    // lane l of a transfer fetches chunk l / kPR of the piece's row l % kPR
-    const uint32_t k_voff = (l / PR) * 8 < Dr ? (l % PR) * row_bytes + ((l / PR) << 4) : head_bytes;
+    const uint32_t k_voff = L::lane_offset(l, row_bytes, Dr, head_bytes);
     // (The transfers are issued from assembly, out of the compiler's sight: it would otherwise
     // make the wave wait for all of them before its next transpose read of LDS.  stage() orders
     // them against the reads.)
     // piece n of this wave's share of tile kt; tensor 0: K, 1: V
     auto dma_piece = [&](int tensor, int kt, int buf, int n) __attribute__((always_inline)) {
         const int ii = w + n * C::kNW;  // which piece of the tile: wave-uniform
-        const uint32_t lds = tensor ? lds0 + C::kOffV + buf * C::kVTileBytes + ii * C::kVPieceBytes
-                                    : lds0 + buf * C::kKTileBytes + ii * C::kKPieceBytes;
+        const uint32_t lds = lds0 + (tensor ? C::kOffV : 0) + buf * C::kKTileBytes + L::base(ii);
         if constexpr (NT) dma16_between_nt(tensor ? Vd : Kd, lds, k_voff, kt * tile_bytes + ii * PR * row_bytes);
         else dma16_between(tensor ? Vd : Kd, lds, k_voff, kt * tile_bytes + ii * PR * row_bytes);
     };
@@ -203,17 +191,14 @@ attn_fwd_wide_kernel(const FwdArgs a)
         for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
     const float c = a.scale_log2e;
 
-    const int k_lane = (r / PR) * C::kKPieceBytes + (h * PR + r % PR) * 16;
+    const int k_lane = L::at(r, h);
     // transpose reads of the V tile: the 16-lane group reads rows 4h + e (e = 0..3; +8 for the
     // second read), 64 bytes of d block 0 of each row -- the keys of contraction half h in the
     // order the accumulator of S^T holds them
-    auto v_at = [](int row, int chunk) {
-        return (row / PR) * C::kVPieceBytes + (chunk * PR + row % PR) * 16;
-    };
     int v_lane[2];
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-        v_lane[j] = C::kOffV + v_at(8 * j + 4 * h + ((l & 15) >> 2), 2 * ((l >> 4) & 1) + ((l >> 1) & 1)) + (l & 1) * 8;
+        v_lane[j] = C::kOffV + L::at(8 * j + 4 * h + ((l & 15) >> 2), 2 * ((l >> 4) & 1) + ((l >> 1) & 1)) + (l & 1) * 8;
 
     // Per-lane LDS addresses of the current tile's fragments, set once per tile and made opaque
     // to the compiler, so that sub-tile, contraction step and d block are folded into the 16-bit
@@ -228,10 +213,10 @@ attn_fwd_wide_kernel(const FwdArgs a)
     // A operand of contraction step ks of sub-tile u's scores, and of MFMA i of its P V (the two 16-key
     // steps one after the other, d block by d block)
     auto ld_k = [&](int u, int ks) __attribute__((always_inline)) {
-        return *(const elem8 *)(smem + u * C::kKHalfBytes + k_base + ks * C::kKStepBytes);
+        return *(const elem8 *)(smem + u * C::kKHalfBytes + k_base + L::step(ks));
     };
     auto ld_v = [&](int u, int i) __attribute__((always_inline)) {
-        const char *p = smem + (2 * u + i / DB) * C::kVRows16 + (i % DB) * 4 * PR * 16;  // d block: four chunks further
+        const char *p = smem + (2 * u + i / DB) * L::kRows16 + (i % DB) * L::kBlock;
         return join8(lds_read_tr((const elem *)(p + v_base0)), lds_read_tr((const elem *)(p + v_base1)));
     };
     // S^T of sub-tile u, outside the fast loop
@@ -347,8 +332,7 @@ attn_fwd_wide_kernel(const FwdArgs a)
                 const int pc = (w - 1) + 3 * n;  // wave-uniform
                 if (pc >= 2 * C::kKPieces) continue;
                 const int tensor = pc / C::kKPieces, ii = pc % C::kKPieces, buf = (kt & 1) ^ 1;
-                const uint32_t lds = tensor ? lds0 + C::kOffV + buf * C::kVTileBytes + ii * C::kVPieceBytes
-                                            : lds0 + buf * C::kKTileBytes + ii * C::kKPieceBytes;
+                const uint32_t lds = lds0 + (tensor ? C::kOffV : 0) + buf * C::kKTileBytes + L::base(ii);
                 dma16_between_nt(tensor ? Vd : Kd, lds, k_voff, (kt + 1) * tile_bytes + ii * PR * row_bytes);
             }
         } else {
@@ -379,10 +363,10 @@ attn_fwd_wide_kernel(const FwdArgs a)
         const uint32_t q_bytes = rows > 0 ? (uint32_t)(((int64_t)(rows - 1) * a.stride_s + Dr) * 2) : 0u;
         const desc_t Qd = make_desc(a.Q + base + (int64_t)(rows > 0 ? row0 : 0) * a.stride_s, q_bytes);
         const uint32_t q_row_bytes = (uint32_t)a.stride_s * 2u;
-        const uint32_t q_voff = (l / PR) * 8 < Dr ? (l % PR) * q_row_bytes + ((l / PR) << 4) : q_bytes;
+        const uint32_t q_voff = L::lane_offset(l, q_row_bytes, Dr, q_bytes);
 #pragma unroll
         for (int n = 0; n < C::kKPieces / 2; ++n)
-            dma16_between(Qd, lds0 + q_stage + n * C::kKPieceBytes, q_voff,
+            dma16_between(Qd, lds0 + q_stage + L::base(n), q_voff,
                           (half * (C::kKPieces / 2) + n) * PR * q_row_bytes);
     }
     if (n_kt > 0) {
@@ -393,9 +377,9 @@ attn_fwd_wide_kernel(const FwdArgs a)
         // the query rows have landed once at most the transfers of K(0) and V(0) are outstanding
         if (n_kt > 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * C::kKDmaPerWave) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        const char *Qs = smem + q_stage + ((r / PR) * C::kKPieceBytes + (h * PR + r % PR) * 16);
+        const char *Qs = smem + q_stage + L::at(r, h);
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const elem8 *)(Qs + ks * C::kKStepBytes);
+        for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const elem8 *)(Qs + L::step(ks));
         // ... and are in registers before anybody may overwrite the staging space
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
@@ -549,9 +533,7 @@ attn_fwd_wide_kernel(const FwdArgs a)
         const int b = n_kt & 1;
         char *stg = smem + ((w >> 1) == 0 ? b * C::kKTileBytes : C::kOffV + b * C::kVTileBytes) +
                     (w & 1) * C::kKHalfBytes;
-        auto at = [](int row, int chunk) {
-            return (row / PR) * C::kKPieceBytes + (chunk * PR + row % PR) * 16;
-        };
+        auto at = [](int row, int chunk) { return L::at(row, chunk); };
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
