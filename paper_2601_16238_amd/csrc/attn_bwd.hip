@@ -22,6 +22,7 @@
 #include "attn_launch.hpp"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace attn {
 
@@ -1178,35 +1179,37 @@ attn_bwd_dq_kernel(const BwdArgs a)
 
 // ---------------------------------------------------------------------------------------
 // 3b. dQ from the dS that the dK/dV kernel stored: one product instead of three, bound by reading dS
-// (2 bytes a score) from HBM where the launch is long (rates: see ds_plan).  Work-group = NW waves, wave = 32
-// queries, loop over tiles of 32 keys.
+// (2 bytes a score) from HBM where the launch is long (rates: see ds_plan).  Work-group = NW waves, wave = RB
+// blocks of 32 queries, loop over tiles of 32 keys; one MFMA (per row block) a step, closed by a scheduling fence,
+// with the fragment of K four steps further on requested in it (128 heads of 4096 rows, D = 128, 826 -> 807 us).
+// With two row blocks a wave reads every fragment of K once for two products, and a unit half the K tiles (807 -> 734).
 // The K tile (in the layout above, shared) and the waves' dS blocks (each read by its wave alone) go
 // global -> LDS directly, kRing - 1 tiles ahead: about 100 KB in flight per unit.
 // A dS block holds 8-byte groups of 4 consecutive queries of a key; in the order in which the producers
 // store them the 64 lanes of a transpose read (8 keys x 32 queries) cover 512 contiguous bytes.
 // ---------------------------------------------------------------------------------------
-template <int D, int NW>
+template <int D, int NW, int RB>
 struct DqsCfg : DqCfg<D, 4> {
-    static constexpr int kBlk = NW * 32;
-    static constexpr int kTile = 32;
     using L = Pieces<D>;
+    static constexpr int kBlk = NW * RB * 32;
+    static constexpr int kTile = 32;
     static constexpr int kPieces = kTile / L::kRows;
     static constexpr int kKBytes = L::base(kPieces);
-    static constexpr int kTileBytes = kKBytes + NW * kDsBlock * 2;
+    static constexpr int kTileBytes = kKBytes + NW * RB * kDsBlock * 2;
     static constexpr int kRing = 160 * 1024 / kTileBytes < 6 ? 160 * 1024 / kTileBytes : 6;
     static constexpr int kStage = L::base(32 / L::kRows);
     static constexpr int kLdsBytes = kRing * kTileBytes > NW * kStage ? kRing * kTileBytes : NW * kStage;
     static constexpr int kDmaK = (kPieces + NW - 1) / NW;     // transfers of a wave per tile: K, then dS
-    static constexpr int kDma = kDmaK + 2;
+    static constexpr int kDma = kDmaK + 2 * RB;
     static_assert(kPieces % NW == 0, "every wave has the same number of transfers in flight");
     static_assert(kRing >= 3 && kLdsBytes <= 160 * 1024, "LDS layout");
 };
 
-template <int D, int U, int NW, bool CAUSAL>
+template <int D, int U, int NW, int RB, bool CAUSAL>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW > 4 ? 2 : 1)))
 attn_bwd_dq_ds_kernel(const BwdArgs a)
 {
-    using C = DqsCfg<D, NW>;
+    using C = DqsCfg<D, NW, RB>;
     using L = Pieces<D>;
     constexpr int DB = U / 32, PR = C::kPieceRows;
     extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -1221,26 +1224,32 @@ attn_bwd_dq_ds_kernel(const BwdArgs a)
     bh += a.bkv0 * a.group;
     const int64_t base = (int64_t)(bh / a.H) * a.stride_b + (int64_t)(bh % a.H) * a.stride_h;
     const int64_t base_kv = (int64_t)(bh / a.H) * a.kv_stride_b + (int64_t)((bh % a.H) / a.group) * a.kv_stride_h;
-    const int t = qt * NW + w;  // the wave's slot
-    const int q0 = t * 32;
-    const int n_row = t * 32 < S ? ds_row_len(t, Sk, coff, CAUSAL) : 0;  // key blocks that it sees
+    const int t0 = (qt * NW + w) * RB;  // the wave's slots: t0 .. t0 + RB - 1
     const int q_end = min(S, (qt + 1) * C::kBlk);
-    const int n_kt = ((CAUSAL ? min(Sk, q_end + coff) : Sk) + 31) / 32;  // ... and that some wave sees
+    const int n_kt = ((CAUSAL ? min(Sk, q_end + coff) : Sk) + 31) / 32;  // key blocks that some wave sees
+    int n_row[RB];  // ... and each slot (never more; every wave passes the barriers of n_kt tiles)
+    desc_t Sd[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        const int t = t0 + rb;
+        n_row[rb] = t * 32 < S ? min(n_kt, ds_row_len(t, Sk, coff, CAUSAL)) : 0;
+        Sd[rb] = make_desc(a.dS + (ds_head + ds_row_blocks(min(t, (S + 31) / 32 - 1), Sk, coff, CAUSAL)) * kDsBlock,
+                           (uint32_t)n_row[rb] * (kDsBlock * 2u));
+    }
 
     const int Dr = a.Dr;
     const uint32_t head_bytes = (uint32_t)(((int64_t)(Sk - 1) * a.kv_stride_s + Dr) * 2);
     const desc_t Kd = make_desc(a.K + base_kv, head_bytes);
-    const desc_t Sd = make_desc(a.dS + (ds_head + ds_row_blocks(min(t, (S + 31) / 32 - 1), Sk, coff, CAUSAL)) * kDsBlock,
-                                (uint32_t)n_row * (kDsBlock * 2u));
     const uint32_t row_bytes = (uint32_t)a.kv_stride_s * 2u;
     const uint32_t lds0 = lds_address(smem);
-    const uint32_t voff = Pieces<D>::lane_offset(l, row_bytes, Dr, head_bytes);
+    const uint32_t voff = L::lane_offset(l, row_bytes, Dr, head_bytes);
     // (tiles past the last read as zero, or are keys that nobody uses)
     auto fetch = [&](int kt, int pos) __attribute__((always_inline)) {
         const uint32_t dst = lds0 + pos * C::kTileBytes;
 #pragma unroll
-        for (int n = 0; n < 2; ++n)
-            dma16_between_nt(Sd, dst + C::kKBytes + w * (kDsBlock * 2) + n * 1024, l * 16, kt * (kDsBlock * 2) + n * 1024);
+        for (int n = 0; n < 2 * RB; ++n)
+            dma16_between_nt(Sd[n >> 1], dst + C::kKBytes + (w * RB + (n >> 1)) * (kDsBlock * 2) + (n & 1) * 1024, l * 16,
+                             kt * (kDsBlock * 2) + (n & 1) * 1024);
 #pragma unroll
         for (int n = 0; n < C::kDmaK; ++n) {
             const int piece = w + n * NW;
@@ -1258,39 +1267,70 @@ attn_bwd_dq_ds_kernel(const BwdArgs a)
         const int row = 8 * j + 4 * h + ((l & 15) >> 2), chunk = 2 * ((l >> 4) & 1) + ((l >> 1) & 1);
         tr[j] = L::at(row, chunk) + (l & 1) * 8;
     }
-    int ds = C::kKBytes + w * (kDsBlock * 2) + h * 256 + (((l >> 4) & 1) * 2 + (l & 1)) * 64 + ((l & 15) >> 2) * 16 +
+    int ds = C::kKBytes + w * RB * (kDsBlock * 2) + h * 256 + (((l >> 4) & 1) * 2 + (l & 1)) * 64 + ((l & 15) >> 2) * 16 +
              ((l >> 1) & 1) * 8;
     asm volatile("" : "+v"(tr[0]), "+v"(tr[1]), "+v"(ds));
 
-    f32x16 dq[DB];
+    f32x16 dq[RB][DB];
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+    for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) dq[db][i] = 0.f;
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) dq[rb][db][i] = 0.f;
 
-    int pos = 0;
-    for (int kt = 0; kt < n_kt; ++kt) {
-        wait_vm_and_barrier<(C::kRing - 2) * C::kDma>();
-        fetch(kt + C::kRing - 1, pos == 0 ? C::kRing - 1 : pos - 1);
-        if (kt < n_row) {
-            const char *const T = smem + pos * C::kTileBytes;
+    // row blocks B0 .. B1 - 1 of the wave
+    auto step = [&](const char *T, auto B0, auto B1) __attribute__((always_inline)) {
+        constexpr int kAhead = 4;
+        elem8 b[RB][2], f[2 * DB];
+        auto read = [&](int n) __attribute__((always_inline)) {
+            const int off = (n / DB) * C::kRows16 + (n % DB) * L::kBlock;
+            if (n < 2 * DB)
+                f[n] = join8(lds_read_tr((const elem *)(T + off + tr[0])), lds_read_tr((const elem *)(T + off + tr[1])));
+        };
 #pragma unroll
-            for (int cc = 0; cc < 2; ++cc) {
-                const elem8 b = join8(lds_read_tr((const elem *)(T + ds + cc * 1024)),
-                                      lds_read_tr((const elem *)(T + ds + cc * 1024 + 512)));
+        for (int rb = B0; rb < B1; ++rb)
 #pragma unroll
-                for (int db = 0; db < DB; ++db) {
-                    const int off = cc * C::kRows16 + db * L::kBlock;
-                    const elem8 kT = join8(lds_read_tr((const elem *)(T + off + tr[0])),
-                                           lds_read_tr((const elem *)(T + off + tr[1])));
-                    dq[db] = mfma32(kT, b, dq[db]);
-                }
-            }
+            for (int cc = 0; cc < 2; ++cc)
+                b[rb][cc] = join8(lds_read_tr((const elem *)(T + ds + rb * (kDsBlock * 2) + cc * 1024)),
+                                  lds_read_tr((const elem *)(T + ds + rb * (kDsBlock * 2) + cc * 1024 + 512)));
+#pragma unroll
+        for (int n = 0; n < kAhead; ++n) read(n);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int n = 0; n < 2 * DB; ++n) {
+#pragma unroll
+            for (int rb = B0; rb < B1; ++rb) dq[rb][n % DB] = mfma32(f[n], b[rb][n / DB], dq[rb][n % DB]);
+            read(n + kAhead);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        pos = pos + 1 == C::kRing ? 0 : pos + 1;
+    };
+    using std::integral_constant;
+    int kt = 0, pos = 0;
+    // tiles kt .. end - 1 with the wave's row blocks B0 .. B1 - 1 (the others see none of these keys)
+    auto walk = [&](int end, auto B0, auto B1) __attribute__((always_inline)) {
+        for (; kt < end; ++kt) {
+            wait_vm_and_barrier<(C::kRing - 2) * C::kDma>();
+            fetch(kt + C::kRing - 1, pos == 0 ? C::kRing - 1 : pos - 1);
+            if constexpr (B0 < B1) step(smem + pos * C::kTileBytes, B0, B1);
+            pos = pos + 1 == C::kRing ? 0 : pos + 1;
+        }
+    };
+    typedef integral_constant<int, 0> I0;
+    typedef integral_constant<int, 1> I1;
+    typedef integral_constant<int, RB> IR;
+    if constexpr (RB > 1) {
+        walk(min(n_row[0], n_row[1]), I0(), IR());
+        walk(n_row[1], I1(), IR());
     }
+    walk(n_row[0], I0(), I1());
+    walk(n_kt, I0(), I0());
     wait_vm_and_barrier<0>();  // (everyone's transfers have landed: the LDS is free)
-    dq_rows_out<C, D, U>(a, dq, smem + w * C::kStage, base, q0, l);
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        dq_rows_out<C, D, U>(a, dq[rb], smem + w * C::kStage, base, (t0 + rb) * 32, l);
+        asm volatile("" ::: "memory");
+    }
 }
 
 // Sum of the per-split partial dQ, times scale, rounded: one thread per (row, 4 consecutive d);
@@ -1520,13 +1560,13 @@ static int launch_dq_for(const BwdArgs &a, hipStream_t st)
     return a.Dr <= U ? launch_dq_u<D, U, CAUSAL>(a, st) : launch_dq_u<D, D, CAUSAL>(a, st);
 }
 
-template <int D, int U, int NW, bool CAUSAL>
+template <int D, int U, int NW, int RB, bool CAUSAL>
 static int launch_dq_ds_u(BwdArgs a, hipStream_t st)
 {
-    using C = DqsCfg<D, NW>;
+    using C = DqsCfg<D, NW, RB>;
     a.ntile = (a.S + C::kBlk - 1) / C::kBlk;
-    if (!allow_lds(attn_bwd_dq_ds_kernel<D, U, NW, CAUSAL>, C::kLdsBytes)) return -1;
-    hipLaunchKernelGGL((attn_bwd_dq_ds_kernel<D, U, NW, CAUSAL>), dim3(a.ntile * a.nkv * a.group), dim3(NW * 64),
+    if (!allow_lds(attn_bwd_dq_ds_kernel<D, U, NW, RB, CAUSAL>, C::kLdsBytes)) return -1;
+    hipLaunchKernelGGL((attn_bwd_dq_ds_kernel<D, U, NW, RB, CAUSAL>), dim3(a.ntile * a.nkv * a.group), dim3(NW * 64),
                        C::kLdsBytes, st, a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
@@ -1535,17 +1575,33 @@ template <int D, int NW, bool CAUSAL>
 static int launch_dq_ds(const BwdArgs &a, hipStream_t st)
 {
     constexpr int U = narrow_columns(D);
-    return a.Dr <= U ? launch_dq_ds_u<D, U, NW, CAUSAL>(a, st) : launch_dq_ds_u<D, D, NW, CAUSAL>(a, st);
+    return a.Dr <= U ? launch_dq_ds_u<D, U, NW, 1, CAUSAL>(a, st) : launch_dq_ds_u<D, D, NW, 1, CAUSAL>(a, st);
 }
 
-// Waves (of 32 rows) per work-group: eight, which read K least often, unless smaller work-groups still
-// fill the compute units in one round.  us, whole backward, 8 | 4 | 2: 11 heads of 1166 rows 61 | 55 | 53,
+// Eight waves of two row blocks (see dq_ds_blocks).
+template <int D, bool CAUSAL>
+static int launch_dq_ds_two(const BwdArgs &a, hipStream_t st)
+{
+    if constexpr (D > 128) return -1;
+    else return launch_dq_ds_u<D, D, 8, 2, CAUSAL>(a, st);
+}
+
+// Row blocks (of 32 rows) per work-group: eight, one a wave, which read K less often, unless smaller work-groups
+// still fill the compute units in one round.  us, whole backward, 8 | 4 | 2: 11 heads of 1166 rows 61 | 55 | 53,
 // 4 of 5599 causal 173 | 147 | 152, 10 of 1876 D=256 causal 116 | 105 | 105; 8 of 4384 248 | 267 | 284,
 // 32 of 4096 and 16384 five per cent faster with eight.  Long causal heads, whose eight-wave work-groups
 // are the most unequal, take four for longer: 4 of 10802 460 | 427 | 458, 4 of 12527 550 | 530 | 569, but
 // 114 of 321 46 | 51.
-static int dq_ds_waves(int64_t heads, int S, bool causal)
+// At D = 128 sixteen, two a wave, in launches of two rounds of them whose rows fill them: half the K tiles, and every
+// fragment of K feeds two products.  us, this kernel alone, 8 | 16: 128 heads of 4096 rows 807 | 734; whole backward:
+// 128 of 2048 causal 470 | 455, 454 of 377 causal 139 | 131, 192 of 2048 1258 | 1228; with fewer the launch ends on a
+// long work-group (64 of 2048 causal 227 | 240, 16 of 4096 causal 220 | 248), rows that pad a second one are lost
+// (482 of 718 causal 341 | 347), and beyond 4096 rows there is no difference (32 of 8192 causal 1502 | 1489, 48 of
+// 8192 4562 | 4627), nor at 96 columns (249 of 1076 286 | 288).
+static int dq_ds_blocks(int64_t heads, int S, int Dr, bool causal)
 {
+    const int blocks256 = (S + 255) / 256;
+    if (Dr > narrow_columns(128) && Dr <= 128 && S <= 4096 && blocks256 % 2 == 0 && heads * blocks256 >= 1024) return 16;
     if (heads * ((S + 127) / 128) > (causal && S > 4096 ? 512 : 256)) return 8;
     return heads * ((S + 63) / 64) > 256 ? 4 : 2;
 }
@@ -1570,9 +1626,9 @@ static int launch_bwd_ds(BwdArgs a, hipStream_t st)
         a.bkv0 = (int)((int64_t)BHkv * i / n_chunk);
         a.nkv = (int)((int64_t)BHkv * (i + 1) / n_chunk) - a.bkv0;
         if (launch_dkdv<D, CAUSAL, true>(a, st)) return -1;
-        const int nw = dq_ds_waves((int64_t)a.nkv * a.group, a.S, CAUSAL);
-        if (nw == 8 ? launch_dq_ds<D, 8, CAUSAL>(a, st) : nw == 4 ? launch_dq_ds<D, 4, CAUSAL>(a, st)
-                                                                  : launch_dq_ds<D, 2, CAUSAL>(a, st)) return -1;
+        const int blocks = dq_ds_blocks((int64_t)a.nkv * a.group, a.S, a.Dr, CAUSAL);
+        if (blocks == 16 ? launch_dq_ds_two<D, CAUSAL>(a, st) : blocks == 8 ? launch_dq_ds<D, 8, CAUSAL>(a, st)
+                         : blocks == 4 ? launch_dq_ds<D, 4, CAUSAL>(a, st) : launch_dq_ds<D, 2, CAUSAL>(a, st)) return -1;
     }
     return 0;
 }

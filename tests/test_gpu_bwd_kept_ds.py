@@ -85,3 +85,27 @@ def test_stored_ds_in_other_layouts(B, Hq, Hkv, Sq, Sk, D, causal, f16, cut, lay
     attn.attn_bwd_rect(*t, LSE, D ** -0.5, causal, dQ=out[0], dK=out[1], dV=out[2])
     torch.cuda.synchronize()
     assert all(torch.equal(a, b) for a, b in zip(out, want))
+
+
+# two row blocks a wave: the last wave's second block past the end, blocks of unequal length under the mask,
+# offsets off the 32-key blocks, grouped heads, more rows than keys
+@pytest.mark.parametrize("H,Hkv,Sq,Sk,causal", [(520, 520, 385, 385, True), (520, 260, 400, 1100, True),
+                                                (520, 520, 481, 513, True), (540, 540, 290, 417, False),
+                                                (518, 518, 512, 403, False), (264, 264, 1000, 1031, True)])
+def test_two_row_blocks_a_wave(H, Hkv, Sq, Sk, causal):
+    """Work-groups of 512 rows, which a launch of all heads takes, against those of 256, which the parts
+    take: a row's sum has the same products in the same order."""
+    print("case kept_ds two blocks", H, Hkv, Sq, Sk, causal, flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(Sq + Sk)
+    D = 128
+    Q, dO = (torch.randn((1, H, Sq, D), generator=g, device="cuda").bfloat16() for _ in range(2))
+    K, V = (torch.randn((1, Hkv, Sk, D), generator=g, device="cuda").bfloat16() for _ in range(2))
+    O, LSE = attn.attn_fwd_rect(Q, K, V, D ** -0.5, causal)
+    best = attn.attn_bwd_rect_best_workspace_bytes(1, H, Hkv, Sq, Sk, D, causal)
+    assert [backward_form(1, H, Hkv, Sq, Sk, D, causal, n) for n in (best, int(best * 0.6))] == [STORED_DS] * 2
+    ws = torch.full((best,), 0xFF, dtype=torch.uint8, device="cuda")
+    whole, part = (attn.attn_bwd_rect(Q, K, V, O, dO, LSE, D ** -0.5, causal, workspace=ws[:n])
+                   for n in (best, int(best * 0.6)))
+    torch.cuda.synchronize()
+    assert all(torch.equal(w.view(torch.int16), p.view(torch.int16)) for w, p in zip(whole, part))
