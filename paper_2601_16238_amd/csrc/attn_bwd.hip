@@ -1463,7 +1463,8 @@ static int launch_dkdv_split(BwdArgs a, hipStream_t st)
 // on launches of at least two rounds of work-groups, of six (192 keys, 12 waves at 168
 // registers: three per SIMD hide more of each other's latencies).  Measured: -2.5..4 % on the
 // large shapes; slower on small launches (more of a 192-key block is padding) and at D = 64
-// (the larger work-group no longer fits a compute unit twice).
+// (the larger work-group no longer fits a compute unit twice).  Or, at D = 128 too, the kernel of
+// attn_bwd_solo.hip (256 keys), where dkdv_takes_solo says so.
 template <int D, int U, bool CAUSAL, bool DS>
 static int launch_dkdv_u(const BwdArgs &a, hipStream_t st)
 {
@@ -1474,6 +1475,7 @@ static int launch_dkdv_u(const BwdArgs &a, hipStream_t st)
     else {
         if constexpr (D == 128) {
             const int64_t wgs6 = (int64_t)a.nkv * ((a.Sk + 191) / 192);
+            if (dkdv_takes_solo(a.nkv, a.group, a.S, a.Sk, CAUSAL)) return launch_bwd_dkdv_solo(a, CAUSAL, DS, st);
             if (wgs6 >= 512) return launch_dkdv_p<D, U, 6, CAUSAL, DS>(a, st);
         }
         return launch_dkdv_p<D, U, 4, CAUSAL, DS>(a, st);
@@ -1792,6 +1794,30 @@ struct BlockChunks {
         return flat * ((longest + L - 1) / L) + floor_sum(falling, L, step, shortest + L - 1);
     }
 };
+
+// Whether the unsplit dK/dV kernel at D = 65 .. 128 is that of attn_bwd_solo.hip: where an estimate of the launch is
+// below that of the pairs.  A work-group takes a fixed time and one per slot; without a mask all of them are equal and
+// run in rounds of one per unit, under one the launch takes as long as the longest or the work spread evenly.  (Per
+// key a slot of 256 takes 0.84 of the time of one of 128 or 192, but its rounds are coarser, more of the last key
+// block and of the diagonal is idle, and one wave per SIMD waits for its K and V alone.)  The constants, relative
+// ones, are a fit to the difference of the two over 298 whole backwards of 128 .. 16384 rows, D = 80 .. 128, both
+// masks, up to 2000 work-groups; of these the rule takes 0.985 of the time of the pairs on average (the better of
+// the two 0.982), none more than 1.022.  us, whole backward: B=4 H=32 S=4096 2921 -> 2735, causal 1625 -> 1580; B=1 H=16
+// S=16384 causal 2835 -> 2690; 104 heads on 26 of 1156 rows D = 96 271 -> 232; but 256 of 372 causal 65 | 77.
+bool dkdv_takes_solo(int BHkv, int group, int S, int Sk, bool causal)
+{
+    const int64_t units = 256;
+    auto time = [&](int keys, float fixed, float slot) {
+        const int n_block = (Sk + keys - 1) / keys;
+        const float longest = fixed + slot * dkdv_slots(0, keys, group, S, Sk, causal);
+        if (!causal) return ((int64_t)BHkv * n_block + units - 1) / units * longest;
+        const BlockChunks head(n_block, keys, group, S, Sk, causal);
+        return std::max(longest, BHkv * (fixed * n_block + slot * head.of(1)) / units);
+    };
+    if ((int64_t)BHkv * ((Sk + 127) / 128) < units) return false;
+    const bool six = (int64_t)BHkv * ((Sk + 191) / 192) >= 512;
+    return time(256, 7.7f, 1.026f) < 0.98f * (six ? time(192, 2.0f, 0.916f) : time(128, 3.6f, 0.611f));
+}
 
 // Split the dK/dV kernel over the query slots when its work-groups (one per key block of a K/V head)
 // leave compute units idle: few K/V heads, e.g. grouped-query heads, whose one work-group per block

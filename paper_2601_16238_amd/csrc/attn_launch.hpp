@@ -138,6 +138,8 @@ int dq_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps, int most 
 // the slots per chunk (0: not split, one work-group per key block), at most `most` chunks in all; a pure
 // host function of the shape.
 int dkdv_split_plan(int BHkv, int group, int S, int Sk, int D, bool causal, int *chunk, int64_t most = 512);
+// Whether the unsplit dK/dV kernel for D = 128 is that of attn_bwd_solo.hip; a pure host function of the shape.
+bool dkdv_takes_solo(int BHkv, int group, int S, int Sk, bool causal);
 // K/V heads whose dS the backward keeps at a time in `room` bytes (0: it recomputes it for dQ); a pure host
 // function of the shape and the room.
 int ds_plan(int BHkv, int group, int S, int Sk, int D, bool causal, size_t room);
@@ -191,6 +193,10 @@ int bwd_small_max_rows(int D);
 bool bwd_is_small(int BHkv, int group, int S, int Sk, int D);  // whether a whole backward is that launch
 int launch_bwd_small(const BwdArgsT<__bf16> &a, int D, bool causal, hipStream_t st);
 int launch_bwd_small(const BwdArgsT<_Float16> &a, int D, bool causal, hipStream_t st);
+// dK and dV of the K/V heads bkv0 .. bkv0 + nkv - 1 by work-groups of 256 keys (attn_bwd_solo.hip; kernels for D = 128),
+// storing dS if `ds`.
+int launch_bwd_dkdv_solo(const BwdArgsT<__bf16> &a, bool causal, bool ds, hipStream_t st);
+int launch_bwd_dkdv_solo(const BwdArgsT<_Float16> &a, bool causal, bool ds, hipStream_t st);
 int launch_bwd(const BwdArgsT<__bf16> &a, int D, bool causal, hipStream_t st, unsigned stages);
 int launch_bwd(const BwdArgsT<_Float16> &a, int D, bool causal, hipStream_t st, unsigned stages);
 
