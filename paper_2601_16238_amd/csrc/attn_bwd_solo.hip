@@ -39,26 +39,6 @@ struct DkdvSoloCfg {
     static_assert(kWaves * kStage <= (kRing - kAhead) * kSlotBytes, "staging space of the prologue");
 };
 
-// The product with its result in the vector half of the register file (c += a b; mfma_v0: c = a b).  As assembly: for
-// the scores and dP the compiler would use the accumulation half as it does for the accumulators, which fill it, and
-// move 64 registers between the halves several times a slot.  It also does not know, then, that a vector instruction
-// may read the result only 11 wait states (44 cycles) after the issue, so the code keeps two of these products, of 32
-// cycles each, in between: the `after` statements, which order the reads behind them.  An operand must not come from a
-// vector instruction (they are LDS reads, and registers set before the loop).
-#ifdef ATTN_F16
-#define ATTN_MFMA "v_mfma_f32_32x32x16_f16"
-#else
-#define ATTN_MFMA "v_mfma_f32_32x32x16_bf16"
-#endif
-__device__ __forceinline__ void mfma_v(f32x16 &c, elem8 a, elem8 b)
-{
-    asm volatile(ATTN_MFMA " %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
-}
-__device__ __forceinline__ void mfma_v0(f32x16 &c, elem8 a, elem8 b)
-{
-    asm volatile(ATTN_MFMA " %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(b));
-}
-
 // x is read only behind this point, which follows the products above it.
 __device__ __forceinline__ void after(f32x16 (&x)[2]) { asm volatile("" : "+v"(x[0]), "+v"(x[1])); }
 
@@ -293,7 +273,7 @@ attn_bwd_dkdv_solo_kernel(const BwdArgs a)
         };
         // Visible rows of block b: >= key - coff - q_lo (causal) and <= S - 1 - q_lo.
         auto hide = [&]() __attribute__((always_inline)) {
-            asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");  // (S comes from the MFMAs just issued, see mfma_v)
+            asm volatile("s_nop 15\n\ts_nop 15" : "+v"(s[0]), "+v"(s[1]));  // (from the MFMAs just issued, see mfma_v)
             const int hi = S - 1 - q_lo - 4 * h;
 #pragma unroll
             for (int b = 0; b < 2; ++b) {

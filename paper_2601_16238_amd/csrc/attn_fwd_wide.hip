@@ -107,6 +107,8 @@ attn_fwd_wide_kernel(const FwdArgs a)
     // which every lane fetches 16 bytes of its own row touch 32 rows per instruction and keep
     // the work-group's last wave from even issuing its K and V transfers for thousands of cycles.
     constexpr bool kStageQ = D > 128;
+    // the fast loop's scores in the vector half of the register file (B=4 H=16 S=4096 D=256 causal 609 -> 588 us)
+    constexpr bool kVec = D > 128 && !NT;
     elem8 qf[KS];
     if constexpr (!kStageQ) {
 #pragma unroll
@@ -230,6 +232,7 @@ attn_fwd_wide_kernel(const FwdArgs a)
     auto mask = [&](int kt, int u, f32x16 &s) __attribute__((always_inline)) {
         const int kb = kt * C::kBC + 32 * u;
         if ((kb + 32 > Sk) || (CAUSAL && kb + 31 > q0e)) {
+            if (kVec) asm volatile("s_nop 15\n\ts_nop 15" : "+v"(s));  // (from the MFMA just issued, see mfma_v)
             const int lim = (CAUSAL ? min(qpos + coff, Sk - 1) : Sk - 1) - kb - 4 * h;
 #pragma unroll
             for (int i = 0; i < 16; ++i)
@@ -431,14 +434,17 @@ attn_fwd_wide_kernel(const FwdArgs a)
                 const int ph = n / kSteps, j = n % kSteps;
                 if (ph < 4) f[ph][j] = ph < 2 ? ld_k(ph, j) : ld_v(ph - 2, j);
             };
+            if (!kVec)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) sA[i] = sB[i] = 0.f;
+                for (int i = 0; i < 16; ++i) sA[i] = sB[i] = 0.f;
 #pragma unroll
             for (int n = 0; n < kAhead; ++n) fetch(n);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int j = 0; j < kSteps; ++j) {          // A
-                sA = mfma32(f[0][j], qf[j], sA);
+                if (!kVec) sA = mfma32(f[0][j], qf[j], sA);
+                else if (j) mfma_v(sA, f[0][j], qf[j]);
+                else mfma_v0(sA, f[0][j], qf[j]);
                 fetch(j + kAhead);
                 if (j & 1) dma_piece(0, kt + 1, (kt & 1) ^ 1, j >> 1);
                 __builtin_amdgcn_sched_barrier(0);
@@ -446,18 +452,27 @@ attn_fwd_wide_kernel(const FwdArgs a)
             mask(kt, 0, sA);
 #pragma unroll
             for (int j = 0; j < kSteps; ++j) {          // B
-                sB = mfma32(f[1][j], qf[j], sB);
+                if (!kVec) sB = mfma32(f[1][j], qf[j], sB);
+                else if (j) mfma_v(sB, f[1][j], qf[j]);
+                else mfma_v0(sB, f[1][j], qf[j]);
+                if (kVec && j == 1) asm volatile("" : "+v"(sA));  // (read two products after its last, see mfma_v)
                 fetch(kSteps + j + kAhead);
                 if (j & 1) dma_piece(1, kt + 1, (kt & 1) ^ 1, j >> 1);
                 probs_step(j, sA, eA, sumA);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (__builtin_expect(overflow(sumA), 0)) { redo = 0; break; }
+            if (__builtin_expect(overflow(sumA), 0)) {
+                // (nothing else may be written to sB's registers while its last product is in flight)
+                if (kVec) asm volatile("s_nop 15\n\ts_nop 15" : "+v"(sB));
+                redo = 0;
+                break;
+            }
             pack16(eA, pA0, pA1);
             mask(kt, 1, sB);
 #pragma unroll
             for (int j = 0; j < kSteps; ++j) {          // C
                 o[j % DB] = mfma32(f[2][j], j < DB ? pA0 : pA1, o[j % DB]);
+                if constexpr (kVec) if (j == 1) asm volatile("" : "+v"(sB), "+a"(o[0]), "+a"(o[1]));
                 fetch(2 * kSteps + j + kAhead);
                 probs_step(j, sB, eB, sumB);
                 __builtin_amdgcn_sched_barrier(0);
