@@ -350,11 +350,22 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
         int ds_len = ds_row_len(t, Sk, coff, CAUSAL);
         const uint32_t ds_voff = (uint32_t)k0 * 64u + (uint32_t)(((r >> 2) * 16 + h * 4 + (r & 3)) * 16);
         constexpr int kNt = 2;  // non-temporal (plain: dQ 3 .. 10 % longer)
-        auto store_ds = [&](elem8 d0, elem8 d1) __attribute__((always_inline)) {
+        auto ds_rsrc = [&]() __attribute__((always_inline)) {
+            return make_rsrc(ds_row, DS ? (uint32_t)ds_len * (kDsBlock * 2u) : 0u);
+        };
+        auto store_ds = [&](rsrc_t row, elem8 d0, elem8 d1) __attribute__((always_inline)) {
             // (blocks that no row of the slot sees, and keys past the last, lie past the row's end: not stored)
-            const rsrc_t row = make_rsrc(ds_row, (uint32_t)ds_len * (kDsBlock * 2u));
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, d0), row, (int)ds_voff, 0, kNt);
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, d1), row, (int)ds_voff, 128, kNt);
+        };
+        auto next_slot = [&]() __attribute__((always_inline)) {
+            if (!DS) advance_fetch();
+            rs = ring_next(rs);
+            ++t;
+            if (DS) {
+                ds_row += (CAUSAL ? ds_len : ds_len | 1) * kDsBlock;
+                if (CAUSAL) ds_len = ds_row_len(t, Sk, coff, true);
+            }
         };
         for (int g = 0; g < n_seq; ++g) {
             slot_barrier();
@@ -365,26 +376,26 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
                 const char *Qt = smem + rs * C::kSlotBytes;
                 const float *st = reinterpret_cast<const float *>(smem + C::kOffStat + rs * C::kStatBytes);
                 const int q_lo = t * C::kRows;
+                const rsrc_t row = ds_rsrc();
                 f32x16 s, dp;
                 // register i <-> query row q_lo + 8*(i/4) + 4h + i%4.  The dP accumulator starts
                 // from -delta of its row, so that it ends as dP - delta.  The lane's key is fixed;
                 // P = exp2(c S - lse2) per row.
-                f32x16 zero, nd;
+                const bool masked = (q_lo + 32 > S) || (CAUSAL && q_lo + coff < k0 + 31);
+                // score i = `with` unless its row is visible: row offsets >= key - coff - q_lo (causal), <= S - 1 - q_lo
+                auto hide = [&](float with) __attribute__((always_inline)) {
+                    const int lo = (CAUSAL ? key - coff - q_lo : -64) - 4 * h;
+                    const int hi = S - 1 - q_lo - 4 * h;
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const f32x4 d4 = *(const f32x4 *)(st + 32 + 8 * g + 4 * h);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) nd[4 * g + e] = d4[e];
-                }
-#pragma unroll
-                for (int i = 0; i < 16; ++i) zero[i] = 0.f;
-                {
-                    // Every MFMA is a step of its own, closed by a scheduling fence, with the read of
-                    // the fragment four MFMAs further on (the compiler reads a fragment right
-                    // before its MFMA and waits); S first, so that its exp2 run next to the
-                    // MFMAs of dP.  us: B=4 H=16 S=4096 D=256 causal 1216 -> 1118 (with the
-                    // consumers' steps), B=1 H=16 S=4096 D=128 causal 142 -> 135 (S=16384 the same within noise);
-                    // two or six MFMAs ahead are the same
+                    for (int i = 0; i < 16; ++i) {
+                        const int ro = 8 * (i / 4) + (i % 4);
+                        if (ro < lo || ro > hi) s[i] = with;
+                    }
+                };
+                if constexpr (D > 128) {
+                    // One wave per SIMD: the scores in the vector half of the register file, the mask on S instead
+                    // of P (so that P is packed next to the MFMAs of dP), the next slot's scalar work between
+                    // the MFMAs of S: in this order nothing but dS is left behind the last MFMA.
                     constexpr int kAhead = 4;
                     elem8 f[2 * KS];
                     auto fetch = [&](int n) __attribute__((always_inline)) {
@@ -393,54 +404,106 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
                     };
                     f32x4 l4[4];
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) l4[g] = *(const f32x4 *)(st + 8 * g + 4 * h);
-#pragma unroll
                     for (int n = 0; n < kAhead; ++n) fetch(n);
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int ks = 0; ks < KS; ++ks) {
-                        s = mfma32(f[ks], kf[ks], ks ? s : zero);
+                        if (ks) mfma_v(s, f[ks], kf[ks]);
+                        else mfma_v0(s, f[ks], kf[ks]);
                         fetch(ks + kAhead);
+                        if (ks == 2) next_slot();
+                        if (ks == KS - 4) {
+#pragma unroll
+                            for (int g4 = 0; g4 < 4; ++g4) {
+                                l4[g4] = *(const f32x4 *)(st + 8 * g4 + 4 * h);
+                                const f32x4 d4 = *(const f32x4 *)(st + 32 + 8 * g4 + 4 * h);
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) dp[4 * g4 + e] = d4[e];
+                            }
+                        }
                         __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if (masked) {
+                        asm volatile("s_nop 15\n\ts_nop 15" : "+v"(s));  // (from the MFMA just issued, see mfma_v)
+                        hide(-INFINITY);
                     }
 #pragma unroll
                     for (int ks = 0; ks < KS; ++ks) {
-                        dp = mfma32(f[KS + ks], vf[ks], ks ? dp : nd);
+                        mfma_v(dp, f[KS + ks], vf[ks]);
                         fetch(KS + ks + kAhead);
+                        if (ks == 1) asm volatile("" : "+v"(s));  // (read two products after its last, see mfma_v)
 #pragma unroll
                         for (int i = exps_before(ks, KS); i < exps_before(ks + 1, KS); ++i)
                             s[i] = fast_exp2(__builtin_fmaf(s[i], c, -l4[i / 4][i % 4]));
                         __builtin_amdgcn_sched_barrier(0);
                     }
-                }
-                if ((q_lo + 32 > S) || (CAUSAL && q_lo + coff < k0 + 31)) {
-                    // visible row offsets: >= key - coff - q_lo (causal) and <= S - 1 - q_lo
-                    const int lo = (CAUSAL ? key - coff - q_lo : -64) - 4 * h;
-                    const int hi = S - 1 - q_lo - 4 * h;
+                    elem8 *x = Xs + (g & 1) * (C::kPairs * 256);
+                    x[0] = pack8(s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7]);
+                    x[64] = pack8(s[8], s[9], s[10], s[11], s[12], s[13], s[14], s[15]);
+                    asm volatile("s_nop 11" : "+v"(dp));  // (from the MFMA just issued)
+                } else {
+                    f32x16 zero, nd;
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int ro = 8 * (i / 4) + (i % 4);
-                        if (ro < lo || ro > hi) s[i] = 0.f;
+                    for (int g = 0; g < 4; ++g) {
+                        const f32x4 d4 = *(const f32x4 *)(st + 32 + 8 * g + 4 * h);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) nd[4 * g + e] = d4[e];
                     }
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) zero[i] = 0.f;
+                    {
+                        // Every MFMA is a step of its own, closed by a scheduling fence, with the read of
+                        // the fragment four MFMAs further on (the compiler reads a fragment right
+                        // before its MFMA and waits); S first, so that its exp2 run next to the
+                        // MFMAs of dP.  us: B=4 H=16 S=4096 D=256 causal 1216 -> 1118 (with the
+                        // consumers' steps), B=1 H=16 S=4096 D=128 causal 142 -> 135 (S=16384 the same within noise);
+                        // two or six MFMAs ahead are the same
+                        constexpr int kAhead = 4;
+                        elem8 f[2 * KS];
+                        auto fetch = [&](int n) __attribute__((always_inline)) {
+                            if (n < 2 * KS)
+                                f[n] = *(const elem8 *)(Qt + (n / KS) * C::kTensorBytes + (lane_off ^ ((n % KS) * 32)));
+                        };
+                        f32x4 l4[4];
+#pragma unroll
+                        for (int g = 0; g < 4; ++g) l4[g] = *(const f32x4 *)(st + 8 * g + 4 * h);
+#pragma unroll
+                        for (int n = 0; n < kAhead; ++n) fetch(n);
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int ks = 0; ks < KS; ++ks) {
+                            s = mfma32(f[ks], kf[ks], ks ? s : zero);
+                            fetch(ks + kAhead);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+#pragma unroll
+                        for (int ks = 0; ks < KS; ++ks) {
+                            dp = mfma32(f[KS + ks], vf[ks], ks ? dp : nd);
+                            fetch(KS + ks + kAhead);
+#pragma unroll
+                            for (int i = exps_before(ks, KS); i < exps_before(ks + 1, KS); ++i)
+                                s[i] = fast_exp2(__builtin_fmaf(s[i], c, -l4[i / 4][i % 4]));
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
+                    if (masked) hide(0.f);
                 }
 #pragma unroll
                 for (int i = 0; i < 16; ++i) dp[i] *= s[i];  // dS = P o (dP - delta)
                 elem8 *x = Xs + (g & 1) * (C::kPairs * 256);
-                x[0] = pack8(s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7]);
-                x[64] = pack8(s[8], s[9], s[10], s[11], s[12], s[13], s[14], s[15]);
+                if (D <= 128) {
+                    x[0] = pack8(s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7]);
+                    x[64] = pack8(s[8], s[9], s[10], s[11], s[12], s[13], s[14], s[15]);
+                }
                 const elem8 d0 = pack8(dp[0], dp[1], dp[2], dp[3], dp[4], dp[5], dp[6], dp[7]);
                 const elem8 d1 = pack8(dp[8], dp[9], dp[10], dp[11], dp[12], dp[13], dp[14], dp[15]);
                 x[128] = d0;
                 x[192] = d1;
-                if (DS) store_ds(d0, d1);
+                if (DS) store_ds(D > 128 ? row : ds_rsrc(), d0, d1);
+            } else if (D > 128) {
+                next_slot();
             }
-            if (!DS) advance_fetch();
-            rs = ring_next(rs);
-            ++t;
-            if (DS) {
-                ds_row += (CAUSAL ? ds_len : ds_len | 1) * kDsBlock;
-                if (CAUSAL) ds_len = ds_row_len(t, Sk, coff, true);
-            }
+            if (D <= 128) next_slot();
             if (t == n_slot) {
                 t = t0;
                 if (DS) {
@@ -482,9 +545,13 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
         };
         const elem8 *const Xc = reinterpret_cast<const elem8 *>(smem + C::kOffXchg) +
                                  (2 * half) * 256 + kind * 128 + l;
-        auto consume = [&](int t, int g, int rs) {
+        // (D > 128: with the transfers of slot tf into ring position rd between the products, if `fetch`)
+        auto consume = [&](int t, int g, int rs, int rd, auto fetch) {
             const bool actA = block_active(t, kA), actB = block_active(t, kB);
-            if (!actA) return;  // kA < kB: then the second block is not active either
+            if (!actA) {  // kA < kB: then the second block is not active either
+                if (D > 128 && fetch()) dma_pieces(tf, rd);
+                return;
+            }
             const char *Tt = smem + rs * C::kSlotBytes + (kind ? 0 : C::kTensorBytes);
             const elem8 *x = Xc + (g & 1) * (C::kPairs * 256);
             const elem8 opA[2] = {x[0], x[64]};
@@ -503,8 +570,8 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
                              lds_read_tr((const elem *)(Tt + ((tr_off[1] ^ x) + o))));
             };
             if constexpr (D > 128) {
-                // one wave per SIMD: fenced steps as in the producers (no gain at D <= 128; neither
-                // has requesting slot tf's rows between these MFMAs)
+                // one wave per SIMD: fenced steps as in the producers (no gain at D <= 128), with the
+                // transfers between them (in front of them they cost the D = 256 consumers 300 cycles a slot)
                 constexpr int kAhead = 4;
                 elem8 T[2 * DB];
 #pragma unroll
@@ -515,6 +582,9 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
                     acc[0][n % DB] = mfma32(T[n], opA[n / DB], acc[0][n % DB]);
                     if (n + kAhead < 2 * DB) T[n + kAhead] = frag(n + kAhead);
                     acc[1][n % DB] = mfma32(T[n], opB[n / DB], acc[1][n % DB]);
+                    constexpr int kN = fetch() ? C::kDmaPerWave : 0;
+#pragma unroll
+                    for (int i = kN * n / (2 * DB); i < kN * (n + 1) / (2 * DB); ++i) dma_piece(tf, rd, i);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             } else {
@@ -542,16 +612,20 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
             // slot g + kAhead goes into the ring position that slot g - 2 has left
             int rd = rs + C::kAhead;
             rd = rd >= C::kRing ? rd - C::kRing : rd;
-            dma_pieces(tf, rd);
-            if (DS && pair == C::kPairs - 1) dma_stat(tf, rd);
-            advance_fetch();
-            if (g > 0) consume(tp, g - 1, rs == 0 ? C::kRing - 1 : rs - 1);
+            if (D <= 128 || g == 0) dma_pieces(tf, rd);
+            auto requested = [&]() __attribute__((always_inline)) {
+                if (DS && pair == C::kPairs - 1) dma_stat(tf, rd);
+                advance_fetch();
+            };
+            if (D <= 128) requested();
+            if (g > 0) consume(tp, g - 1, rs == 0 ? C::kRing - 1 : rs - 1, rd, std::true_type());
+            if (D > 128) requested();
             rs = ring_next(rs);
             tp = t;
             if (++t == n_slot) t = t0;
         }
         wait_vm_and_barrier<0>();
-        if (n_seq > 0) consume(tp, n_seq - 1, rs == 0 ? C::kRing - 1 : rs - 1);
+        if (n_seq > 0) consume(tp, n_seq - 1, rs == 0 ? C::kRing - 1 : rs - 1, 0, std::false_type());
 
         // The accumulators hold 4 consecutive columns of one key per register group: stored
         // directly, every instruction writes 8-byte pieces of 32 rows (32 such stores per wave).
