@@ -58,7 +58,7 @@ struct FwdCfg {
     // V tiles: two, or three for the main loop, which multiplies P of a sub-tile by V one sub-tile
     // later and therefore still reads tile kt-1 while tile kt+1 is arriving
     static constexpr int kVBufs = kMain ? 3 : 2;
-    // Eight waves: the query rows reach the registers through LDS (see the kernel's prologue):
+    // The query rows reach the registers through LDS (see the kernel's prologue):
     // the 64 rows of a pair of waves are staged like a K tile, pair 0 in K buffer 2, pair 1 in
     // V buffer 1 (both free until the first tile barrier), pairs 2 and 3 behind the V buffers.
     static constexpr int kQStage = NW == 8 ? 2 * kKTile : 0;
@@ -113,13 +113,15 @@ attn_fwd_kernel(const FwdArgs a)
     const int q = q0 + r;                 // this lane's query row
     const int qc = q < S ? q : S - 1;     // clamped for loads; rows >= S are never stored
 
-    // Q fragments, B operand of K Q^T: lane holds Q[q][16*ks + 8h .. +7].  Fewer than eight
-    // waves load them straight from memory.  Eight waves take them through LDS (below): a load
-    // in which every lane fetches 16 bytes of its own row touches 32 rows per instruction, and
-    // the 64 such instructions of a work-group took its last wave 5000-7000 cycles to get issued
-    // (measured) -- time in which the compute unit, which holds one such work-group, does nothing.
+    // Q fragments, B operand of K Q^T: lane holds Q[q][16*ks + 8h .. +7].  A lone wave loads them
+    // straight from memory.  Others take them through LDS (below): a load in which every lane
+    // fetches 16 bytes of its own row touches 32 rows per instruction, and the 64 such instructions of
+    // a work-group of eight waves took its last wave 5000-7000 cycles to get issued (measured) -- time
+    // in which the compute unit, which holds one such work-group, does nothing.  With fewer waves
+    // (this and the rows of O below; us): 2 heads of 128 rows D = 64 5.3 -> 4.7, 512 of 200 causal 18.2 ->
+    // 16.4, 64 of 1024 causal 19.2 -> 18.5, 768 of 65 the same.
     elem8 qf[KS];
-    if constexpr (NW != 8) {
+    if constexpr (NW == 1) {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
             qf[ks] = as_elem8(ld_row16(Qp + (int64_t)qc * a.stride_s, ks * 16 + 8 * h, Dr));
@@ -314,11 +316,11 @@ attn_fwd_kernel(const FwdArgs a)
 
     // ---- prologue: K(0), K(1), V(0) resident; V(1) in flight; first S^T block computed and
     // the K fragments of the second sub-tile on their way.
-    // Eight waves: the wave's 32 query rows as half of a K-layout tile, by the same direct
+    // The wave's 32 query rows as half of a K-layout tile, by the same direct
     // transfers (whole rows of four per instruction), issued before those of K and V.  Rows past
     // S-1 and columns Dr..D-1 read as zero.
     uint32_t q_stage = 0;
-    if constexpr (NW == 8) {
+    if constexpr (NW > 1) {
         const int pair = __builtin_amdgcn_readfirstlane(w) >> 1, half = __builtin_amdgcn_readfirstlane(w) & 1;
         q_stage = (pair == 0 ? 2 * C::kKTile : pair == 1 ? 3 * C::kKTile + C::kVTile
                                                           : 3 * C::kKTile + 3 * C::kVTile + (pair - 2) * C::kKTile) * 2 +
@@ -354,7 +356,7 @@ attn_fwd_kernel(const FwdArgs a)
                 rs[ks][j] = *(const f32x4 *)(a.rope_sin + pos + 16 * ks + 8 * h + 4 * j);
             }
     }
-    if constexpr (NW == 8) {
+    if constexpr (NW > 1) {
         // the wave's own query rows have landed once at most the later transfers (K(0), K(1),
         // V(0)) are outstanding; with the rotary table rows in flight as well, whose place in the
         // order of issue is the compiler's choice, everything is awaited
@@ -565,14 +567,14 @@ attn_fwd_kernel(const FwdArgs a)
     // Epilogue: O = O_acc / l, LSE = ln2 * (m + log2 l).
     const float lt = xhalf_sum(lsum);
     const float lr = xhalf_sum(hsum);  // sum of the rounded probabilities
-    // Eight waves.  The accumulator holds 4 consecutive columns of one row per register group, so
+    // The accumulator holds 4 consecutive columns of one row per register group, so
     // a direct store writes 16 bytes to each of 32 rows per instruction, sixteen times per wave.
     // The rows go through LDS instead and leave whole, 16 bytes per lane and four (D = 128) or
     // eight rows per instruction: half as many stores, each over contiguous memory.  The wave's
     // staging space (32 rows in the K tile's layout) lies in the K buffers and the query staging
     // space, which nobody reads after the last tile barrier.
     constexpr int kWaveBytes = C::kKHalf * 2;
-    char *const stg = smem + (NW != 8 ? 0 : w < 6 ? w * kWaveBytes
+    char *const stg = smem + (w < 6 ? w * kWaveBytes
                                                   : (3 * C::kKTile + 3 * C::kVTile) * 2 + (w - 6) * kWaveBytes);
     auto at = [](int row, int chunk) { return L::at(row, chunk); };
     if (SPLIT) {
@@ -580,7 +582,7 @@ attn_fwd_kernel(const FwdArgs a)
         // range contributes O = 0 with LSE = -inf
         const float inv = lr > 0.f ? 1.0f / lr : 0.f;
         const int64_t row0 = ((int64_t)blockIdx.y * a.BH + bh) * S;
-        if constexpr (NW == 8) {
+        {
             // through LDS like O below; an fp32 row is twice as long, so it goes in two halves
             constexpr int CPR = D / 8, RPI = 64 / CPR;
             const int lr_ = l / CPR, lc = l % CPR;
@@ -607,23 +609,11 @@ attn_fwd_kernel(const FwdArgs a)
                 asm volatile("" ::: "memory");
             }
             if (q < S && h == 0) a.LSEpart[row0 + q] = lt > 0.f ? (m + fast_log2(lt)) * kLn2 : -INFINITY;
-        } else if (q < S) {
-            float *Op = a.Opart + (row0 + q) * D;
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    f32x4 ov;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) ov[e] = o[db][4 * g + e] * inv;
-                    *(f32x4 *)(Op + 32 * db + 8 * g + 4 * h) = ov;
-                }
-            if (h == 0) a.LSEpart[row0 + q] = lt > 0.f ? (m + fast_log2(lt)) * kLn2 : -INFINITY;
         }
         return;
     }
     const float inv = 1.0f / lr;
-    if constexpr (NW == 8) {
+    {
         constexpr int CPR = D / 8, RPI = 64 / CPR;  // chunks per row; rows per store instruction
 #pragma unroll
         for (int db = 0; db < DB; ++db)
@@ -640,17 +630,6 @@ attn_fwd_kernel(const FwdArgs a)
             if (row < S && lc * 8 < Dr) *(u32x4 *)(a.O + base + (int64_t)row * a.stride_s + lc * 8) = v;
         }
         if (q < S && h == 0) a.LSE[(int64_t)bh * S + q] = (m + fast_log2(lt)) * kLn2;
-    } else if (q < S) {
-        elem *Op = a.O + base + (int64_t)q * a.stride_s;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const elem4 ov = pack4(o[db][4 * g] * inv, o[db][4 * g + 1] * inv,
-                                        o[db][4 * g + 2] * inv, o[db][4 * g + 3] * inv);
-                if (32 * db + 8 * g + 4 * h < Dr) *(elem4 *)(Op + 32 * db + 8 * g + 4 * h) = ov;
-            }
-        if (h == 0) a.LSE[(int64_t)bh * S + q] = (m + fast_log2(lt)) * kLn2;
     }
 }
 
