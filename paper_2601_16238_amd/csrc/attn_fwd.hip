@@ -761,23 +761,12 @@ static int launch_fwd_nw(const FwdArgs &a, bool causal, hipStream_t st)
                   : launch_fwd_kernel<D, U, NW, false, false, MAIN>(a, st);
 }
 
-// Whether four waves at D = 64 take the form with the pipelined main loop.  The generic form takes a lone
-// wave about 990 cycles per sub-tile, most of them between its phases, not in arithmetic or waits for
-// memory; the main loop needs a third V buffer and more registers, so that two work-groups fit a compute
-// unit instead of three.  It is entered from three whole tiles on.  Time relative to the generic form:
-// launches of up to two work-groups per unit 0.8 (8 heads of 2048 rows, causal) .. 0.98 (256 of 200, no
-// mask); more of them, sequences below 1024 rows: 1.05 .. 1.27 (384 heads of 135 rows 13.3 -> 15.5 us, 192 of
-// 464 causal 19.3 -> 21.4), except where they fill two rounds: 0.92 .. 1.04 with 897 .. 1024; longer
-// sequences: 1.0 +- 0.08, worst in the second round's lower half (96 heads of 1024 rows 1.09).
-static bool four_wave_main(const FwdArgs &a)
-{
-    if (a.nsplit > 1) return true;  // at least four tiles each
-    if (a.Sk < 192) return false;
-    const int64_t wgs = (int64_t)a.BH * a.nqt;
-    if (wgs <= 512) return true;
-    if (wgs > 896 && wgs <= 1024) return a.Sk >= 512;
-    return a.S >= 1024 && (a.S >= 2400 || wgs <= 672 || wgs > 1024);
-}
+// Whether four waves at D = 64 take the form with the pipelined main loop: from four tiles on.  (It is entered from
+// three whole tiles on, and its third V buffer and registers still let three work-groups share a compute unit.)  Over
+// 150 problems of 64 .. 3300 rows, up to 4000 work-groups, time relative to the generic form: 0.79 .. 1.04 from 256 keys on,
+// 0.94 on average (36 heads of 900 rows causal 19.6 -> 16.8 us, 275 of 349 rows on 1104 keys 39.4 -> 34.1), 0.96 .. 1.04 with
+// 192 .. 255, 1.0 .. 1.05 with fewer (347 of 95 7.6 -> 8.0).
+static bool four_wave_main(const FwdArgs &a) { return a.nsplit > 1 || a.Sk >= 256; }
 
 // Waves per work-group: 8 (256 query rows) unless the sequence is too short to fill them.
 // With D = 128 at least 4 (waves whose rows lie past the end compute and store nothing useful,
@@ -812,10 +801,24 @@ static int fwd_waves_for(int S, int D, int BH, bool causal, int split_keys)
     return blocks32;  // 1 or 2
 }
 
+// ... of an unsplit launch at D = 64 from 225 rows on (split ones, and the plan that splits them: the rule above).  Of
+// four-wave work-groups with the main loop three share a compute unit, and a fourth of a unit's rows is the finer
+// grain; eight waves only without a mask where they find a unit each and twice as many of four do not (32 heads of
+// 1957 rows 41 | 39 us, 0.92 .. 0.96 of the time), for narrow tensors also where two of them fill every unit (32 of 3569,
+// D = 32, 93 | 86).  us, eight -> four: 65 of 817 34 -> 20, 128 of 1674 on few units 30 -> 23, 454 of 388 47 -> 40; causal 2473
+// of 282 174 -> 94, 675 of 703 95 -> 77, 72 of 3851 207 -> 184.  Of 220 problems of up to 20 rounds 156 change, to
+// 0.85 of the time on average, none above 1.06 (narrow ones; 1.04 above 32 columns).
+static int fwd_waves_unsplit(int S, int BH, bool causal, bool narrow)
+{
+    const int64_t w8 = (int64_t)BH * ((S + 255) / 256), w4 = (int64_t)BH * ((S + 127) / 128);
+    return !causal && w4 > 256 && (w8 <= 256 || (narrow && w8 > 384 && w8 <= 512)) ? 8 : 4;
+}
+
 template <int D, int U = D>
 static int launch_fwd_d(FwdArgs a, bool causal, hipStream_t st)
 {
-    const int nw = fwd_waves_for(a.S, D, a.BH, causal, a.nsplit > 1 ? a.Sk : 0);
+    const int nw = D == 64 && a.nsplit <= 1 && a.S > 224 ? fwd_waves_unsplit(a.S, a.BH, causal, U < D)
+                                                         : fwd_waves_for(a.S, D, a.BH, causal, a.nsplit > 1 ? a.Sk : 0);
     a.nqt = (a.S + nw * 32 - 1) / (nw * 32);
     if (nw == 8) return launch_fwd_nw<D, U, 8, true>(a, causal, st);
     if constexpr (D < 128) {

@@ -12,6 +12,12 @@ SHAPES = [(1, 6, 191, 191, 64, True), (1, 6, 192, 192, 64, True), (1, 256, 200, 
           (1, 257, 200, 200, 64, False), (1, 257, 225, 225, 40, True), (3, 150, 129, 300, 64, False),
           (3, 150, 129, 520, 64, True), (1, 86, 1030, 1030, 64, True), (1, 60, 1100, 1100, 64, True)]
 
+# ... and those that choose between four waves and eight: three and four tiles; 256 and 257 work-groups of four waves and of
+# eight, without a mask; narrow tensors; many heads under a mask; more keys than rows
+SHAPES += [(1, 40, 255, 255, 64, False), (1, 40, 256, 256, 64, False), (1, 85, 300, 300, 64, False), (1, 86, 300, 300, 64, False),
+           (1, 128, 257, 257, 64, False), (1, 129, 257, 257, 64, False), (1, 193, 260, 260, 32, False),
+           (1, 513, 300, 300, 64, True), (2, 48, 240, 577, 48, False)]
+
 
 @pytest.mark.parametrize("B,H,Sq,Sk,D,causal", SHAPES)
 def test_four_waves(B, H, Sq, Sk, D, causal):
