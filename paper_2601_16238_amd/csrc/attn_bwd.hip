@@ -1591,20 +1591,28 @@ static int launch_dq_split(BwdArgs a, hipStream_t st)
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// Waves per work-group of the unsplit dQ kernel (D = 64 or 128): eight, i.e. 256 rows, unless they would
+// Waves per work-group of the unsplit dQ kernel (D = 64 or 128).  At D = 128 eight, i.e. 256 rows, unless they would
 // leave compute units (256) idle while 128-row ones would not (few heads and rows against many keys, e.g.
-// chunked prefill); at D = 128, where one work-group fills a unit either way, without a mask also where the
-// 128-row ones would need a second round (32 heads of 1537 rows 84 -> 64 us, 48 of 1024 61 -> 43).  Under a
-// causal mask 128-row work-groups also balance the unequal tiles better as long as the launch is small: at
-// D = 128 up to one 256-row work-group per unit (B=1 H=16 S=4096: 135 -> 117 us, B=1 H=8 S=8192: 256 -> 220
-// us; with 1.25 per unit already 15 % slower), at D = 64 (two fit a unit) up to four (B=8 H=8 S=1024: 28.9
-// -> 26.6 us, B=4 H=8 S=2048: 45.4 -> 42.0 us).
-static int dq_waves(int BH, int S, int D, bool causal)
+// chunked prefill); without a mask also where the 128-row ones would need a second round (32 heads of 1537 rows
+// 84 -> 64 us, 48 of 1024 61 -> 43).  Under a causal mask 128-row work-groups also balance the unequal tiles better as
+// long as the launch is small: up to one 256-row work-group per unit (B=1 H=16 S=4096: 135 -> 117 us, B=1 H=8 S=8192:
+// 256 -> 220 us; with 1.25 per unit already 15 % slower).
+// At D = 64 three work-groups of four waves share a unit, and from 225 rows on four are taken except where eight are better:
+// without a mask where those find a unit each and twice as many of four do not (14 heads of 3820 rows 88 | 82 us), and
+// for narrow tensors where two of eight fill every unit (23 of 4854, D = 32, 155 | 130) or, causal, in large launches
+// (136 of 2198 109 | 102).  us, eight -> four: 102 of 869 46 -> 38, 316 of 318 32 -> 23; causal 860 of 330 65 -> 42, 364 of 1230
+// 159 -> 140, 102 of 4484 422 -> 391; 0.91 of the time of the former rule (eight where they fill the units, under a mask
+// four times) on average over 110 problems, 0.87 over the 75 that change, none above 1.04.
+static int dq_waves(int BH, int S, int D, bool causal, bool narrow = false)
 {
     const int blocks32 = (S + 31) / 32;
     const int64_t wgs8 = (int64_t)BH * ((S + 255) / 256), wgs4 = (int64_t)BH * ((S + 127) / 128);
-    const bool prefer4 = causal && (D == 64 ? wgs8 < 1024 : wgs8 <= 256);
-    const bool fill8 = wgs8 >= 256 || (D == 128 && !causal && wgs4 > 256);
+    if (D == 64 && blocks32 >= 8) {
+        if (causal) return narrow && wgs8 >= 1024 ? 8 : 4;
+        return wgs4 > 256 && (wgs8 <= 256 || (narrow && wgs8 > 384 && wgs8 <= 512)) ? 8 : 4;
+    }
+    const bool prefer4 = causal && wgs8 <= 256;
+    const bool fill8 = wgs8 >= 256 || (!causal && wgs4 > 256);
     if (blocks32 >= 8 && fill8 && !prefer4) return 8;
     if (blocks32 >= 3) return std::min(blocks32, 4);
     // (one wave: only D = 64; with D = 128 a lone wave would spill while it streams tiles)
@@ -1619,7 +1627,7 @@ static int launch_dq_u(const BwdArgs &a, hipStream_t st)
     if constexpr (D > 128) return a.dq_nsplit > 1 ? -1 : launch_dq<D, U, 4, CAUSAL>(a, st);
     else {
     if (a.dq_nsplit > 1) return launch_dq_split<D, U, CAUSAL>(a, st);
-    const int nw = dq_waves(a.BH, a.S, D, CAUSAL);
+    const int nw = dq_waves(a.BH, a.S, D, CAUSAL, U < D);
     if (nw == 8) return launch_dq<D, U, 8, CAUSAL>(a, st);
     if (nw == 4) return launch_dq<D, U, 4, CAUSAL>(a, st);
     if (nw == 3) return launch_dq<D, U, 3, CAUSAL>(a, st);
