@@ -46,7 +46,8 @@ def measured_traffic_bytes(workload, kernel):
         return None
     for ln in lines[start:]:
         f = ln.split()
-        if len(f) == 5 and f[0].startswith(kernel + "<"):
+        # (dK/dV of large launches: attn_bwd_dkdv_solo_kernel)
+        if len(f) == 5 and f[0].replace("_solo_kernel<", "_kernel<").startswith(kernel + "<"):
             return int((float(f[3]) + float(f[4])) * 1024 * 1024)
     return None
 

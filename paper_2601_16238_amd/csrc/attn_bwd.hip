@@ -7,6 +7,7 @@
 //               accumulates in registers                           (3 GEMMs per tile pair)
 // or, above D = 64 where the workspace holds dS: 1, 2 (which also stores dS), and
 //   3b. dQ    : the same from the stored dS                        (1 GEMM per tile pair; waits for dS)
+// (2 in attn_bwd_solo.hip for launches that dkdv_takes_solo names)
 // or, for calls of few work-groups: 1, then 2 and 3 side by side in one launch.
 // With dP = dO V^T and dS = P o (dP - delta):
 //   dV = P^T dO,  dK = scale * dS^T Q,  dQ = scale * dS K.
