@@ -107,7 +107,9 @@ attn_bwd_dkdv_solo_kernel(const BwdArgs a)
         }
     };
     // The next slot is in LDS, for every wave: this one's transfers of it are older than those of the kAhead - 1 slots
-    // after it (stores in between only make the wait longer).
+    // after it (stores in between only make the wait longer).  The transfers behind the barrier go into the ring position
+    // of the slot before the current one: its fragments were operands of products that stand before the barrier, so
+    // no wave has reads of it left to wait for.
     auto admit = [&]() __attribute__((always_inline)) {
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"((C::kAhead - 1) * C::kDma) : "memory");
         __builtin_amdgcn_s_barrier();
@@ -195,7 +197,9 @@ attn_bwd_dkdv_solo_kernel(const BwdArgs a)
     int ds_len = ds_row_len(t0, Sk, coff, CAUSAL);
     const uint32_t ds_voff = (uint32_t)k0 * 64u + (uint32_t)(((r >> 2) * 16 + h * 4 + (r & 3)) * 16);
 
-    // (after the barrier that admits slot g come the transfers of slot g + kAhead)
+    // (after the barrier that admits slot g come the transfers of slot g + kAhead; those of the first two go into the
+    // space that K and V were sorted through, whose reads have to be done)
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     admit();
     dma_slot();
     step_fetch();
