@@ -383,20 +383,21 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
                 // from -delta of its row, so that it ends as dP - delta.  The lane's key is fixed;
                 // P = exp2(c S - lse2) per row.
                 const bool masked = (q_lo + 32 > S) || (CAUSAL && q_lo + coff < k0 + 31);
-                // score i = `with` unless its row is visible: row offsets >= key - coff - q_lo (causal), <= S - 1 - q_lo
-                auto hide = [&](float with) __attribute__((always_inline)) {
+                // P = 0 unless the row is visible: row offsets >= key - coff - q_lo (causal), <= S - 1 - q_lo.  (P, not S:
+                // a row whose statistics are NaN says nothing about keys that it does not see.)
+                auto hide = [&]() __attribute__((always_inline)) {
                     const int lo = (CAUSAL ? key - coff - q_lo : -64) - 4 * h;
                     const int hi = S - 1 - q_lo - 4 * h;
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
                         const int ro = 8 * (i / 4) + (i % 4);
-                        if (ro < lo || ro > hi) s[i] = with;
+                        if (ro < lo || ro > hi) s[i] = 0.f;
                     }
                 };
                 if constexpr (D > 128) {
-                    // One wave per SIMD: the scores in the vector half of the register file, the mask on S instead
-                    // of P (so that P is packed next to the MFMAs of dP), the next slot's scalar work between
-                    // the MFMAs of S: in this order nothing but dS is left behind the last MFMA.
+                    // One wave per SIMD: the scores in the vector half of the register file, the next slot's scalar work
+                    // between the MFMAs of S: in this order P is packed while the last MFMA of dP runs, and
+                    // nothing but dS is left behind it.
                     constexpr int kAhead = 4;
                     elem8 f[2 * KS];
                     auto fetch = [&](int n) __attribute__((always_inline)) {
@@ -424,10 +425,6 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
                         }
                         __builtin_amdgcn_sched_barrier(0);
                     }
-                    if (masked) {
-                        asm volatile("s_nop 15\n\ts_nop 15" : "+v"(s));  // (from the MFMA just issued, see mfma_v)
-                        hide(-INFINITY);
-                    }
 #pragma unroll
                     for (int ks = 0; ks < KS; ++ks) {
                         mfma_v(dp, f[KS + ks], vf[ks]);
@@ -438,6 +435,7 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
                             s[i] = fast_exp2(__builtin_fmaf(s[i], c, -l4[i / 4][i % 4]));
                         __builtin_amdgcn_sched_barrier(0);
                     }
+                    if (masked) hide();
                     elem8 *x = Xs + (g & 1) * (C::kPairs * 256);
                     x[0] = pack8(s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7]);
                     x[64] = pack8(s[8], s[9], s[10], s[11], s[12], s[13], s[14], s[15]);
@@ -487,7 +485,7 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
                             __builtin_amdgcn_sched_barrier(0);
                         }
                     }
-                    if (masked) hide(0.f);
+                    if (masked) hide();
                 }
 #pragma unroll
                 for (int i = 0; i < 16; ++i) dp[i] *= s[i];  // dS = P o (dP - delta)

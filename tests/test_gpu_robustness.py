@@ -204,3 +204,31 @@ def test_stage_wise_backward_equals_the_full_call(B, H, S, D, causal):
     gref = oracle.attn_bwd(x["Q"], x["K"], x["V"], x["dO"], x["scale"], causal)
     for nm, t, r in zip(("dQ", "dK", "dV"), outs, gref):
         check_bf16(nm, to_f64(t), r)
+
+
+@pytest.mark.parametrize("H,Hkv,Sq,Sk,D", [(72, 36, 700, 2311, 128), (72, 36, 700, 2311, 96), (2, 2, 700, 931, 256),
+                                           (36, 36, 700, 931, 256), (2, 2, 700, 931, 128), (2, 2, 700, 931, 64)])
+def test_a_nan_row_leaves_the_keys_that_it_does_not_see(H, Hkv, Sq, Sk, D):
+    """Under a causal mask dV of a key is a sum over the rows that see it: with a row of Q, and so of O and LSE, without
+    a value the others' are the same bits, also in the row's own blocks (the row and the key limit lie inside them).
+    The largest launches of 65 to 128 columns run the dK/dV kernel of 64 keys a wave, and D = 256 has its own."""
+    print("case nan_row", H, Hkv, Sq, Sk, D, flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(D)
+    Q, dO = (torch.randn((1, H, Sq, D), generator=g, device="cuda").bfloat16() for _ in range(2))
+    K, V = (torch.randn((1, Hkv, Sk, D), generator=g, device="cuda").bfloat16() for _ in range(2))
+
+    def dv(best):
+        O, LSE = attn.attn_fwd_rect(Q, K, V, D ** -0.5, True)
+        n = attn.attn_bwd_rect_best_workspace_bytes(1, H, Hkv, Sq, Sk, D, True) if best else (8 * H * Sq + 255) // 256 * 256
+        ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+        return attn.attn_bwd_rect(Q, K, V, O, dO, LSE, D ** -0.5, True, workspace=ws)[2].view(torch.int16)
+
+    row, head = 333, H - 1
+    seen = row + Sk - Sq + 1
+    clean = [dv(best) for best in (False, True)]
+    Q[0, head, row] = float("nan")
+    for best, want in zip((False, True), clean):
+        got = dv(best)
+        torch.cuda.synchronize()
+        assert torch.equal(got[:, :-1], want[:, :-1]) and torch.equal(got[:, -1, seen:], want[:, -1, seen:])
