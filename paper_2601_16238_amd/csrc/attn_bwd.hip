@@ -439,7 +439,7 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
                     elem8 *x = Xs + (g & 1) * (C::kPairs * 256);
                     x[0] = pack8(s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7]);
                     x[64] = pack8(s[8], s[9], s[10], s[11], s[12], s[13], s[14], s[15]);
-                    asm volatile("s_nop 11" : "+v"(dp));  // (from the MFMA just issued)
+                    mfma_settled(dp);
                 } else {
                     f32x16 zero, nd;
 #pragma unroll

@@ -286,7 +286,7 @@ attn_bwd_dkdv_solo_kernel(const BwdArgs a)
         // heads on 26 of 1156 rows D = 96.  (Zeros in P behind a branch next to the exp2 of either half: up to 1.010, and
         // 1.018; a loop of its own for such slots: up to 1.006, and 1.023.)
         auto hide = [&]() __attribute__((always_inline)) {
-            asm volatile("s_nop 15\n\ts_nop 15" : "+v"(s[0]), "+v"(s[1]));  // (from the MFMAs just issued, see mfma_v)
+            mfma_settled(s[0], s[1]);
             read_lse(0, 4);
             const int hi = S - 1 - q_lo - 4 * h;
 #pragma unroll

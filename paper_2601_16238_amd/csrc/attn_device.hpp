@@ -37,11 +37,11 @@ __device__ __forceinline__ f32x16 mfma32(elem8 a, elem8 b, f32x16 c)
 // The product with its result in the vector half of the register file (c += a b; mfma_v0: c = a b), for kernels of
 // one wave per SIMD.  As assembly: where a kernel needs more than 256 registers the compiler puts the result of every
 // MFMA into the accumulation half, and scores, which vector instructions read next, are moved back one by one.  It does
-// not know, then, that a vector instruction may read the result only 11 wait states (44 cycles) after the issue: the
-// caller keeps two more products, of 32 cycles each, in between, and orders the reads behind them (an empty asm statement
-// on the result, and on a product's if that is not volatile itself), also where it goes on without the result, whose
-// registers are then another value's.  Nor must an operand come from a vector instruction
-// (they are LDS reads, and registers set before the loop).
+// not know, then, that a vector instruction may read the result only 12 wait states (48 cycles) after the issue, the
+// s_nop 11 that it puts there itself: the caller keeps two more products, of 32 cycles each, in between, and orders the
+// reads behind them (an empty asm statement on the result, and on a product's if that is not volatile itself), or calls
+// mfma_settled, also where it goes on without the result, whose registers are then another value's.  Nor must an operand
+// come from a vector instruction (they are LDS reads, and registers set before the loop).
 #ifdef ATTN_F16
 #define ATTN_MFMA "v_mfma_f32_32x32x16_f16"
 #else
@@ -55,6 +55,9 @@ __device__ __forceinline__ void mfma_v0(f32x16 &c, elem8 a, elem8 b)
 {
     asm volatile(ATTN_MFMA " %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(b));
 }
+// The results of products just issued may be read.
+__device__ __forceinline__ void mfma_settled(f32x16 &c) { asm volatile("s_nop 11" : "+v"(c)); }
+__device__ __forceinline__ void mfma_settled(f32x16 &c, f32x16 &d) { asm volatile("s_nop 11" : "+v"(c), "+v"(d)); }
 
 // Row of a 32x32 accumulator block held in register i by a lane of half h = lane/32.
 __device__ __forceinline__ constexpr int acc_row(int i, int h) { return 8 * (i / 4) + 4 * h + (i % 4); }

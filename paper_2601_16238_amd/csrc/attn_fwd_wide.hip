@@ -232,7 +232,7 @@ attn_fwd_wide_kernel(const FwdArgs a)
     auto mask = [&](int kt, int u, f32x16 &s) __attribute__((always_inline)) {
         const int kb = kt * C::kBC + 32 * u;
         if ((kb + 32 > Sk) || (CAUSAL && kb + 31 > q0e)) {
-            if (kVec) asm volatile("s_nop 15\n\ts_nop 15" : "+v"(s));  // (from the MFMA just issued, see mfma_v)
+            if (kVec) mfma_settled(s);
             const int lim = (CAUSAL ? min(qpos + coff, Sk - 1) : Sk - 1) - kb - 4 * h;
 #pragma unroll
             for (int i = 0; i < 16; ++i)
@@ -463,7 +463,7 @@ attn_fwd_wide_kernel(const FwdArgs a)
             }
             if (__builtin_expect(overflow(sumA), 0)) {
                 // (nothing else may be written to sB's registers while its last product is in flight)
-                if (kVec) asm volatile("s_nop 15\n\ts_nop 15" : "+v"(sB));
+                if (kVec) mfma_settled(sB);
                 redo = 0;
                 break;
             }
