@@ -1590,25 +1590,26 @@ static int launch_dq_split(BwdArgs a, hipStream_t st)
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
+#ifndef ATTN_F16
 // Waves per work-group of the unsplit dQ kernel (D = 64 or 128).  At D = 128 eight, i.e. 256 rows, unless they would
 // leave compute units (256) idle while 128-row ones would not (few heads and rows against many keys, e.g.
 // chunked prefill); without a mask also where the 128-row ones would need a second round (32 heads of 1537 rows
 // 84 -> 64 us, 48 of 1024 61 -> 43).  Under a causal mask 128-row work-groups also balance the unequal tiles better as
 // long as the launch is small: up to one 256-row work-group per unit (B=1 H=16 S=4096: 135 -> 117 us, B=1 H=8 S=8192:
 // 256 -> 220 us; with 1.25 per unit already 15 % slower).
-// At D = 64 three work-groups of four waves share a unit, and from 225 rows on four are taken except where eight are better:
-// without a mask where those find a unit each and twice as many of four do not (14 heads of 3820 rows 88 | 82 us), and
-// for narrow tensors where two of eight fill every unit (23 of 4854, D = 32, 155 | 130) or, causal, in large launches
-// (136 of 2198 109 | 102).  us, eight -> four: 102 of 869 46 -> 38, 316 of 318 32 -> 23; causal 860 of 330 65 -> 42, 364 of 1230
-// 159 -> 140, 102 of 4484 422 -> 391; 0.91 of the time of the former rule (eight where they fill the units, under a mask
-// four times) on average over 110 problems, 0.87 over the 75 that change, none above 1.04.
-static int dq_waves(int BH, int S, int D, bool causal, bool narrow = false)
+// At D = 64 from 225 rows on: without a mask see WaveRule; causal four, except for narrow tensors in large launches.  us,
+// four | eight: 14 heads of 3820 rows 88 | 82, 102 of 869 38 | 46, 316 of 318 23 | 32, 23 of 5113 210 | 203, but 147 of
+// 766 40 | 41; causal 860 of 330 42 | 65, 364 of 1230 140 | 159, 102 of 4484 391 | 422, D = 32 136 of 2198 109 | 102, 1229 of
+// 453 72 | 65, 76 of 3367 142 | 114.  Without a mask, over 340 problems of 228 .. 6200 rows and 200 .. 5000 work-groups of
+// four, 1.000 of the time of the better of the two on average, none above 1.013; causal and above 32 columns, over 171 from
+// 1024 work-groups of eight on, 0.80 of the time of eight, none above 1.025 (64 of 4075 207 | 202).
+int dq_waves(int BH, int S, int Sk, int D, bool causal, bool narrow)
 {
     const int blocks32 = (S + 31) / 32;
     const int64_t wgs8 = (int64_t)BH * ((S + 255) / 256), wgs4 = (int64_t)BH * ((S + 127) / 128);
     if (D == 64 && blocks32 >= 8) {
-        if (causal) return narrow && wgs8 >= 1024 ? 8 : 4;
-        return wgs4 > 256 && (wgs8 <= 256 || (narrow && wgs8 > 384 && wgs8 <= 512)) ? 8 : 4;
+        static const WaveRule rule = {{5.9f, 3.4f, {0.49f, 0.91f, 1.29f}, 3}, {5.65f, 3.7f, {0.85f, 1.52f}, 2}, 1280};
+        return (causal ? narrow && wgs8 >= 1024 : takes_eight_waves(rule, BH, S, Sk, narrow)) ? 8 : 4;
     }
     const bool prefer4 = causal && wgs8 <= 256;
     const bool fill8 = wgs8 >= 256 || (!causal && wgs4 > 256);
@@ -1617,6 +1618,7 @@ static int dq_waves(int BH, int S, int D, bool causal, bool narrow = false)
     // (one wave: only D = 64; with D = 128 a lone wave would spill while it streams tiles)
     return D == 128 ? 2 : blocks32;
 }
+#endif
 
 template <int D, int U, bool CAUSAL>
 static int launch_dq_u(const BwdArgs &a, hipStream_t st)
@@ -1626,7 +1628,7 @@ static int launch_dq_u(const BwdArgs &a, hipStream_t st)
     if constexpr (D > 128) return a.dq_nsplit > 1 ? -1 : launch_dq<D, U, 4, CAUSAL>(a, st);
     else {
     if (a.dq_nsplit > 1) return launch_dq_split<D, U, CAUSAL>(a, st);
-    const int nw = dq_waves(a.BH, a.S, D, CAUSAL, U < D);
+    const int nw = dq_waves(a.BH, a.S, a.Sk, D, CAUSAL, U < D);
     if (nw == 8) return launch_dq<D, U, 8, CAUSAL>(a, st);
     if (nw == 4) return launch_dq<D, U, 4, CAUSAL>(a, st);
     if (nw == 3) return launch_dq<D, U, 3, CAUSAL>(a, st);
@@ -1839,7 +1841,7 @@ int dq_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps, int most)
         // (the unsplit launch mostly has work-groups of 128 rows, the split one of 256)
         nsplit = longest_split_plan(D > 64 ? LongestCost{7.0f, 1.38f, 1.6f, 2.2f, 256} : LongestCost{7.0f, 0.94f, 1.0f, 1.6f, 512},
                                     wgs, tiles, tiles - S / 128.0f, (size_t)BH * S * D * 4, causal, std::min(most, 16),
-                                    S, dq_waves(BH, S, D, causal) == 8 ? wgs : (int64_t)BH * ((S + 127) / 128));
+                                    S, dq_waves(BH, S, Sk, D, causal, false) == 8 ? wgs : (int64_t)BH * ((S + 127) / 128));
     const int tiles_per = (tiles + nsplit - 1) / nsplit;
     nsplit = (tiles + tiles_per - 1) / tiles_per;  // no empty split
     if (kps) *kps = tiles_per * 64;

@@ -780,7 +780,7 @@ static int fwd_waves_for(int S, int D, int BH, bool causal, int split_keys)
     // D = 64 under a causal mask with fewer than four 256-row work-groups per compute unit:
     // 128-row work-groups (two or three fit a compute unit at D = 64) balance the unequal tiles
     // better.  Measured: B=8 H=8 S=1024 26.5 -> 24.3 us, B=16 H=16 S=512 29.5 -> 27.6 us; not
-    // so without a mask (+5 %), at D = 128 (+4..33 % on mid-size shapes) or on large problems.
+    // so at D = 128 (+4..33 % on mid-size shapes).  (Split launches; unsplit ones: fwd_waves_unsplit.)
     if (blocks32 >= 8 && D == 64 && causal && (int64_t)BH * ((S + 255) / 256) < 1024) return 4;
     if (blocks32 >= 8) return 8;
     // Five to seven blocks at D = 128, where a work-group fills a unit whatever its waves: two work-groups of
@@ -801,23 +801,27 @@ static int fwd_waves_for(int S, int D, int BH, bool causal, int split_keys)
     return blocks32;  // 1 or 2
 }
 
-// ... of an unsplit launch at D = 64 from 225 rows on (split ones, and the plan that splits them: the rule above).  Of
-// four-wave work-groups with the main loop three share a compute unit, and a fourth of a unit's rows is the finer
-// grain; eight waves only without a mask where they find a unit each and twice as many of four do not (32 heads of
-// 1957 rows 41 | 39 us, 0.92 .. 0.96 of the time), for narrow tensors also where two of them fill every unit (32 of 3569,
-// D = 32, 93 | 86).  us, eight -> four: 65 of 817 34 -> 20, 128 of 1674 on few units 30 -> 23, 454 of 388 47 -> 40; causal 2473
-// of 282 174 -> 94, 675 of 703 95 -> 77, 72 of 3851 207 -> 184.  Of 220 problems of up to 20 rounds 156 change, to
-// 0.85 of the time on average, none above 1.06 (narrow ones; 1.04 above 32 columns).
-static int fwd_waves_unsplit(int S, int BH, bool causal, bool narrow)
+#ifndef ATTN_F16
+// ... of an unsplit launch at D = 64 from 225 rows on (split ones, and the plan that splits them: the rule above; the
+// rule without a mask: see WaveRule).  us, four | eight: 32 heads of 1957 rows 41 | 39, 65 of 817 20 | 34, 454 of 388
+// 40 | 47, 22 of 4747 163 | 157, 39 of 2809 99 | 97, but 159 of 700 32 | 34; D = 32: 1272 of 234 29 | 27, 80 of
+// 3047 155 | 145, 134 of 583 20 | 23, 250 of 291 12 | 13.  Over 600 problems of 228 .. 6200 rows and 200 .. 5000
+// work-groups of four it takes 1.000 of the time of the better of the two on average, none above 1.04 (1.01 above 32
+// columns).  Causal, where work-groups are unequal and a round has no sharp end, four: 2473 of 282 94 | 174, 675 of 703
+// 77 | 95, 72 of 3851 184 | 207; of 286 problems from 1024 work-groups of eight on (below, the rule above takes four as
+// well) 0.77 of the time of eight on average and none above it, up to 32 columns 0.92 and up to 1.09 in two rounds that eight
+// just fill (53 of 5231 165 | 151).
+int fwd_waves_unsplit(int BH, int S, int Sk, bool causal, bool narrow)
 {
-    const int64_t w8 = (int64_t)BH * ((S + 255) / 256), w4 = (int64_t)BH * ((S + 127) / 128);
-    return !causal && w4 > 256 && (w8 <= 256 || (narrow && w8 > 384 && w8 <= 512)) ? 8 : 4;
+    static const WaveRule rule = {{6.2f, 2.2f, {0.41f, 0.77f, 1.10f}, 3}, {6.2f, 2.6f, {0.71f, 1.39f}, 2}, 1792};
+    return !causal && takes_eight_waves(rule, BH, S, Sk, narrow) ? 8 : 4;
 }
+#endif
 
 template <int D, int U = D>
 static int launch_fwd_d(FwdArgs a, bool causal, hipStream_t st)
 {
-    const int nw = D == 64 && a.nsplit <= 1 && a.S > 224 ? fwd_waves_unsplit(a.S, a.BH, causal, U < D)
+    const int nw = D == 64 && a.nsplit <= 1 && a.S > 224 ? fwd_waves_unsplit(a.BH, a.S, a.Sk, causal, U < D)
                                                          : fwd_waves_for(a.S, D, a.BH, causal, a.nsplit > 1 ? a.Sk : 0);
     a.nqt = (a.S + nw * 32 - 1) / (nw * 32);
     if (nw == 8) return launch_fwd_nw<D, U, 8, true>(a, causal, st);

@@ -128,6 +128,31 @@ int fwd_split_plan(int BH, int S, int Sk, int D, bool causal, bool packed, int *
 struct LongestCost { float fixed, alone, alone_split, full; int resident; };
 int longest_split_plan(const LongestCost &c, int64_t wgs, int tiles, float average, size_t part_bytes, bool causal,
                        int most, int S = 0, int64_t unsplit_wgs = 0);
+// Four or eight waves (128 or 256 rows) per work-group at D = 64 without a mask, where all work-groups are equal.  Of four
+// waves three work-groups share a compute unit, 768 are resident, of eight two: a launch that just passes its last round
+// pays for a whole one.  RoundCost: us of a launch besides its rounds, of a further round besides its tiles, and of a
+// 64-key tile with one, two, three work-groups on a unit.
+//  - Above 32 columns four, except where eight find a unit each and twice as many of four do not, or (from `keys` on)
+//    where those of eight are resident at once and those of four are not.
+//  - Up to 32 columns two of eight waves fill a unit as well as three of four, and it is the rounds that decide: the lesser of the
+//    two estimates.
+struct RoundCost { float fixed, round, tile[3]; int per_cu; };
+struct WaveRule { RoundCost four, eight; int keys; };
+inline float rounds_us(const RoundCost &c, int64_t wgs, int tiles)
+{
+    const int64_t resident = 256 * c.per_cu, before = (wgs - 1) / resident, last = wgs - before * resident;
+    return c.fixed + before * (c.round + tiles * c.tile[c.per_cu - 1]) + tiles * c.tile[(last + 255) / 256 - 1];
+}
+inline bool takes_eight_waves(const WaveRule &c, int BH, int S, int Sk, bool narrow)
+{
+    const int64_t w8 = (int64_t)BH * ((S + 255) / 256), w4 = (int64_t)BH * ((S + 127) / 128);
+    if (narrow) return rounds_us(c.eight, w8, (Sk + 63) / 64) < rounds_us(c.four, w4, (Sk + 63) / 64);
+    return w4 > 256 && (w8 <= 256 || (w4 > 768 && w8 <= 512 && Sk >= c.keys));
+}
+// Waves per work-group of the unsplit forward at D = 64 from 225 rows on, and of the unsplit dQ kernel at D = 64 and 128
+// (narrow: tensors of at most narrow_columns(D)); pure host functions of the shape.
+int fwd_waves_unsplit(int BH, int S, int Sk, bool causal, bool narrow);
+int dq_waves(int BH, int S, int Sk, int D, bool causal, bool narrow);
 // `stages`: bit 0 row statistics, bit 1 dK/dV, bit 2 dQ.  With bits 0 and 2 the dQ kernel
 // forms the statistics (and runs first); bit 0 without bit 2 runs the separate kernel.
 // Number of key splits the dQ kernel would use for this problem (1: none) and the keys per

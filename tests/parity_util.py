@@ -121,6 +121,14 @@ def backward_form(B, Hq, Hkv, Sq, Sk, D, causal, workspace_bytes):
     return binding.lib().attn_bwd_rect_form(ctypes.byref(p), workspace_bytes)
 
 
+def host_rule(name, *args):
+    """A rule of the dispatch, a host function of the shape inside the library: attn::name(int or bool, ...)."""
+    letters = "".join("b" if isinstance(a, bool) else "i" for a in args)
+    f = getattr(binding.lib(), "_ZN4attn%d%sE%s" % (len(name), name, letters))
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_bool if isinstance(a, bool) else ctypes.c_int for a in args]
+    return f(*args)
+
+
 def in_layout(t, layout):
     """t [B,H,S,D] with the same values in [B,S,H,D] storage, or ("padded") with 8 unused columns after every
     row, 3 unused rows after every head and an unused head after every batch entry, all NaN."""
