@@ -848,7 +848,8 @@ static bool streams(int S, int D, bool packed) { return D > 128 || S <= 32 || pa
 #ifndef ATTN_F16  // functions of the shape only: defined once, by the bf16 build
 // Split over the keys.  A launch of few work-groups lasts as long as its longest one; a split shortens
 // that, but every split writes an fp32 partial result that the merge reads.  The launch's time is estimated
-// for every number of splits and the best is taken if it is at least 3 % below the unsplit one.  SplitCost:
+// for every number of splits and the best is taken if it is at least 3 % below the unsplit one (below it, where that is
+// another kernel's).  SplitCost:
 // us that a launch takes besides its tiles, that a further work-group on the same unit takes besides its
 // own; a 64-key tile of a work-group alone on its compute unit, and its share of the unit when several are
 // (no tile takes less than the shares of all of them); work-groups that fit a unit.
@@ -867,7 +868,8 @@ static bool streams(int S, int D, bool packed) { return D > 128 || S <= 32 || pa
 // of 3430 unsplit 98 (133 with 2).  D = 64 without mask: 96 heads of 118 rows on 6729 keys 93, 40 with 4.
 struct SplitCost { float fixed, start, tile, share; int per_cu; };
 
-static int fwd_splits(const SplitCost &c, int64_t wgs, int tiles, int S, float part_mb, bool equal, int most)
+// unsplit: us of the launch without a split where it is another kernel's, else 0.
+static int fwd_splits(const SplitCost &c, int64_t wgs, int tiles, int S, float part_mb, bool equal, int most, float unsplit)
 {
     const int64_t resident = 256 * c.per_cu;
     auto tile_us = [&](int64_t on_a_unit) { return std::max(c.tile, std::min<int64_t>(on_a_unit, c.per_cu) * c.share); };
@@ -912,7 +914,7 @@ static int fwd_splits(const SplitCost &c, int64_t wgs, int tiles, int S, float p
     // 9329 D = 96 (185) 172 | 117, and with more, where the unsplit launch takes a second round: 8 of 8394 D = 128
     // (264) 201 | 175; three pay for longer, 4 of 13775 D = 128 (216) 309 | 304 | 259.
     const bool no_two = !equal && S > 4096 && c.per_cu == 1 && wgs > 188 && wgs <= 256;
-    float least = 0.97f * estimate(1);
+    float least = unsplit > 0 ? unsplit : 0.97f * estimate(1);
     for (int n = no_two ? 3 : 2; n <= most && 4 * n <= tiles && n * wgs <= 1024; ++n) {
         const float t = estimate(n);
         if (t < least) { least = t; best = n; }
@@ -943,7 +945,19 @@ int fwd_split_plan(int BH, int S, int Sk, int D, bool causal, bool packed, int *
                                : nw == 8         ? SplitCost{6.0f, 0.9f, 0.97f, 0.97f, 2}
                                : nw == 4 || wide ? SplitCost{4.9f, 1.0f, 0.73f, 0.58f, 2}
                                                  : SplitCost{4.1f, 0.2f, 0.84f, 0.56f, 3};
-        nsplit = fwd_splits(cost, wgs, tiles, S, (float)BH * S * D * 4e-6f, !causal || S <= tile_rows, std::min(most, 128));
+        // D = 64 without a mask from 225 rows on: the split launch has eight waves, the unsplit one mostly four (see
+        // fwd_waves_unsplit) and is the quicker one for longer.  us, split as if it had eight too | unsplit: 20 heads of
+        // 1119 rows 24 | 17, 21 of 1353 28 | 19, 34 of 572 on 1393 keys 23 | 16; split still: 5 of 5391 on 8474 84 | 95, 43 of
+        // 706 on 3476 42 | 48.  Of 381 problems that were split 230 still are; 1.004 of the time of the better of the two
+        // on average (1.09 before).  (The costs are a few per cent above the average measured, so that a split that
+        // pays stays: over 260 other problems whose plan changed 0.84 of the time before, none above 1.013.)
+        float unsplit = 0.0f;
+        if (D == 64 && !causal && !wide && S > 224) {
+            const bool eight = fwd_waves_unsplit(BH, S, Sk, false, false) == 8;
+            unsplit = rounds_us(eight ? RoundCost{6.0f, 7.9f, {0.97f, 2.08f}, 2} : RoundCost{4.8f, 2.6f, {0.65f, 1.1f, 1.65f}, 3},
+                                (int64_t)BH * ((S + (eight ? 255 : 127)) / (eight ? 256 : 128)), tiles);
+        }
+        nsplit = fwd_splits(cost, wgs, tiles, S, (float)BH * S * D * 4e-6f, !causal || S <= tile_rows, std::min(most, 128), unsplit);
     } else if (S > 32 && rule == SplitRule::longest) {
         const LongestCost cost = D > 128 ? LongestCost{10.0f, 4.3f, 4.3f, 5.0f, 256}
                                  : D > 64 ? LongestCost{7.0f, 1.38f, 1.38f, 1.8f, 256}

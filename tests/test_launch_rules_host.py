@@ -1,7 +1,10 @@
 """Which form of a kernel a launch takes (host only): the rules on the shape, at problems whose forms were timed against
 each other."""
+import ctypes
+
 import pytest
 
+from paper_2601_16238_amd import binding
 from parity_util import host_rule
 
 
@@ -23,3 +26,14 @@ def test_waves_of_the_unsplit_forward_at_64_columns(BH, S, Sk, narrow, waves):
     (162, 768, False, 4), (225, 458, False, 4), (9, 5052, False, 8), (316, 318, False, 4)])  # 43 | 46, 31 | 33, 105 | 96
 def test_waves_of_the_unsplit_dq_at_64_columns(BH, S, narrow, waves):
     assert host_rule("dq_waves", BH, S, S, 64, False, narrow) == waves
+
+
+# us split | unsplit where the plan had split as if the unsplit launch had eight waves too: 24 | 17, 22 | 15, 28 | 19, 14 | 10,
+# 23 | 16, 27 | 21; splits that pay: 31 | 61, 42 | 48, 84 | 95, 46 | 49, 66 | 70
+@pytest.mark.parametrize("BH,S,Sk,nsplit", [
+    (20, 1119, 1119, 1), (16, 1175, 1175, 1), (21, 1353, 1353, 1), (11, 604, 604, 1), (34, 572, 1393, 1), (27, 869, 1886, 1),
+    (1, 5740, 5740, 10), (43, 706, 3476, 3), (5, 5391, 8474, 2), (15, 1284, 4319, 2), (83, 463, 3625, 3)])
+def test_the_forward_at_64_columns_is_split_where_that_is_quicker(BH, S, Sk, nsplit):
+    f = binding.lib()._ZN4attn14fwd_split_planEiiiibbPiiNS_9SplitRuleE
+    f.argtypes = [ctypes.c_int] * 4 + [ctypes.c_bool] * 2 + [ctypes.c_void_p, ctypes.c_int, ctypes.c_int]
+    assert f(BH, S, Sk, 64, False, False, None, 128, 0) == nsplit
