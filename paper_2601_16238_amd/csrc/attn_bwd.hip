@@ -1671,25 +1671,34 @@ static int launch_dq_ds_two(const BwdArgs &a, hipStream_t st)
     else return launch_dq_ds_u<D, D, 8, 2, CAUSAL>(a, st);
 }
 
+#ifndef ATTN_F16
 // Row blocks (of 32 rows) per work-group: eight, one a wave, which read K less often, unless smaller work-groups
 // still fill the compute units in one round.  us, whole backward, 8 | 4 | 2: 11 heads of 1166 rows 61 | 55 | 53,
 // 4 of 5599 causal 173 | 147 | 152, 10 of 1876 D=256 causal 116 | 105 | 105; 8 of 4384 248 | 267 | 284,
 // 32 of 4096 and 16384 five per cent faster with eight.  Long causal heads, whose eight-wave work-groups
 // are the most unequal, take four for longer: 4 of 10802 460 | 427 | 458, 4 of 12527 550 | 530 | 569, but
 // 114 of 321 46 | 51.
-// At D = 128 sixteen, two a wave, in launches of two rounds of them whose rows fill them: half the K tiles, and every
-// fragment of K feeds two products.  us, this kernel alone, 8 | 16: 128 heads of 4096 rows 807 | 734; whole backward:
-// 128 of 2048 causal 470 | 455, 454 of 377 causal 139 | 131, 192 of 2048 1258 | 1228; with fewer the launch ends on a
-// long work-group (64 of 2048 causal 227 | 240, 16 of 4096 causal 220 | 248), rows that pad a second one are lost
-// (482 of 718 causal 341 | 347), and beyond 4096 rows there is no difference (32 of 8192 causal 1502 | 1489, 48 of
-// 8192 4562 | 4627), nor at 96 columns (249 of 1076 286 | 288).
-static int dq_ds_blocks(int64_t heads, int S, int Dr, bool causal)
+// At D = 128 sixteen, two a wave, in launches of two rounds of them: half the K tiles, and every fragment of K feeds
+// two products.  us, this kernel alone, 8 | 16: 128 heads of 4096 rows 807 | 734; whole backward: 128 of 2048 causal
+// 470 | 455, 192 of 2048 1258 | 1228.  Not
+//  - with fewer work-groups, when the launch ends on a long one (64 of 2048 causal 227 | 240, 16 of 4096 causal 220 | 248),
+//    which from 4097 rows on takes two and a half rounds to hide;
+//  - where the rows that only pad them cost more: a ninth more rows without a mask (1.00 of the time there, 1.02 with a
+//    fifth), a seventeenth under one (1.00, and 1.01 with a ninth);
+//  - under a mask below 1600 rows, of which a work-group of 512 sees too unequal parts (1.004 on average, 442 of 935 1.037);
+//  - at 96 columns (249 of 1076 286 | 288).
+// Over 560 whole backwards of 370 .. 9400 rows and 640 .. 4100 blocks of 256 the rule takes sixteen in 190: 0.988 of the
+// time of eight on average, one of them above 1.02; over 260 others in 95: 0.988, none above 1.019.
+int dq_ds_blocks(int heads, int S, int Dr, bool causal)
 {
-    const int blocks256 = (S + 255) / 256;
-    if (Dr > narrow_columns(128) && Dr <= 128 && S <= 4096 && blocks256 % 2 == 0 && heads * blocks256 >= 1024) return 16;
-    if (heads * ((S + 127) / 128) > (causal && S > 4096 ? 512 : 256)) return 8;
-    return heads * ((S + 63) / 64) > 256 ? 4 : 2;
+    const int blocks256 = (S + 255) / 256, padded = (blocks256 + 1) / 2 * 2;  // in blocks of 256 rows
+    if (Dr > narrow_columns(128) && Dr <= 128 && (int64_t)heads * blocks256 >= (S > 4096 ? 1280 : 1024) &&
+        (causal ? S >= 1600 && 17 * padded <= 18 * blocks256 : 9 * padded <= 10 * blocks256))
+        return 16;
+    if ((int64_t)heads * ((S + 127) / 128) > (causal && S > 4096 ? 512 : 256)) return 8;
+    return (int64_t)heads * ((S + 63) / 64) > 256 ? 4 : 2;
 }
+#endif
 
 template <int D>
 static int launch_delta(const BwdArgs &a, hipStream_t st)
@@ -1711,7 +1720,7 @@ static int launch_bwd_ds(BwdArgs a, hipStream_t st)
         a.bkv0 = (int)((int64_t)BHkv * i / n_chunk);
         a.nkv = (int)((int64_t)BHkv * (i + 1) / n_chunk) - a.bkv0;
         if (launch_dkdv<D, CAUSAL, true>(a, st)) return -1;
-        const int blocks = dq_ds_blocks((int64_t)a.nkv * a.group, a.S, a.Dr, CAUSAL);
+        const int blocks = dq_ds_blocks(a.nkv * a.group, a.S, a.Dr, CAUSAL);
         if (blocks == 16 ? launch_dq_ds_two<D, CAUSAL>(a, st) : blocks == 8 ? launch_dq_ds<D, 8, CAUSAL>(a, st)
                          : blocks == 4 ? launch_dq_ds<D, 4, CAUSAL>(a, st) : launch_dq_ds<D, 2, CAUSAL>(a, st)) return -1;
     }

@@ -153,6 +153,8 @@ inline bool takes_eight_waves(const WaveRule &c, int BH, int S, int Sk, bool nar
 // (narrow: tensors of at most narrow_columns(D)); pure host functions of the shape.
 int fwd_waves_unsplit(int BH, int S, int Sk, bool causal, bool narrow);
 int dq_waves(int BH, int S, int Sk, int D, bool causal, bool narrow);
+// Blocks of 32 rows per work-group of dQ from the stored dS (tensors of Dr columns); a pure host function of the shape.
+int dq_ds_blocks(int heads, int S, int Dr, bool causal);
 // `stages`: bit 0 row statistics, bit 1 dK/dV, bit 2 dQ.  With bits 0 and 2 the dQ kernel
 // forms the statistics (and runs first); bit 0 without bit 2 runs the separate kernel.
 // Number of key splits the dQ kernel would use for this problem (1: none) and the keys per

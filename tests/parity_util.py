@@ -125,7 +125,8 @@ def host_rule(name, *args):
     """A rule of the dispatch, a host function of the shape inside the library: attn::name(int or bool, ...)."""
     letters = "".join("b" if isinstance(a, bool) else "i" for a in args)
     f = getattr(binding.lib(), "_ZN4attn%d%sE%s" % (len(name), name, letters))
-    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_bool if isinstance(a, bool) else ctypes.c_int for a in args]
+    f.restype = ctypes.c_bool if "takes" in name else ctypes.c_int
+    f.argtypes = [ctypes.c_bool if isinstance(a, bool) else ctypes.c_int for a in args]
     return f(*args)
 
 

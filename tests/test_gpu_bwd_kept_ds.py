@@ -7,7 +7,7 @@ import torch
 import oracle
 import paper_2601_16238_amd as attn
 from paper_2601_16238_amd import workloads as wl
-from parity_util import DKDV_CUT, STORED_DS, backward_form, bf16_round, check_grad, f16_round, in_layout, to_f64
+from parity_util import host_rule, DKDV_CUT, STORED_DS, backward_form, bf16_round, check_grad, f16_round, in_layout, to_f64
 
 pytestmark = pytest.mark.gpu
 
@@ -89,12 +89,15 @@ def test_stored_ds_in_other_layouts(B, Hq, Hkv, Sq, Sk, D, causal, f16, cut, lay
 
 # two row blocks a wave: the last wave's second block past the end, blocks of unequal length under the mask,
 # offsets off the 32-key blocks, grouped heads, more rows than keys
-@pytest.mark.parametrize("H,Hkv,Sq,Sk,causal", [(520, 520, 385, 385, True), (520, 260, 400, 1100, True),
-                                                (520, 520, 481, 513, True), (540, 540, 290, 417, False),
-                                                (518, 518, 512, 403, False), (264, 264, 1000, 1031, True)])
-def test_two_row_blocks_a_wave(H, Hkv, Sq, Sk, causal):
+# (blocks: of 32 rows, per work-group of the launch of all heads; that of eight, one a wave, runs the other cases)
+@pytest.mark.parametrize("H,Hkv,Sq,Sk,causal,blocks", [
+    (520, 520, 385, 385, True, 8), (520, 260, 400, 1100, True, 8), (520, 520, 481, 513, True, 8), (264, 264, 1000, 1031, True, 8),
+    (540, 540, 290, 417, False, 16), (518, 518, 512, 403, False, 16)])
+def test_two_row_blocks_a_wave(H, Hkv, Sq, Sk, causal, blocks):
     """Work-groups of 512 rows, which a launch of all heads takes, against those of 256, which the parts
     take: a row's sum has the same products in the same order."""
+    assert host_rule("dq_ds_blocks", H, Sq, 128, causal) == blocks
+    assert host_rule("dq_ds_blocks", (Hkv + 1) // 2 * (H // Hkv), Sq, 128, causal) == 8
     print("case kept_ds two blocks", H, Hkv, Sq, Sk, causal, flush=True)
     g = torch.Generator(device="cuda")
     g.manual_seed(Sq + Sk)
@@ -109,3 +112,36 @@ def test_two_row_blocks_a_wave(H, Hkv, Sq, Sk, causal):
                    for n in (best, int(best * 0.6)))
     torch.cuda.synchronize()
     assert all(torch.equal(w.view(torch.int16), p.view(torch.int16)) for w, p in zip(whole, part))
+
+
+# the same, and a last work-group of one row and of half its waves
+@pytest.mark.parametrize("H,Hkv,Sq,Sk,causal", [(120, 120, 2049, 417, False), (120, 60, 2290, 517, False), (132, 132, 1825, 1825, True),
+                                                (132, 66, 2017, 2400, True), (130, 130, 2033, 2065, True), (76, 76, 4130, 4161, True)])
+@pytest.mark.parametrize("layout", ["BHSD", "BSHD", "padded"])
+def test_two_row_blocks_a_wave_in_longer_calls(H, Hkv, Sq, Sk, causal, layout):
+    """All heads at once, in work-groups of 512 rows, against one half and then the other, in those of 256."""
+    print("case kept_ds two blocks", H, Hkv, Sq, Sk, causal, layout, flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(Sq + Sk)
+    D, G = 128, H // Hkv
+    Q, dO = (torch.randn((2, H // 2, Sq, D), generator=g, device="cuda").bfloat16() for _ in range(2))
+    K, V = (torch.randn((2, Hkv // 2, Sk, D), generator=g, device="cuda").bfloat16() for _ in range(2))
+    O, LSE = attn.attn_fwd_rect(Q, K, V, D ** -0.5, causal)
+
+    def backward(t, lse, want):
+        B, Hq, Hk = t[0].shape[0], t[0].shape[1], t[1].shape[1]
+        best = attn.attn_bwd_rect_best_workspace_bytes(B, Hq, Hk, Sq, Sk, D, causal)
+        assert backward_form(B, Hq, Hk, Sq, Sk, D, causal, best) == STORED_DS
+        assert host_rule("dq_ds_blocks", B * Hq, Sq, D, causal) == want
+        out = [torch.full(x.shape, float("nan"), dtype=x.dtype, device="cuda") for x in t[:3]]
+        out = [o if x.is_contiguous() else in_layout(o, layout) for o, x in zip(out, t)]
+        attn.attn_bwd_rect(*t, lse, D ** -0.5, causal, dQ=out[0], dK=out[1], dV=out[2],
+                           workspace=torch.full((best,), 0xFF, dtype=torch.uint8, device="cuda"))
+        return out
+
+    t = (Q, K, V, O, dO)
+    whole = backward([x if layout == "BHSD" else in_layout(x, layout) for x in t], LSE, 16)
+    for b in range(2):
+        half = backward([x[b:b + 1].contiguous() for x in t], LSE[b:b + 1].contiguous(), 8)
+        for w, p in zip(whole, half):
+            assert torch.equal(w[b:b + 1].contiguous().view(torch.int16), p.view(torch.int16))

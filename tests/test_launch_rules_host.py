@@ -37,3 +37,15 @@ def test_the_forward_at_64_columns_is_split_where_that_is_quicker(BH, S, Sk, nsp
     f = binding.lib()._ZN4attn14fwd_split_planEiiiibbPiiNS_9SplitRuleE
     f.argtypes = [ctypes.c_int] * 4 + [ctypes.c_bool] * 2 + [ctypes.c_void_p, ctypes.c_int, ctypes.c_int]
     assert f(BH, S, Sk, 64, False, False, None, 128, 0) == nsplit
+
+
+# whole backward, us with eight | sixteen blocks or the latter's time relative to the former's
+@pytest.mark.parametrize("heads,S,causal,blocks", [
+    (128, 4096, False, 16), (128, 2048, True, 16), (192, 2048, False, 16),  # 1258 | 1228
+    (78, 5545, False, 16), (77, 4360, True, 16), (91, 7289, True, 16), (89, 5211, False, 16),  # 0.975, 0.981, 0.968, 0.98
+    (120, 2300, False, 16), (100, 3800, False, 16), (100, 3800, True, 8),  # fifteen blocks of 256: a sixteenth only pads
+    (442, 935, True, 8), (507, 905, True, 8), (482, 718, True, 8), (482, 718, False, 8),  # 1.037, 1.031, 341 | 347
+    (64, 2048, True, 8), (16, 4096, True, 8), (16, 16384, True, 8), (11, 1166, False, 2)])
+def test_row_blocks_of_dq_from_the_stored_ds(heads, S, causal, blocks):
+    assert host_rule("dq_ds_blocks", heads, S, 128, causal) == blocks
+    assert host_rule("dq_ds_blocks", heads, S, 96, causal) == min(blocks, 8)
