@@ -50,3 +50,21 @@ def test_skipped_columns_change_nothing(B, Hq, Hkv, Sq, Sk, D, full, causal, dty
             else:
                 x, y = x.double(), y.double()
                 assert bool(((x - y).abs() <= 2.0 ** -10 * (y.abs() + y.abs().max())).all()), name
+
+
+@pytest.mark.parametrize("H,Sq,Sk,D,causal", [(8, 373, 5508, 32, True), (8, 1100, 1100, 24, True), (4, 60, 4000, 32, False),
+                                              (2, 257, 4100, 32, False), (16, 172, 1599, 96, False), (8, 700, 2100, 80, True)])
+def test_partial_results_of_a_split_have_no_columns_that_are_skipped(H, Sq, Sk, D, causal):
+    """(They would be written, and up to twice the bytes with them, only to be dropped by the merge.)"""
+    print("case narrow partials", H, Sq, Sk, D, causal, flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(Sq + Sk)
+    Q = torch.randn((1, H, Sq, D), generator=g, device="cuda").bfloat16()
+    K, V = (torch.randn((1, H, Sk, D), generator=g, device="cuda").bfloat16() for _ in range(2))
+    wide, used = (64, 32) if D <= 64 else (128, 96)
+    n = attn.attn_fwd_rect_workspace_bytes(1, H, H, Sq, Sk, D, causal)
+    ws = torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda")
+    attn.attn_fwd_rect(Q, K, V, D ** -0.5, causal, workspace=ws)
+    part = ws.view(torch.int32)[:H * Sq * wide].view(-1, wide)  # of the first split, which every row sees
+    torch.cuda.synchronize()
+    assert bool((part[:, :D] != -1).all()) and bool((part[:, used:] == -1).all())
