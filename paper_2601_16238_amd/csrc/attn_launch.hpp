@@ -155,6 +155,11 @@ int fwd_waves_unsplit(int BH, int S, int Sk, bool causal, bool narrow);
 int dq_waves(int BH, int S, int Sk, int D, bool causal, bool narrow);
 // Blocks of 32 rows per work-group of dQ from the stored dS (tensors of Dr columns); a pure host function of the shape.
 int dq_ds_blocks(int heads, int S, int Dr, bool causal);
+// LDS with which two work-groups share a compute unit (160 KB) and not three, for launches that are quicker that way.
+constexpr int kLdsTwoPerUnit = 54784;
+// Whether the causal split forward of four waves at D = 64 is one (BH heads, nsplit splits of kps keys); a pure host
+// function of the shape.
+bool fwd_split_takes_two(int BH, int S, int Sk, int nsplit, int kps);
 // `stages`: bit 0 row statistics, bit 1 dK/dV, bit 2 dQ.  With bits 0 and 2 the dQ kernel
 // forms the statistics (and runs first); bit 0 without bit 2 runs the separate kernel.
 // Number of key splits the dQ kernel would use for this problem (1: none) and the keys per

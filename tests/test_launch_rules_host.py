@@ -49,3 +49,12 @@ def test_the_forward_at_64_columns_is_split_where_that_is_quicker(BH, S, Sk, nsp
 def test_row_blocks_of_dq_from_the_stored_ds(heads, S, causal, blocks):
     assert host_rule("dq_ds_blocks", heads, S, 128, causal) == blocks
     assert host_rule("dq_ds_blocks", heads, S, 96, causal) == min(blocks, 8)
+
+
+# us with two work-groups on a unit | three
+@pytest.mark.parametrize("BH,S,Sk,nsplit,two", [
+    (8, 4471, 4481, 3, True), (8, 4605, 4605, 3, True), (7, 5079, 5079, 3, True), (9, 2375, 2375, 4, True),  # 47 | 54, 39 | 43, 46 | 53, 27 | 29
+    (5, 4129, 4129, 4, True), (5, 7688, 7688, 3, True),
+    (1, 1000, 1000, 3, True), (22, 2682, 2893, 2, False), (18, 3564, 3832, 2, False), (10, 5626, 5626, 2, False)])  # 43 | 37, 57 | 48, 55 | 53
+def test_work_groups_of_the_causal_split_forward_on_a_unit(BH, S, Sk, nsplit, two):
+    assert host_rule("fwd_split_takes_two", BH, S, Sk, nsplit, ((Sk + 63) // 64 + nsplit - 1) // nsplit * 64) == two
