@@ -1562,14 +1562,22 @@ static int launch_dkdv(const BwdArgs &a, hipStream_t st)
     return a.Dr <= U ? launch_dkdv_u<D, U, CAUSAL, DS>(a, st) : launch_dkdv_u<D, D, CAUSAL, DS>(a, st);
 }
 
+#ifndef ATTN_F16
+// Work-groups of one wave (at most 32 rows), of which three fit a unit: 769 .. 1024 take two rounds anyway, and two of
+// two a unit are quicker than one of three and the rest.  us, whole backward, 1024 heads on 512 of 32 rows and 4000 keys 395 | 434
+// (960 375 | 413, 800 338 | 352), of 18 and 1000 102 | 107; outside 1.04 .. 1.34 times as long.  Not so with more waves.
+bool dq_takes_two(int nw, int wgs) { return nw == 1 && wgs > 768 && wgs <= 1024; }
+#endif
+
 template <int D, int U, int NW, bool CAUSAL>
 static int launch_dq(BwdArgs a, hipStream_t st)
 {
     using C = DqCfg<D, NW>;
     a.ntile = (a.S + C::kBlk - 1) / C::kBlk;
-    if (!allow_lds(attn_bwd_dq_kernel<D, U, NW, CAUSAL, false>, C::kLdsBytes)) return -1;
+    const int lds = D == 64 && dq_takes_two(NW, a.ntile * a.BH) ? std::max(C::kLdsBytes, kLdsTwoPerUnit) : C::kLdsBytes;
+    if (!allow_lds(attn_bwd_dq_kernel<D, U, NW, CAUSAL, false>, lds)) return -1;
     hipLaunchKernelGGL((attn_bwd_dq_kernel<D, U, NW, CAUSAL, false>), dim3(a.ntile * a.BH),
-                       dim3(C::kThreads), C::kLdsBytes, st, a);
+                       dim3(C::kThreads), lds, st, a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

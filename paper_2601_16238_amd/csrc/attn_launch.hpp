@@ -160,6 +160,8 @@ constexpr int kLdsTwoPerUnit = 54784;
 // Whether the causal split forward of four waves at D = 64 is one (BH heads, nsplit splits of kps keys); a pure host
 // function of the shape.
 bool fwd_split_takes_two(int BH, int S, int Sk, int nsplit, int kps);
+// Whether the unsplit dQ launch of `wgs` work-groups of nw waves at D = 64 is one; a pure host function of the shape.
+bool dq_takes_two(int nw, int wgs);
 // `stages`: bit 0 row statistics, bit 1 dK/dV, bit 2 dQ.  With bits 0 and 2 the dQ kernel
 // forms the statistics (and runs first); bit 0 without bit 2 runs the separate kernel.
 // Number of key splits the dQ kernel would use for this problem (1: none) and the keys per

@@ -58,3 +58,9 @@ def test_row_blocks_of_dq_from_the_stored_ds(heads, S, causal, blocks):
     (1, 1000, 1000, 3, True), (22, 2682, 2893, 2, False), (18, 3564, 3832, 2, False), (10, 5626, 5626, 2, False)])  # 43 | 37, 57 | 48, 55 | 53
 def test_work_groups_of_the_causal_split_forward_on_a_unit(BH, S, Sk, nsplit, two):
     assert host_rule("fwd_split_takes_two", BH, S, Sk, nsplit, ((Sk + 63) // 64 + nsplit - 1) // nsplit * 64) == two
+
+
+def test_work_groups_of_one_wave_of_dq_on_a_unit():
+    """Two, not three, where both take two rounds."""
+    assert [host_rule("dq_takes_two", 1, n) for n in (512, 768, 769, 960, 1024, 1025, 1536)] == [False] * 2 + [True] * 3 + [False] * 2
+    assert not host_rule("dq_takes_two", 2, 960) and not host_rule("dq_takes_two", 4, 960)
