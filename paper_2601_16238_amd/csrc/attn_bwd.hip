@@ -634,6 +634,7 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
         // of them have landed), in the slots' swizzled row layout.
         elem *const out = kind ? a.dK : a.dV;
         const float sc = kind ? a.scale : 1.f;
+        const int64_t row_stride = D > 128 ? in_sgpr(a.kv_stride_s) : a.kv_stride_s;
         {
             constexpr int RPI = 64 / CPR;  // rows per store instruction
             const int last = rs == 0 ? C::kRing - 1 : rs - 1;  // ring position of the last slot
@@ -689,7 +690,7 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
                     const u32x4 v = *(const u32x4 *)(stg + row * RB + ((lc ^ swz(row)) << 4));
                     const int okey = kA + 32 * kb + row;
                     if (okey < Sk && lc * 8 < Dr)
-                        *(u32x4 *)(out + base_kv + (int64_t)okey * a.kv_stride_s + lc * 8) = v;
+                        *(u32x4 *)(out + base_kv + (int64_t)okey * row_stride + lc * 8) = v;
                 }
                 asm volatile("" ::: "memory");
             }
@@ -824,6 +825,8 @@ __device__ __forceinline__ void dq_rows_out(const BwdArgs &a, f32x16 (&dq)[U / 3
         // lie in ring position 2 have moved to the position that the last two tiles did not use: other
         // waves may still be reading those.)
         const float sc = a.scale;
+        const int64_t row_stride = D > 128 ? in_sgpr(a.stride_s) : a.stride_s;
+        elem *const out = (D > 128 ? in_sgpr(a.dQ) : a.dQ) + base;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -835,7 +838,7 @@ __device__ __forceinline__ void dq_rows_out(const BwdArgs &a, f32x16 (&dq)[U / 3
         for (int j = 0; j < 32 / RPI; ++j) {
             const u32x4 v = *(const u32x4 *)(stg + at(RPI * j + lr, lc));
             const int row = q0 + RPI * j + lr;
-            if (row < S && lc * 8 < Dr) *(u32x4 *)(a.dQ + base + (int64_t)row * a.stride_s + lc * 8) = v;
+            if (row < S && lc * 8 < Dr) *(u32x4 *)(out + (int64_t)row * row_stride + lc * 8) = v;
         }
     }
 }

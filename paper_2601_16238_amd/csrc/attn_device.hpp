@@ -82,6 +82,15 @@ __device__ __forceinline__ float xhalf_sum(float x)
     return __uint_as_float(r.x) + __uint_as_float(r.y);
 }
 
+// x in scalar registers of its own.  (A member of the argument block that spills does so with the registers that it was
+// loaded with, sixteen at a time, and every use in a loop over rows brings all of them back, one instruction each.)
+template <typename T>
+__device__ __forceinline__ T in_sgpr(T x)
+{
+    asm volatile("" : "+s"(x));
+    return x;
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
 

@@ -204,3 +204,11 @@ def test_staging_space_is_read_before_the_ring_takes_it(kernels):
             elif op == "s_barrier":
                 break
         assert n_read >= 24 and not reading, name
+
+
+def test_rows_leave_without_the_argument_block(kernels):
+    """The launch of dK/dV and dQ side by side at D = 256 keeps more scalars than there are registers: none of the rows that it
+    loads and stores may bring a spilled block of arguments back (16 lane reads a row, 1.2 us of a call of 13)."""
+    found = {k: sum(op == "v_readlane_b32" for _, op, *_ in code) for k, code in kernels.items()
+             if re.search("bwd_pair_kernelILi256ELi(192|256)ELb[01]ELb0E", k)}
+    assert len(found) == 8 and max(found.values()) < 100, found
