@@ -119,9 +119,13 @@ attn_fwd_kernel(const FwdArgs a)
     // a work-group of eight waves took its last wave 5000-7000 cycles to get issued (measured) -- time
     // in which the compute unit, which holds one such work-group, does nothing.  With fewer waves
     // (this and the rows of O below; us): 2 heads of 128 rows D = 64 5.3 -> 4.7, 512 of 200 causal 18.2 ->
-    // 16.4, 64 of 1024 causal 19.2 -> 18.5, 768 of 65 the same.
+    // 16.4, 64 of 1024 causal 19.2 -> 18.5, 768 of 65 the same.  Not for narrow tensors, whose rows are half (three
+    // quarters) of what is then moved: 512 of 41 rows D = 16 4.4, 4.9 through LDS, 4096 of 41 D = 32 causal 19.9 and 21.2, 32 of
+    // 214 D = 80 causal 8.3 and 8.7.
+    constexpr bool kNarrow = U < D && NW < 8;
+    constexpr bool kStageQ = NW > 1 && !kNarrow;
     elem8 qf[KS];
-    if constexpr (NW == 1) {
+    if constexpr (!kStageQ) {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
             qf[ks] = as_elem8(ld_row16(Qp + (int64_t)qc * a.stride_s, ks * 16 + 8 * h, Dr));
@@ -320,7 +324,7 @@ attn_fwd_kernel(const FwdArgs a)
     // transfers (whole rows of four per instruction), issued before those of K and V.  Rows past
     // S-1 and columns Dr..D-1 read as zero.
     uint32_t q_stage = 0;
-    if constexpr (NW > 1) {
+    if constexpr (kStageQ) {
         const int pair = __builtin_amdgcn_readfirstlane(w) >> 1, half = __builtin_amdgcn_readfirstlane(w) & 1;
         q_stage = (pair == 0 ? 2 * C::kKTile : pair == 1 ? 3 * C::kKTile + C::kVTile
                                                           : 3 * C::kKTile + 3 * C::kVTile + (pair - 2) * C::kKTile) * 2 +
@@ -356,7 +360,7 @@ attn_fwd_kernel(const FwdArgs a)
                 rs[ks][j] = *(const f32x4 *)(a.rope_sin + pos + 16 * ks + 8 * h + 4 * j);
             }
     }
-    if constexpr (NW > 1) {
+    if constexpr (kStageQ) {
         // the wave's own query rows have landed once at most the later transfers (K(0), K(1),
         // V(0)) are outstanding; with the rotary table rows in flight as well, whose place in the
         // order of issue is the compiler's choice, everything is awaited
@@ -567,7 +571,7 @@ attn_fwd_kernel(const FwdArgs a)
     // Epilogue: O = O_acc / l, LSE = ln2 * (m + log2 l).
     const float lt = xhalf_sum(lsum);
     const float lr = xhalf_sum(hsum);  // sum of the rounded probabilities
-    // The accumulator holds 4 consecutive columns of one row per register group, so
+    // (Narrow tensors, see above: directly.)  The accumulator holds 4 consecutive columns of one row per register group, so
     // a direct store writes 16 bytes to each of 32 rows per instruction, sixteen times per wave.
     // The rows go through LDS instead and leave whole, 16 bytes per lane and four (D = 128) or
     // eight rows per instruction: half as many stores, each over contiguous memory.  The wave's
@@ -613,7 +617,18 @@ attn_fwd_kernel(const FwdArgs a)
         return;
     }
     const float inv = 1.0f / lr;
-    {
+    if constexpr (kNarrow) {
+        if (q >= S) return;
+        elem *const Op = a.O + base + (int64_t)q * a.stride_s;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                if (32 * db + 8 * g + 4 * h < Dr)
+                    *(elem4 *)(Op + 32 * db + 8 * g + 4 * h) = pack4(o[db][4 * g] * inv, o[db][4 * g + 1] * inv,
+                                                                     o[db][4 * g + 2] * inv, o[db][4 * g + 3] * inv);
+        if (h == 0) a.LSE[(int64_t)bh * S + q] = (m + fast_log2(lt)) * kLn2;
+    } else {
         constexpr int CPR = D / 8, RPI = 64 / CPR;  // chunks per row; rows per store instruction
 #pragma unroll
         for (int db = 0; db < DB; ++db)
