@@ -750,15 +750,20 @@ static int launch_fwd_merge(const FwdArgs &a, hipStream_t st)
 }
 
 #ifndef ATTN_F16
-// Three work-groups of four waves fit a unit, but under a mask the work-groups of a split that lies behind their rows end
+// Three work-groups of four waves fit a unit.  Unsplit, where all of them are resident, from 2000 rows on two are
+// quicker, as heavy ones then do not meet three to a unit (0.97 of the time on average, D <= 32 0.98, never more than 1.09;
+// over 70 problems.  With more work-groups three, 0.83 .. 1.01 of the time on average in every class of 270, though some
+// heads end unevenly: 41 of 3283 D = 48 87 | 103 us).  Split, under a mask, the work-groups of a split that lies behind their rows end
 // at once, and the heavy ones among the others are better spread: two on a unit, as with the larger tiles in LDS before, with
 // up to 612 of the others in two or three splits and 500 in more (8 heads of 4471 rows, 3 splits, 54 | 47 us, D = 32 43 | 37);
 // three with more of them (22 of 2682, 2 splits, D = 32 37 | 43; on average 1.05 with 3 or 4 splits, 1.12 with 2).  Over 408
 // problems; with few of either the same.
-bool fwd_split_takes_two(int BH, int S, int Sk, int nsplit, int kps)
+bool fwd_takes_two(int BH, int S, int Sk, int nsplit, int kps)
 {
+    const int64_t wgs = (int64_t)BH * ((S + 127) / 128);
+    if (nsplit <= 1) return S >= 2000 && wgs > 512 && wgs <= 768;
     const float splits_seen = ((Sk + 63) / 64 - S / 128.0f) * 64 / kps + 0.5f;  // of a query tile, on average
-    return (int64_t)BH * ((S + 127) / 128) * std::min((float)nsplit, splits_seen) <= (nsplit > 3 ? 500 : 612);
+    return wgs * std::min((float)nsplit, splits_seen) <= (nsplit > 3 ? 500 : 612);
 }
 #endif
 
@@ -767,7 +772,7 @@ static int launch_fwd_kernel(const FwdArgs &a, hipStream_t st)
 {
     using C = FwdCfg<D, NW, MAIN>;
     int lds = C::kLdsBytes;
-    if (D == 64 && NW == 4 && CAUSAL && SPLIT && fwd_split_takes_two(a.BH, a.S, a.Sk, a.nsplit, a.kps))
+    if (D == 64 && NW == 4 && CAUSAL && MAIN && fwd_takes_two(a.BH, a.S, a.Sk, a.nsplit, a.kps))
         lds = std::max(lds, kLdsTwoPerUnit);
     if (hipFuncSetAttribute((const void *)attn_fwd_kernel<D, U, NW, CAUSAL, SPLIT, MAIN>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)

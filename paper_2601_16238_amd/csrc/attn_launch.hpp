@@ -157,9 +157,9 @@ int dq_waves(int BH, int S, int Sk, int D, bool causal, bool narrow);
 int dq_ds_blocks(int heads, int S, int Dr, bool causal);
 // LDS with which two work-groups share a compute unit (160 KB) and not three, for launches that are quicker that way.
 constexpr int kLdsTwoPerUnit = 54784;
-// Whether the causal split forward of four waves at D = 64 is one (BH heads, nsplit splits of kps keys); a pure host
-// function of the shape.
-bool fwd_split_takes_two(int BH, int S, int Sk, int nsplit, int kps);
+// Whether the causal forward of four waves at D = 64 is one (BH heads, nsplit splits of kps keys); a pure host function
+// of the shape.
+bool fwd_takes_two(int BH, int S, int Sk, int nsplit, int kps);
 // Whether the unsplit dQ launch of `wgs` work-groups of nw waves at D = 64 is one; a pure host function of the shape.
 bool dq_takes_two(int nw, int wgs);
 // `stages`: bit 0 row statistics, bit 1 dK/dV, bit 2 dQ.  With bits 0 and 2 the dQ kernel

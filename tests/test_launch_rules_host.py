@@ -55,9 +55,11 @@ def test_row_blocks_of_dq_from_the_stored_ds(heads, S, causal, blocks):
 @pytest.mark.parametrize("BH,S,Sk,nsplit,two", [
     (8, 4471, 4481, 3, True), (8, 4605, 4605, 3, True), (7, 5079, 5079, 3, True), (9, 2375, 2375, 4, True),  # 47 | 54, 39 | 43, 46 | 53, 27 | 29
     (5, 4129, 4129, 4, True), (5, 7688, 7688, 3, True),
-    (1, 1000, 1000, 3, True), (22, 2682, 2893, 2, False), (18, 3564, 3832, 2, False), (10, 5626, 5626, 2, False)])  # 43 | 37, 57 | 48, 55 | 53
-def test_work_groups_of_the_causal_split_forward_on_a_unit(BH, S, Sk, nsplit, two):
-    assert host_rule("fwd_split_takes_two", BH, S, Sk, nsplit, ((Sk + 63) // 64 + nsplit - 1) // nsplit * 64) == two
+    (1, 1000, 1000, 3, True), (22, 2682, 2893, 2, False), (18, 3564, 3832, 2, False), (10, 5626, 5626, 2, False),  # 43 | 37, 57 | 48, 55 | 53
+    (15, 6235, 6235, 1, True), (30, 2845, 2845, 1, True), (24, 4096, 4096, 1, True),  # 73 | 77, 45 | 47
+    (64, 1024, 1024, 1, False), (60, 1280, 1280, 1, False), (25, 4096, 4096, 1, False)])
+def test_work_groups_of_the_causal_forward_on_a_unit(BH, S, Sk, nsplit, two):
+    assert host_rule("fwd_takes_two", BH, S, Sk, nsplit, ((Sk + 63) // 64 + nsplit - 1) // nsplit * 64) == two
 
 
 def test_work_groups_of_one_wave_of_dq_on_a_unit():
