@@ -36,7 +36,7 @@
 namespace attn {
 
 // MAIN: the form with the pipelined main loop (eight waves always; four waves at D = 64 in launches that
-// four_wave_main chooses).
+// fwd_takes_main chooses).
 template <int D, int NW, bool MAIN>
 struct FwdCfg {
     static constexpr int kThreads = NW * 64;
@@ -788,7 +788,7 @@ static int launch_fwd_kernel(const FwdArgs &a, hipStream_t st)
 template <int D, int U, int NW, bool MAIN>
 static int launch_fwd_nw(const FwdArgs &a, bool causal, hipStream_t st)
 {
-    // (four waves at D = 64 are split in the form with the main loop only, see four_wave_main)
+    // (four waves at D = 64 are split in the form with the main loop only, see fwd_takes_main)
     if constexpr (MAIN || NW != 4 || D != 64)
         if (a.nsplit > 1)
             return causal ? launch_fwd_kernel<D, U, NW, true, true, MAIN>(a, st)
@@ -797,12 +797,18 @@ static int launch_fwd_nw(const FwdArgs &a, bool causal, hipStream_t st)
                   : launch_fwd_kernel<D, U, NW, false, false, MAIN>(a, st);
 }
 
+#ifndef ATTN_F16
 // Whether four waves at D = 64 take the form with the pipelined main loop: from four tiles on.  (It is entered from
 // three whole tiles on, and its third V buffer and registers still let three work-groups share a compute unit.)  Over
 // 150 problems of 64 .. 3300 rows, up to 4000 work-groups, time relative to the generic form: 0.79 .. 1.04 from 256 keys on,
 // 0.94 on average (36 heads of 900 rows causal 19.6 -> 16.8 us, 275 of 349 rows on 1104 keys 39.4 -> 34.1), 0.96 .. 1.04 with
-// 192 .. 255, 1.0 .. 1.05 with fewer (347 of 95 7.6 -> 8.0).
-static bool four_wave_main(const FwdArgs &a) { return a.nsplit > 1 || a.Sk >= 256; }
+// 192 .. 255, 1.0 .. 1.05 with fewer (347 of 95 7.6 -> 8.0).  For narrow tensors without a mask from three tiles on in launches
+// of at most two work-groups per unit: 64 of 195 rows D = 32 6.5 -> 6.1, 250 of 200 9.0 -> 8.8, the same with more.
+bool fwd_takes_main(int wgs, int Sk, int nsplit, bool causal, bool narrow)
+{
+    return nsplit > 1 || Sk >= 256 || (narrow && !causal && Sk >= 192 && wgs <= 512);
+}
+#endif
 
 // Waves per work-group: 8 (256 query rows) unless the sequence is too short to fill them.
 // With D = 128 at least 4 (waves whose rows lie past the end compute and store nothing useful,
@@ -862,7 +868,7 @@ static int launch_fwd_d(FwdArgs a, bool causal, hipStream_t st)
     a.nqt = (a.S + nw * 32 - 1) / (nw * 32);
     if (nw == 8) return launch_fwd_nw<D, U, 8, true>(a, causal, st);
     if constexpr (D < 128) {
-        if (nw == 4 && four_wave_main(a)) return launch_fwd_nw<D, U, 4, true>(a, causal, st);
+        if (nw == 4 && fwd_takes_main(a.BH * a.nqt, a.Sk, a.nsplit, causal, U < D)) return launch_fwd_nw<D, U, 4, true>(a, causal, st);
         if (nw == 2) return launch_fwd_nw<D, U, 2, false>(a, causal, st);
         if (nw == 1) return launch_fwd_nw<D, U, 1, false>(a, causal, st);
     }

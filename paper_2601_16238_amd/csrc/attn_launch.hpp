@@ -153,6 +153,8 @@ inline bool takes_eight_waves(const WaveRule &c, int BH, int S, int Sk, bool nar
 // (narrow: tensors of at most narrow_columns(D)); pure host functions of the shape.
 int fwd_waves_unsplit(int BH, int S, int Sk, bool causal, bool narrow);
 int dq_waves(int BH, int S, int Sk, int D, bool causal, bool narrow);
+// Whether the forward of `wgs` work-groups of four waves at D = 64 has the pipelined main loop; likewise.
+bool fwd_takes_main(int wgs, int Sk, int nsplit, bool causal, bool narrow);
 // Blocks of 32 rows per work-group of dQ from the stored dS (tensors of Dr columns); a pure host function of the shape.
 int dq_ds_blocks(int heads, int S, int Dr, bool causal);
 // LDS with which two work-groups share a compute unit (160 KB) and not three, for launches that are quicker that way.

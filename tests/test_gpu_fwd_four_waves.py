@@ -16,7 +16,8 @@ SHAPES = [(1, 6, 191, 191, 64, True), (1, 6, 192, 192, 64, True), (1, 256, 200, 
 # eight, without a mask; narrow tensors; many heads under a mask; more keys than rows
 SHAPES += [(1, 40, 255, 255, 64, False), (1, 40, 256, 256, 64, False), (1, 85, 300, 300, 64, False), (1, 86, 300, 300, 64, False),
            (1, 128, 257, 257, 64, False), (1, 129, 257, 257, 64, False), (1, 193, 260, 260, 32, False),
-           (1, 513, 300, 300, 64, True), (2, 48, 240, 577, 48, False)]
+           (1, 513, 300, 300, 64, True), (2, 48, 240, 577, 48, False), (1, 64, 192, 192, 32, False), (1, 256, 195, 195, 24, False),
+           (1, 257, 200, 200, 32, False), (1, 64, 191, 191, 32, False)]
 
 
 @pytest.mark.parametrize("B,H,Sq,Sk,D,causal", SHAPES)

@@ -66,3 +66,12 @@ def test_work_groups_of_one_wave_of_dq_on_a_unit():
     """Two, not three, where both take two rounds."""
     assert [host_rule("dq_takes_two", 1, n) for n in (512, 768, 769, 960, 1024, 1025, 1536)] == [False] * 2 + [True] * 3 + [False] * 2
     assert not host_rule("dq_takes_two", 2, 960) and not host_rule("dq_takes_two", 4, 960)
+
+
+def test_main_loop_of_four_waves_at_64_columns():
+    """Narrow tensors without a mask: from three tiles on where two work-groups share a unit at most (6.1 us, 6.5 without it)."""
+    def rule(wgs, Sk, nsplit=1, causal=False, narrow=True):
+        return host_rule("fwd_takes_main", wgs, Sk, nsplit, causal, narrow)
+    assert rule(128, 192) and rule(512, 255) and not rule(128, 191) and not rule(513, 255)
+    assert not rule(128, 255, causal=True) and not rule(128, 255, narrow=False) and rule(2000, 256, causal=True, narrow=False)
+    assert rule(128, 100, nsplit=2)
