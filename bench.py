@@ -9,6 +9,7 @@ microbenchmark: seeded inputs, warm-up, synchronise around the timed region, mea
 import argparse
 import json
 import os
+import re
 import sys
 import time
 
@@ -33,8 +34,8 @@ MEASURED_TRAFFIC_BYTES = {
 def measured_traffic_bytes(workload, kernel):
     """HBM bytes per launch of `kernel` on `workload` (read + written, scaled counter readings)
     from the committed rocprofv3 summary of that workload, profiles/<workload>_kernel_trace_and_
-    hbm_traffic.txt; None if there is none.  The first line of the kernel counts: the summary lists the stage-wise
-    instances first.  The figure is of the kernels that the summary was made with, by hand: a change to a
+    hbm_traffic.txt; None if there is none.  `kernel` with its template arguments, or of a name alone the first
+    instance.  The figure is of the kernels that the summary was made with, by hand: a change to a
     kernel's traffic needs a new one."""
     path = os.path.join(ROOT, "profiles", "%s_kernel_trace_and_hbm_traffic.txt" % workload)
     try:
@@ -46,8 +47,7 @@ def measured_traffic_bytes(workload, kernel):
         return None
     for ln in lines[start:]:
         f = ln.split()
-        # (dK/dV of large launches: attn_bwd_dkdv_solo_kernel)
-        if len(f) == 5 and f[0].replace("_solo_kernel<", "_kernel<").startswith(kernel + "<"):
+        if len(f) == 5 and (f[0] + "<").startswith(kernel + "<"):
             return int((float(f[3]) + float(f[4])) * 1024 * 1024)
     return None
 
@@ -117,6 +117,36 @@ def backward_form(binding, workspace_bytes, *problem):
         binding.lib().attn_bwd_rect_form(ctypes.byref(p), workspace_bytes) % 16]
 
 
+# Algorithmic products (GEMM = 2*N_s*D flops, N_s = S^2 or S^2/2) of a launch: forward 2; dK/dV 4 (S, dP, dV, dK); dQ 1
+# (the S and dP that it recomputes without the stored dS are overhead, not algorithmic work); one kernel for all, 5.
+GEMMS = (("attn_fwd_merge", 0), ("attn_fwd", 2), ("attn_bwd_small", 5), ("attn_bwd_pair_merge", 0), ("attn_bwd_pair", 5),
+         ("attn_bwd_dkdv_merge", 0), ("attn_bwd_dkdv", 4), ("attn_bwd_dq_merge", 0), ("attn_bwd_dq", 1))
+
+
+def launched_kernels(torch, step, steps):
+    """{kernel with its template arguments: (ms per step, launches per step)} of `steps` more steps, traced; None where a
+    profiler traces the process already, or torch's is not there."""
+    if "ROCP_TOOL_LIBRARIES" in os.environ:
+        return None
+    try:
+        from torch.profiler import ProfilerActivity, profile
+        with profile(activities=[ProfilerActivity.CUDA]) as prof:
+            for _ in range(steps):
+                step()
+            torch.cuda.synchronize()
+    except (ImportError, RuntimeError) as e:
+        print("no kernel trace: %s" % e, file=sys.stderr)
+        return None
+    times = {}
+    for e in prof.events():
+        m = re.match(r"_ZN4attn\d+(attn_\w+?_kernel)I(.*?)EEv", e.name)
+        if m:
+            name = "%s<%s>" % (m[1], ",".join(re.findall(r"L[ib](\d+)E", m[2] + "E")))
+            times.setdefault(name, []).append(e.time_range.elapsed_us() * 1e-3)
+    # (the median launch: the first ones after the trace is set up run at another clock)
+    return {k: (sorted(t)[len(t) // 2] * len(t) / steps, len(t) / steps) for k, t in times.items()}
+
+
 def measure(torch, attn, wl, w, steps, warmup):
     import numpy as np
     from paper_2601_16238_amd import binding
@@ -156,9 +186,7 @@ def measure(torch, attn, wl, w, steps, warmup):
     n = max(3, steps // 2)
 
     def stage_ms(fn):
-        # the shorter of two loops: these figures pick the kernel the roofline is quoted for, and
-        # one disturbed loop (seen once: a 1.3 ms stage read 4.5 ms next to an undisturbed step)
-        # would pick the wrong one
+        # the shorter of two loops (one disturbed: a 1.3 ms stage read 4.5 ms next to an undisturbed step)
         return min(time_calls(torch, fn, n), time_calls(torch, fn, n))
 
     ms = {"fwd": stage_ms(fwd), "bwd": stage_ms(bwd),
@@ -189,10 +217,8 @@ def measure(torch, attn, wl, w, steps, warmup):
         res["gbs_bwd_graph_replay"] = b_bwd / (ms["bwd_graph_replay"] * 1e-3) / 1e9
         res["tflops_fwdbwd_graph_replay"] = (f_fwd + f_bwd) / (
             (ms["fwd_graph_replay"] + ms["bwd_graph_replay"]) * 1e-3) / 1e12
-    # Algorithmic FLOPs per launch of each MFMA kernel (GEMM = 2*N_s*D flops, N_s = S^2 or
-    # S^2/2): forward 2 GEMMs; dK/dV kernel 4 (S, dP, dV, dK); dQ kernel 1 (dQ -- its
-    # recomputed S and dP are overhead, not algorithmic work).
     gemm = f_fwd / 2.0
+    # the stage-wise dK/dV and dQ (one after the other, without the stored dS)
     kern = {"attn_fwd_kernel": (2 * gemm, ms["fwd"]), "attn_bwd_dkdv_kernel": (4 * gemm, ms["bwd_dkdv"]),
             "attn_bwd_dq_kernel": (1 * gemm, ms["bwd_dq"])}
     if (not gqa or w.B * Hkv >= 256) and w.S <= (256 if w.D <= 64 else 128 if w.D <= 128 else 0):
@@ -202,6 +228,16 @@ def measure(torch, attn, wl, w, steps, warmup):
     res["kernels"] = {k: {"ms": t, "achieved_tflops": f / (t * 1e-3) / 1e12,
                           "frac": f / (t * 1e-3) / 1e12 / PEAK_BF16_TFLOPS}
                       for k, (f, t) in kern.items()}
+    # ... and the kernels that the timed step launches: traced, and where they ran longer under the trace than the forward
+    # and the backward are timed without it, those times in the traced proportions
+    launched = launched_kernels(torch, step, max(10, n)) or {}
+    res["launched"] = {}
+    for part in ("fwd", "bwd"):
+        ours = {k: v for k, v in launched.items() if k.startswith("attn_" + part)}
+        scale = min(1.0, ms[part] / max(1e-9, sum(t for t, _ in ours.values())))
+        for k, (t, c) in ours.items():
+            f = next((g for p, g in GEMMS if k.startswith(p)), 0) * gemm / (t * scale * 1e-3) / 1e12
+            res["launched"][k] = {"ms": t * scale, "launches": c, "achieved_tflops": f, "frac": f / PEAK_BF16_TFLOPS}
     return res
 
 
@@ -602,7 +638,8 @@ def main():
         return
     w = wl.WORKLOADS[a.workload] if a.workload in wl.WORKLOADS else wl.GQA_WORKLOADS[a.workload]
     r = measure(torch, attn, wl, w, a.steps, a.warmup)
-    dom = max(r["kernels"], key=lambda k: r["kernels"][k]["ms"])
+    kernels = r["launched"] or r["kernels"]
+    dom = max(kernels, key=lambda k: kernels[k]["ms"])
     out = {
         "metric": "attention fwd+bwd TFLOP/s (FLOPs = 4*B*H*S^2*D fwd, /2 causal, bwd = 2.5x fwd)",
         "value": r["tflops_fwdbwd"], "unit": "TFLOP/s", "n_gpus": 1, "steps": a.steps,
@@ -617,10 +654,11 @@ def main():
         "tflops": {"fwd": r["tflops_fwd"], "bwd": r["tflops_bwd"], "fwd_bwd": r["tflops_fwdbwd"]},
         "ms": r["ms"], "backward": r["backward"],
         "algorithmic_gbs": {"fwd": r["gbs_fwd"], "bwd": r["gbs_bwd"], "hbm_peak": PEAK_HBM_GBS},
-        "roofline": {"kernel": dom, "bound": "mfma", "achieved": r["kernels"][dom]["achieved_tflops"],
-                     "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": r["kernels"][dom]["frac"],
+        "roofline": {"kernel": dom, "bound": "mfma", "achieved": kernels[dom]["achieved_tflops"],
+                     "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": kernels[dom]["frac"],
+                     "of": "the timed step" if r["launched"] else "the stage-wise calls",
                      "traffic": measured_traffic_bytes(w.name, dom)},
-        "roofline_all": r["kernels"],
+        "roofline_all": kernels, "roofline_stage_wise": r["kernels"],
     }
     probe = measure_mfma_peak(torch, attn)
     out["mfma_probe"] = probe

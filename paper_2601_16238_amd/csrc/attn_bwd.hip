@@ -224,12 +224,13 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
     }
     // stats: lanes 0-31 fetch lse2 (second half of the head's workspace), 32-63 delta
     const uint32_t stat_voff = (uint32_t)(h ? r : S + r) * 4u;
-    // The statistics of a slot are requested by one producer, its Q and dO pieces by the
-    // CONSUMERS, consumer c taking the pieces that pair c is assigned (they have no other vector
-    // memory traffic and are the shorter chain of a slot; with the producers issuing them between
-    // their MFMAs the kernel was 2-5 % slower), right after the slot barrier, into a ring position
-    // that nobody reads before a later barrier.  (Spread between the consumers' MFMAs instead they
-    // measured the same or up to 2.5 % slower.)
+    // The Q and dO pieces of a slot are requested by the CONSUMERS, consumer c taking the pieces that
+    // pair c is assigned (they have no other vector memory traffic and are the shorter chain of a
+    // slot; with the producers issuing them between their MFMAs the kernel was 2-5 % slower), into a
+    // ring position that nobody reads before a later barrier: at D <= 128 right after the slot barrier
+    // (spread between the consumers' MFMAs the same or up to 2.5 % slower), at D = 256 between their MFMAs
+    // (see consume).  Its statistics are requested by one producer, or where the producers store dS, which
+    // nobody waits for, by the last pair's consumer.
     auto dma_stat = [&](int t, int rs) __attribute__((always_inline)) {
         if (DS)
             dma4(Wd, lds0 + C::kOffStat + rs * C::kStatBytes, stat_voff, (uint32_t)(t * C::kRows * 4));
@@ -269,8 +270,8 @@ __device__ __forceinline__ void bwd_dkdv(const BwdArgs &a, int block, int ntile)
             wait_vm_and_barrier<(C::kAhead - 1) * C::kDmaPerWave>();
         }
     };
-    // slot and head of the next transfer (both roles keep count: the producers for the statistics,
-    // the consumers for the rows): the slots of the group's query heads form ONE sequence (head
+    // slot and head of the next transfer (both roles keep count: the producers, unless they store dS,
+    // for the statistics, the consumers for the rows): the slots of the group's query heads form ONE sequence (head
     // after head, slots t0 .. n_slot-1 of each), so that the ring stays full across the change of
     // head; past the last head the rows lie beyond S and read as zero
     int tf = t_first, gqf = g_first;
