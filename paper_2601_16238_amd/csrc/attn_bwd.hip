@@ -1578,8 +1578,10 @@ static int launch_dq(BwdArgs a, hipStream_t st)
 {
     using C = DqCfg<D, NW>;
     a.ntile = (a.S + C::kBlk - 1) / C::kBlk;
-    const int lds = D == 64 && dq_takes_two(NW, a.ntile * a.BH) ? std::max(C::kLdsBytes, kLdsTwoPerUnit) : C::kLdsBytes;
-    if (!allow_lds(attn_bwd_dq_kernel<D, U, NW, CAUSAL, false>, lds)) return -1;
+    constexpr int kMost = D == 64 && NW == 1 ? std::max(C::kLdsBytes, kLdsTwoPerUnit) : C::kLdsBytes;
+    const int lds = D == 64 && dq_takes_two(NW, a.ntile * a.BH) ? kMost : C::kLdsBytes;
+    // (one limit for every launch of the kernel: another thread may be between its own call here and its launch)
+    if (!allow_lds(attn_bwd_dq_kernel<D, U, NW, CAUSAL, false>, kMost)) return -1;
     hipLaunchKernelGGL((attn_bwd_dq_kernel<D, U, NW, CAUSAL, false>), dim3(a.ntile * a.BH),
                        dim3(C::kThreads), lds, st, a);
     return hipGetLastError() == hipSuccess ? 0 : -1;

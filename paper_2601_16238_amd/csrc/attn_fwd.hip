@@ -771,11 +771,12 @@ template <int D, int U, int NW, bool CAUSAL, bool SPLIT, bool MAIN>
 static int launch_fwd_kernel(const FwdArgs &a, hipStream_t st)
 {
     using C = FwdCfg<D, NW, MAIN>;
-    int lds = C::kLdsBytes;
-    if (D == 64 && NW == 4 && CAUSAL && MAIN && fwd_takes_two(a.BH, a.S, a.Sk, a.nsplit, a.kps))
-        lds = std::max(lds, kLdsTwoPerUnit);
+    constexpr bool kTwo = D == 64 && NW == 4 && CAUSAL && MAIN;  // the launches that may ask for more
+    constexpr int kMost = kTwo ? std::max(C::kLdsBytes, kLdsTwoPerUnit) : C::kLdsBytes;
+    const int lds = kTwo && fwd_takes_two(a.BH, a.S, a.Sk, a.nsplit, a.kps) ? kMost : C::kLdsBytes;
+    // (one limit for every launch of the kernel: another thread may be between its own call here and its launch)
     if (hipFuncSetAttribute((const void *)attn_fwd_kernel<D, U, NW, CAUSAL, SPLIT, MAIN>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+                            hipFuncAttributeMaxDynamicSharedMemorySize, kMost) != hipSuccess)
         return -1;
     hipLaunchKernelGGL((attn_fwd_kernel<D, U, NW, CAUSAL, SPLIT, MAIN>),
                        dim3(a.nqt * a.BH, SPLIT ? a.nsplit : 1), dim3(C::kThreads),
