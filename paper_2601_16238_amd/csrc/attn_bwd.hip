@@ -861,7 +861,7 @@ __device__ __forceinline__ void bwd_dq(const BwdArgs &a, int block, int ntile, i
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int S = a.S;
     int bh, rank;
-    xcd_tile_order<CAUSAL, D == 64 && NW == 4>(block, ntile, a.BH, bh, rank);
+    xcd_tile_order<CAUSAL, D == 64 && NW == 4, (D == 64 && NW == 4 ? 8 : 4)>(block, ntile, a.BH, bh, rank);
     const int qt = CAUSAL ? ntile - 1 - rank : rank;  // heaviest first
     const int64_t base = (int64_t)(bh / a.H) * a.stride_b + (int64_t)(bh % a.H) * a.stride_h;
     // grouped-query heads: query head h reads K/V head h / group

@@ -335,7 +335,11 @@ __device__ __forceinline__ int xcd_contiguous_order(int id, int total)
 // PAIRED: two work-groups are resident on a compute unit.  A causal launch of at most that many is
 // balanced by giving each unit a heavy and a light one: the second round in reverse order (64 heads of
 // 1024 rows, D = 64, forward 22.5 -> 19.9 us, dK/dV 29.7 -> 28.0).
-template <bool CAUSAL, bool PAIRED = false>
+// FEW: a launch of fewer work-groups per unit than that is one of few rounds; twice as many where three share a unit and
+// not one or two (the forward and dQ of four waves at D = 64: with 4 launches of 1024 .. 2048 ended on the long
+// work-groups of a last group of heads, 41 heads of 3283 rows D = 48 forward 106 us, 75 so, 64 of 2967 D = 32 81 and 65; on
+// average over 190 forwards and 150 dQ 0.92 and 0.95 of the time, at most 1.08 and 1.10; with more work-groups the same).
+template <bool CAUSAL, bool PAIRED = false, int FEW = 4>
 __device__ __forceinline__ void xcd_tile_order(int id_, int ntile_, int BH_, int &bh, int &rank)
 {
     // (unsigned throughout: nothing here is negative, and an unsigned division by a run-time
@@ -353,7 +357,7 @@ __device__ __forceinline__ void xcd_tile_order(int id_, int ntile_, int BH_, int
         if (CAUSAL && PAIRED && n <= 2 * kCuPerXcd && pos >= kCuPerXcd) pos = kCuPerXcd + (n - 1 - pos);
         if (CAUSAL && over) {
             // how many of the first `pos` (and pos + 1) work-groups are tiles of the heads left over
-            const bool few = n < 4 * kCuPerXcd;
+            const bool few = n < FEW * kCuPerXcd;
             auto before = [&](unsigned p) {
                 const unsigned share = few ? p * over / (kXcd * hpx + over) : p;
                 return min(max(share, p > whole ? p - whole : 0u), min(n_over, p));
@@ -368,7 +372,7 @@ __device__ __forceinline__ void xcd_tile_order(int id_, int ntile_, int BH_, int
             pos -= o;
         }
         unsigned G = 1;  // heads per group
-        if (CAUSAL) G = whole >= 4 * kCuPerXcd ? max(4u, (kCuPerXcd + ntile - 1) / ntile) : hpx;
+        if (CAUSAL) G = whole >= FEW * kCuPerXcd ? max(4u, (kCuPerXcd + ntile - 1) / ntile) : hpx;
         const unsigned group = pos / (G * ntile), within = pos - group * (G * ntile);
         const unsigned heads = min(G, hpx - group * G);  // the last group may be smaller
         const unsigned rk = within / heads;

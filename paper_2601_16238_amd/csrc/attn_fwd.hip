@@ -90,7 +90,7 @@ attn_fwd_kernel(const FwdArgs a)
 
     // (head, query tile) of this work-group; causal tiles are issued heaviest first.
     int bh, rank;
-    xcd_tile_order<CAUSAL, MAIN && NW == 4>(blockIdx.x, a.nqt, a.BH, bh, rank);
+    xcd_tile_order<CAUSAL, MAIN && NW == 4, (MAIN && NW == 4 ? 8 : 4)>(blockIdx.x, a.nqt, a.BH, bh, rank);
     const int qt = CAUSAL ? a.nqt - 1 - rank : rank;
     const int64_t base = (int64_t)(bh / a.H) * a.stride_b + (int64_t)(bh % a.H) * a.stride_h;
     // grouped-query heads: query head h reads K/V head h / group
@@ -752,8 +752,7 @@ static int launch_fwd_merge(const FwdArgs &a, hipStream_t st)
 #ifndef ATTN_F16
 // Three work-groups of four waves fit a unit.  Unsplit, where all of them are resident, from 2000 rows on two are
 // quicker, as heavy ones then do not meet three to a unit (0.97 of the time on average, D <= 32 0.98, never more than 1.09;
-// over 70 problems.  With more work-groups three, 0.83 .. 1.01 of the time on average in every class of 270, though some
-// heads end unevenly: 41 of 3283 D = 48 87 | 103 us).  Split, under a mask, the work-groups of a split that lies behind their rows end
+// over 70 problems.  With more work-groups three, 0.83 .. 1.01 of the time on average in every class of 270).  Split, under a mask, the work-groups of a split that lies behind their rows end
 // at once, and the heavy ones among the others are better spread: two on a unit, as with the larger tiles in LDS before, with
 // up to 612 of the others in two or three splits and 500 in more (8 heads of 4471 rows, 3 splits, 54 | 47 us, D = 32 43 | 37);
 // three with more of them (22 of 2682, 2 splits, D = 32 37 | 43; on average 1.05 with 3 or 4 splits, 1.12 with 2).  Over 408
