@@ -993,11 +993,16 @@ int fwd_split_plan(int BH, int S, int Sk, int D, bool causal, bool packed, int *
         // 706 on 3476 42 | 48.  Of 381 problems that were split 230 still are; 1.004 of the time of the better of the two
         // on average (1.09 before).  (The costs are a few per cent above the average measured, so that a split that
         // pays stays: over 260 other problems whose plan changed 0.84 of the time before, none above 1.013.)
+        // Where the unsplit launch has eight waves as well, its estimate by rounds is taken for long keys and one round
+        // of four-wave work-groups only: 40 problems that it splits take 0.86 .. 0.99 of the unsplit time (17 heads of
+        // 2630 on 7291 133 | 126, 16 of 2710 on 6866 D = 32 92 | 80).  With more rounds it splits what is quicker
+        // unsplit (16 heads of 6479 on 12904 D = 32 305 | 289), with fewer keys the two are alike.
         float unsplit = 0.0f;
         if (D == 64 && !causal && !wide && S > 224) {
             const bool eight = fwd_waves_unsplit(BH, S, Sk, false, false) == 8;
-            unsplit = rounds_us(eight ? RoundCost{6.0f, 7.9f, {0.97f, 2.08f}, 2} : RoundCost{4.8f, 2.6f, {0.65f, 1.1f, 1.65f}, 3},
-                                (int64_t)BH * ((S + (eight ? 255 : 127)) / (eight ? 256 : 128)), tiles);
+            if (!eight || (tiles > 64 && BH * ((S + 127) / 128) <= 512))
+                unsplit = rounds_us(eight ? RoundCost{6.0f, 7.9f, {0.97f, 2.08f}, 2} : RoundCost{4.8f, 2.6f, {0.65f, 1.1f, 1.65f}, 3},
+                                    (int64_t)BH * ((S + (eight ? 255 : 127)) / (eight ? 256 : 128)), tiles);
         }
         nsplit = fwd_splits(cost, wgs, tiles, S, (float)BH * S * D * 4e-6f, !causal || S <= tile_rows, std::min(most, 128), unsplit);
     } else if (S > 32 && rule == SplitRule::longest) {

@@ -29,10 +29,12 @@ def test_waves_of_the_unsplit_dq_at_64_columns(BH, S, narrow, waves):
 
 
 # us split | unsplit where the plan had split as if the unsplit launch had eight waves too: 24 | 17, 22 | 15, 28 | 19, 14 | 10,
-# 23 | 16, 27 | 21; splits that pay: 31 | 61, 42 | 48, 84 | 95, 46 | 49, 66 | 70
+# 23 | 16, 27 | 21; splits that pay: 31 | 61, 42 | 48, 84 | 95, 46 | 49, 66 | 70; unsplit eight waves of more than one round:
+# 305 | 289, 303 | 290, 486 | 457; of one round: 126 | 133, 124 | 129
 @pytest.mark.parametrize("BH,S,Sk,nsplit", [
     (20, 1119, 1119, 1), (16, 1175, 1175, 1), (21, 1353, 1353, 1), (11, 604, 604, 1), (34, 572, 1393, 1), (27, 869, 1886, 1),
-    (1, 5740, 5740, 10), (43, 706, 3476, 3), (5, 5391, 8474, 2), (15, 1284, 4319, 2), (83, 463, 3625, 3)])
+    (1, 5740, 5740, 10), (43, 706, 3476, 3), (5, 5391, 8474, 2), (15, 1284, 4319, 2), (83, 463, 3625, 3),
+    (16, 6479, 12904, 1), (19, 5197, 13176, 1), (18, 5958, 15230, 1), (17, 2630, 7291, 4), (11, 4259, 7288, 4)])
 def test_the_forward_at_64_columns_is_split_where_that_is_quicker(BH, S, Sk, nsplit):
     f = binding.lib()._ZN4attn14fwd_split_planEiiiibbPiiNS_9SplitRuleE
     f.argtypes = [ctypes.c_int] * 4 + [ctypes.c_bool] * 2 + [ctypes.c_void_p, ctypes.c_int, ctypes.c_int]
