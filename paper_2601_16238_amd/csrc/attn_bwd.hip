@@ -1902,27 +1902,36 @@ struct BlockChunks {
 };
 
 // Whether the unsplit dK/dV kernel at D = 65 .. 128 is that of attn_bwd_solo.hip: where an estimate of the launch is
-// below that of the pairs.  A work-group takes a fixed time and one per slot; without a mask all of them are equal and
-// run in rounds of one per unit, under one the launch takes as long as the longest or the work spread evenly.  (Per
-// key a slot of 256 takes 0.84 of the time of one of 128 or 192, but its rounds are coarser, more of the last key
-// block and of the diagonal is idle, and one wave per SIMD waits for its K and V alone.)  The constants, relative
-// ones, are a fit to the difference of the two over 298 whole backwards of 128 .. 16384 rows, D = 80 .. 128, both
-// masks, up to 2000 work-groups; of these the rule takes 0.985 of the time of the pairs on average (the better of
-// the two 0.982), none more than 1.022.  us, whole backward: B=4 H=32 S=4096 2921 -> 2735, causal 1625 -> 1580; B=1 H=16
-// S=16384 causal 2835 -> 2690; 104 heads on 26 of 1156 rows D = 96 271 -> 232; but 256 of 372 causal 65 | 77.
+// below that of the pairs.  A work-group takes a fixed time and one per slot.  Without a mask all of them are equal and
+// run in rounds of one per unit.  Under one the launch takes as long as the work spread evenly, and no less than r
+// times its work-group number 256 (r - 1) for any r, longest first, as some unit runs r of those up to it: with more
+// keys than rows most key blocks see every slot, and these run in rounds too.  (Per key a slot of 256 takes 0.84 of the
+// time of one of 128 or 192, but its rounds are coarser, more of the last key block and of the diagonal is idle, and
+// one wave per SIMD waits for its K and V alone.)  The constants, relative ones, are fits to the difference of the two in
+// whole backwards of D = 80 .. 128.  Without a mask: of 412 of 1 .. 4096 rows the rule takes 0.921 of the time of the
+// pairs on average (the better of the two 0.920), none more than 1.041.  Causal, 698 of 1 .. 7000 rows, half of them
+// square: 0.995 (0.987), 12 more than 1.02 and none more than 1.096; with the work spread evenly alone, and the constants
+// of the other mask, 95 were and one 1.30 (88 heads on 22 of 583 rows on 2989 keys 235 | 306 us), 1.002 on average.
+// 220 more causal ones, drawn among those that take this kernel: 0.940 of the pairs, 9 above 1.02, 1.19 the most.
+// us, whole backward: B=4 H=32 S=4096 2921 -> 2735, causal 1625 -> 1580; B=1 H=16 S=16384 causal 2835 -> 2690; 104 heads
+// on 26 of 1156 rows D = 96 271 -> 232; but 256 of 372 causal 65 | 77.
 bool dkdv_takes_solo(int BHkv, int group, int S, int Sk, bool causal)
 {
     const int64_t units = 256;
     auto time = [&](int keys, float fixed, float slot) {
         const int n_block = (Sk + keys - 1) / keys;
-        const float longest = fixed + slot * dkdv_slots(0, keys, group, S, Sk, causal);
-        if (!causal) return ((int64_t)BHkv * n_block + units - 1) / units * longest;
+        const int64_t wgs = (int64_t)BHkv * n_block;
+        auto length = [&](int64_t wg) { return fixed + slot * dkdv_slots((int)(wg / BHkv), keys, group, S, Sk, causal); };
+        if (!causal) return (wgs + units - 1) / units * length(0);
         const BlockChunks head(n_block, keys, group, S, Sk, causal);
-        return std::max(longest, BHkv * (fixed * n_block + slot * head.of(1)) / units);
+        float t = BHkv * (fixed * n_block + slot * head.of(1)) / units;
+        for (int r = 0; r < 16 && r * units < wgs; ++r) t = std::max(t, (r + 1) * length(r * units));
+        return t;
     };
     if ((int64_t)BHkv * ((Sk + 127) / 128) < units) return false;
     const bool six = (int64_t)BHkv * ((Sk + 191) / 192) >= 512;
-    return time(256, 7.7f, 1.026f) < 0.98f * (six ? time(192, 2.0f, 0.916f) : time(128, 3.6f, 0.611f));
+    if (!causal) return time(256, 7.7f, 1.026f) < 0.98f * (six ? time(192, 2.0f, 0.916f) : time(128, 3.6f, 0.611f));
+    return time(256, 6.2f, 1.026f) < (six ? time(192, 2.9f, 0.82f) : time(128, 4.2f, 0.475f));
 }
 
 // Split the dK/dV kernel over the query slots when its work-groups (one per key block of a K/V head)

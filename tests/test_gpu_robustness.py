@@ -206,7 +206,7 @@ def test_stage_wise_backward_equals_the_full_call(B, H, S, D, causal):
         check_bf16(nm, to_f64(t), r)
 
 
-@pytest.mark.parametrize("H,Hkv,Sq,Sk,D", [(72, 36, 700, 2311, 128), (72, 36, 700, 2311, 96), (2, 2, 700, 931, 256),
+@pytest.mark.parametrize("H,Hkv,Sq,Sk,D", [(128, 64, 700, 2311, 128), (128, 64, 700, 2311, 96), (72, 36, 700, 2311, 128), (2, 2, 700, 931, 256),
                                            (36, 36, 700, 931, 256), (2, 2, 700, 931, 128), (2, 2, 700, 931, 64)])
 def test_a_nan_row_leaves_the_keys_that_it_does_not_see(H, Hkv, Sq, Sk, D):
     """Under a causal mask dV of a key is a sum over the rows that see it: with a row of Q, and so of O and LSE, without

@@ -77,3 +77,14 @@ def test_main_loop_of_four_waves_at_64_columns():
     assert rule(128, 192) and rule(512, 255) and not rule(128, 191) and not rule(513, 255)
     assert not rule(128, 255, causal=True) and not rule(128, 255, narrow=False) and rule(2000, 256, causal=True, narrow=False)
     assert rule(128, 100, nsplit=2)
+
+
+# whole backward, us with dK/dV by pairs of waves | by one wave per SIMD
+@pytest.mark.parametrize("heads,group,S,Sk,causal,solo", [
+    (22, 4, 583, 2989, True, False), (18, 1, 917, 3848, True, False), (9, 1, 1166, 7659, True, False),  # 235 | 306, 126 | 146, 169 | 193
+    (57, 1, 1528, 1528, True, False), (25, 2, 1534, 3086, True, False), (83, 4, 1113, 1113, True, False),  # 153 | 178, 254 | 283, 343 | 389
+    (20, 4, 161, 3150, True, False), (128, 8, 142, 733, True, False),  # 1.18, 1.12
+    (128, 1, 4096, 4096, True, True), (16, 1, 16384, 16384, True, True), (109, 2, 2180, 2180, True, True), (14, 1, 1569, 8812, True, True),  # 1625 | 1580, 2835 | 2690, 833 | 748, 324 | 286
+    (128, 1, 4096, 4096, False, True), (26, 4, 1156, 1156, False, True), (256, 1, 372, 372, True, False)])  # 2921 | 2735, 271 | 232, 65 | 77
+def test_one_wave_per_simd_for_dkdv(heads, group, S, Sk, causal, solo):
+    assert host_rule("dkdv_takes_solo", heads, group, S, Sk, causal) == solo
