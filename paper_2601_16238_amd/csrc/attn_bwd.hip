@@ -1552,7 +1552,7 @@ static int launch_dkdv_u(const BwdArgs &a, hipStream_t st)
     else {
         if constexpr (D == 128) {
             const int64_t wgs6 = (int64_t)a.nkv * ((a.Sk + 191) / 192);
-            if (dkdv_takes_solo(a.nkv, a.group, a.S, a.Sk, CAUSAL)) return launch_bwd_dkdv_solo(a, CAUSAL, DS, st);
+            if (dkdv_takes_solo(a.nkv, a.group, a.S, a.Sk, CAUSAL, DS)) return launch_bwd_dkdv_solo(a, CAUSAL, DS, st);
             if (wgs6 >= 512) return launch_dkdv_p<D, U, 6, CAUSAL, DS>(a, st);
         }
         return launch_dkdv_p<D, U, 4, CAUSAL, DS>(a, st);
@@ -1909,13 +1909,16 @@ struct BlockChunks {
 // time of one of 128 or 192, but its rounds are coarser, more of the last key block and of the diagonal is idle, and
 // one wave per SIMD waits for its K and V alone.)  The constants, relative ones, are fits to the difference of the two in
 // whole backwards of D = 80 .. 128.  Without a mask: of 412 of 1 .. 4096 rows the rule takes 0.921 of the time of the
-// pairs on average (the better of the two 0.920), none more than 1.041.  Causal, 698 of 1 .. 7000 rows, half of them
-// square: 0.995 (0.987), 12 more than 1.02 and none more than 1.096; with the work spread evenly alone, and the constants
-// of the other mask, 95 were and one 1.30 (88 heads on 22 of 583 rows on 2989 keys 235 | 306 us), 1.002 on average.
-// 220 more causal ones, drawn among those that take this kernel: 0.940 of the pairs, 9 above 1.02, 1.19 the most.
+// pairs on average (the better of the two 0.920), none more than 1.041.  Causal, 984 of 1 .. 16384 rows, a third of them
+// square: 0.980 (0.975), 25 more than 1.02, the most 1.19 (152 heads on 76 of 212 rows on 804 keys); with the work spread
+// evenly alone, and the constants of the other mask, 95 of the first 698 were, one 1.30 (88 heads on 22 of 583 rows on 2989
+// keys 235 | 306 us).  Where dS is not stored this kernel gains more, 320 heads of 2048 rows 1247 | 1207 us (stored 1165 |
+// 1172), 256 of 3000 2002 | 1919: 3 % more may be estimated for it there.
+// 150 more causal ones, drawn among those that take this kernel: 0.967 of the pairs, 22 above 1.02, the most 1.24 (9 heads of
+// 958 rows on 7320 keys 86 | 106).
 // us, whole backward: B=4 H=32 S=4096 2921 -> 2735, causal 1625 -> 1580; B=1 H=16 S=16384 causal 2835 -> 2690; 104 heads
 // on 26 of 1156 rows D = 96 271 -> 232; but 256 of 372 causal 65 | 77.
-bool dkdv_takes_solo(int BHkv, int group, int S, int Sk, bool causal)
+bool dkdv_takes_solo(int BHkv, int group, int S, int Sk, bool causal, bool stored)
 {
     const int64_t units = 256;
     auto time = [&](int keys, float fixed, float slot) {
@@ -1931,7 +1934,7 @@ bool dkdv_takes_solo(int BHkv, int group, int S, int Sk, bool causal)
     if ((int64_t)BHkv * ((Sk + 127) / 128) < units) return false;
     const bool six = (int64_t)BHkv * ((Sk + 191) / 192) >= 512;
     if (!causal) return time(256, 7.7f, 1.026f) < 0.98f * (six ? time(192, 2.0f, 0.916f) : time(128, 3.6f, 0.611f));
-    return time(256, 6.2f, 1.026f) < (six ? time(192, 2.9f, 0.82f) : time(128, 4.2f, 0.475f));
+    return time(256, 6.2f, 1.026f) < (stored ? 1.0f : 1.03f) * (six ? time(192, 2.9f, 0.82f) : time(128, 4.2f, 0.475f));
 }
 
 // Split the dK/dV kernel over the query slots when its work-groups (one per key block of a K/V head)

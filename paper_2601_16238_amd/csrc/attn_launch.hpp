@@ -175,7 +175,7 @@ int dq_split_plan(int BH, int S, int Sk, int D, bool causal, int *kps, int most 
 // host function of the shape.
 int dkdv_split_plan(int BHkv, int group, int S, int Sk, int D, bool causal, int *chunk, int64_t most = 512);
 // Whether the unsplit dK/dV kernel for D = 128 is that of attn_bwd_solo.hip; a pure host function of the shape.
-bool dkdv_takes_solo(int BHkv, int group, int S, int Sk, bool causal);
+bool dkdv_takes_solo(int BHkv, int group, int S, int Sk, bool causal, bool stored);
 // K/V heads whose dS the backward keeps at a time in `room` bytes (0: it recomputes it for dQ); a pure host
 // function of the shape and the room.
 int ds_plan(int BHkv, int group, int S, int Sk, int D, bool causal, size_t room);

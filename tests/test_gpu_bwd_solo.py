@@ -36,11 +36,11 @@ def test_keys_by_the_wave(H, Hkv, Sq, Sk, D, causal, f16):
         k = [x[:, lo:hi].contiguous() for x in (K, V)]
         return attn.attn_bwd_rect(q[0], *k, q[1], q[2], q[3], D ** -0.5, causal, workspace=ws)
 
-    assert host_rule("dkdv_takes_solo", Hkv, H // Hkv, Sq, Sk, causal)
+    assert all(host_rule("dkdv_takes_solo", Hkv, H // Hkv, Sq, Sk, causal, stored) for stored in (False, True))
     whole = backward(0, Hkv, 0)
     n = 255 // ((Sk + 127) // 128)  # fewer than a work-group of 128 keys per compute unit: the pairs
     for lo in range(0, Hkv, n):
-        assert not host_rule("dkdv_takes_solo", min(n, Hkv - lo), H // Hkv, Sq, Sk, causal)
+        assert not host_rule("dkdv_takes_solo", min(n, Hkv - lo), H // Hkv, Sq, Sk, causal, False)
         part = backward(lo, min(lo + n, Hkv), 0)
         for w, p in zip(whole[1:], part[1:]):
             assert torch.equal(w[:, lo:lo + n].view(torch.int16), p.view(torch.int16))
@@ -68,7 +68,7 @@ def test_other_layouts(B, H, Hkv, Sq, Sk, D, causal, layout):
     Q, dO = (torch.randn((B, H, Sq, D), generator=g, device="cuda").bfloat16() for _ in range(2))
     K, V = (torch.randn((B, Hkv, Sk, D), generator=g, device="cuda").bfloat16() for _ in range(2))
     O, LSE = attn.attn_fwd_rect(Q, K, V, D ** -0.5, causal)
-    assert host_rule("dkdv_takes_solo", B * Hkv, H // Hkv, Sq, Sk, causal)
+    assert all(host_rule("dkdv_takes_solo", B * Hkv, H // Hkv, Sq, Sk, causal, stored) for stored in (False, True))
     best = attn.attn_bwd_rect_best_workspace_bytes(B, H, Hkv, Sq, Sk, D, causal)
     assert backward_form(B, H, Hkv, Sq, Sk, D, causal, best) == STORED_DS
     for n in ((8 * B * H * Sq + 255) // 256 * 256, best):
@@ -96,7 +96,7 @@ def test_stage_by_stage(H, Hkv, S, D, causal):
     K, V = (torch.randn((1, Hkv, S, D), generator=g, device="cuda").bfloat16() for _ in range(2))
     O, LSE = attn.attn_fwd_gqa(Q, K, V, D ** -0.5, causal)
     O = (O.float() * 8).round().div(8).bfloat16()
-    assert host_rule("dkdv_takes_solo", Hkv, H // Hkv, S, S, causal)
+    assert host_rule("dkdv_takes_solo", Hkv, H // Hkv, S, S, causal, False)
     ws = torch.full(((8 * H * S + 255) // 256 * 256,), 0xFF, dtype=torch.uint8, device="cuda")
     whole = attn.attn_bwd_gqa(Q, K, V, O, dO, LSE, D ** -0.5, causal, workspace=ws)
     out = [torch.full_like(x, float("nan")) for x in (Q, K, V)]

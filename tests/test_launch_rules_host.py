@@ -80,11 +80,13 @@ def test_main_loop_of_four_waves_at_64_columns():
 
 
 # whole backward, us with dK/dV by pairs of waves | by one wave per SIMD
-@pytest.mark.parametrize("heads,group,S,Sk,causal,solo", [
-    (22, 4, 583, 2989, True, False), (18, 1, 917, 3848, True, False), (9, 1, 1166, 7659, True, False),  # 235 | 306, 126 | 146, 169 | 193
-    (57, 1, 1528, 1528, True, False), (25, 2, 1534, 3086, True, False), (83, 4, 1113, 1113, True, False),  # 153 | 178, 254 | 283, 343 | 389
-    (20, 4, 161, 3150, True, False), (128, 8, 142, 733, True, False),  # 1.18, 1.12
-    (128, 1, 4096, 4096, True, True), (16, 1, 16384, 16384, True, True), (109, 2, 2180, 2180, True, True), (14, 1, 1569, 8812, True, True),  # 1625 | 1580, 2835 | 2690, 833 | 748, 324 | 286
-    (128, 1, 4096, 4096, False, True), (26, 4, 1156, 1156, False, True), (256, 1, 372, 372, True, False)])  # 2921 | 2735, 271 | 232, 65 | 77
-def test_one_wave_per_simd_for_dkdv(heads, group, S, Sk, causal, solo):
-    assert host_rule("dkdv_takes_solo", heads, group, S, Sk, causal) == solo
+@pytest.mark.parametrize("heads,group,S,Sk,causal,stored,solo", [
+    (22, 4, 583, 2989, True, True, False), (18, 1, 917, 3848, True, True, False), (57, 1, 1528, 1528, True, False, False),  # 235 | 306, 126 | 146, 153 | 178
+    (25, 2, 1534, 3086, True, True, False), (83, 4, 1113, 1113, True, True, False), (9, 1, 1166, 7659, True, False, False),  # 254 | 283, 343 | 389, 169 | 193
+    (20, 4, 161, 3150, True, True, False), (128, 8, 142, 733, True, True, False),  # 1.18, 1.12
+    (128, 1, 4096, 4096, True, True, True), (16, 1, 16384, 16384, True, True, True), (14, 1, 1569, 8812, True, True, True),  # 1625 | 1580, 2835 | 2690, 324 | 286
+    (320, 1, 2048, 2048, True, False, True), (320, 1, 2048, 2048, True, True, False),  # 1247 | 1207, 1165 | 1172
+    (256, 1, 3000, 3000, True, False, True), (64, 1, 2048, 2048, True, False, True), (512, 1, 1536, 1536, True, False, False),  # 2002 | 1919, 255 | 237, 1214 | 1229
+    (128, 1, 4096, 4096, False, True, True), (26, 4, 1156, 1156, False, True, True), (256, 1, 372, 372, True, True, False)])  # 2921 | 2735, 271 | 232, 65 | 77
+def test_one_wave_per_simd_for_dkdv(heads, group, S, Sk, causal, stored, solo):
+    assert host_rule("dkdv_takes_solo", heads, group, S, Sk, causal, stored) == solo
